@@ -21,7 +21,7 @@ namespace pdhg {
 
 constexpr int kBlock = 256;      // threads per workgroup (4 wave64)
 constexpr int kMaxSeg = 40;      // length classes per matrix
-constexpr int kShortMax = 64;    // rows up to this length go to SELL-64 slices
+constexpr int kShortMax = 64;    // rows up to this length go to SELL-64 slices (large matrices; see short_rows_max)
 
 struct Error {
     pdhg_err code;
@@ -96,6 +96,7 @@ struct HMat {
     int64_t nnz = 0;          // real entries
     int64_t stored = 0;       // entries incl. padding
     int32_t R_long = 0, nslices = 0;
+    int32_t stream = 0;       // 1: entries are read with non-temporal loads (see streamed)
     DBuf<int32_t> rowptr, colidx, slice_ptr;
     DBuf<double> val;
     SegTable seg{};
@@ -108,7 +109,7 @@ struct MatView {
     const int32_t *colidx;
     double *val;
     const int32_t *slice_ptr;
-    int32_t rows, R_long, nslices, pad;
+    int32_t rows, R_long, nslices, stream;
     SegTable seg;
 };
 
@@ -121,7 +122,7 @@ inline MatView view(const HMat &M) {
     v.rows = M.rows;
     v.R_long = M.R_long;
     v.nslices = M.nslices;
-    v.pad = 0;
+    v.stream = M.stream;
     v.seg = M.seg;
     return v;
 }
@@ -145,6 +146,7 @@ struct PanelMat {
     int32_t R = 0, S = 0, P = 0, W64 = 0;   // rows, panel size, panels, mask words per row
     int32_t vlen = 0;                       // length of the gathered vector
     int32_t W = 0;                          // workgroups per panel
+    int32_t stream = 0;                     // as HMat::stream
     int32_t nslices = 0, nwg = 0, nx = 0;
     int64_t entries = 0;                    // real entries
     DBuf<uint16_t> idx;      // soff[nslices] entries
@@ -167,7 +169,7 @@ struct PanelView {
     const uint64_t *mask;
     const int32_t *xptr, *xslot;
     double *part;
-    int32_t R, S, P, W64, vlen, W;
+    int32_t R, S, P, W64, vlen, W, stream;
 };
 
 inline PanelView view(const PanelMat &M) {
@@ -189,6 +191,7 @@ inline PanelView view(const PanelMat &M) {
     v.W64 = M.W64;
     v.vlen = M.vlen;
     v.W = M.W;
+    v.stream = M.stream;
     return v;
 }
 

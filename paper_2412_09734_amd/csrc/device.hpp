@@ -31,8 +31,49 @@ __device__ __forceinline__ RowCtx row_ctx(const SegTable &T) {
     return r;
 }
 
+// A matrix entry: non-temporal where the matrices are streamed (HMat::stream).
+template <bool NT, class T>
+__device__ __forceinline__ T load_entry(const T *__restrict__ p) {
+    if constexpr (NT) return __builtin_nontemporal_load(p);
+    else return *p;
+}
+
+// acc + the products of the lane's entries e, e + L, ..., in that order, U at a
+// time: as in sell_group the U loads of a group are unconditional, at indices
+// clamped to the row's last entry, so that all of them (and then their gathers)
+// are in flight before the first product, and products past the row are dropped
+// by a select. One entry at a time, a 2,000-entry column cost its lanes 31
+// dependent round trips.
+template <int U, bool NT>
+__device__ __forceinline__ double lane_entries_dot(const int32_t *__restrict__ colidx,
+                                                   const double *__restrict__ val,
+                                                   const double *__restrict__ v, int32_t e, int32_t e1,
+                                                   int32_t L) {
+    double acc = 0.0;
+    for (; e < e1; e += U * L) {
+        int32_t c[U];
+        double a[U], x[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int32_t q = min(e + u * L, e1 - 1);
+            c[u] = load_entry<NT>(colidx + q);
+            a[u] = load_entry<NT>(val + q);
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) x[u] = v[c[u]];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const double t = fma(a[u], x[u], acc);
+            acc = e + u * L < e1 ? t : acc;
+        }
+    }
+    return acc;
+}
+
 // sum_e val[e] * v[colidx[e]] over the row, lanes strided; the lane-group
-// butterfly leaves the same total in every lane of the group.
+// butterfly leaves the same total in every lane of the group. Rows of at most
+// 64 lanes x 4 entries have 2 to 4 entries per lane (make_segments).
+template <bool NT>
 __device__ __forceinline__ double row_dot(const int32_t *__restrict__ rowptr,
                                           const int32_t *__restrict__ colidx,
                                           const double *__restrict__ val,
@@ -41,9 +82,9 @@ __device__ __forceinline__ double row_dot(const int32_t *__restrict__ rowptr,
     const int32_t L = 1 << rc.lg;
     if (rc.valid) {
         const int32_t lane = (int32_t)(threadIdx.x & (uint32_t)(L - 1));
-        const int32_t e1 = rowptr[rc.row + 1];
-        for (int32_t e = rowptr[rc.row] + lane; e < e1; e += L)
-            acc = fma(__builtin_nontemporal_load(&val[e]), v[__builtin_nontemporal_load(&colidx[e])], acc);
+        const int32_t e = rowptr[rc.row] + lane, e1 = rowptr[rc.row + 1];
+        if (e1 - e <= 4 * L) acc = lane_entries_dot<4, NT>(colidx, val, v, e, e1, L);
+        else acc = lane_entries_dot<8, NT>(colidx, val, v, e, e1, L);
     }
     for (int32_t off = L >> 1; off > 0; off >>= 1) acc += __shfl_xor(acc, off);
     return acc;
@@ -89,7 +130,7 @@ __device__ __forceinline__ int32_t slice_of(const MatView &M) {
 // the compiler issues all of them before the first product (with predicated
 // loads it waits on each in turn); products of entries past w are dropped by a
 // select, so the sum is exactly that of the entries < w.
-template <int U, class Idx, class Gather>
+template <int U, bool NT, class Idx, class Gather>
 __device__ __forceinline__ double sell_group(const Idx *__restrict__ ci,
                                              const double *__restrict__ va, int32_t k,
                                              int32_t w, double acc, Gather gather) {
@@ -98,8 +139,8 @@ __device__ __forceinline__ double sell_group(const Idx *__restrict__ ci,
 #pragma unroll
     for (int u = 0; u < U; ++u) {
         const int32_t e = 64 * min(k + u, w - 1);
-        c[u] = (int32_t)__builtin_nontemporal_load(ci + e);
-        a[u] = __builtin_nontemporal_load(va + e);
+        c[u] = (int32_t)load_entry<NT>(ci + e);
+        a[u] = load_entry<NT>(va + e);
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) xv[u] = gather(c[u]);
@@ -114,20 +155,27 @@ __device__ __forceinline__ double sell_group(const Idx *__restrict__ ci,
 // Sum of the w entries of a SELL-64 lane in entry order: groups of
 // kSellUnroll, then one tail group of 1, 2, 4 or kSellUnroll (w is
 // wave-uniform, so the group sizes are too).
-template <class Idx, class Gather>
-__device__ __forceinline__ double sell_lane_dot(const Idx *__restrict__ ci,
+template <bool NT, class Idx, class Gather>
+__device__ __forceinline__ double sell_lane_sum(const Idx *__restrict__ ci,
                                                 const double *__restrict__ va, int32_t w,
                                                 Gather gather) {
     double acc = 0.0;
     int32_t k = 0;
     for (; k + kSellUnroll <= w; k += kSellUnroll)
-        acc = sell_group<kSellUnroll>(ci, va, k, w, acc, gather);
+        acc = sell_group<kSellUnroll, NT>(ci, va, k, w, acc, gather);
     const int32_t rest = w - k;
-    if (rest > 4) acc = sell_group<kSellUnroll>(ci, va, k, w, acc, gather);
-    else if (rest > 2) acc = sell_group<4>(ci, va, k, w, acc, gather);
-    else if (rest == 2) acc = sell_group<2>(ci, va, k, w, acc, gather);
-    else if (rest == 1) acc = sell_group<1>(ci, va, k, w, acc, gather);
+    if (rest > 4) acc = sell_group<kSellUnroll, NT>(ci, va, k, w, acc, gather);
+    else if (rest > 2) acc = sell_group<4, NT>(ci, va, k, w, acc, gather);
+    else if (rest == 2) acc = sell_group<2, NT>(ci, va, k, w, acc, gather);
+    else if (rest == 1) acc = sell_group<1, NT>(ci, va, k, w, acc, gather);
     return acc;
+}
+
+template <class Idx, class Gather>
+__device__ __forceinline__ double sell_lane_dot(int32_t stream, const Idx *__restrict__ ci,
+                                                const double *__restrict__ va, int32_t w,
+                                                Gather gather) {
+    return stream ? sell_lane_sum<true>(ci, va, w, gather) : sell_lane_sum<false>(ci, va, w, gather);
 }
 
 // Row sum over SELL-64 slice sl (wave-uniform) for the row of this lane:
@@ -144,7 +192,7 @@ __device__ __forceinline__ RowSum sell_row_dot(const MatView &M, const double *_
         const int32_t w = (__builtin_amdgcn_readfirstlane(M.slice_ptr[sl + 1]) - b) >> 6;
         const int32_t *__restrict__ ci = M.colidx + b + lane;
         const double *__restrict__ va = M.val + b + lane;
-        acc = sell_lane_dot(ci, va, w, [&](int32_t c) { return x[c]; });
+        acc = sell_lane_dot(M.stream, ci, va, w, [&](int32_t c) { return x[c]; });
     }
     r.s = acc;
     return r;
@@ -158,7 +206,8 @@ __device__ __forceinline__ RowSum mat_row_dot(const MatView &M, const double *__
     if (sl < 0) {
         RowSum r;
         const RowCtx rc = row_ctx(M.seg);
-        r.s = row_dot(M.rowptr, M.colidx, M.val, x, rc);
+        r.s = M.stream ? row_dot<true>(M.rowptr, M.colidx, M.val, x, rc)
+                       : row_dot<false>(M.rowptr, M.colidx, M.val, x, rc);
         r.row = rc.row;
         r.valid = rc.valid && rc.lead;
         return r;

@@ -174,7 +174,7 @@ __global__ __launch_bounds__(kPanelThreads) void k_panel_dot(PanelView P,
         nslot = P.slot[(size_t)nx * 64 + lane];
         const uint16_t *__restrict__ ip = P.idx + b + lane;
         const double *__restrict__ vp = P.val + b + lane;
-        const double acc = sell_lane_dot(ip, vp, w, [&](int32_t c) { return sh[c]; });
+        const double acc = sell_lane_dot(P.stream, ip, vp, w, [&](int32_t c) { return sh[c]; });
         if (slot >= 0) P.part[slot] = acc;
         sl += stride;
     }
@@ -270,7 +270,7 @@ __global__ __launch_bounds__(kPanelThreads) void k_dual_hot(
         const int32_t r = M.R_long + sl * 64 + lane;
         DualIn in{};
         if (r < M.rows) in = dual_load(r, y, y0, lc, uc);
-        const double acc = sell_lane_dot(ci, va, w, [&](int32_t c) { return c < H ? sh[c] : xext[c]; });
+        const double acc = sell_lane_dot(M.stream, ci, va, w, [&](int32_t c) { return c < H ? sh[c] : xext[c]; });
         if (r < M.rows) dual_store(r, acc, in, y, st, j, gamma);
         sl += nw;
     }

@@ -501,7 +501,7 @@ struct PlainCsr {
 
 // Convert a plain CSR whose rows are sorted by descending length into the
 // hybrid layout (long rows as CSR with lane groups, the rest as SELL-64).
-static void to_hybrid(hipStream_t s, PlainCsr &P, int32_t cols, HMat &H) {
+static void to_hybrid(hipStream_t s, PlainCsr &P, int32_t cols, int32_t short_max, HMat &H) {
     const int32_t R = P.rows;
     H.rows = R;
     H.cols = cols;
@@ -509,7 +509,7 @@ static void to_hybrid(hipStream_t s, PlainCsr &P, int32_t cols, HMat &H) {
     DBuf<int32_t> info;
     info.alloc(33);
     PDHG_HIP(hipMemsetAsync(info.p, 0, 33 * sizeof(int32_t), s));
-    if (R > 0) k_long_rows<<<blocks_for(R), kBlock, 0, s>>>(P.rowptr.p, R, kShortMax, info.p);
+    if (R > 0) k_long_rows<<<blocks_for(R), kBlock, 0, s>>>(P.rowptr.p, R, short_max, info.p);
     int32_t hinfo[33];
     PDHG_HIP(hipMemcpyAsync(hinfo, info.p, sizeof(hinfo), hipMemcpyDeviceToHost, s));
     PDHG_HIP(hipStreamSynchronize(s));
@@ -631,6 +631,40 @@ static int32_t panel_rows(const pdhg_options &o, int32_t m) {
     if (o.panel_rows > 0) return o.panel_rows;
     return m > 262144 ? kPanelMax : 0;
 }
+
+// Entries of x_ext staged in LDS by the dual product (0: off).
+static int32_t hot_columns(const pdhg_options &o, int32_t n) {
+    if (o.hot_cols >= 0) return std::min(o.hot_cols, n);
+    return n > 262144 ? kHotMax : 0;
+}
+
+// Longest rows of a matrix of `rows` rows and nnz entries that a single thread
+// sums (SELL-64). Up to 49,152 rows a thread per row leaves the chip short of
+// waves and the longest row's chain of loads is the product's time: rows longer
+// than 4 entries go to lane groups with at most four entries a lane. Beyond,
+// the threads are enough, and the limit only has to cover the bulk of the rows
+// (half as long again as the mean), which coalesce better a thread per row.
+// Layouts set by hand (panel_rows, hot_cols) keep one base layout, so that they
+// sum in the same order.
+// Measured, us per iteration at limit 4 / 16 / 32 / 64 for A~ and A~': Zipf
+// 30,001 x 60,013 19.6 / 20.3 / 21.1 / 29.2; 15,000 x 30,000 11.5 / 12.5 / 13.7
+// / 17; uniform 60,000 x 120,000 with 10 per column 30.3 / 29.4 / 26.4 / 26.3.
+static int32_t short_rows_max(const pdhg_options &o, int32_t m, int32_t n, int32_t rows, int64_t nnz) {
+    if (o.panel_rows >= 0 || o.hot_cols >= 0 || panel_rows(o, m) > 0 || hot_columns(o, n) > 0) return kShortMax;
+    if (rows <= 49152) return 4;
+    int32_t limit = 16;
+    while (limit < kShortMax && 2 * (int64_t)limit * rows < 3 * nnz) limit *= 2;
+    return limit;
+}
+
+// Whether the iterations read the entries of A~ and A~' with non-temporal
+// loads. Both copies (24 bytes per entry) of up to 9 M entries stay in the L2s
+// and the 256 MB memory-side cache from one iteration to the next, which the
+// hint would give up; larger ones only push the gathered vectors out of L2.
+// Measured, us per iteration without / with the hint on Zipf LPs: 0.6 M
+// entries 15.9 / 19.6, 5 M 74.6 / 94.0, 8 M 107.9 / 114.7, 10 M 137.5 / 136.1,
+// 16 M 228.7 / 217.2, 20 M 280.0 / 263.7.
+static bool streamed(int64_t nnz) { return nnz > 9000000; }
 
 // With the LDS panels in use, the columns of A that k_primal_sell runs (the
 // SELL-64 rows of A~' from R on, R as keep_panel_rows sets it) are reordered
@@ -815,8 +849,9 @@ void build_matrices(Handle &h, const pdhg_problem &p) {
                                                                 PT.colidx.p, PT.val.p);
         }
         PDHG_HIP(hipStreamSynchronize(s));
-        to_hybrid(s, PA, n, h.A);
-        to_hybrid(s, PT, m, h.AT);
+        to_hybrid(s, PA, n, short_rows_max(h.opt, m, n, m, nnz), h.A);
+        to_hybrid(s, PT, m, short_rows_max(h.opt, m, n, n, nnz), h.AT);
+        h.A.stream = h.AT.stream = h.PT.stream = streamed(nnz) ? 1 : 0;
         if (p.q_format == PDHG_FMT_NONE) keep_panel_rows(h, PT, m);
     }
     PDHG_HIP(hipStreamSynchronize(s));
@@ -1083,8 +1118,7 @@ void build_fast_layouts(Handle &h) {
     int dev = 0, cus = 0;
     PDHG_HIP(hipGetDevice(&dev));
     PDHG_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
-    const int32_t hot = h.opt.hot_cols < 0 ? (n > 262144 ? kHotMax : 0) : h.opt.hot_cols;
-    h.hot_cols = (m > 0 && h.A.nslices > 0) ? std::min(hot, n) : 0;
+    h.hot_cols = (m > 0 && h.A.nslices > 0) ? hot_columns(h.opt, n) : 0;
     h.dual_wgs = 2 * std::max(1, cus);
     PanelMat &P = h.PT;
     if (P.R == 0) return;
