@@ -319,8 +319,7 @@ __device__ double bidiag_lambda_max_wg(const double *alpha, const double *beta, 
         const double er = i + 1 < k ? fabs(alpha[i] * beta[i]) : 0.0;
         g = fmax(g, di + el + er);
     }
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) g = fmax(g, __shfl_xor(g, off));
+    g = wave_max(g);
     if ((t & 63) == 0) wmax[t >> 6] = g;
     __syncthreads();
     double hi = 0.0;

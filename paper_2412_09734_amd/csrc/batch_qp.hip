@@ -178,31 +178,25 @@ __device__ __forceinline__ double qv_row(const QArgs &a, const QI &q, int32_t j,
     return acc + q.dd[j] * vv[j];
 }
 
-// Eight wave sums at once: the first three butterfly steps (lane bits 5, 4, 3)
-// each halve the values a lane carries, so 3 + 3 + 1 exchanges of the last
-// value finish the job instead of 8 x 6. Lane l ends with the total of
+// Eight wave sums at once: the first two butterfly steps (lane bits 5, 4) each
+// halve the values a lane carries (a lane swap pairs two values' halves), the
+// third picks one of the last two. Lane l ends with the total of
 // value 4 bit3(l) + 2 bit4(l) + bit5(l).
 __device__ __forceinline__ double wave_sum_x8(const double (&s)[8]) {
-    const int lane = (int)(threadIdx.x & 63);
     double a[4], b[2];
-    const bool h5 = (lane >> 5) & 1, h4 = (lane >> 4) & 1, h3 = (lane >> 3) & 1;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-        const double keep = h5 ? s[2 * i + 1] : s[2 * i];
-        const double send = h5 ? s[2 * i] : s[2 * i + 1];
-        a[i] = keep + __shfl_xor(send, 32);
+        const Pair p = swap32(s[2 * i], s[2 * i + 1]);
+        a[i] = p.a + p.b;
     }
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
-        const double keep = h4 ? a[2 * i + 1] : a[2 * i];
-        const double send = h4 ? a[2 * i] : a[2 * i + 1];
-        b[i] = keep + __shfl_xor(send, 16);
+        const Pair p = swap16(a[2 * i], a[2 * i + 1]);
+        b[i] = p.a + p.b;
     }
-    double c = (h3 ? b[1] : b[0]) + __shfl_xor(h3 ? b[0] : b[1], 8);
-    c += __shfl_xor(c, 4);
-    c += __shfl_xor(c, 2);
-    c += __shfl_xor(c, 1);
-    return c;
+    const double c0 = b[0] + dpp_get<kDppRor + 8>(b[0]), c1 = b[1] + dpp_get<kDppRor + 8>(b[1]);
+    double c = (threadIdx.x & 8) ? c1 : c0;
+    return group_reduce(c, 3, [](double p, double q) { return p + q; });
 }
 
 // t = F~' w over the instance: per p, each thread's columns in order, then the

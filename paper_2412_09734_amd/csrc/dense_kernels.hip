@@ -113,7 +113,7 @@ __global__ __launch_bounds__(WIDE ? kWideBlock : kBlock) void k_dense_rows(
 #pragma unroll
     for (int q = 0; q < R; ++q) {
         if (MODE == ROW_ABSMAX) {
-            for (int off = 32; off > 0; off >>= 1) acc[q] = fmax(acc[q], __shfl_xor(acc[q], off));
+            acc[q] = wave_max(acc[q]);
         } else {
             acc[q] = wave_sum(acc[q]);
         }

@@ -8,6 +8,61 @@ namespace pdhg {
 
 constexpr int kSellUnroll = 8;   // SELL-64 entries whose loads are in flight together
 
+// Cross-lane moves on the vector unit. A __shfl_xor of a double is two LDS-pipe
+// permutes of about a hundred cycles each, one after another in a butterfly;
+// these are a few cycles. In the descending order 32, 16, 8, 4, 2, 1 the
+// partner sums below equal the xor butterfly's bit for bit: the swaps pair
+// lanes i and i ^ 32 (i ^ 16), and a rotation by 8, 4, 2 or 1 inside a row of
+// 16 lanes reads lane i ^ 8 (4, 2, 1) once the values repeat with period 16
+// (8, 4, 2).
+struct Pair {
+    double a, b;
+};
+// Lanes 32..63 of a change places with lanes 0..31 of b.
+__device__ __forceinline__ Pair swap32(double a, double b) {
+    const auto lo = __builtin_amdgcn_permlane32_swap((unsigned)__double2loint(a), (unsigned)__double2loint(b), false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap((unsigned)__double2hiint(a), (unsigned)__double2hiint(b), false, false);
+    return Pair{__hiloint2double((int)hi[0], (int)lo[0]), __hiloint2double((int)hi[1], (int)lo[1])};
+}
+// Lanes 16..31 and 48..63 of a change places with lanes 0..15 and 32..47 of b.
+__device__ __forceinline__ Pair swap16(double a, double b) {
+    const auto lo = __builtin_amdgcn_permlane16_swap((unsigned)__double2loint(a), (unsigned)__double2loint(b), false, false);
+    const auto hi = __builtin_amdgcn_permlane16_swap((unsigned)__double2hiint(a), (unsigned)__double2hiint(b), false, false);
+    return Pair{__hiloint2double((int)hi[0], (int)lo[0]), __hiloint2double((int)hi[1], (int)lo[1])};
+}
+// The value of another lane of the row of 16 (a DPP control word).
+constexpr int kDppRor = 0x120;          // + n: rotate by n
+constexpr int kDppXor1 = 0xB1;          // quad permutations [1, 0, 3, 2] and [2, 3, 0, 1]
+constexpr int kDppXor2 = 0x4E;
+constexpr int kDppHalfMirror = 0x141;   // lane 7 - i of each 8
+constexpr int kDppMirror = 0x140;       // lane 15 - i of each 16
+template <int CTRL>
+__device__ __forceinline__ double dpp_get(double v) {
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xf, 0xf, false);
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xf, 0xf, false);
+    return __hiloint2double(hi, lo);
+}
+
+// op over the lanes of each aligned group of L = 2^lg lanes, in every lane of
+// the group, smallest distance first (a mirror reads lane i ^ 4, or i ^ 8, of
+// values that are equal over quads, or over eights).
+template <class Op>
+__device__ __forceinline__ double group_reduce(double v, int32_t lg, Op op) {
+    if (lg > 0) v = op(v, dpp_get<kDppXor1>(v));
+    if (lg > 1) v = op(v, dpp_get<kDppXor2>(v));
+    if (lg > 2) v = op(v, dpp_get<kDppHalfMirror>(v));
+    if (lg > 3) v = op(v, dpp_get<kDppMirror>(v));
+    if (lg > 4) {
+        const Pair p = swap16(v, v);
+        v = op(p.a, p.b);
+    }
+    if (lg > 5) {
+        const Pair p = swap32(v, v);
+        v = op(p.a, p.b);
+    }
+    return v;
+}
+
 struct RowCtx {
     int32_t row;
     int32_t lg;    // log2(lanes per row)
@@ -86,8 +141,7 @@ __device__ __forceinline__ double row_dot(const int32_t *__restrict__ rowptr,
         if (e1 - e <= 4 * L) acc = lane_entries_dot<4, NT>(colidx, val, v, e, e1, L);
         else acc = lane_entries_dot<8, NT>(colidx, val, v, e, e1, L);
     }
-    for (int32_t off = L >> 1; off > 0; off >>= 1) acc += __shfl_xor(acc, off);
-    return acc;
+    return group_reduce(acc, rc.lg, [](double p, double q) { return p + q; });
 }
 
 // Row reduction of |val| (max when MAXNORM, else sum) without a vector.
@@ -104,11 +158,7 @@ __device__ __forceinline__ double row_absnorm(const int32_t *__restrict__ rowptr
             acc = MAXNORM ? fmax(acc, a) : acc + a;
         }
     }
-    for (int32_t off = L >> 1; off > 0; off >>= 1) {
-        const double o = __shfl_xor(acc, off);
-        acc = MAXNORM ? fmax(acc, o) : acc + o;
-    }
-    return acc;
+    return group_reduce(acc, rc.lg, [](double p, double q) { return MAXNORM ? fmax(p, q) : p + q; });
 }
 
 struct RowSum {
@@ -277,10 +327,21 @@ __device__ __forceinline__ void mat_scale_entries(const MatView &M, const double
     }
 }
 
+// op over the 64 lanes, in every lane (the xor butterfly from 32 down to 1).
+template <class Op>
+__device__ __forceinline__ double wave_reduce(double v, Op op) {
+    Pair p = swap32(v, v);
+    v = op(p.a, p.b);
+    p = swap16(v, v);
+    v = op(p.a, p.b);
+    v = op(v, dpp_get<kDppRor + 8>(v));
+    v = op(v, dpp_get<kDppRor + 4>(v));
+    v = op(v, dpp_get<kDppRor + 2>(v));
+    return op(v, dpp_get<kDppRor + 1>(v));
+}
+
 __device__ __forceinline__ double wave_sum(double s) {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off);
-    return s;
+    return wave_reduce(s, [](double p, double q) { return p + q; });
 }
 
 // Deterministic workgroup sum of K values per thread: wave butterflies, then
@@ -326,9 +387,7 @@ __device__ __forceinline__ void block_sum_all(double (&v)[K]) {
 }
 
 __device__ __forceinline__ double wave_max(double s) {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) s = fmax(s, __shfl_xor(s, off));
-    return s;
+    return wave_reduce(s, [](double p, double q) { return fmax(p, q); });
 }
 
 // Workgroup maxima of K values per thread (order-free), written by threads

@@ -86,7 +86,7 @@ __global__ __launch_bounds__(kBlock) void k_qp_csr(const DevState *__restrict__ 
     double acc = 0.0;
     if (row < n)
         for (int32_t e = rp[row] + lane; e < rp[row + 1]; e += 8) acc = fma(va[e], v[ci[e]], acc);
-    for (int off = 4; off > 0; off >>= 1) acc += __shfl_xor(acc, off);
+    acc = group_reduce(acc, 3, [](double p, double q) { return p + q; });
     if (row < n && lane == 0) qv[row] = acc;
 }
 
