@@ -13,52 +13,9 @@
 #include <memory>
 #include <vector>
 
-#include "device.hpp"
+#include "batch_qp.hpp"
 
 namespace pdhg {
-
-constexpr int kRmax = 32;   // largest supported rank of F
-constexpr int kCkpt = 50;   // checkpoint spacing of the unrolled QP
-constexpr int kWaveRowsMax = 256;   // row limit of the wave-per-row mode
-
-struct QArgs {
-    int32_t B, m, n, r;
-    int32_t wave_rows;      // 1: each constraint row is reduced by one wave (few, long rows)
-    const int32_t *arp, *aci, *trp, *tci;
-    const double *ava, *tva, *Dr, *Dc;
-    double eta;
-    const double *FT;       // F~' [r_pad][n], r_pad = r rounded up to 8, zero rows past r
-    const double *d_o;      // original d [B][n]
-    double *normq;          // [B]
-    const double *c_o, *lc_o, *uc_o, *lv_o, *uv_o;
-    double *c, *lc, *uc, *lv, *uv, *dd;   // scaled, per instance
-    double *x, *y, *xb, *yb, *x0, *y0, *xe, *v;
-    const double *x_init, *y_init;
-    double *x_out, *y_out;
-    double *res;            // [B][12]
-    int32_t *queue;
-    // unrolled
-    int64_t T;
-    int32_t replay;
-    uint8_t *restart;
-    double *omega;
-    int32_t *kk;
-    uint64_t *xmask, *ymask;   // [B][T][words]
-    double *ckpt;              // [B][nck][2n + 2m]
-    double *vseg;              // [B][kCkpt][n]
-    double *vall;              // [B][T][n] every momentum point, or null (recompute from checkpoints)
-    const double *gx, *gy;
-    double *gc, *glc, *guc, *gd;
-    double *bxb, *byb, *bw, *bqv;   // reverse scratch
-};
-
-struct QOpts {
-    double eps, gamma, beta_suff, beta_nec, beta_art, power_tol;
-    double eps_pinf, eps_dinf;   // infeasibility certificate tolerances
-    int64_t limit;
-    int32_t check_every, power_max_iters;
-    int32_t detect, pad;         // 1: test the rays at checks
-};
 
 template <int BT, int K>
 __device__ __forceinline__ void qsum(double (&v)[K]) {
@@ -79,16 +36,6 @@ __device__ __forceinline__ void qsum(double (&v)[K]) {
         v[q] = s;
     }
     __syncthreads();
-}
-
-template <int BT>
-__device__ __forceinline__ int32_t qnext(int32_t *queue) {
-    __shared__ int32_t id;
-    if (threadIdx.x == 0) id = atomicAdd(queue, 1);
-    __syncthreads();
-    const int32_t r = id;
-    __syncthreads();
-    return r;
 }
 
 __device__ __forceinline__ double qdot(const int32_t *__restrict__ rp, const int32_t *__restrict__ ci,
@@ -176,27 +123,6 @@ __device__ __forceinline__ double qv_row(const QArgs &a, const QI &q, int32_t j,
     }
     for (; p < a.r; ++p) acc = fma(fj[(size_t)p * n], t[p], acc);
     return acc + q.dd[j] * vv[j];
-}
-
-// Eight wave sums at once: the first two butterfly steps (lane bits 5, 4) each
-// halve the values a lane carries (a lane swap pairs two values' halves), the
-// third picks one of the last two. Lane l ends with the total of
-// value 4 bit3(l) + 2 bit4(l) + bit5(l).
-__device__ __forceinline__ double wave_sum_x8(const double (&s)[8]) {
-    double a[4], b[2];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const Pair p = swap32(s[2 * i], s[2 * i + 1]);
-        a[i] = p.a + p.b;
-    }
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-        const Pair p = swap16(a[2 * i], a[2 * i + 1]);
-        b[i] = p.a + p.b;
-    }
-    const double c0 = b[0] + dpp_get<kDppRor + 8>(b[0]), c1 = b[1] + dpp_get<kDppRor + 8>(b[1]);
-    double c = (threadIdx.x & 8) ? c1 : c0;
-    return group_reduce(c, 3, [](double p, double q) { return p + q; });
 }
 
 // t = F~' w over the instance: per p, each thread's columns in order, then the
@@ -901,8 +827,6 @@ __global__ __launch_bounds__(kBlock) void k_bqp_scale_factor(int32_t n, int32_t 
 // ---------------------------------------------------------------------------
 // host side
 
-#include "batch_internal.hpp"
-
 namespace pdhg {
 
 static QOpts qopts(const pdhg_options &o) {
@@ -990,8 +914,6 @@ static int32_t q_wgs(BatchHandle &h, K kernel, int BT, size_t lds = 0) {
     return wg;
 }
 
-enum class QK { norm, solve, unrolled, backward };
-
 template <int BT>
 static void qlaunch_t(BatchHandle &h, QK which, const QArgs &a, const QOpts &o) {
     PDHG_HIP(hipMemsetAsync(h.queue.p, 0, sizeof(int32_t), h.stream));
@@ -1036,6 +958,15 @@ static void qlaunch_t(BatchHandle &h, QK which, const QArgs &a, const QOpts &o) 
 
 static void qlaunch(BatchHandle &h, QK which, const QArgs &a) {
     const QOpts o = qopts(h.opt);
+    // one constraint row: the kernels that keep F~ in registers, unless the
+    // caller chose another shape; a reverse pass that recomputes its segments
+    // runs the general kernel
+    const int32_t row_threads = qrow_fits(h);
+    if (row_threads > 0 && which != QK::norm && (!h.threads_set || h.threads == row_threads) &&
+        !(which == QK::backward && !a.vall)) {
+        qrow_launch(h, which, a, o);
+        return;
+    }
     // the QP kernels spill registers at 1024 threads: at most 512 unless the
     // caller chose the shape
     const int32_t threads = h.threads_set ? h.threads : std::min(h.threads, 512);
@@ -1139,9 +1070,10 @@ void bqp_unrolled(BatchHandle &h, int64_t T, int32_t replay, double *x_out, doub
         h.ckpt.alloc((size_t)h.B * nck * (2 * (size_t)h.n + 2 * (size_t)h.m));
         h.vseg.alloc((size_t)h.B * kCkpt * h.n);
         // on-chip instances keep every momentum point (at most 16 GiB), so the
-        // reverse pass needs no recomputation; larger ones recompute segments
+        // reverse pass needs no recomputation; others recompute segments
         const size_t vbytes = (size_t)h.B * (size_t)T * (size_t)h.n * sizeof(double);
-        h.u_vall = q_onchip_bytes_bwd(h.n, h.m) <= kQOnchipBytes && vbytes <= ((size_t)16 << 30);
+        h.u_vall = (q_onchip_bytes_bwd(h.n, h.m) <= kQOnchipBytes || qrow_fits(h) > 0) &&
+                   vbytes <= ((size_t)16 << 30);
         if (h.u_vall)
             h.vall.alloc((size_t)h.B * (size_t)T * (size_t)h.n);
         else
