@@ -24,6 +24,7 @@ namespace pdhg {
 
 static thread_local std::string g_err = "";
 constexpr int kTimingEvents = 7;   // per timed plain iteration
+constexpr int kSmallPeriods = 8;   // check periods per launch of the one-workgroup solve
 
 void fail(pdhg_err code, const std::string &msg) { throw Error{code, msg}; }
 
@@ -215,7 +216,12 @@ static void run_solve(Handle &h, const double *x_init, const double *y_init, dou
     const int32_t C = h.opt.check_every;
     const int64_t L = h.opt.iteration_limit;
     // graphs hold the solve's controller constants: polishing phases run unrolled
-    const bool graphs = h.opt.use_graph && !h.polish;
+    // a small LP's check periods run inside one workgroup, several to a launch
+    // unless the host has to look between them; kernel timings ask for the
+    // multi-kernel iteration
+    const bool small = h.opt.timing_chunk < 0 && small_lp_fits(h) > 0;
+    const int32_t periods = h.opt.verbose || h.opt.time_limit_s > 0.0 ? 1 : kSmallPeriods;
+    const bool graphs = h.opt.use_graph && !h.polish && !small;
     if (graphs) build_graph(h);
 
     std::vector<hipEvent_t> tev;
@@ -234,7 +240,13 @@ static void run_solve(Handle &h, const double *x_init, const double *y_init, dou
             bool final = false;
             const bool time_up = h.opt.time_limit_s > 0.0 && now_s() - t0 > h.opt.time_limit_s;
             int64_t plain = 0;
-            if (time_up) {
+            if (small) {
+                launch_small_lp(h, periods, time_up ? PDHG_TIME_LIMIT : 0);
+                // the launch ends at iteration min(t + periods C, L - 1), and runs
+                // the last check itself when that falls inside its periods
+                final = time_up || L - 1 - t <= (int64_t)(periods - 1) * C;
+                plain = std::min((int64_t)periods * C, L - 1 - t) - 1;
+            } else if (time_up) {
                 enqueue_check(h, 0, 1, PDHG_TIME_LIMIT);
                 final = true;
             } else if (t == L - 1) {

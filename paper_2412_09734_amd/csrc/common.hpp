@@ -361,7 +361,12 @@ void batch_update_data(BatchHandle &b, const double *c, const double *lc, const 
                        const double *lv, const double *uv);
 void batch_destroy(BatchHandle *b);
 
+// ---- one-workgroup solve of a small LP (lp_small.hip) --------------------------
+int32_t small_lp_fits(const Handle &h);
+void launch_small_lp(Handle &h, int32_t periods, int32_t force_last);
+
 // ---- iteration kernels (lp_kernels.hip) -------------------------------------
+CtlConst lp_constants(const Handle &h);
 void launch_primal(Handle &h, int32_t j, hipEvent_t *timing = nullptr);
 void launch_dual(Handle &h, int32_t j);
 void launch_primal_check(Handle &h, double tau_override = -1.0);

@@ -8,7 +8,7 @@
 // Check iteration (every check_every steps) = primal/dual variants that keep
 // (xhat, yhat), two extra products A~'yhat and A~ xhat fused with the KKT and
 // fixed-point-residual sums, a one-workgroup controller and an apply kernel.
-#include "device.hpp"
+#include "lp_check.hpp"
 
 namespace pdhg {
 
@@ -315,33 +315,6 @@ __global__ __launch_bounds__(kBlock) void k_dual_chk(
 // A'dy = (q - A~'y0) / D_c), per workgroup into rays[4]: sums of the dual
 // ray's l_v'lam+ - u_v'lam- and of c'dx, maxima of |g - lam| and of the
 // distance of dx to the recession cone of [l_v, u_v]. q is kept in qhat.
-// Column side of a check for row r of A~' given q = (A~'yhat)_r (see k_check_n).
-__device__ __forceinline__ void check_n_terms(
-    int32_t r, double q, const double *__restrict__ xhat, const double *__restrict__ x,
-    const double *__restrict__ x0, const double *__restrict__ aty, const double *__restrict__ Dc,
-    const double *__restrict__ c_o, const double *__restrict__ lv_o, const double *__restrict__ uv_o,
-    const double *__restrict__ q0, double *__restrict__ qhat, double (&v)[6], double (&rsum)[2],
-    double (&rmax)[2]) {
-    const double xh = xhat[r];
-    const double dx = xh - x[r];
-    v[0] = dx * dx;
-    v[1] = (q - aty[r]) * dx;
-    const double d0 = xh - x0[r];
-    v[2] = d0 * d0;
-    const double d = Dc[r];
-    const double xo = d * xh;
-    const double g = c_o[r] - q / d;
-    const double lo = lv_o[r], hi = uv_o[r];
-    const bool lf = isfinite(lo), uf = isfinite(hi);
-    const double lam = (!lf && !uf) ? 0.0 : (lf && !uf) ? fmax(g, 0.0) : (!lf && uf) ? fmin(g, 0.0) : g;
-    const double rd = g - lam;
-    v[3] = rd * rd;
-    v[4] = c_o[r] * xo;
-    v[5] = (lf ? lo * fmax(lam, 0.0) : 0.0) - (uf ? hi * fmax(-lam, 0.0) : 0.0);
-    qhat[r] = q;
-    ray_col_terms(q, q0[r], d, d0, c_o[r], lo, hi, rsum, rmax);
-}
-
 __global__ __launch_bounds__(kBlock) void k_check_n(
     MatView M, const double *__restrict__ yhat, const double *__restrict__ xhat,
     const double *__restrict__ x, const double *__restrict__ x0, const double *__restrict__ aty,
@@ -415,26 +388,9 @@ __global__ __launch_bounds__(kBlock) void k_check_m(
     const DevState *__restrict__ st) {
     if (st->done) return;
     const RowSum rs = mat_row_dot(M, xhat);
-    const double p = rs.s;
     double v[4] = {0.0, 0.0, 0.0, 0.0};
     double rsum[1] = {0.0}, rmax[2] = {0.0, 0.0};
-    if (rs.valid) {
-        const int32_t r = rs.row;
-        const double d = Dr[r];
-        const double ax = p / d;
-        const double lo = lc_o[r], hi = uc_o[r];
-        const double rpr = ax - clampd(ax, lo, hi);
-        v[0] = rpr * rpr;
-        const double yh = yhat[r];
-        const double yo = d * yh;
-        v[1] = (isfinite(lo) ? lo * fmax(yo, 0.0) : 0.0) - (isfinite(hi) ? hi * fmax(-yo, 0.0) : 0.0);
-        const double dy = yh - y[r];
-        v[2] = dy * dy;
-        const double d0 = yh - y0[r];
-        v[3] = d0 * d0;
-        phat[r] = p;
-        ray_row_terms(p, p0[r], d, d0, lo, hi, rsum, rmax);
-    }
+    if (rs.valid) check_m_terms(rs.row, rs.s, yhat, y, y0, Dr, lc_o, uc_o, p0, phat, v, rsum, rmax);
     block_sum_store<4>(v, partials + (size_t)blockIdx.x * 4);
     block_sum_store<1>(rsum, rays + (size_t)blockIdx.x * 3);
     block_max_store<2>(rmax, rays + (size_t)blockIdx.x * 3 + 1);
@@ -456,100 +412,7 @@ __global__ __launch_bounds__(kBlock) void k_controller(
     check_totals(pn, nbn, pm, nbm, prn, prm, rays, vn, vm, rs, rx);
     if (threadIdx.x != 0) return;
 
-    const int64_t t = st->t_next;
-    const int64_t k = st->first ? 0 : st->k_base + st->plain_prev;
-    const double P = vn[4];
-    const double D = vm[1] + vn[5];
-    const double abs_p = sqrt(vm[0]), abs_d = sqrt(vn[3]), abs_g = fabs(P - D);
-    const double rel_p = abs_p / (1.0 + K.bnorm);
-    const double rel_d = abs_d / (1.0 + K.cnorm);
-    const double rel_g = abs_g / (1.0 + fabs(P) + fabs(D));
-    double kkt = rel_p;
-    if (rel_d > kkt || isnan(rel_d)) kkt = rel_d;
-    if (rel_g > kkt || isnan(rel_g)) kkt = rel_g;
-    st->kkt = kkt;
-    st->rel_p = rel_p;
-    st->rel_d = rel_d;
-    st->rel_g = rel_g;
-    st->pobj = P;
-    st->dobj = D;
-    st->abs_p = abs_p;
-    st->abs_d = abs_d;
-    st->abs_g = abs_g;
-    st->k_check = k;
-    st->t_done = t;
-    st->first = 0;
-    st->plain_prev = chunk_plain;
-    st->t_next = t + 1 + chunk_plain;
-    if (isnan(kkt)) {
-        st->done = 1;
-        st->status = PDHG_NUMERICAL_ERROR;
-        st->action = 2;
-        return;
-    }
-    // a polishing phase stops on its own residual alone
-    const double term_val = K.term == 1 ? rel_p : K.term == 2 ? rel_d : kkt;
-    if (term_val <= K.eps) {
-        st->done = 1;
-        st->status = PDHG_OPTIMAL;
-        st->action = 2;
-        return;
-    }
-    if (rays) {
-        const double obj_d = rs[0] + rs[2], obj_p = rs[1];
-        if (K.eps_pinf > 0.0 && obj_d > 0.0 && rx[0] <= K.eps_pinf * obj_d) {
-            st->done = 1;
-            st->status = PDHG_PRIMAL_INFEASIBLE;
-            st->ray_scale = 1.0 / obj_d;
-            st->action = 2;
-            return;
-        }
-        if (K.eps_dinf > 0.0 && obj_p < 0.0 && rx[1] <= K.eps_dinf * (-obj_p)) {
-            st->done = 1;
-            st->status = PDHG_DUAL_INFEASIBLE;
-            st->ray_scale = -1.0 / obj_p;
-            st->action = 2;
-            return;
-        }
-    }
-    if (is_last) {
-        st->done = 1;
-        st->status = last_status;
-        st->action = 2;
-        return;
-    }
-    const double tau = st->tau, sigma = st->sigma;
-    double r2 = vn[0] / tau + vm[2] / sigma + 2.0 * vn[1];
-    const double r = r2 > 0.0 ? sqrt(r2) : 0.0;
-    st->last_r = r;
-    int restart = 0;
-    if (t == 0) {
-        st->r_start = r;
-        st->r_prev = r;
-    } else if (r <= K.beta_suff * st->r_start ||
-               (r <= K.beta_nec * st->r_start && r > st->r_prev) ||
-               (double)k >= K.beta_art * (double)t) {
-        restart = 1;
-    } else {
-        st->r_prev = r;
-    }
-    if (restart) {
-        const double dxr = sqrt(vn[2]), dyr = sqrt(vm[3]);
-        double omega = st->omega;
-        if (dxr > 1e-10 && dyr > 1e-10) omega = exp(0.5 * log(dyr / dxr) + 0.5 * log(omega));
-        st->omega = omega;
-        st->tau = K.eta / omega;
-        st->sigma = K.eta * omega;
-        st->r_start = r;
-        st->r_prev = r;
-        st->restarts += 1;
-        st->k_base = 0;
-        st->action = 1;
-        st->anchor_valid = 1;   // k_apply stores the new anchor's products
-    } else {
-        st->k_base = k + 1;
-        st->action = 0;
-    }
+    check_decide(st, vn, vm, rs, rx, rays, K, chunk_plain, is_last, last_status);
 }
 
 // Restart (z <- zhat, anchor <- zhat) or Halpern step at the check iteration.
@@ -824,6 +687,12 @@ void launch_check_sums(Handle &h) {
 }
 
 void launch_controller(Handle &h, int32_t chunk_plain, int32_t is_last, int32_t last_status) {
+    k_controller<<<1, kBlock, 0, h.stream>>>(h.st.p, h.pn.p, h.nbn, h.pm.p, h.nbm, h.prn.p,
+                                              h.prm.p, lp_constants(h), chunk_plain, is_last, last_status);
+}
+
+// The controller's constants of an LP solve, or of a polishing phase.
+CtlConst lp_constants(const Handle &h) {
     CtlConst K;
     K.eps = h.polish ? h.opt.eps_feas_polish : h.opt.eps;
     K.bnorm = h.bnorm;
@@ -832,14 +701,14 @@ void launch_controller(Handle &h, int32_t chunk_plain, int32_t is_last, int32_t 
     K.beta_suff = h.opt.restart_sufficient;
     K.beta_nec = h.opt.restart_necessary;
     K.beta_art = h.opt.restart_artificial;
+    K.norm_q = 0.0;
     K.qp = 0;
     K.detect = !h.polish && (h.opt.eps_primal_infeasible > 0.0 || h.opt.eps_dual_infeasible > 0.0);
     K.eps_pinf = h.opt.eps_primal_infeasible;
     K.eps_dinf = h.opt.eps_dual_infeasible;
     K.term = h.polish;
     K.pad = 0;
-    k_controller<<<1, kBlock, 0, h.stream>>>(h.st.p, h.pn.p, h.nbn, h.pm.p, h.nbm, h.prn.p,
-                                              h.prm.p, K, chunk_plain, is_last, last_status);
+    return K;
 }
 
 void launch_apply(Handle &h) {
