@@ -4,8 +4,8 @@
 // so the vector units keep up with HBM and matrix cores would not help):
 //   rows pass    : a_i = A~_i . v, one wave per four rows (a workgroup per four
 //                  rows when there are few), fused with the dual step
-//   columns pass : partial sums of A~' w over 256-column tiles and row splits,
-//                  then a finalize kernel that adds the splits in fixed order
+//   columns pass : partial sums of A~' w over 256-column tiles (64-column ones
+//                  where there are few) and row splits, then a finalize kernel that adds the splits in fixed order
 //                  and applies the primal step.
 // The epilogues repeat the formulas of the sparse kernels exactly.
 #include "device.hpp"
@@ -14,6 +14,7 @@ namespace pdhg {
 
 constexpr int kDenseSplits = 16;   // most row splits of the column pass
 constexpr int kSplitRows = 256;    // fewest rows per split of the column pass
+constexpr int kNarrowWgs = 1024;   // workgroups that the narrow column pass aims at
 
 enum RowMode : int32_t {
     ROW_DUAL = 0,      // y <- Halpern(prox)
@@ -47,77 +48,92 @@ struct DenseVecs {
     double gamma, tau_o, sigma_o;
 };
 
-constexpr int kWideRows = 4;     // rows per workgroup of the WIDE row pass
-constexpr int kWideBlock = 512;  // threads per workgroup of the WIDE row pass
+constexpr int kGroupRows = 4;   // rows that a wave, or a workgroup, sums together
 
-// Row pass: a = sum_c A[i][c] v[c], or |A| norms. WIDE = false: one wave per
-// four rows (lanes strided over the columns, each v[c] loaded once for the
-// four rows, butterflies), sixteen rows per workgroup; WIDE = true: the whole
-// workgroup on kWideRows rows (for few, long rows: enough loads in flight to
-// stream HBM, each v[c] loaded once for them), wave totals added in wave order.
-template <int MODE, bool WIDE>
-__global__ __launch_bounds__(WIDE ? kWideBlock : kBlock) void k_dense_rows(
-    const double *__restrict__ A, int32_t m, int32_t n, const double *__restrict__ v, DenseVecs d) {
+// Columns c, c + L, ..., U of them, of kGroupRows rows: every load is issued
+// before the first f(row, k, entry). TAIL: some of the columns are past n;
+// their loads are clamped to the last one and come out as 0.
+template <int U, bool NT, bool TAIL, class F>
+__device__ __forceinline__ void row_columns(const double *const (&Ar)[kGroupRows], int32_t c, int32_t L, int32_t n, F f) {
+    double a[kGroupRows][U];
+#pragma unroll
+    for (int q = 0; q < kGroupRows; ++q)
+#pragma unroll
+        for (int k = 0; k < U; ++k) a[q][k] = load_entry<NT>(Ar[q] + (TAIL ? min(c + k * L, n - 1) : c + k * L));
+    __builtin_amdgcn_sched_barrier(0);   // the scheduler would sink loads between the products
+#pragma unroll
+    for (int q = 0; q < kGroupRows; ++q)
+#pragma unroll
+        for (int k = 0; k < U; ++k) f(q, k, TAIL && c + k * L >= n ? 0.0 : a[q][k]);
+}
+
+// acc over a lane's columns c, c + L, ... of the rows: products with v, or
+// (MODE) maxima and sums of absolute values. U columns x 4 rows of independent
+// loads in flight per lane, each row added in column order; the last columns go
+// in one clamped group of 4, 8 or 16 (one at a time they cost a lane of a
+// 3,001-column row 15 round trips).
+template <int MODE, bool NT>
+__device__ __forceinline__ void row_sums(const double *const (&Ar)[kGroupRows], const double *__restrict__ v, int32_t c,
+                                         int32_t L, int32_t n, double (&acc)[kGroupRows]) {
+    constexpr int U = 16;
+    constexpr bool NORM = MODE == ROW_ABSMAX || MODE == ROW_ABSSUM;
+    double x[U];
+    auto take = [&](int q, int k, double a) {
+        if constexpr (MODE == ROW_ABSMAX) acc[q] = fmax(acc[q], fabs(a));
+        else if constexpr (MODE == ROW_ABSSUM) acc[q] += fabs(a);
+        else acc[q] = fma(a, x[k], acc[q]);
+    };
+    auto load_x = [&](int count, bool tail) {
+        if constexpr (!NORM) {
+#pragma unroll
+            for (int k = 0; k < U; ++k)
+                if (k < count) x[k] = v[tail ? min(c + k * L, n - 1) : c + k * L];
+        }
+    };
+    for (; c + (U - 1) * L < n; c += U * L) {
+        load_x(U, false);
+        row_columns<U, NT, false>(Ar, c, L, n, take);
+    }
+    if (c + 7 * L < n) {
+        load_x(U, true);
+        row_columns<U, NT, true>(Ar, c, L, n, take);
+    } else if (c + 3 * L < n) {
+        load_x(8, true);
+        row_columns<8, NT, true>(Ar, c, L, n, take);
+    } else if (c < n) {
+        load_x(4, true);
+        row_columns<4, NT, true>(Ar, c, L, n, take);
+    }
+}
+
+// Row pass: a = sum_c A[i][c] v[c], or |A| norms, for groups of four rows, each
+// v[c] loaded once for the four. W = 1: a wave per group (lanes strided over the
+// columns, butterflies), four groups per workgroup; W = 4, 8: a workgroup of W
+// waves per group (few rows: enough waves and loads in flight), wave totals
+// added in wave order. stream: the matrix is larger than the caches.
+template <int MODE, int W>
+__global__ __launch_bounds__(W == 1 ? kBlock : 64 * W) void k_dense_rows(
+    const double *__restrict__ A, int32_t m, int32_t n, const double *__restrict__ v, DenseVecs d, int32_t stream) {
     if (d.st && d.st->done) return;
-    constexpr int BS = WIDE ? kWideBlock : kBlock;   // threads per workgroup
+    constexpr bool WIDE = W > 1;
+    constexpr int BS = WIDE ? 64 * W : kBlock;        // threads per workgroup
     constexpr int L = WIDE ? BS : 64;                 // lanes per row
-    constexpr int R = WIDE ? kWideRows : 4;   // rows per workgroup (WIDE) or per wave
+    constexpr int R = kGroupRows;
     const int64_t row0 = WIDE ? (int64_t)blockIdx.x * R
                               : (((int64_t)blockIdx.x * kBlock + threadIdx.x) >> 6) * R;
     const int32_t lane = WIDE ? (int32_t)threadIdx.x : (int32_t)(threadIdx.x & 63);
     double acc[R];
 #pragma unroll
     for (int q = 0; q < R; ++q) acc[q] = 0.0;
-    const double *__restrict__ Ar[R];
-    bool live[R];
+    if (row0 < m) {
+        const double *Ar[R];   // rows past the last one repeat it; their sums are dropped
 #pragma unroll
-    for (int q = 0; q < R; ++q) {
-        live[q] = row0 + q < m;
-        Ar[q] = A + (size_t)(live[q] ? row0 + q : 0) * n;
-    }
-    if (MODE == ROW_ABSMAX || MODE == ROW_ABSSUM) {
-#pragma unroll
-        for (int q = 0; q < R; ++q) {
-            if (!live[q]) continue;
-            for (int32_t c = lane; c < n; c += L) {
-                const double a = fabs(Ar[q][c]);
-                acc[q] = MODE == ROW_ABSMAX ? fmax(acc[q], a) : acc[q] + a;
-            }
-        }
-    } else if (live[0]) {
-        // U columns x R rows of independent loads in flight per lane, each
-        // row added in column order
-        constexpr int U = 16;
-        int32_t c = lane;
-        for (; c + (U - 1) * L < n; c += U * L) {
-            double x[U], a[R][U];
-#pragma unroll
-            for (int k = 0; k < U; ++k) x[k] = v[c + k * L];
-#pragma unroll
-            for (int q = 0; q < R; ++q)
-#pragma unroll
-                for (int k = 0; k < U; ++k)
-                    a[q][k] = live[q] ? __builtin_nontemporal_load(Ar[q] + c + k * L) : 0.0;
-#pragma unroll
-            for (int q = 0; q < R; ++q)
-#pragma unroll
-                for (int k = 0; k < U; ++k) acc[q] = fma(a[q][k], x[k], acc[q]);
-        }
-        for (; c < n; c += L) {
-            const double x = v[c];
-#pragma unroll
-            for (int q = 0; q < R; ++q)
-                if (live[q]) acc[q] = fma(__builtin_nontemporal_load(Ar[q] + c), x, acc[q]);
-        }
+        for (int q = 0; q < R; ++q) Ar[q] = A + (size_t)min(row0 + q, (int64_t)m - 1) * n;
+        if (stream) row_sums<MODE, true>(Ar, v, lane, L, n, acc);
+        else row_sums<MODE, false>(Ar, v, lane, L, n, acc);
     }
 #pragma unroll
-    for (int q = 0; q < R; ++q) {
-        if (MODE == ROW_ABSMAX) {
-            acc[q] = wave_max(acc[q]);
-        } else {
-            acc[q] = wave_sum(acc[q]);
-        }
-    }
+    for (int q = 0; q < R; ++q) acc[q] = MODE == ROW_ABSMAX ? wave_max(acc[q]) : wave_sum(acc[q]);
     double accv = acc[0];
     int64_t row = row0;
     if constexpr (WIDE) {
@@ -196,48 +212,71 @@ __global__ __launch_bounds__(WIDE ? kWideBlock : kBlock) void k_dense_rows(
     }
 }
 
+// acc over rows [i, r1) of one column (Ac = its first entry): products with w,
+// or maxima / sums of absolute values. U rows' loads in flight, added in row
+// order; the last rows go in one clamped group.
+enum ColSum : int32_t { SUM_DOT = 0, SUM_ABSMAX = 1, SUM_ABS = 2 };
+template <int KIND, bool NT>
+__device__ __forceinline__ double col_rows(const double *__restrict__ Ac, const double *__restrict__ w, int32_t i,
+                                           int32_t r1, int32_t n) {
+    double acc = 0.0;
+    auto rows = [&](auto width, bool tail) {
+        constexpr int U = decltype(width)::value;
+        double a[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) a[u] = load_entry<NT>(Ac + (size_t)(tail ? min(i + u, r1 - 1) : i + u) * n);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const double e = tail && i + u >= r1 ? 0.0 : a[u];
+            if constexpr (KIND == SUM_ABSMAX) acc = fmax(acc, fabs(e));
+            else if constexpr (KIND == SUM_ABS) acc += fabs(e);
+            else acc = fma(e, w[tail ? min(i + u, r1 - 1) : i + u], acc);
+        }
+    };
+    for (; i + 15 < r1; i += 16) rows(std::integral_constant<int, 16>(), false);
+    if (i + 7 < r1) rows(std::integral_constant<int, 16>(), true);
+    else if (i + 3 < r1) rows(std::integral_constant<int, 8>(), true);
+    else if (i < r1) rows(std::integral_constant<int, 4>(), true);
+    return acc;
+}
+
 // Partial column sums: partials[split][c] = sum over the split's rows of A[i][c] w[i];
-// the splits are gridDim.y equal runs of rows.
-template <bool ABSMAX, bool ABSSUM>
+// the splits are gridDim.y equal runs of rows. NARROW = false: 256-column tiles,
+// a thread per column. NARROW = true: 64-column tiles whose four waves take a
+// quarter of the split's rows each, added in wave order: four times the
+// workgroups for the same partials, for matrices with few tiles.
+template <int KIND, bool NARROW>
 __global__ __launch_bounds__(kBlock) void k_dense_cols_partial(const double *__restrict__ A,
                                                                int32_t m, int32_t n,
                                                                const double *__restrict__ w,
                                                                double *__restrict__ partials,
-                                                               const DevState *__restrict__ st) {
+                                                               const DevState *__restrict__ st,
+                                                               int32_t stream) {
     if (st && st->done) return;
-    const int64_t col = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    const int32_t split = blockIdx.y;
-    const int32_t splits = (int32_t)gridDim.y;
-    const int32_t rows_per = (m + splits - 1) / splits;
-    const int32_t r0 = split * rows_per, r1 = min(m, r0 + rows_per);
-    if (col >= n) return;
+    const int32_t split = blockIdx.y, splits = (int32_t)gridDim.y;
+    const int32_t per = (m + splits - 1) / splits;
+    const int32_t wave = NARROW ? __builtin_amdgcn_readfirstlane((int32_t)(threadIdx.x >> 6)) : 0;
+    const int64_t col = NARROW ? (int64_t)blockIdx.x * 64 + (threadIdx.x & 63) : (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    const int32_t end = min(m, (split + 1) * per);
+    const int32_t part = NARROW ? (per + 3) / 4 : per;
+    const int32_t r0 = split * per + wave * part, r1 = NARROW ? min(end, r0 + part) : end;
     double acc = 0.0;
-    const double *__restrict__ Ac = A + col;
-    int32_t i = r0;
-    if (ABSMAX || ABSSUM) {
-        for (; i < r1; ++i) {
-            const double a = fabs(Ac[(size_t)i * n]);
-            acc = ABSMAX ? fmax(acc, a) : acc + a;
-        }
-    } else {
-        // sixteen, then eight rows' loads in flight per thread, added in row order
-        for (; i + 15 < r1; i += 16) {
-            double a[16];
-#pragma unroll
-            for (int u = 0; u < 16; ++u) a[u] = __builtin_nontemporal_load(Ac + (size_t)(i + u) * n);
-#pragma unroll
-            for (int u = 0; u < 16; ++u) acc = fma(a[u], w[i + u], acc);
-        }
-        for (; i + 7 < r1; i += 8) {
-            double a[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) a[u] = __builtin_nontemporal_load(Ac + (size_t)(i + u) * n);
-#pragma unroll
-            for (int u = 0; u < 8; ++u) acc = fma(a[u], w[i + u], acc);
-        }
-        for (; i < r1; ++i) acc = fma(__builtin_nontemporal_load(Ac + (size_t)i * n), w[i], acc);
+    if (col < n) {
+        if (stream) acc = col_rows<KIND, true>(A + col, w, r0, r1, n);
+        else acc = col_rows<KIND, false>(A + col, w, r0, r1, n);
     }
-    partials[(size_t)split * n + col] = acc;
+    if constexpr (NARROW) {
+        __shared__ double sh[4][64];
+        sh[wave][threadIdx.x & 63] = acc;
+        __syncthreads();
+        if (wave != 0) return;
+#pragma unroll
+        for (int q = 1; q < 4; ++q) {
+            const double o = sh[q][threadIdx.x];
+            acc = KIND == SUM_ABSMAX ? fmax(acc, o) : acc + o;
+        }
+    }
+    if (col < n) partials[(size_t)split * n + col] = acc;
 }
 
 // Splits added in order 0..S-1, then the column epilogue.
@@ -249,7 +288,16 @@ __global__ __launch_bounds__(kBlock) void k_dense_cols_final(int32_t n, int32_t 
     const int64_t r = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     double s = 0.0;
     if (r < n) {
-        for (int q = 0; q < splits; ++q) {
+        // eight splits' loads in flight, added in order
+        int32_t q = 0;
+        for (; q + 8 <= splits; q += 8) {
+            double p[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) p[u] = part[(size_t)(q + u) * n + r];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) s = MODE == COL_ABSMAX ? fmax(s, p[u]) : s + p[u];
+        }
+        for (; q < splits; ++q) {
             const double p = part[(size_t)q * n + r];
             s = MODE == COL_ABSMAX ? fmax(s, p) : s + p;
         }
@@ -379,37 +427,77 @@ static DenseVecs dvecs(Handle &h, int32_t j) {
     return d;
 }
 
-// Few rows (fewer than 4 per CU) get a workgroup each, otherwise a wave per four.
-static bool wide_rows(int32_t m) { return m < 1024; }
-static unsigned row_blocks(int32_t m) {
-    return wide_rows(m) ? (unsigned)std::max<int64_t>(1, ceil_div(m, kWideRows)) : dblk((int64_t)(m + 3) / 4 * 64);
+// Waves per group of four rows: one where the groups alone give the chip enough
+// waves, four below 2,048 rows, eight for fewer and long rows. Measured, us per
+// iteration with 1 / 4 / 8: 1,537 x 3,001 25.1 / 23.1 / 24.4, 8,000 x 5,000 113 /
+// 116 / 131, 700 x 1,500 16.3 / 11.9 / 11.8, 300 x 700 12.1 / 10.7 / 11.2, 300 x 100,003
+// 295 / 120 / 109.
+static int32_t row_waves(int32_t m, int32_t n) {
+    if (m >= 2048) return 1;
+    return m < 1024 && n >= 16384 ? 8 : 4;
 }
+static unsigned row_blocks(int32_t m, int32_t n) {
+    return row_waves(m, n) > 1 ? (unsigned)std::max<int64_t>(1, ceil_div(m, kGroupRows))
+                            : dblk(ceil_div(m, kGroupRows) * 64);
+}
+
+// Whether the passes read the matrix with non-temporal loads. Up to 45 M entries
+// (360 MB) enough of it stays in the L2s and the 256 MB memory-side cache
+// between the passes to be read with ordinary ones. Measured, us per iteration
+// ordinary / non-temporal: 500 x 20,000 36 / 47, 300 x 100,003 120 / 180, 8,000 x
+// 5,000 116 / 119, 12,000 x 5,000 179 / 173, 8,000 x 16,000 354 / 326.
+static int32_t dense_stream(int32_t m, int32_t n) { return (int64_t)m * n > 45000000 ? 1 : 0; }
 
 template <int MODE>
 static void launch_rows(hipStream_t s, const double *A, int32_t m, int32_t n, const double *v,
                         const DenseVecs &d) {
-    if (wide_rows(m))
-        k_dense_rows<MODE, true><<<row_blocks(m), kWideBlock, 0, s>>>(A, m, n, v, d);
-    else
-        k_dense_rows<MODE, false><<<row_blocks(m), kBlock, 0, s>>>(A, m, n, v, d);
+    const int32_t w = row_waves(m, n), stream = dense_stream(m, n);
+    if (w == 8) k_dense_rows<MODE, 8><<<row_blocks(m, n), 512, 0, s>>>(A, m, n, v, d, stream);
+    else if (w == 4) k_dense_rows<MODE, 4><<<row_blocks(m, n), 256, 0, s>>>(A, m, n, v, d, stream);
+    else k_dense_rows<MODE, 1><<<row_blocks(m, n), kBlock, 0, s>>>(A, m, n, v, d, stream);
 }
 static unsigned col_blocks(int32_t n) { return dblk(n); }
-// Row splits of the column pass: up to kDenseSplits, at least kSplitRows rows each.
-static int32_t col_splits(int32_t m) {
-    return (int32_t)std::min<int64_t>(kDenseSplits, std::max<int64_t>(1, m / kSplitRows));
+
+// Row splits of the column pass. Wide tiles: up to kDenseSplits, at least
+// kSplitRows rows each. Where that leaves fewer than 128 workgroups, narrow
+// tiles and enough splits for kNarrowWgs workgroups, with at least 64 rows each.
+// Measured, us per iteration wide / narrow: 700 x 1,500 (12 wide workgroups) 22.2 /
+// 11.9, 1,537 x 3,001 (72) 29.4 / 23.1, 500 x 20,000 (79) 41.1 / 36.0, 2,500 x 5,500
+// (198) 42.2 / 46.0, 300 x 100,003 (391) 115 / 120.
+struct ColPlan {
+    bool narrow;
+    int32_t splits;
+};
+static ColPlan col_plan(int32_t m, int32_t n) {
+    const int32_t wide = (int32_t)std::min<int64_t>(kDenseSplits, std::max<int64_t>(1, m / kSplitRows));
+    if ((int64_t)col_blocks(n) * wide >= 128) return {false, wide};
+    const int64_t tiles = ceil_div(n, 64);
+    const int64_t want = std::min<int64_t>(ceil_div(kNarrowWgs, tiles), ceil_div(m, 64));
+    return {true, (int32_t)std::max<int64_t>(1, want)};
+}
+static int32_t col_splits(const Handle &h) { return col_plan(h.m, h.n).splits; }
+
+template <int KIND>
+static void launch_cols(hipStream_t s, const double *A, int32_t m, int32_t n, const double *w, double *part,
+                        const DevState *st) {
+    const ColPlan p = col_plan(m, n);
+    const int32_t stream = dense_stream(m, n);
+    if (p.narrow)
+        k_dense_cols_partial<KIND, true><<<dim3((unsigned)ceil_div(n, 64), p.splits), kBlock, 0, s>>>(A, m, n, w, part, st, stream);
+    else
+        k_dense_cols_partial<KIND, false><<<dim3(col_blocks(n), p.splits), kBlock, 0, s>>>(A, m, n, w, part, st, stream);
 }
 
-int32_t dense_row_blocks(const Handle &h) { return (int32_t)row_blocks(h.m); }
+int32_t dense_row_blocks(const Handle &h) { return (int32_t)row_blocks(h.m, h.n); }
 int32_t dense_col_blocks(const Handle &h) { return (int32_t)col_blocks(h.n); }
 
 static void cols_partial(Handle &h, const double *w, const DevState *st) {
-    dim3 grid(col_blocks(h.n), col_splits(h.m));
-    k_dense_cols_partial<false, false><<<grid, kBlock, 0, h.stream>>>(h.Ad.p, h.m, h.n, w, h.dpart.p, st);
+    launch_cols<SUM_DOT>(h.stream, h.Ad.p, h.m, h.n, w, h.dpart.p, st);
 }
 
 void dense_primal(Handle &h, int32_t j) {
     cols_partial(h, h.y.p, h.st.p);
-    k_dense_cols_final<COL_PRIMAL><<<col_blocks(h.n), kBlock, 0, h.stream>>>(h.n, col_splits(h.m), h.dpart.p, dvecs(h, j));
+    k_dense_cols_final<COL_PRIMAL><<<col_blocks(h.n), kBlock, 0, h.stream>>>(h.n, col_splits(h), h.dpart.p, dvecs(h, j));
 }
 
 void dense_dual(Handle &h, int32_t j) {
@@ -421,7 +509,7 @@ void dense_primal_check(Handle &h, double tau_override) {
     cols_partial(h, h.y.p, h.st.p);
     DenseVecs d = dvecs(h, 0);
     d.tau_o = tau_override;
-    k_dense_cols_final<COL_PRIMAL_CHK><<<col_blocks(h.n), kBlock, 0, h.stream>>>(h.n, col_splits(h.m), h.dpart.p, d);
+    k_dense_cols_final<COL_PRIMAL_CHK><<<col_blocks(h.n), kBlock, 0, h.stream>>>(h.n, col_splits(h), h.dpart.p, d);
 }
 
 void dense_dual_check(Handle &h, double sigma_override) {
@@ -438,7 +526,7 @@ void dense_check_sums(Handle &h) {
     d.q0 = h.q0.p;
     d.qhat = h.qhat.p;
     d.rays = h.prn.p;
-    k_dense_cols_final<COL_CHECK_N><<<col_blocks(h.n), kBlock, 0, h.stream>>>(h.n, col_splits(h.m), h.dpart.p, d);
+    k_dense_cols_final<COL_CHECK_N><<<col_blocks(h.n), kBlock, 0, h.stream>>>(h.n, col_splits(h), h.dpart.p, d);
     if (h.m > 0) {
         DenseVecs e = dvecs(h, 0);
         e.partials = h.pm.p;
@@ -465,7 +553,7 @@ void dense_cols_sq(Handle &h, const double *w, double *out, double *partials) {
     d.st = nullptr;
     d.out = out;
     d.partials = partials;
-    k_dense_cols_final<COL_STORE_SQ><<<col_blocks(h.n), kBlock, 0, h.stream>>>(h.n, col_splits(h.m), h.dpart.p, d);
+    k_dense_cols_final<COL_STORE_SQ><<<col_blocks(h.n), kBlock, 0, h.stream>>>(h.n, col_splits(h), h.dpart.p, d);
 }
 
 void dense_build(Handle &h, const pdhg_problem &p) {
@@ -486,7 +574,7 @@ void dense_build(Handle &h, const pdhg_problem &p) {
     h.perm_c.alloc(h.n);
     if (h.m) k_iota<<<dblk(h.m), kBlock, 0, s>>>(h.perm_r.p, h.m);
     k_iota<<<dblk(h.n), kBlock, 0, s>>>(h.perm_c.p, h.n);
-    h.dpart.alloc((size_t)kDenseSplits * h.n);
+    h.dpart.alloc((size_t)col_splits(h) * h.n);
     h.A.rows = h.m;
     h.A.cols = h.n;
     h.A.nnz = total;
@@ -508,17 +596,16 @@ void dense_scale(Handle &h) {
         DenseVecs d = dvecs(h, 0);
         d.st = nullptr;
         d.out = rn.p;
-        dim3 grid(col_blocks(n), col_splits(m));
         if (pc) {
             launch_rows<ROW_ABSSUM>(s, h.Ad.p, m, n, nullptr, d);
-            k_dense_cols_partial<false, true><<<grid, kBlock, 0, s>>>(h.Ad.p, m, n, nullptr, h.dpart.p, nullptr);
+            launch_cols<SUM_ABS>(s, h.Ad.p, m, n, nullptr, h.dpart.p, nullptr);
             d.out = cn.p;
-            k_dense_cols_final<COL_ABSSUM><<<col_blocks(n), kBlock, 0, s>>>(n, col_splits(m), h.dpart.p, d);
+            k_dense_cols_final<COL_ABSSUM><<<col_blocks(n), kBlock, 0, s>>>(n, col_splits(h), h.dpart.p, d);
         } else {
             launch_rows<ROW_ABSMAX>(s, h.Ad.p, m, n, nullptr, d);
-            k_dense_cols_partial<true, false><<<grid, kBlock, 0, s>>>(h.Ad.p, m, n, nullptr, h.dpart.p, nullptr);
+            launch_cols<SUM_ABSMAX>(s, h.Ad.p, m, n, nullptr, h.dpart.p, nullptr);
             d.out = cn.p;
-            k_dense_cols_final<COL_ABSMAX><<<col_blocks(n), kBlock, 0, s>>>(n, col_splits(m), h.dpart.p, d);
+            k_dense_cols_final<COL_ABSMAX><<<col_blocks(n), kBlock, 0, s>>>(n, col_splits(h), h.dpart.p, d);
         }
         launch_factors(h, rn.p, cn.p);
         k_dense_scale<<<8192, kBlock, 0, s>>>(h.Ad.p, m, n, rn.p, cn.p);
