@@ -256,7 +256,9 @@ struct Handle {
     int32_t q_rank = 0;
     DBuf<int32_t> q_rp, q_ci;            // CSR
     DBuf<double> q_va, q_dense, q_f, q_d;  // CSR values, dense n x n, factor n x r, diagonal
-    DBuf<double> xbar, ybar, qv_in, qv, qpart, qt;
+    DBuf<double> xbar, ybar, qv_in, qv, qpart, qt;   // qv_in, qv: v and Q~ v of the next iteration
+    DBuf<double> q_ft, qpart_next;       // factor transposed, partial sums of F~'v (rank <= 32)
+    DBuf<double> qxb_in, qxb;            // checks: xbar and Q~ xbar
     // dense constraint matrix (row-major, scaled in place) and column-pass partials
     bool dense = false;
     DBuf<double> Ad, dpart;

@@ -344,6 +344,27 @@ __device__ __forceinline__ double wave_sum(double s) {
     return wave_reduce(s, [](double p, double q) { return p + q; });
 }
 
+// Eight wave sums at once: the first two butterfly steps (lane bits 5, 4) each
+// halve the values a lane carries (a lane swap pairs two values' halves), the
+// third picks one of the last two. Lane l ends with the total of
+// value 4 bit3(l) + 2 bit4(l) + bit5(l).
+__device__ __forceinline__ double wave_sum_x8(const double (&s)[8]) {
+    double a[4], b[2];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const Pair p = swap32(s[2 * i], s[2 * i + 1]);
+        a[i] = p.a + p.b;
+    }
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const Pair p = swap16(a[2 * i], a[2 * i + 1]);
+        b[i] = p.a + p.b;
+    }
+    const double c0 = b[0] + dpp_get<kDppRor + 8>(b[0]), c1 = b[1] + dpp_get<kDppRor + 8>(b[1]);
+    double c = (threadIdx.x & 8) ? c1 : c0;
+    return group_reduce(c, 3, [](double p, double q) { return p + q; });
+}
+
 // Deterministic workgroup sum of K values per thread: wave butterflies, then
 // the BT / 64 wave totals in fixed order (BT: threads of the workgroup).
 // Result written by threads 0..K-1 to out.
