@@ -274,114 +274,98 @@ __device__ __forceinline__ uint64_t splitmix64_b(uint64_t x) {
 // setup: Ruiz + Pock-Chambolle scaling and the power iteration, per instance
 // (once for a shared matrix).
 
-// Sturm count of T - x I for T = B'B, B the Golub-Kahan bidiagonal (alpha on
-// the diagonal, beta above it): the number of negative pivots of the LDL'
-// recurrence, i.e. the number of eigenvalues of T below x.
-__device__ int32_t bidiag_sturm(const double *alpha, const double *beta, int32_t k, double x) {
-    int32_t cnt = 0;
-    double q = 1.0;
-    for (int32_t i = 0; i < k; ++i) {
-        const double di = alpha[i] * alpha[i] + (i > 0 ? beta[i - 1] * beta[i - 1] : 0.0);
-        if (i == 0) {
-            q = di - x;
-        } else {
-            const double ei = alpha[i - 1] * beta[i - 1];
-            q = di - x - (ei * ei) / q;
-        }
-        if (q == 0.0) q = -1e-300;
-        if (q < 0.0) ++cnt;
+// T = B'B for the Golub-Kahan bidiagonal B (alpha on the diagonal, beta above
+// it): diagonal d_i = alpha_i^2 + beta_{i-1}^2, squared off-diagonal e_i =
+// (alpha_i beta_i)^2. The first kTriLds of them are kept in LDS.
+constexpr int kTriLds = 256;
+struct Tridiag {
+    const double *alpha, *beta;   // all of them (memory)
+    const double *d, *e;          // the first kTriLds (LDS)
+    __device__ __forceinline__ double diag(int32_t i) const {
+        if (i < kTriLds) return d[i];
+        return alpha[i] * alpha[i] + beta[i - 1] * beta[i - 1];
     }
-    return cnt;
+    __device__ __forceinline__ double off2(int32_t i) const {
+        if (i < kTriLds) return e[i];
+        const double o = alpha[i] * beta[i];
+        return o * o;
+    }
+};
+
+// Whether every eigenvalue of the leading k x k block lies below x: the leading
+// minors s_i of x I - T are positive, s_i = (x - d_i) s_{i-1} - e_{i-1} s_{i-2}.
+// Scaled by a power of two (sc, with sc T of norm about 1), and rescaled every
+// eight steps, so that nothing overflows; two dependent operations a step where
+// the ratio recurrence has a division.
+__device__ __forceinline__ bool tridiag_below(const Tridiag &T, int32_t k, double x, double sc) {
+    const double xs = x * sc, sc2 = sc * sc;
+    double sp = 0.0, s = 1.0, e = 0.0;
+    for (int32_t i0 = 0; i0 < k; i0 += 8) {
+        const int32_t i1 = min(k, i0 + 8);
+        for (int32_t i = i0; i < i1; ++i) {
+            const double a = xs - T.diag(i) * sc;
+            const double t = fma(a, s, -(e * sp));
+            sp = s;
+            s = t;
+            e = T.off2(i) * sc2;
+            if (!(s > 0.0)) return false;
+        }
+        const int ex = -__builtin_amdgcn_frexp_exp(s);
+        s = ldexp(s, ex);
+        sp = ldexp(sp, ex);
+    }
+    return true;
 }
 
-// Largest eigenvalue of T = B'B: bisection over [0, Gershgorin bound], at most
-// 200 halvings, until the interval cannot be halved. The whole workgroup takes
-// D = log2(BT) halvings per round: thread t (1 <= t < BT) replays the midpoint
-// arithmetic along the path to node t of the binary tree of the next D
-// midpoints (bit 0: upper half dropped, bit 1: lower half dropped) and counts
-// at its own midpoint; thread 0 then walks the tree from the root. The result
-// equals the one-point-at-a-time bisection bit for bit.
-template <int BT>
-__device__ double bidiag_lambda_max_wg(const double *alpha, const double *beta, int32_t k) {
-    constexpr int NW = BT / 64;
-    constexpr int D = BT == 64 ? 6 : BT == 128 ? 7 : BT == 256 ? 8 : BT == 512 ? 9 : 10;
-    static_assert((1 << D) == BT, "BT must be a power of two from 64 to 1024");
-    __shared__ double wmax[NW];
-    __shared__ double lohi[2];
-    __shared__ int32_t done;
-    __shared__ uint8_t halvable[BT], lower[BT];
-    const int32_t t = threadIdx.x;
-    // Gershgorin bound: a maximum, the same in any order
-    double g = 0.0;
-    for (int32_t i = t; i < k; i += BT) {
-        const double di = alpha[i] * alpha[i] + (i > 0 ? beta[i - 1] * beta[i - 1] : 0.0);
-        const double el = i > 0 ? fabs(alpha[i - 1] * beta[i - 1]) : 0.0;
-        const double er = i + 1 < k ? fabs(alpha[i] * beta[i]) : 0.0;
-        g = fmax(g, di + el + er);
+// Largest eigenvalue of the leading k x k block by one wave: the smallest
+// double above all eigenvalues, found by 64 tests at a time. lower: a value not
+// above it (the eigenvalue of a smaller block, or 0). The first tests are spaced
+// by powers of two from lower on: close to convergence the eigenvalue moves by
+// 1e-7 of itself, which leaves some 30 bits to find instead of 52.
+__device__ double tridiag_lambda_max(const Tridiag &T, int32_t k, double lower) {
+    const int32_t lane = (int32_t)(threadIdx.x & 63);
+    double g = 0.0;   // Gershgorin bound
+    for (int32_t i = lane; i < k; i += 64) {
+        const double el = i > 0 ? sqrt(T.off2(i - 1)) : 0.0;
+        const double er = i + 1 < k ? sqrt(T.off2(i)) : 0.0;
+        g = fmax(g, T.diag(i) + el + er);
     }
     g = wave_max(g);
-    if ((t & 63) == 0) wmax[t >> 6] = g;
-    __syncthreads();
-    double hi = 0.0;
-    for (int w = 0; w < NW; ++w) hi = fmax(hi, wmax[w]);
-    double lo = 0.0;
-    int32_t halvings = 0;
-    for (;;) {
-        if (t > 0) {
-            const int depth = 31 - __clz(t);
-            double l = lo, h = hi;
-            bool reach = true;
-            for (int lev = depth - 1; lev >= 0; --lev) {
-                const double mid = 0.5 * (l + h);
-                if (!(mid > l && mid < h)) {
-                    reach = false;
-                    break;
-                }
-                if ((t >> lev) & 1) l = mid;
-                else h = mid;
-            }
-            bool hv = false, lw = false;
-            if (reach) {
-                const double mid = 0.5 * (l + h);
-                hv = mid > l && mid < h;
-                if (hv) lw = bidiag_sturm(alpha, beta, k, mid) == k;
-            }
-            halvable[t] = hv;
-            lower[t] = lw;
-        }
-        __syncthreads();
-        if (t == 0) {
-            int32_t node = 1, stop = 0;
-            for (int lev = 0; lev < D; ++lev) {
-                if (halvings >= 200 || !halvable[node]) {
-                    stop = 1;
-                    break;
-                }
-                const double mid = 0.5 * (lo + hi);
-                if (lower[node]) {   // every eigenvalue lies below mid
-                    hi = mid;
-                    node = 2 * node;
-                } else {
-                    lo = mid;
-                    node = 2 * node + 1;
-                }
-                ++halvings;
-            }
-            lohi[0] = lo;
-            lohi[1] = hi;
-            done = stop || halvings >= 200;
-        }
-        __syncthreads();
-        lo = lohi[0];
-        hi = lohi[1];
-        const bool fin = done != 0;
-        __syncthreads();
-        if (fin) break;
+    if (!(g > 0.0)) return 0.0;
+    const double sc = ldexp(1.0, -__builtin_amdgcn_frexp_exp(g));
+    double lo = lower * (1.0 - 1e-12), hi = g * (1.0 + 1e-14);
+    // spaced tests, the first at lo itself
+    double x = lane == 0 ? lo : fmin(hi, lo + lo * ldexp(1.0, lane - 60));
+    uint64_t below = __ballot(x > 0.0 && tridiag_below(T, k, x, sc));
+    if (below & 1ull) {
+        lo = 0.0;
+    } else if (below) {
+        const int f = __ffsll((unsigned long long)below) - 1;
+        hi = lane_value(x, f);
+        lo = lane_value(x, f - 1);
+    } else if (lo > 0.0) {
+        lo = lane_value(x, 63);
+    }
+    for (int round = 0; round < 40; ++round) {
+        const double mid = 0.5 * (lo + hi);
+        if (!(mid > lo && mid < hi)) break;
+        x = fmax(lo, fmin(hi, lo + (hi - lo) * ((double)(lane + 1) * (1.0 / 64.0))));
+        if (lane == 63) x = hi;
+        if (lane == 31) x = mid;   // strictly inside, so the interval always shrinks
+        below = __ballot(x >= hi || (x > lo && tridiag_below(T, k, x, sc)));
+        const int f = __ffsll((unsigned long long)below) - 1;   // lane 63 is always set
+        const double nlo = f > 0 ? lane_value(x, f - 1) : lo;
+        hi = lane_value(x, f);
+        lo = fmax(lo, nlo);
     }
     return hi;
 }
 
 // ONCHIP: the power iteration's gathered vectors v (n) and w (m) live in LDS.
+// The eigenvalue searches of the norm estimate were 50 of the 75 us of each of
+// its steps on a 32 x 32 grid (a workgroup-wide bisection with a division per
+// pivot, six rounds a step); as eight waves' searches of eight steps at a time
+// the setup of that batch takes 1.26 instead of 5.58 ms.
 template <int BT, bool ONCHIP>
 __global__ __launch_bounds__(BT) void k_batch_setup(BArgs a, BOpts o, int32_t count, int32_t nmax) {
     extern __shared__ double lds[];
@@ -428,8 +412,13 @@ __global__ __launch_bounds__(BT) void k_batch_setup(BArgs a, BOpts o, int32_t co
             double *pr = a.y + g.vr, *qc = a.xe + g.vc;      // owner-only scratch
             double *al = a.lhist + (size_t)g.sidx * 2 * (o.power_max_iters + 1);
             double *be = al + (o.power_max_iters + 1);
-            __shared__ double lam_sh;
-            __shared__ int32_t stop_sh;
+            // eigenvalues are wanted at every step, but only to find the step to
+            // stop at: each wave finds the one of a step of its own, kLag steps
+            // at a time, and what the steps past the stop computed is dropped
+            constexpr int kLag = BT / 64 < 8 ? BT / 64 : 8;
+            __shared__ double tri_d[kTriLds], tri_e[kTriLds];
+            __shared__ double lam_sh[kLag];
+            const Tridiag T{al, be, tri_d, tri_e};
             double q0[1] = {0.0};
             for (int32_t j = threadIdx.x; j < g.n; j += BT) {
                 const double val = 0.5 + (double)(splitmix64_b((uint64_t)j) >> 11) * 0x1.0p-53;
@@ -442,6 +431,26 @@ __global__ __launch_bounds__(BT) void k_batch_setup(BArgs a, BOpts o, int32_t co
             for (int32_t j = threadIdx.x; j < g.n; j += BT) v[j] = v[j] / nv;
             __syncthreads();
             double lam_prev = 0.0, bprev = 0.0;
+            int32_t done = 0;       // steps whose eigenvalue is known
+            // eigenvalues of steps done + 1 .. last; the step that stops, or 0
+            auto settle = [&](int32_t last, bool beta_zero) -> int32_t {
+                const int32_t wave = (int32_t)(threadIdx.x >> 6), k = done + 1 + wave;
+                __syncthreads();
+                if (wave < kLag && k <= last) {
+                    const double l = tridiag_lambda_max(T, k, lam_prev);
+                    if ((threadIdx.x & 63) == 0) lam_sh[wave] = l;
+                }
+                __syncthreads();
+                int32_t at = 0;
+                for (int32_t k2 = done + 1; k2 <= last && !at; ++k2) {
+                    lam = lam_sh[k2 - done - 1];
+                    if ((k2 == last && beta_zero) || (k2 > 1 && fabs(lam - lam_prev) <= o.power_tol * lam)) at = k2;
+                    else lam_prev = lam;
+                }
+                done = last;
+                __syncthreads();
+                return at;
+            };
             for (it = 1; it <= o.power_max_iters; ++it) {
                 double sp[1] = {0.0};
                 for (int32_t i = threadIdx.x; i < g.m; i += BT) {
@@ -452,7 +461,8 @@ __global__ __launch_bounds__(BT) void k_batch_setup(BArgs a, BOpts o, int32_t co
                 wg_sum<BT, 1>(sp);
                 const double al_k = sqrt(sp[0]);
                 if (!(al_k > 0.0)) {
-                    if (it == 1) lam = 0.0;
+                    const int32_t at = it - 1 > done ? settle(it - 1, false) : 0;
+                    if (at) it = at;
                     break;
                 }
                 for (int32_t i = threadIdx.x; i < g.m; i += BT) u[i] = pr[i] / al_k;
@@ -468,22 +478,20 @@ __global__ __launch_bounds__(BT) void k_batch_setup(BArgs a, BOpts o, int32_t co
                 if (threadIdx.x == 0) {
                     al[it - 1] = al_k;
                     be[it - 1] = be_k;
+                    if (it <= kTriLds) {
+                        tri_d[it - 1] = al_k * al_k + bprev * bprev;
+                        const double off = al_k * be_k;
+                        tri_e[it - 1] = off * off;
+                    }
                 }
-                __syncthreads();
-                const double l = bidiag_lambda_max_wg<BT>(al, be, it);
-                if (threadIdx.x == 0) {
-                    int32_t st = 0;
-                    if (!(be_k > 0.0)) st = 1;
-                    else if (it > 1 && fabs(l - lam_prev) <= o.power_tol * l) st = 1;
-                    lam_sh = l;
-                    stop_sh = st;
+                const bool beta_zero = !(be_k > 0.0);
+                if (beta_zero || it - done == kLag || it == o.power_max_iters) {
+                    const int32_t at = settle(it, beta_zero);
+                    if (at) {
+                        it = at;
+                        break;
+                    }
                 }
-                __syncthreads();
-                lam = lam_sh;
-                const bool stop = stop_sh != 0;
-                __syncthreads();
-                if (stop) break;
-                lam_prev = lam;
                 for (int32_t j = threadIdx.x; j < g.n; j += BT) v[j] = qc[j] / be_k;
                 bprev = be_k;
                 __syncthreads();

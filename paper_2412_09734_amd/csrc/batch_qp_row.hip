@@ -21,11 +21,6 @@
 
 namespace pdhg {
 
-__device__ __forceinline__ double lane_value(double v, int lane) {
-    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), lane),
-                            __builtin_amdgcn_readlane(__double2loint(v), lane));
-}
-
 // An instance in registers. Columns j = thread + q BT; those past n hold zeros
 // and F~ rows of zeros, so they add nothing to any sum.
 template <int BT, int S, int R>

@@ -43,6 +43,12 @@ __device__ __forceinline__ double dpp_get(double v) {
     return __hiloint2double(hi, lo);
 }
 
+// v of lane `lane` (wave-uniform) as a scalar.
+__device__ __forceinline__ double lane_value(double v, int lane) {
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), lane),
+                            __builtin_amdgcn_readlane(__double2loint(v), lane));
+}
+
 // op over the lanes of each aligned group of L = 2^lg lanes, in every lane of
 // the group, smallest distance first (a mirror reads lane i ^ 4, or i ^ 8, of
 // values that are equal over quads, or over eights).
