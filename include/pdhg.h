@@ -368,7 +368,7 @@ pdhg_err pdhg_linear_costs_backward(int32_t B, int32_t n, int32_t p, const doubl
 /* For callers that cannot allocate device memory (code under HIP graph
  * capture, serving loops, harnesses that forbid hipMalloc): the same weight
  * gradient as pdhg_linear_costs_backward, bit for bit, with its partial sums
- * in a static 32 KB device array (64 x 64 doubles, one per GPU, held until the
+ * in a static 256 KB device array (64 x 512 doubles, one per GPU, held until the
  * process ends) instead of a buffer allocated per call. It allocates nothing
  * and returns once the work is enqueued on `stream` (no wait). Limit: p <= 64
  * (PDHG_ERR_INVALID_ARG beyond). Every call on one GPU uses that GPU's array,
