@@ -809,43 +809,21 @@ __global__ __launch_bounds__(BT) void k_batch_solve(BArgs a, BOpts o) {
     }
 }
 
-// Entries per column slice and per row slice of the register-resident matrix
-// (node-arc incidence matrices: two entries per column, node degree <= 8).
-constexpr int kResCol = 2, kResRow = 8;
-
-// A double in LDS at a byte offset from the start of the dynamic allocation.
-__device__ __forceinline__ double lds_at(const double *lds, int32_t off) {
-    return *reinterpret_cast<const double *>(reinterpret_cast<const char *>(lds) + off);
-}
-
 // Same iteration with the gathered vectors held on chip: y (for A~'y) and
 // x_ext (for A~x_ext; at checks the PDHG points) live in LDS, next to the
-// per-row anchor and bounds; each thread owns S columns and S rows (RES: S/4
-// rows), in SELL-64 slices, so a wave's slices are whole.
-//   RES = false: the matrix entries stream from the shared SELL-64 copies (L2)
-//     on every product; the per-column iterate, anchor, cost and bounds stay
-//     in registers.
-//   RES = true (a shared matrix whose column slices hold at most kResCol and
-//     row slices at most kResRow entries): every thread loads its slices'
-//     entries once per instance into registers, with each index turned into
-//     the byte offset of the LDS element it gathers, so an iteration reads no
-//     matrix data from memory: a product is LDS gathers and FMAs. The anchor,
-//     cost and upper bound of the columns move to LDS to make room.
-// Entries past a slice's width are zeros gathering element 0, which adds
-// +0 like the slices' own padding. Same arithmetic and summation order as
+// per-row anchor and bounds; each thread owns S columns and S rows, in SELL-64
+// slices, so a wave's slices are whole. The matrix entries stream from the
+// SELL-64 copies (L2) on every product; the per-column iterate, anchor, cost
+// and bounds stay in registers. Same arithmetic and summation order as
 // k_batch_solve.
-template <int BT, int S, bool RES, bool RAYS>
+template <int BT, int S, bool RAYS>
 __global__ __launch_bounds__(BT) void k_batch_solve_lds(BArgs a, BOpts o, int32_t nmax, int32_t mmax) {
-    constexpr int SR = RES ? (S >= 4 ? S / 4 : 1) : S;   // row slices per thread
     extern __shared__ double lds[];
     double *sx = lds;                 // x_ext, at checks x^
     double *sy = lds + nmax;          // y, at checks y^
     double *slc = sy + mmax;          // scaled row bounds
     double *suc = slc + mmax;
     double *y0 = suc + mmax;          // dual anchor
-    double *sx0 = y0 + mmax;          // RES: primal anchor
-    double *scr = sx0 + nmax;         // RES: scaled cost
-    double *suv = scr + nmax;         // RES: scaled upper bound
     for (;;) {
         const int32_t b = next_instance<BT>(a.queue);
         if (b >= a.B) return;
@@ -866,12 +844,9 @@ __global__ __launch_bounds__(BT) void k_batch_solve_lds(BArgs a, BOpts o, int32_
         const double eta = a.eta[g.sidx];
         const double gam = o.gamma;
 
-        // streamed: slice start and width of each owned column / row
+        // slice start and width of each owned column / row
         int32_t tbase[S], tw[S], abase[S], aw[S];
-        // resident: the owned slices' entries (LDS byte offset, value)
-        int32_t tci[S][kResCol], rci[SR][kResRow];
-        double tva[S][kResCol], rva[SR][kResRow];
-        // per-column iterate and bounds in registers (streamed: also anchor, cost)
+        // per-column iterate, anchor, cost and bounds
         double xr[S], x0r[S], cr[S], lvr[S], uvr[S];
         double nrm[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
@@ -884,7 +859,7 @@ __global__ __launch_bounds__(BT) void k_batch_solve_lds(BArgs a, BOpts o, int32_
                 tbase[q] = a.tsp[sl];
                 tw[q] = (a.tsp[sl + 1] - tbase[q]) >> 6;
             }
-            if (q < SR && j < g.m) {
+            if (j < g.m) {
                 const int32_t sl = as0 + (j >> 6);
                 abase[q] = a.asp[sl];
                 aw[q] = (a.asp[sl + 1] - abase[q]) >> 6;
@@ -893,20 +868,17 @@ __global__ __launch_bounds__(BT) void k_batch_solve_lds(BArgs a, BOpts o, int32_
                 const double d = Dc[j];
                 const double cj = d * c_o[j];
                 const double l = lv_o[j] / d, u = uv_o[j] / d;
-                if constexpr (RES) scr[j] = cj;
-                else cr[q] = cj;
+                cr[q] = cj;
                 lvr[q] = l;
-                if constexpr (RES) suv[j] = u;
-                else uvr[q] = u;
+                uvr[q] = u;
                 nrm[0] += cj * cj;
                 nrm[2] += c_o[j] * c_o[j];
                 const double v0 = a.x_init ? a.x_init[g.vc + j] / d : 0.0;
                 xr[q] = clampd(v0, l, u);
-                if constexpr (RES) sx0[j] = xr[q];
-                else x0r[q] = xr[q];
+                x0r[q] = xr[q];
             }
             const int32_t i = j;
-            if (q < SR && i < g.m) {
+            if (i < g.m) {
                 const double d = Dr[i];
                 const double l = d * lc_o[i], u = d * uc_o[i];
                 slc[i] = l;
@@ -926,68 +898,12 @@ __global__ __launch_bounds__(BT) void k_batch_solve_lds(BArgs a, BOpts o, int32_
                 y0[i] = yv;
             }
         }
-        // RES: the owned slices' entries into registers
-        auto load_matrix = [&]() {
-            if constexpr (RES) {
-#pragma unroll
-                for (int q = 0; q < S; ++q) {
-#pragma unroll
-                    for (int u = 0; u < kResCol; ++u) {
-                        const bool in = u < tw[q];
-                        const int32_t e = tbase[q] + 64 * u + lane;
-                        tci[q][u] = 8 * (nmax + (in ? tsci[e] : 0));
-                        tva[q][u] = in ? tsva[e] : 0.0;
-                    }
-                }
-#pragma unroll
-                for (int q = 0; q < SR; ++q) {
-#pragma unroll
-                    for (int u = 0; u < kResRow; ++u) {
-                        const bool in = u < aw[q];
-                        const int32_t e = abase[q] + 64 * u + lane;
-                        rci[q][u] = 8 * (in ? asci[e] : 0);
-                        rva[q][u] = in ? asva[e] : 0.0;
-                    }
-                }
-            }
-        };
-        load_matrix();
         // A~'y (gathering y from LDS) for owned column q; A~x_ext for owned row q
         auto col_dot = [&](int q) -> double {
-            if constexpr (RES) {
-                double s = 0.0;
-#pragma unroll
-                for (int u = 0; u < kResCol; ++u) s = fma(tva[q][u], lds_at(lds, tci[q][u]), s);
-                return s;
-            } else {
-                return sell_dot_bw(tsci, tsva, tbase[q], tw[q], lane, sy);
-            }
+            return sell_dot_bw(tsci, tsva, tbase[q], tw[q], lane, sy);
         };
         auto row_dot = [&](int q) -> double {
-            if constexpr (RES) {
-                double s = 0.0;
-#pragma unroll
-                for (int u = 0; u < kResRow; ++u) s = fma(rva[q][u], lds_at(lds, rci[q][u]), s);
-                return s;
-            } else {
-                return sell_dot_bw(asci, asva, abase[q], aw[q], lane, sx);
-            }
-        };
-        auto x0_of = [&](int q, int32_t j) -> double {
-            if constexpr (RES) return sx0[j];
-            else return x0r[q];
-        };
-        auto set_x0 = [&](int q, int32_t j, double v) {
-            if constexpr (RES) sx0[j] = v;
-            else x0r[q] = v;
-        };
-        auto c_of = [&](int q, int32_t j) -> double {
-            if constexpr (RES) return scr[j];
-            else return cr[q];
-        };
-        auto uv_of = [&](int q, int32_t j) -> double {
-            if constexpr (RES) return suv[j];
-            else return uvr[q];
+            return sell_dot_bw(asci, asva, abase[q], aw[q], lane, sx);
         };
         wg_sum<BT, 4>(nrm);
         const double cn = sqrt(nrm[0]), bn = sqrt(nrm[1]);
@@ -1017,19 +933,19 @@ __global__ __launch_bounds__(BT) void k_batch_solve_lds(BArgs a, BOpts o, int32_
                 const int32_t j = tid + q * BT;
                 if (j < g.n) {
                     const double s = col_dot(q);
-                    const double xhat = clampd(xr[q] - tau * (c_of(q, j) - s), lvr[q], uv_of(q, j));
+                    const double xhat = clampd(xr[q] - tau * (cr[q] - s), lvr[q], uvr[q]);
                     sx[j] = 2.0 * xhat - xr[q];
                     if (keep) {
                         xh[j] = xhat;
                         aty[j] = s;
                     } else {
-                        xr[q] = ak * ((1.0 + gam) * xhat - gam * xr[q]) + bk * x0_of(q, j);
+                        xr[q] = ak * ((1.0 + gam) * xhat - gam * xr[q]) + bk * x0r[q];
                     }
                 }
             }
             __syncthreads();
 #pragma unroll
-            for (int q = 0; q < SR; ++q) {
+            for (int q = 0; q < S; ++q) {
                 const int32_t i = tid + q * BT;
                 if (i < g.m) {
                     const double av = row_dot(q);
@@ -1056,7 +972,7 @@ __global__ __launch_bounds__(BT) void k_batch_solve_lds(BArgs a, BOpts o, int32_
             for (int q = 0; q < S; ++q) {
                 const int32_t j = tid + q * BT;
                 if (j < g.n) sx[j] = xh[j];
-                if (q < SR && j < g.m) sy[j] = yh[j];
+                if (j < g.m) sy[j] = yh[j];
             }
             __syncthreads();
             // KKT sums, then (RAYS) the ray sums: v[10], v[11] over the columns
@@ -1074,7 +990,7 @@ __global__ __launch_bounds__(BT) void k_batch_solve_lds(BArgs a, BOpts o, int32_
                     const double dx = xhv - xr[q];
                     v[0] += dx * dx;
                     v[1] += (qq - aty[j]) * dx;
-                    const double d0 = xhv - x0_of(q, j);
+                    const double d0 = xhv - x0r[q];
                     v[2] += d0 * d0;
                     const double d = Dc[j];
                     const double gr = c_o[j] - qq / d;
@@ -1088,7 +1004,7 @@ __global__ __launch_bounds__(BT) void k_batch_solve_lds(BArgs a, BOpts o, int32_
                     if constexpr (RAYS) {
                         a.qh[g.vc + j] = qq;
                         double s2[2], m2[2];
-                        ray_col_terms(qq, a.q0[g.vc + j], d, xhv - x0_of(q, j), c_o[j], lo, hi, s2, m2);
+                        ray_col_terms(qq, a.q0[g.vc + j], d, xhv - x0r[q], c_o[j], lo, hi, s2, m2);
                         v[10] += s2[0];
                         v[11] += s2[1];
                         rmx[0] = fmax(rmx[0], m2[0]);
@@ -1097,7 +1013,7 @@ __global__ __launch_bounds__(BT) void k_batch_solve_lds(BArgs a, BOpts o, int32_
                 }
             }
 #pragma unroll
-            for (int q = 0; q < SR; ++q) {
+            for (int q = 0; q < S; ++q) {
                 const int32_t i = tid + q * BT;
                 if (i < g.m) {
                     const double p = row_dot(q);
@@ -1184,9 +1100,9 @@ __global__ __launch_bounds__(BT) void k_batch_solve_lds(BArgs a, BOpts o, int32_
                     const int32_t j = tid + q * BT;
                     if (j < g.n) {
                         xr[q] = xh[j];
-                        set_x0(q, j, xr[q]);
+                        x0r[q] = xr[q];
                     }
-                    if (q < SR && j < g.m) {
+                    if (j < g.m) {
                         sy[j] = yh[j];
                         y0[j] = yh[j];
                     }
@@ -1206,8 +1122,8 @@ __global__ __launch_bounds__(BT) void k_batch_solve_lds(BArgs a, BOpts o, int32_
 #pragma unroll
                 for (int q = 0; q < S; ++q) {
                     const int32_t j = tid + q * BT;
-                    if (j < g.n) xr[q] = ak * ((1.0 + gam) * xh[j] - gam * xr[q]) + bk * x0_of(q, j);
-                    if (q < SR && j < g.m) sy[j] = ak * ((1.0 + gam) * yh[j] - gam * y[j]) + bk * y0[j];
+                    if (j < g.n) xr[q] = ak * ((1.0 + gam) * xh[j] - gam * xr[q]) + bk * x0r[q];
+                    if (j < g.m) sy[j] = ak * ((1.0 + gam) * yh[j] - gam * y[j]) + bk * y0[j];
                 }
                 ++k;
             }
@@ -1220,8 +1136,8 @@ __global__ __launch_bounds__(BT) void k_batch_solve_lds(BArgs a, BOpts o, int32_
 #pragma unroll
         for (int q = 0; q < S; ++q) {
             const int32_t j = threadIdx.x + q * BT;
-            if (j < g.n) a.x_out[g.vc + j] = Dc[j] * (xray ? (xh[j] - x0_of(q, j)) * ray_scale : xh[j]);
-            if (q < SR && j < g.m) a.y_out[g.vr + j] = Dr[j] * (yray ? (yh[j] - y0[j]) * ray_scale : yh[j]);
+            if (j < g.n) a.x_out[g.vc + j] = Dc[j] * (xray ? (xh[j] - x0r[q]) * ray_scale : xh[j]);
+            if (j < g.m) a.y_out[g.vr + j] = Dr[j] * (yray ? (yh[j] - y0[j]) * ray_scale : yh[j]);
         }
         if (threadIdx.x == 0) {
             BatchRes r;
@@ -1237,6 +1153,499 @@ __global__ __launch_bounds__(BT) void k_batch_solve_lds(BArgs a, BOpts o, int32_
             r.restarts = restarts;
             r.status = status;
             r.power_iters = a.power_iters[g.sidx];
+            a.res[b] = r;
+        }
+        __syncthreads();
+    }
+}
+
+// ---------------------------------------------------------------------------
+// solve with a register-resident matrix
+
+// Entries per column slice and per row slice of the register-resident matrix
+// (node-arc incidence matrices: two entries per column, node degree <= 8).
+constexpr int kResCol = 2, kResRow = 8;
+
+// A double in LDS at a byte offset from the start of the dynamic allocation.
+__device__ __forceinline__ double lds_at(const double *lds, int32_t off) {
+    return *reinterpret_cast<const double *>(reinterpret_cast<const char *>(lds) + off);
+}
+
+// LDS of k_batch_solve_res, in doubles: y and y0 of the owned rows and x_ext
+// and x0 of the owned columns (whole slots, so slots past the end need no
+// test; one pad double after every 32 columns, see res_pos), and the momentum
+// factors of kResSteps iterations.
+constexpr int kResSteps = 64;
+
+// An element of the LDS: kept as the 32-bit address itself, a gather is one
+// instruction without address arithmetic.
+typedef __attribute__((address_space(3))) double LdsDouble;
+
+// clampd without the two instructions that fmin / fmax spend on quieting a
+// signalling NaN among loaded bounds (none reaches here: bounds are results
+// of products and quotients).
+__device__ __forceinline__ double clamp_quiet(double v, double lo, double hi) {
+    double r;
+    asm("v_max_f64 %0, %1, %2" : "=v"(r) : "v"(v), "v"(lo));
+    asm("v_min_f64 %0, %1, %2" : "=v"(r) : "v"(r), "v"(hi));
+    return r;
+}
+
+// LDS element of column j. A row's entries are often a fixed stride apart
+// from the next row's (4 for the out-arcs of grid nodes), which would put a
+// wave's gathers on a few banks; the pad shifts every 32 columns by one.
+__host__ __device__ constexpr int32_t res_pos(int32_t j) { return j + (j >> 5); }
+
+// A value that is the same in every lane, as a scalar.
+__device__ __forceinline__ double uniform_value(double v) { return lane_value(v, 0); }
+
+template <int BT, int S>
+struct ResLds {
+    static constexpr int SR = S >= 4 ? S / 4 : 1;   // row slots per thread
+    static constexpr int32_t y0 = SR * BT;
+    static constexpr int32_t x = 2 * SR * BT;
+    static constexpr int32_t x0 = x + S * res_pos(BT);
+    static constexpr int32_t aty = x0 + S * res_pos(BT);   // A~'y of the iteration before a check
+    static constexpr int32_t step = aty + S * BT;
+    static constexpr size_t bytes = ((size_t)step + 4 * kResSteps) * sizeof(double);
+};
+
+// The iteration of k_batch_solve for a shared matrix whose column slices hold
+// at most kResCol entries and row slices at most kResRow (node-arc incidence
+// matrices: two entries per column, node degree <= 8); S columns and SR rows
+// per thread. Everything an instance needs stays in registers for its whole
+// solve - the entries of the owned columns and rows, each index turned into
+// the LDS address of what it gathers, and x, x0, c~, l~, u~, y, y0 and the
+// clamp bounds of the dual step - except the gathered vectors in LDS. The
+// loop has no branch per slot (slots past the end work on zeros and write
+// into LDS nobody gathers), so all gathers of a phase are in flight at once;
+// the momentum factors come from a table that the first wave's lanes fill for
+// kResSteps iterations at a time, and the dual step is w = y - sigma a,
+// y^ = w - clamp(w, -sigma u_c, -sigma l_c): no division is left in the loop.
+// Checks work on the same registers: c_j x_j and l_j lambda_j are the same
+// products in scaled space, the products of the anchor that the rays compare
+// with are gathered again from x0 and y0 in LDS, and only D_c, D_r, the row
+// bounds and (afterwards) the row entries are read from memory.
+//
+// What bounds it: at 32x32 grids (3,968 columns, 1,024 rows; 512 threads, 8
+// columns and 2 rows each) an iteration issues 960 wave instructions and keeps
+// the LDS busy for 1,400 cycles, which the two barriers put one after the
+// other: 0.99 us, and 1.23 us with a check every 64 iterations. Streaming the
+// row bounds, cost and anchor from LDS with a branch per slot and four
+// divisions took 2.82 us (2,650 wave instructions, 2,350 LDS cycles, 1,000 of
+// them bank conflicts). Checks in rolled loops from memory cost 58 us each,
+// at 1,024 threads 146 us of spills: hence 512 threads at most.
+template <int BT, int S>
+__global__ __launch_bounds__(BT) void k_batch_solve_res(BArgs a, BOpts o) {
+    using L = ResLds<BT, S>;
+    constexpr int SR = L::SR;
+    constexpr int PX = res_pos(BT);   // LDS elements per column slot
+    extern __shared__ double lds[];
+    LdsDouble *const sy = (LdsDouble *)lds, *const sx = sy + L::x, *const stp = sy + L::step;
+    for (;;) {
+        const int32_t b = next_instance<BT>(a.queue);
+        if (b >= a.B) return;
+        const Geo g = geometry(a, b);
+        const double *Dr = a.Dr, *Dc = a.Dc;
+        const double eta = a.eta[0];
+        const double gam = o.gamma;
+        const LdsDouble *tci[S][kResCol], *rci[SR][kResRow];
+        double tva[S][kResCol], rva[SR][kResRow];
+        double xr[S], x0r[S], cr[S], lr[S], ur[S];
+        double yr[SR], y0r[SR], lo[SR], hi[SR];   // lo, hi: -sigma u_c, -sigma l_c
+        LdsDouble *const myx = sx + res_pos((int32_t)threadIdx.x), *const myy = sy + (int32_t)threadIdx.x;
+        LdsDouble *const myx0 = myx + (L::x0 - L::x), *const myaty = myy + L::aty;
+
+        // entries, scaled data, norms, initial point
+        double nrm[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int q = 0; q < S; ++q) {
+            const int32_t j = (int32_t)threadIdx.x + q * BT;
+            xr[q] = x0r[q] = cr[q] = lr[q] = ur[q] = 0.0;
+            int32_t e0 = 0, w = 0;
+            if (j < g.n) {
+                e0 = a.tsp[j >> 6];
+                w = (a.tsp[(j >> 6) + 1] - e0) >> 6;
+                const double d = Dc[j], co = a.c_o[g.vc + j];
+                cr[q] = d * co;
+                lr[q] = a.lv_o[g.vc + j] / d;
+                ur[q] = a.uv_o[g.vc + j] / d;
+                nrm[0] += cr[q] * cr[q];
+                nrm[2] += co * co;
+                xr[q] = clampd(a.x_init ? a.x_init[g.vc + j] / d : 0.0, lr[q], ur[q]);
+                x0r[q] = xr[q];
+            }
+#pragma unroll
+            for (int u = 0; u < kResCol; ++u) {
+                const bool in = u < w;
+                const int32_t e = e0 + 64 * u + (j & 63);
+                tci[q][u] = sy + (in ? a.tsci[e] : 0);
+                tva[q][u] = in ? a.tsva[e] : 0.0;
+            }
+            myx0[q * PX] = x0r[q];
+        }
+#pragma unroll
+        for (int q = 0; q < SR; ++q) {
+            const int32_t i = (int32_t)threadIdx.x + q * BT;
+            yr[q] = y0r[q] = lo[q] = hi[q] = 0.0;
+            if (i < g.m) {
+                const double d = Dr[i], loo = a.lc_o[g.vr + i], hio = a.uc_o[g.vr + i];
+                const double l = d * loo, u = d * hio;
+                double bb = 0.0, bo = 0.0;
+                if (isfinite(l)) bb = fmax(bb, fabs(l));
+                if (isfinite(u)) bb = fmax(bb, fabs(u));
+                if (isfinite(loo)) bo = fmax(bo, fabs(loo));
+                if (isfinite(hio)) bo = fmax(bo, fabs(hio));
+                nrm[1] += bb * bb;
+                nrm[3] += bo * bo;
+                yr[q] = clampd(a.y_init ? a.y_init[g.vr + i] / d : 0.0, isfinite(u) ? -INFINITY : 0.0,
+                               isfinite(l) ? INFINITY : 0.0);
+                y0r[q] = yr[q];
+            }
+            myy[q * BT] = yr[q];
+            myy[L::y0 + q * BT] = yr[q];
+        }
+        wg_sum<BT, 4>(nrm);
+        // what all threads know lives in scalar registers
+        const double cn = sqrt(nrm[0]), bn = sqrt(nrm[1]);
+        const double cnorm = uniform_value(sqrt(nrm[2])), bnorm = uniform_value(sqrt(nrm[3]));
+        double omega = uniform_value((cn > 1e-10 && bn > 1e-10) ? cn / bn : 1.0);
+        double tau = uniform_value(eta / omega), sigma = uniform_value(eta * omega);
+        // entries of the owned rows
+        auto load_rows = [&]() {
+            int32_t t0 = (int32_t)threadIdx.x;
+            asm volatile("" : "+v"(t0));
+#pragma unroll
+            for (int q = 0; q < SR; ++q) {
+                const int32_t i = t0 + q * BT;
+                int32_t e0 = 0, w = 0;
+                if (i < g.m) {
+                    e0 = a.asp[i >> 6];
+                    w = (a.asp[(i >> 6) + 1] - e0) >> 6;
+                }
+#pragma unroll
+                for (int u = 0; u < kResRow; ++u) {
+                    const bool in = u < w;
+                    const int32_t e = e0 + 64 * u + (i & 63);
+                    rci[q][u] = sx + res_pos(in ? a.asci[e] : 0);
+                    rva[q][u] = in ? a.asva[e] : 0.0;
+                }
+            }
+        };
+        load_rows();
+        // clamp bounds of the dual step at this sigma
+        auto dual_bounds = [&]() {
+            int32_t t0 = (int32_t)threadIdx.x;
+            asm volatile("" : "+v"(t0));
+#pragma unroll
+            for (int q = 0; q < SR; ++q) {
+                const int32_t i = t0 + q * BT;
+                if (i < g.m) {
+                    lo[q] = -sigma * (Dr[i] * a.uc_o[g.vr + i]);
+                    hi[q] = -sigma * (Dr[i] * a.lc_o[g.vr + i]);
+                }
+            }
+        };
+        dual_bounds();
+
+        // (A~'v)_j of owned column q, v = y (off 0) or y0 in LDS; (A~v)_i of
+        // owned row q, v = x_ext (off 0) or x0
+        auto col_dot = [&](int q, int off) {
+            double s = 0.0;
+#pragma unroll
+            for (int u = 0; u < kResCol; ++u) s = fma(tva[q][u], tci[q][u][off], s);
+            return s;
+        };
+        auto row_dot = [&](int q, int off) {
+            double s = 0.0;
+#pragma unroll
+            for (int u = 0; u < kResRow; ++u) s = fma(rva[q][u], rci[q][u][off], s);
+            return s;
+        };
+        // x^ of the owned columns and s = A~'y, x_ext to LDS; y^ of the owned
+        // rows. All of a phase's gathers are in flight before its products.
+        auto columns = [&](double (&s)[S], double (&xn)[S]) {
+            double gy[S][kResCol];
+#pragma unroll
+            for (int q = 0; q < S; ++q)
+#pragma unroll
+                for (int u = 0; u < kResCol; ++u) gy[q][u] = *tci[q][u];
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int q = 0; q < S; ++q) {
+                s[q] = 0.0;
+#pragma unroll
+                for (int u = 0; u < kResCol; ++u) s[q] = fma(tva[q][u], gy[q][u], s[q]);
+                xn[q] = clamp_quiet(xr[q] - tau * (cr[q] - s[q]), lr[q], ur[q]);
+                myx[q * PX] = 2.0 * xn[q] - xr[q];
+            }
+        };
+        auto rows = [&](double (&yn)[SR]) {
+            double gx[SR][kResRow];
+#pragma unroll
+            for (int q = 0; q < SR; ++q)
+#pragma unroll
+                for (int u = 0; u < kResRow; ++u) gx[q][u] = *rci[q][u];
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int q = 0; q < SR; ++q) {
+                double s = 0.0;
+#pragma unroll
+                for (int u = 0; u < kResRow; ++u) s = fma(rva[q][u], gx[q][u], s);
+                const double w = fma(-sigma, s, yr[q]);
+                yn[q] = w - clamp_quiet(w, lo[q], hi[q]);
+            }
+        };
+
+        int64_t t = 0, k = 0, restarts = 0;
+        int32_t tc = 0;   // t modulo check_every
+        double r_start = 0.0, r_prev = 0.0;
+        int32_t status = 0;
+        bool anchor_valid = false;   // x0, y0 are the point of a restart
+        double ray_scale = 0.0;
+        double kkt = 0.0, rel_p = 0.0, rel_d = 0.0, rel_g = 0.0, P = 0.0, D = 0.0;
+        for (;;) {
+            // iterations t .. t + plain - 1 run without a check, then one that
+            // keeps its PDHG point for the check
+            int32_t plain = tc == 0 ? 0 : o.check_every - tc;
+            if ((int64_t)plain > o.limit - 1 - t) plain = (int32_t)(o.limit - 1 - t);
+            plain = __builtin_amdgcn_readfirstlane(plain);
+            for (int32_t p = 0; p < plain; p += kResSteps) {
+                const int32_t cnt = plain - p < kResSteps ? plain - p : kResSteps;
+                // x <- A x^ - G x + B x0 in iterations p .. p + cnt - 1
+                if ((int32_t)threadIdx.x < cnt) {
+                    const int32_t u = (int32_t)threadIdx.x;
+                    const double kk = (double)(k + p + u);
+                    const double ak = (kk + 1.0) / (kk + 2.0);
+                    stp[4 * u] = ak * (1.0 + gam);
+                    stp[4 * u + 1] = ak * gam;
+                    stp[4 * u + 2] = 1.0 / (kk + 2.0);
+                }
+                __syncthreads();
+#pragma unroll 1
+                for (int32_t it = 0; it < cnt; ++it) {
+                    const double A = stp[4 * it], G = stp[4 * it + 1], B = stp[4 * it + 2];
+                    double s[S], xn[S], yn[SR];
+                    columns(s, xn);
+#pragma unroll
+                    for (int q = 0; q < S; ++q) xr[q] = A * xn[q] - G * xr[q] + B * x0r[q];
+                    __syncthreads();
+                    rows(yn);
+#pragma unroll
+                    for (int q = 0; q < SR; ++q) {
+                        yr[q] = A * yn[q] - G * yr[q] + B * y0r[q];
+                        myy[q * BT] = yr[q];
+                    }
+                    __syncthreads();
+                }
+            }
+            t += plain;
+            k += plain;
+            const bool last = t + 1 >= o.limit;
+            // the iteration before the check: its PDHG point replaces x_ext and y in LDS
+            {
+                double s[S], xn[S], yn[SR];
+                columns(s, xn);
+#pragma unroll
+                for (int q = 0; q < S; ++q) myaty[q * BT] = s[q];
+                __syncthreads();
+                rows(yn);
+                __syncthreads();
+#pragma unroll
+                for (int q = 0; q < S; ++q) myx[q * PX] = xn[q];
+#pragma unroll
+                for (int q = 0; q < SR; ++q) myy[q * BT] = yn[q];
+            }
+            __syncthreads();
+            // KKT sums, then the ray sums: v[10], v[11] over the columns
+            // (bound terms, c'dx), v[12] over the rows; rmx the ray violations
+            int32_t t0 = (int32_t)threadIdx.x;
+            asm volatile("" : "+v"(t0));   // addresses are formed here, not kept over the loop
+            const bool rays = o.detect && anchor_valid;
+            double v[13], rmx[2] = {0.0, 0.0};
+#pragma unroll
+            for (int q = 0; q < 13; ++q) v[q] = 0.0;
+            // one slot at a time, x^, x0, y^, y0 from LDS, the rows first: their
+            // entries are loaded again after the check, so that the columns'
+            // terms have room beside the registers that live on
+#pragma unroll
+            for (int q = 0; q < SR; ++q) {
+                const int32_t i = t0 + q * BT;
+                if (i < g.m) {
+                    const double d = Dr[i], loo = a.lc_o[g.vr + i], hio = a.uc_o[g.vr + i], yh = myy[q * BT];
+                    const double p = row_dot(q, 0);
+                    const double ax = p / d;
+                    const double rpr = ax - clampd(ax, loo, hio);
+                    v[6] += rpr * rpr;
+                    const double yo = d * yh;
+                    v[7] += (isfinite(loo) ? loo * fmax(yo, 0.0) : 0.0) - (isfinite(hio) ? hio * fmax(-yo, 0.0) : 0.0);
+                    const double dy = yh - yr[q];
+                    v[8] += dy * dy;
+                    const double d0 = yh - myy[L::y0 + q * BT];
+                    v[9] += d0 * d0;
+                    if (rays) {
+                        double s1[1], m2[2];
+                        ray_row_terms(p, row_dot(q, L::x0 - L::x), d, d0, loo, hio, s1, m2);
+                        v[12] += s1[0];
+                        rmx[0] = fmax(rmx[0], m2[0]);
+                        rmx[1] = fmax(rmx[1], m2[1]);
+                    }
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+#pragma unroll
+            for (int q = 0; q < S; ++q) {
+                const int32_t j = t0 + q * BT;
+                if (j < g.n) {
+                    const double d = Dc[j], xh = myx[q * PX];
+                    const double qq = col_dot(q, 0);
+                    const double dx = xh - xr[q];
+                    v[0] += dx * dx;
+                    v[1] += (qq - myaty[q * BT]) * dx;
+                    const double d0 = xh - myx0[q * PX];
+                    v[2] += d0 * d0;
+                    const double gr = cr[q] - qq;   // D_c times the original-space gradient
+                    const bool lf = isfinite(lr[q]), uf = isfinite(ur[q]);
+                    const double lam = (!lf && !uf) ? 0.0 : (lf && !uf) ? fmax(gr, 0.0) : (!lf && uf) ? fmin(gr, 0.0) : gr;
+                    const double rd = (gr - lam) / d;
+                    v[3] += rd * rd;
+                    v[4] += cr[q] * xh;
+                    v[5] += (lf ? lr[q] * fmax(lam, 0.0) : 0.0) - (uf ? ur[q] * fmax(-lam, 0.0) : 0.0);
+                    if (rays) {
+                        double s2[2], m2[2];
+                        ray_col_terms(qq, col_dot(q, L::y0), d, d0, cr[q] / d, lr[q] * d, ur[q] * d, s2, m2);
+                        v[10] += s2[0];
+                        v[11] += s2[1];
+                        rmx[0] = fmax(rmx[0], m2[0]);
+                        rmx[1] = fmax(rmx[1], m2[1]);
+                    }
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            wg_sum<BT, 13>(v);
+            P = uniform_value(v[4]);
+            D = uniform_value(v[7] + v[5]);
+            rel_p = uniform_value(sqrt(v[6]) / (1.0 + bnorm));
+            rel_d = uniform_value(sqrt(v[3]) / (1.0 + cnorm));
+            rel_g = uniform_value(fabs(P - D) / (1.0 + fabs(P) + fabs(D)));
+            kkt = rel_p;
+            if (rel_d > kkt || isnan(rel_d)) kkt = rel_d;
+            if (rel_g > kkt || isnan(rel_g)) kkt = rel_g;
+            if (isnan(kkt)) {
+                status = PDHG_NUMERICAL_ERROR;
+                break;
+            }
+            if (kkt <= o.eps) {
+                status = PDHG_OPTIMAL;
+                break;
+            }
+            if (rays) {
+                wg_max<BT, 2>(rmx);
+                const double obj_d = v[10] + v[12], obj_p = v[11];
+                if (o.eps_pinf > 0.0 && obj_d > 0.0 && rmx[0] <= o.eps_pinf * obj_d) {
+                    status = PDHG_PRIMAL_INFEASIBLE;
+                    ray_scale = uniform_value(1.0 / obj_d);
+                    break;
+                }
+                if (o.eps_dinf > 0.0 && obj_p < 0.0 && rmx[1] <= o.eps_dinf * (-obj_p)) {
+                    status = PDHG_DUAL_INFEASIBLE;
+                    ray_scale = uniform_value(-1.0 / obj_p);
+                    break;
+                }
+            }
+            if (last) {
+                status = PDHG_ITERATION_LIMIT;
+                break;
+            }
+            const double r2 = v[0] / tau + v[8] / sigma + 2.0 * v[1];
+            const double r = uniform_value(r2 > 0.0 ? sqrt(r2) : 0.0);
+            bool restart = false;
+            if (t == 0) {
+                r_start = r;
+                r_prev = r;
+            } else if (r <= o.beta_suff * r_start || (r <= o.beta_nec * r_start && r > r_prev) ||
+                       (double)k >= o.beta_art * (double)t) {
+                restart = true;
+            } else {
+                r_prev = r;
+            }
+            if (restart) {
+                // exp(log(dyr / dxr) / 2 + log(omega) / 2), without a call that
+                // would save half of the registers
+                const double dxr = sqrt(v[2]), dyr = sqrt(v[9]);
+                if (dxr > 1e-10 && dyr > 1e-10) omega = uniform_value(sqrt(dyr / dxr) * sqrt(omega));
+                tau = uniform_value(eta / omega);
+                sigma = uniform_value(eta * omega);
+#pragma unroll
+                for (int q = 0; q < S; ++q) {
+                    xr[q] = myx[q * PX];
+                    x0r[q] = xr[q];
+                    myx0[q * PX] = xr[q];
+                }
+#pragma unroll
+                for (int q = 0; q < SR; ++q) {
+                    yr[q] = myy[q * BT];
+                    y0r[q] = yr[q];
+                    myy[L::y0 + q * BT] = yr[q];
+                }
+                dual_bounds();
+                anchor_valid = true;
+                k = 0;
+                r_start = r;
+                r_prev = r;
+                ++restarts;
+            } else {
+                const double kk = (double)k;
+                const double ak = (kk + 1.0) / (kk + 2.0), B = 1.0 / (kk + 2.0);
+                const double A = ak * (1.0 + gam), G = ak * gam;
+#pragma unroll
+                for (int q = 0; q < S; ++q) {
+                    x0r[q] = myx0[q * PX];
+                    xr[q] = A * myx[q * PX] - G * xr[q] + B * x0r[q];
+                }
+#pragma unroll
+                for (int q = 0; q < SR; ++q) {
+                    y0r[q] = myy[L::y0 + q * BT];
+                    yr[q] = A * myy[q * BT] - G * yr[q] + B * y0r[q];
+                    myy[q * BT] = yr[q];
+                }
+                ++k;
+            }
+            load_rows();
+            ++t;
+            tc = o.check_every == 1 ? 0 : 1;
+            __syncthreads();
+        }
+        // original-space output of the last PDHG point, or the certifying ray
+        const bool xray = status == PDHG_DUAL_INFEASIBLE, yray = status == PDHG_PRIMAL_INFEASIBLE;
+        int32_t t0 = (int32_t)threadIdx.x;
+        asm volatile("" : "+v"(t0));
+#pragma unroll
+        for (int q = 0; q < S; ++q) {
+            const int32_t j = t0 + q * BT;
+            const double xh = myx[q * PX];
+            if (j < g.n) a.x_out[g.vc + j] = Dc[j] * (xray ? (xh - myx0[q * PX]) * ray_scale : xh);
+        }
+#pragma unroll
+        for (int q = 0; q < SR; ++q) {
+            const int32_t i = t0 + q * BT;
+            const double yh = myy[q * BT];
+            if (i < g.m) a.y_out[g.vr + i] = Dr[i] * (yray ? (yh - myy[L::y0 + q * BT]) * ray_scale : yh);
+        }
+        if (threadIdx.x == 0) {
+            BatchRes r;
+            r.pobj = P;
+            r.dobj = D;
+            r.rel_p = rel_p;
+            r.rel_d = rel_d;
+            r.rel_g = rel_g;
+            r.kkt = kkt;
+            r.omega = omega;
+            r.eta = eta;
+            r.iterations = t + 1;
+            r.restarts = restarts;
+            r.status = status;
+            r.power_iters = a.power_iters[0];
             a.res[b] = r;
         }
         __syncthreads();
@@ -2171,10 +2580,57 @@ static int res_columns(const BatchHandle &h) {
     return 0;
 }
 
-template <int BT, int S, bool RES>
+template <int BT, class K>
+static int32_t resident_lds(BatchHandle &h, K kernel, size_t lds) {
+    int dev = 0, per_cu = 0;
+    PDHG_HIP(hipGetDevice(&dev));
+    hipDeviceProp_t prop;
+    PDHG_HIP(hipGetDeviceProperties(&prop, dev));
+    PDHG_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void *>(kernel), BT, lds));
+    int32_t wg = std::min(h.B, std::max(1, per_cu) * prop.multiProcessorCount);
+    if (h.workgroups > 0) wg = std::min(wg, h.workgroups);
+    return wg;
+}
+
+// Columns per thread of k_batch_solve_res at bt threads, or 0 when the batch
+// does not qualify: a shared matrix with narrow slices, 256 or 512 threads
+// (1,024 would leave 128 registers each and spill) and one row per thread, two
+// at 8 columns.
+static int res_solve_columns(const BatchHandle &h, int32_t bt) {
+    if (!(h.onchip && h.resident && h.shared && h.ts_wmax >= 1 && h.ts_wmax <= kResCol &&
+          h.as_wmax <= kResRow && (bt == 256 || bt == 512)))
+        return 0;
+    if (h.nmax <= 2 * bt && h.mmax <= bt) return 2;
+    if (h.nmax <= 4 * bt && h.mmax <= bt) return 4;
+    if (h.nmax <= 8 * bt && h.mmax <= 2 * bt) return 8;
+    return 0;
+}
+
+// Threads of k_batch_solve_res when the caller chose none, 0 where it does not
+// apply: 256 while that gives a thread at most 4 columns, else 512. Measured
+// per iteration of 256 instances, 2,048 in the batch: 16x16 grids (960
+// columns) 0.33 us at 256 and 0.52 at 512; 22x22 grids (1,848 columns) 0.79 at
+// 256 and 0.62 at 512.
+static int32_t res_solve_threads(const BatchHandle &h) {
+    const int s = res_solve_columns(h, 256);
+    if (s > 0 && s <= 4) return 256;
+    return res_solve_columns(h, 512) > 0 ? 512 : 0;
+}
+
+template <int BT, int S>
+static void launch_solve_res_t(BatchHandle &h, const BOpts &o, const BArgs &a) {
+    constexpr size_t lds = ResLds<BT, S>::bytes;
+    static_assert(lds <= 128 * 1024, "the reductions need LDS of their own");
+    const int32_t wg = resident_lds<BT>(h, &k_batch_solve_res<BT, S>, lds);
+    PDHG_HIP(hipMemsetAsync(h.queue.p, 0, sizeof(int32_t), h.stream));
+    k_batch_solve_res<BT, S><<<wg, BT, lds, h.stream>>>(a, o);
+    PDHG_HIP(hipGetLastError());
+}
+
+template <int BT, int S>
 static void launch_solve_lds_t(BatchHandle &h, const BOpts &o, BArgs a, size_t lds) {
-    const void *kern = o.detect ? reinterpret_cast<const void *>(&k_batch_solve_lds<BT, S, RES, true>)
-                                : reinterpret_cast<const void *>(&k_batch_solve_lds<BT, S, RES, false>);
+    const void *kern = o.detect ? reinterpret_cast<const void *>(&k_batch_solve_lds<BT, S, true>)
+                                : reinterpret_cast<const void *>(&k_batch_solve_lds<BT, S, false>);
     int dev = 0, per_cu = 0;
     PDHG_HIP(hipGetDevice(&dev));
     hipDeviceProp_t prop;
@@ -2184,9 +2640,9 @@ static void launch_solve_lds_t(BatchHandle &h, const BOpts &o, BArgs a, size_t l
     if (h.workgroups > 0) wg = std::min(wg, h.workgroups);
     PDHG_HIP(hipMemsetAsync(h.queue.p, 0, sizeof(int32_t), h.stream));
     if (o.detect)
-        k_batch_solve_lds<BT, S, RES, true><<<wg, BT, lds, h.stream>>>(a, o, h.nmax, h.mmax);
+        k_batch_solve_lds<BT, S, true><<<wg, BT, lds, h.stream>>>(a, o, h.nmax, h.mmax);
     else
-        k_batch_solve_lds<BT, S, RES, false><<<wg, BT, lds, h.stream>>>(a, o, h.nmax, h.mmax);
+        k_batch_solve_lds<BT, S, false><<<wg, BT, lds, h.stream>>>(a, o, h.nmax, h.mmax);
     PDHG_HIP(hipGetLastError());
 }
 
@@ -2309,26 +2765,24 @@ static int32_t default_threads(const BatchHandle &h) {
 template <int BT>
 static void launch_solve_t(BatchHandle &h, const BOpts &o) {
     BArgs a = batch_args(h);
+    if constexpr (BT == 256 || BT == 512) {
+        switch (res_solve_columns(h, BT)) {
+            case 2: return launch_solve_res_t<BT, 2>(h, o, a);
+            case 4: return launch_solve_res_t<BT, 4>(h, o, a);
+            case 8: return launch_solve_res_t<BT, 8>(h, o, a);
+            default: break;
+        }
+    }
     // on-chip variant when x_ext, y and the three per-row vectors fit the
-    // workgroup's LDS and every thread owns at most 8 columns and 8 rows;
-    // register-resident matrix for narrow shared slices when the rows fit
-    // S/4 per thread (S >= 4) and the LDS also holds the column anchor, cost
-    // and upper bound
+    // workgroup's LDS and every thread owns at most 8 columns and 8 rows
     const size_t lds = ((size_t)h.nmax + 4 * (size_t)h.mmax) * sizeof(double);
-    const size_t lds_res = lds + 3 * (size_t)h.nmax * sizeof(double);
     const int32_t need = std::max(h.nmax, h.mmax);
     if (h.onchip && lds <= lds_per_workgroup() && need <= 8 * BT) {
         const size_t l = std::max<size_t>(lds, 8);
-        if (need <= BT) return launch_solve_lds_t<BT, 1, false>(h, o, a, l);
-        if (need <= 2 * BT) return launch_solve_lds_t<BT, 2, false>(h, o, a, l);
-        const bool res = h.resident && h.shared && h.ts_wmax <= kResCol && h.as_wmax <= kResRow &&
-                         lds_res <= lds_per_workgroup() && BT >= 256;
-        if (need <= 4 * BT) {
-            if (res && h.mmax <= BT) return launch_solve_lds_t<BT, 4, true>(h, o, a, lds_res);
-            return launch_solve_lds_t<BT, 4, false>(h, o, a, l);
-        }
-        if (res && h.mmax <= 2 * BT) return launch_solve_lds_t<BT, 8, true>(h, o, a, lds_res);
-        return launch_solve_lds_t<BT, 8, false>(h, o, a, l);
+        if (need <= BT) return launch_solve_lds_t<BT, 1>(h, o, a, l);
+        if (need <= 2 * BT) return launch_solve_lds_t<BT, 2>(h, o, a, l);
+        if (need <= 4 * BT) return launch_solve_lds_t<BT, 4>(h, o, a, l);
+        return launch_solve_lds_t<BT, 8>(h, o, a, l);
     }
 
     int32_t wg = std::min(h.B, resident<BT>(o.detect ? reinterpret_cast<const void *>(&k_batch_solve<BT, true>)
@@ -2347,18 +2801,6 @@ static void launch_solve_t(BatchHandle &h, const BOpts &o) {
 static size_t onchip_lds(const BatchHandle &h) {
     const size_t lds = ((size_t)h.nmax + (size_t)h.mmax) * sizeof(double);
     return (h.onchip && lds <= 65536) ? std::max<size_t>(lds, 8) : 0;
-}
-
-template <int BT, class K>
-static int32_t resident_lds(BatchHandle &h, K kernel, size_t lds) {
-    int dev = 0, per_cu = 0;
-    PDHG_HIP(hipGetDevice(&dev));
-    hipDeviceProp_t prop;
-    PDHG_HIP(hipGetDeviceProperties(&prop, dev));
-    PDHG_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void *>(kernel), BT, lds));
-    int32_t wg = std::min(h.B, std::max(1, per_cu) * prop.multiProcessorCount);
-    if (h.workgroups > 0) wg = std::min(wg, h.workgroups);
-    return wg;
 }
 
 template <int BT>
@@ -2396,7 +2838,8 @@ static void dispatch_setup(BatchHandle &h, int32_t count) {
 // Solves that test infeasibility rays carry a larger register budget: the
 // 1024-thread variants spill, so the default launch takes at most 512 there.
 static void dispatch_solve(BatchHandle &h, const BOpts &o) {
-    const int32_t threads = (o.detect && !h.threads_set) ? std::min(h.threads, 512) : h.threads;
+    int32_t threads = (o.detect && !h.threads_set) ? std::min(h.threads, 512) : h.threads;
+    if (const int32_t t = h.threads_set ? 0 : res_solve_threads(h)) threads = t;
     switch (threads) {
         case 64: launch_solve_t<64>(h, o); break;
         case 128: launch_solve_t<128>(h, o); break;
