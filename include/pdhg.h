@@ -299,9 +299,9 @@ pdhg_err pdhg_batch_solve(pdhg_batch *b, const double *x_init, const double *y_i
  * 256, that give each thread at most 8 columns and 8 rows of the largest
  * instance; QP batches, and LP solves that test infeasibility rays, take at
  * most 512 of them unless this call or pdhg_batch_autotune chose the shape.
- * Solves of a shared matrix with at most 2 entries a column and 8 a row (the
- * matrix then stays in registers) take 256 threads up to 1,024 columns and 256
- * rows, and 512 up to 4,096 and 1,024. */
+ * LP batches on a shared matrix with at most 2 entries a column and 8 a row
+ * (the matrix then stays in registers) start at 256 threads up to 1,024
+ * columns and 256 rows, and at 512 up to 4,096 and 1,024. */
 pdhg_err pdhg_batch_set_launch(pdhg_batch *b, int32_t threads, int32_t workgroups);
 
 /* Time `iterations` iterations of every instance for each supported thread

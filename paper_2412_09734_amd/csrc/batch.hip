@@ -1166,10 +1166,6 @@ __global__ __launch_bounds__(BT) void k_batch_solve_lds(BArgs a, BOpts o, int32_
 // (node-arc incidence matrices: two entries per column, node degree <= 8).
 constexpr int kResCol = 2, kResRow = 8;
 
-// A double in LDS at a byte offset from the start of the dynamic allocation.
-__device__ __forceinline__ double lds_at(const double *lds, int32_t off) {
-    return *reinterpret_cast<const double *>(reinterpret_cast<const char *>(lds) + off);
-}
 
 // LDS of k_batch_solve_res, in doubles: y and y0 of the owned rows and x_ext
 // and x0 of the owned columns (whole slots, so slots past the end need no
@@ -1210,6 +1206,100 @@ struct ResLds {
     static constexpr size_t bytes = ((size_t)step + 4 * kResSteps) * sizeof(double);
 };
 
+// Entries of the columns and rows that a thread owns, each index turned into
+// the LDS address of what it gathers.
+template <int BT, int S>
+struct ResEntries {
+    static constexpr int SR = ResLds<BT, S>::SR;
+    const LdsDouble *tci[S][kResCol], *rci[SR][kResRow];
+    double tva[S][kResCol], rva[SR][kResRow];
+
+    __device__ __forceinline__ void load_col(const BArgs &a, const Geo &g, const LdsDouble *sy, int q, int32_t j) {
+        int32_t e0 = 0, w = 0;
+        if (j < g.n) {
+            e0 = a.tsp[j >> 6];
+            w = (a.tsp[(j >> 6) + 1] - e0) >> 6;
+        }
+#pragma unroll
+        for (int u = 0; u < kResCol; ++u) {
+            const bool in = u < w;
+            const int32_t e = e0 + 64 * u + (j & 63);
+            tci[q][u] = sy + (in ? a.tsci[e] : 0);
+            tva[q][u] = in ? a.tsva[e] : 0.0;
+        }
+    }
+    __device__ __forceinline__ void load_rows(const BArgs &a, const Geo &g, const LdsDouble *sx) {
+        int32_t t0 = (int32_t)threadIdx.x;
+        asm volatile("" : "+v"(t0));   // addresses are formed here, not kept over a loop
+#pragma unroll
+        for (int q = 0; q < SR; ++q) {
+            const int32_t i = t0 + q * BT;
+            int32_t e0 = 0, w = 0;
+            if (i < g.m) {
+                e0 = a.asp[i >> 6];
+                w = (a.asp[(i >> 6) + 1] - e0) >> 6;
+            }
+#pragma unroll
+            for (int u = 0; u < kResRow; ++u) {
+                const bool in = u < w;
+                const int32_t e = e0 + 64 * u + (i & 63);
+                rci[q][u] = sx + res_pos(in ? a.asci[e] : 0);
+                rva[q][u] = in ? a.asva[e] : 0.0;
+            }
+        }
+    }
+    // one product with the vector `off` elements after the gathered one
+    __device__ __forceinline__ double col(int q, int off) const {
+        double s = 0.0;
+#pragma unroll
+        for (int u = 0; u < kResCol; ++u) s = fma(tva[q][u], tci[q][u][off], s);
+        return s;
+    }
+    __device__ __forceinline__ double row(int q, int off) const {
+        double s = 0.0;
+#pragma unroll
+        for (int u = 0; u < kResRow; ++u) s = fma(rva[q][u], rci[q][u][off], s);
+        return s;
+    }
+    // all products of a phase, every gather in flight before the first product
+    __device__ __forceinline__ void cols(double (&s)[S]) const {
+        double v[S][kResCol];
+#pragma unroll
+        for (int q = 0; q < S; ++q)
+#pragma unroll
+            for (int u = 0; u < kResCol; ++u) v[q][u] = *tci[q][u];
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int q = 0; q < S; ++q) {
+            s[q] = 0.0;
+#pragma unroll
+            for (int u = 0; u < kResCol; ++u) s[q] = fma(tva[q][u], v[q][u], s[q]);
+        }
+    }
+    __device__ __forceinline__ void rows(double (&s)[SR]) const {
+        double v[SR][kResRow];
+#pragma unroll
+        for (int q = 0; q < SR; ++q)
+#pragma unroll
+            for (int u = 0; u < kResRow; ++u) v[q][u] = *rci[q][u];
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int q = 0; q < SR; ++q) {
+            s[q] = 0.0;
+#pragma unroll
+            for (int u = 0; u < kResRow; ++u) s[q] = fma(rva[q][u], v[q][u], s[q]);
+        }
+    }
+};
+
+// Factors of x <- A x^ - G x + B x0 at restart length k.
+__device__ __forceinline__ void momentum_factors(double k, double gam, double &A, double &G, double &B) {
+    const double ak = (k + 1.0) / (k + 2.0);
+    A = ak * (1.0 + gam);
+    G = ak * gam;
+    B = 1.0 / (k + 2.0);
+}
+
 // The iteration of k_batch_solve for a shared matrix whose column slices hold
 // at most kResCol entries and row slices at most kResRow (node-arc incidence
 // matrices: two entries per column, node degree <= 8); S columns and SR rows
@@ -1249,8 +1339,7 @@ __global__ __launch_bounds__(BT) void k_batch_solve_res(BArgs a, BOpts o) {
         const double *Dr = a.Dr, *Dc = a.Dc;
         const double eta = a.eta[0];
         const double gam = o.gamma;
-        const LdsDouble *tci[S][kResCol], *rci[SR][kResRow];
-        double tva[S][kResCol], rva[SR][kResRow];
+        ResEntries<BT, S> M;
         double xr[S], x0r[S], cr[S], lr[S], ur[S];
         double yr[SR], y0r[SR], lo[SR], hi[SR];   // lo, hi: -sigma u_c, -sigma l_c
         LdsDouble *const myx = sx + res_pos((int32_t)threadIdx.x), *const myy = sy + (int32_t)threadIdx.x;
@@ -1262,10 +1351,7 @@ __global__ __launch_bounds__(BT) void k_batch_solve_res(BArgs a, BOpts o) {
         for (int q = 0; q < S; ++q) {
             const int32_t j = (int32_t)threadIdx.x + q * BT;
             xr[q] = x0r[q] = cr[q] = lr[q] = ur[q] = 0.0;
-            int32_t e0 = 0, w = 0;
             if (j < g.n) {
-                e0 = a.tsp[j >> 6];
-                w = (a.tsp[(j >> 6) + 1] - e0) >> 6;
                 const double d = Dc[j], co = a.c_o[g.vc + j];
                 cr[q] = d * co;
                 lr[q] = a.lv_o[g.vc + j] / d;
@@ -1275,13 +1361,7 @@ __global__ __launch_bounds__(BT) void k_batch_solve_res(BArgs a, BOpts o) {
                 xr[q] = clampd(a.x_init ? a.x_init[g.vc + j] / d : 0.0, lr[q], ur[q]);
                 x0r[q] = xr[q];
             }
-#pragma unroll
-            for (int u = 0; u < kResCol; ++u) {
-                const bool in = u < w;
-                const int32_t e = e0 + 64 * u + (j & 63);
-                tci[q][u] = sy + (in ? a.tsci[e] : 0);
-                tva[q][u] = in ? a.tsva[e] : 0.0;
-            }
+            M.load_col(a, g, sy, q, j);
             myx0[q * PX] = x0r[q];
         }
 #pragma unroll
@@ -1311,28 +1391,7 @@ __global__ __launch_bounds__(BT) void k_batch_solve_res(BArgs a, BOpts o) {
         const double cnorm = uniform_value(sqrt(nrm[2])), bnorm = uniform_value(sqrt(nrm[3]));
         double omega = uniform_value((cn > 1e-10 && bn > 1e-10) ? cn / bn : 1.0);
         double tau = uniform_value(eta / omega), sigma = uniform_value(eta * omega);
-        // entries of the owned rows
-        auto load_rows = [&]() {
-            int32_t t0 = (int32_t)threadIdx.x;
-            asm volatile("" : "+v"(t0));
-#pragma unroll
-            for (int q = 0; q < SR; ++q) {
-                const int32_t i = t0 + q * BT;
-                int32_t e0 = 0, w = 0;
-                if (i < g.m) {
-                    e0 = a.asp[i >> 6];
-                    w = (a.asp[(i >> 6) + 1] - e0) >> 6;
-                }
-#pragma unroll
-                for (int u = 0; u < kResRow; ++u) {
-                    const bool in = u < w;
-                    const int32_t e = e0 + 64 * u + (i & 63);
-                    rci[q][u] = sx + res_pos(in ? a.asci[e] : 0);
-                    rva[q][u] = in ? a.asva[e] : 0.0;
-                }
-            }
-        };
-        load_rows();
+        M.load_rows(a, g, sx);
         // clamp bounds of the dual step at this sigma
         auto dual_bounds = [&]() {
             int32_t t0 = (int32_t)threadIdx.x;
@@ -1348,51 +1407,20 @@ __global__ __launch_bounds__(BT) void k_batch_solve_res(BArgs a, BOpts o) {
         };
         dual_bounds();
 
-        // (A~'v)_j of owned column q, v = y (off 0) or y0 in LDS; (A~v)_i of
-        // owned row q, v = x_ext (off 0) or x0
-        auto col_dot = [&](int q, int off) {
-            double s = 0.0;
-#pragma unroll
-            for (int u = 0; u < kResCol; ++u) s = fma(tva[q][u], tci[q][u][off], s);
-            return s;
-        };
-        auto row_dot = [&](int q, int off) {
-            double s = 0.0;
-#pragma unroll
-            for (int u = 0; u < kResRow; ++u) s = fma(rva[q][u], rci[q][u][off], s);
-            return s;
-        };
-        // x^ of the owned columns and s = A~'y, x_ext to LDS; y^ of the owned
-        // rows. All of a phase's gathers are in flight before its products.
+        // x^ of the owned columns and s = A~'y, x_ext to LDS; y^ of the owned rows
         auto columns = [&](double (&s)[S], double (&xn)[S]) {
-            double gy[S][kResCol];
-#pragma unroll
-            for (int q = 0; q < S; ++q)
-#pragma unroll
-                for (int u = 0; u < kResCol; ++u) gy[q][u] = *tci[q][u];
-            __builtin_amdgcn_sched_barrier(0);
+            M.cols(s);
 #pragma unroll
             for (int q = 0; q < S; ++q) {
-                s[q] = 0.0;
-#pragma unroll
-                for (int u = 0; u < kResCol; ++u) s[q] = fma(tva[q][u], gy[q][u], s[q]);
                 xn[q] = clamp_quiet(xr[q] - tau * (cr[q] - s[q]), lr[q], ur[q]);
                 myx[q * PX] = 2.0 * xn[q] - xr[q];
             }
         };
         auto rows = [&](double (&yn)[SR]) {
-            double gx[SR][kResRow];
-#pragma unroll
-            for (int q = 0; q < SR; ++q)
-#pragma unroll
-                for (int u = 0; u < kResRow; ++u) gx[q][u] = *rci[q][u];
-            __builtin_amdgcn_sched_barrier(0);
+            M.rows(yn);
 #pragma unroll
             for (int q = 0; q < SR; ++q) {
-                double s = 0.0;
-#pragma unroll
-                for (int u = 0; u < kResRow; ++u) s = fma(rva[q][u], gx[q][u], s);
-                const double w = fma(-sigma, s, yr[q]);
+                const double w = fma(-sigma, yn[q], yr[q]);
                 yn[q] = w - clamp_quiet(w, lo[q], hi[q]);
             }
         };
@@ -1415,11 +1443,11 @@ __global__ __launch_bounds__(BT) void k_batch_solve_res(BArgs a, BOpts o) {
                 // x <- A x^ - G x + B x0 in iterations p .. p + cnt - 1
                 if ((int32_t)threadIdx.x < cnt) {
                     const int32_t u = (int32_t)threadIdx.x;
-                    const double kk = (double)(k + p + u);
-                    const double ak = (kk + 1.0) / (kk + 2.0);
-                    stp[4 * u] = ak * (1.0 + gam);
-                    stp[4 * u + 1] = ak * gam;
-                    stp[4 * u + 2] = 1.0 / (kk + 2.0);
+                    double A, G, B;
+                    momentum_factors((double)(k + p + u), gam, A, G, B);
+                    stp[4 * u] = A;
+                    stp[4 * u + 1] = G;
+                    stp[4 * u + 2] = B;
                 }
                 __syncthreads();
 #pragma unroll 1
@@ -1473,7 +1501,7 @@ __global__ __launch_bounds__(BT) void k_batch_solve_res(BArgs a, BOpts o) {
                 const int32_t i = t0 + q * BT;
                 if (i < g.m) {
                     const double d = Dr[i], loo = a.lc_o[g.vr + i], hio = a.uc_o[g.vr + i], yh = myy[q * BT];
-                    const double p = row_dot(q, 0);
+                    const double p = M.row(q, 0);
                     const double ax = p / d;
                     const double rpr = ax - clampd(ax, loo, hio);
                     v[6] += rpr * rpr;
@@ -1485,7 +1513,7 @@ __global__ __launch_bounds__(BT) void k_batch_solve_res(BArgs a, BOpts o) {
                     v[9] += d0 * d0;
                     if (rays) {
                         double s1[1], m2[2];
-                        ray_row_terms(p, row_dot(q, L::x0 - L::x), d, d0, loo, hio, s1, m2);
+                        ray_row_terms(p, M.row(q, L::x0 - L::x), d, d0, loo, hio, s1, m2);
                         v[12] += s1[0];
                         rmx[0] = fmax(rmx[0], m2[0]);
                         rmx[1] = fmax(rmx[1], m2[1]);
@@ -1498,7 +1526,7 @@ __global__ __launch_bounds__(BT) void k_batch_solve_res(BArgs a, BOpts o) {
                 const int32_t j = t0 + q * BT;
                 if (j < g.n) {
                     const double d = Dc[j], xh = myx[q * PX];
-                    const double qq = col_dot(q, 0);
+                    const double qq = M.col(q, 0);
                     const double dx = xh - xr[q];
                     v[0] += dx * dx;
                     v[1] += (qq - myaty[q * BT]) * dx;
@@ -1513,7 +1541,7 @@ __global__ __launch_bounds__(BT) void k_batch_solve_res(BArgs a, BOpts o) {
                     v[5] += (lf ? lr[q] * fmax(lam, 0.0) : 0.0) - (uf ? ur[q] * fmax(-lam, 0.0) : 0.0);
                     if (rays) {
                         double s2[2], m2[2];
-                        ray_col_terms(qq, col_dot(q, L::y0), d, d0, cr[q] / d, lr[q] * d, ur[q] * d, s2, m2);
+                        ray_col_terms(qq, M.col(q, L::y0), d, d0, cr[q] / d, lr[q] * d, ur[q] * d, s2, m2);
                         v[10] += s2[0];
                         v[11] += s2[1];
                         rmx[0] = fmax(rmx[0], m2[0]);
@@ -1595,9 +1623,8 @@ __global__ __launch_bounds__(BT) void k_batch_solve_res(BArgs a, BOpts o) {
                 r_prev = r;
                 ++restarts;
             } else {
-                const double kk = (double)k;
-                const double ak = (kk + 1.0) / (kk + 2.0), B = 1.0 / (kk + 2.0);
-                const double A = ak * (1.0 + gam), G = ak * gam;
+                double A, G, B;
+                momentum_factors((double)k, gam, A, G, B);
 #pragma unroll
                 for (int q = 0; q < S; ++q) {
                     x0r[q] = myx0[q * PX];
@@ -1611,7 +1638,7 @@ __global__ __launch_bounds__(BT) void k_batch_solve_res(BArgs a, BOpts o) {
                 }
                 ++k;
             }
-            load_rows();
+            M.load_rows(a, g, sx);
             ++t;
             tc = o.check_every == 1 ? 0 : 1;
             __syncthreads();
@@ -1867,237 +1894,210 @@ __global__ __launch_bounds__(BT) void k_batch_unrolled(BArgs a, BOpts o, UArgs u
     }
 }
 
-// Register-resident matrix for the unrolled forward and its reverse pass
-// (a shared matrix whose column slices hold at most kResCol and row slices at
-// most kResRow entries; S columns and S/4 rows per thread): the owned slices'
-// entries with every index turned into the byte offset of the LDS element it
-// gathers, y (for A~') after nmax doubles of x_ext (for A~).
-template <int BT, int S>
-struct ResSlices {
-    static constexpr int SR = S >= 4 ? S / 4 : 1;
-    int32_t tci[S][kResCol], rci[SR][kResRow];
-    double tva[S][kResCol], rva[SR][kResRow];
+// The 64-bit word that lane `l` (wave-uniform) holds, as a scalar, and the own
+// lane's bit of such a word.
+__device__ __forceinline__ uint64_t mask_word(uint64_t w, int32_t l) {
+    return (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int32_t)(w >> 32), l) << 32 |
+           (uint32_t)__builtin_amdgcn_readlane((int32_t)w, l);
+}
+__device__ __forceinline__ bool lane_bit(uint64_t w) { return __builtin_amdgcn_inverse_ballot_w64(w); }
+// Lane l's copy of (w1, w0) becomes the word w. The wait covers the two states
+// that a comparison's scalar result needs before a vector instruction reads it.
+__device__ __forceinline__ void put_word(uint32_t &w0, uint32_t &w1, uint64_t w, int l) {
+    asm("s_nop 1\n\tv_writelane_b32 %0, %2, %4\n\tv_writelane_b32 %1, %3, %4"
+        : "+v"(w0), "+v"(w1)
+        : "s"((uint32_t)w), "s"((uint32_t)(w >> 32)), "i"(l));
+}
 
-    __device__ __forceinline__ void load(const BArgs &a, const Geo &g, int32_t nmax) {
-        const int32_t lane = (int32_t)(threadIdx.x & 63);
-#pragma unroll
-        for (int q = 0; q < S; ++q) {
-            const int32_t j = threadIdx.x + q * BT;
-            int32_t base = 0, w = 0;
-            if (j < g.n) {
-                base = a.tsp[j >> 6];
-                w = (a.tsp[(j >> 6) + 1] - base) >> 6;
-            }
-#pragma unroll
-            for (int u = 0; u < kResCol; ++u) {
-                const bool in = u < w;
-                const int32_t e = base + 64 * u + lane;
-                tci[q][u] = 8 * (nmax + (in ? a.tsci[e] : 0));
-                tva[q][u] = in ? a.tsva[e] : 0.0;
-            }
-        }
-#pragma unroll
-        for (int q = 0; q < SR; ++q) {
-            const int32_t i = threadIdx.x + q * BT;
-            int32_t base = 0, w = 0;
-            if (i < g.m) {
-                base = a.asp[i >> 6];
-                w = (a.asp[(i >> 6) + 1] - base) >> 6;
-            }
-#pragma unroll
-            for (int u = 0; u < kResRow; ++u) {
-                const bool in = u < w;
-                const int32_t e = base + 64 * u + lane;
-                rci[q][u] = 8 * (in ? a.asci[e] : 0);
-                rva[q][u] = in ? a.asva[e] : 0.0;
-            }
-        }
-    }
-    // (A~' y)_j of owned column q, y in LDS after nmax doubles
-    __device__ __forceinline__ double col(const double *lds, int q) const {
-        double s = 0.0;
-#pragma unroll
-        for (int u = 0; u < kResCol; ++u) s = fma(tva[q][u], lds_at(lds, tci[q][u]), s);
-        return s;
-    }
-    // (A~ v)_i of owned row q, v at the start of the LDS
-    __device__ __forceinline__ double row(const double *lds, int q) const {
-        double s = 0.0;
-#pragma unroll
-        for (int u = 0; u < kResRow; ++u) s = fma(rva[q][u], lds_at(lds, rci[q][u]), s);
-        return s;
-    }
-};
-
-// k_batch_unrolled for a register-resident shared matrix (grid batches): the
-// same iterations, records and arithmetic, with x, x^ and l~_v of the owned
-// columns and y^ of the owned rows in registers, and x_ext, y, x0, y0, c~,
-// u~_v, l~_c, u~_c in LDS.
+// k_batch_unrolled for a register-resident shared matrix (grid batches), in the
+// manner of k_batch_solve_res: restarts are decided (or replayed) only where a
+// check falls, the iterations in between run without a branch. A wave's
+// projection masks are comparisons left in scalar registers; each goes to a
+// lane of its own and one store per iteration writes them all.
+// What bounds it: the instructions and LDS gathers of k_batch_solve_res plus
+// the comparisons and lane writes of the masks (176 vector instructions a wave
+// at 8 columns a thread). Per iteration of 256 instances: 32x32 grids 1.68 us
+// (3.44 us with a branch per slot, divisions, and one store per mask word),
+// 22x22 0.82 (2.16), 12x12 0.62 (1.56).
 template <int BT, int S>
-__global__ __launch_bounds__(BT) void k_batch_unrolled_res(BArgs a, BOpts o, UArgs u, int32_t nmax,
-                                                           int32_t mmax) {
-    using RS = ResSlices<BT, S>;
-    constexpr int SR = RS::SR;
+__global__ __launch_bounds__(BT) void k_batch_unrolled_res(BArgs a, BOpts o, UArgs u) {
+    using L = ResLds<BT, S>;
+    constexpr int SR = L::SR;
+    constexpr int PX = res_pos(BT);
+    constexpr int NW = BT / 64;
     extern __shared__ double lds[];
-    double *sx = lds, *sy = lds + nmax;
-    double *slc = sy + mmax, *suc = slc + mmax, *sy0 = suc + mmax;
-    double *sx0 = sy0 + mmax, *scr = sx0 + nmax, *suv = scr + nmax;
+    LdsDouble *const sy = (LdsDouble *)lds, *const sx = sy + L::x, *const stp = sy + L::step;
     for (;;) {
         const int32_t b = next_instance<BT>(a.queue);
         if (b >= a.B) return;
         const Geo g = geometry(a, b);
         const int32_t lane = (int32_t)(threadIdx.x & 63);
-        const double *Dr = a.Dr + g.dr, *Dc = a.Dc + g.dc;
-        const double *c_o = a.c_o + g.vc, *lv_o = a.lv_o + g.vc, *uv_o = a.uv_o + g.vc;
-        const double *lc_o = a.lc_o + g.vr, *uc_o = a.uc_o + g.vr;
+        const int32_t wave = __builtin_amdgcn_readfirstlane((int32_t)threadIdx.x >> 6);
+        const double *Dr = a.Dr, *Dc = a.Dc;
         uint8_t *rs_ = u.restart + (size_t)b * u.T;
         double *om_ = u.omega + (size_t)b * u.T;
         int32_t *kk_ = u.kk + (size_t)b * u.T;
-        uint64_t *xm = u.xmask + u.xm_off[b], *ym = u.ymask + u.ym_off[b];
         const int32_t xw = (g.n + 63) >> 6, yw = (g.m + 63) >> 6;
-        const double eta = a.eta[g.sidx];
+        uint64_t *xm = u.xmask + u.xm_off[b], *ym = u.ymask + u.ym_off[b];
+        // lane q stores column slot q's mask; lanes 2q, 2q + 1 those of row slot q
+        const int32_t xword = wave + lane * NW, yword = 2 * (wave + (lane >> 1) * NW) + (lane & 1);
+        const bool xmine = lane < S && xword < xw, ymine = lane < 2 * SR && yword < 2 * yw;
+        const double eta = a.eta[0];
         const double gam = o.gamma;
-        RS M;
-        M.load(a, g, nmax);
-        double xr[S], xhr[S], lvr[S], yhr[SR];
+        ResEntries<BT, S> M;
+        double xr[S], x0r[S], cr[S], lr[S], ur[S], xn[S];
+        double yr[SR], y0r[SR], lo[SR], hi[SR], yn[SR];
+        LdsDouble *const myx = sx + res_pos((int32_t)threadIdx.x), *const myy = sy + (int32_t)threadIdx.x;
         double nrm[2] = {0.0, 0.0};
 #pragma unroll
         for (int q = 0; q < S; ++q) {
-            const int32_t j = threadIdx.x + q * BT;
-            xr[q] = xhr[q] = lvr[q] = 0.0;
+            const int32_t j = (int32_t)threadIdx.x + q * BT;
+            xr[q] = cr[q] = lr[q] = ur[q] = 0.0;
             if (j < g.n) {
                 const double d = Dc[j];
-                const double cj = d * c_o[j];
-                scr[j] = cj;
-                lvr[q] = lv_o[j] / d;
-                suv[j] = uv_o[j] / d;
-                nrm[0] += cj * cj;
+                cr[q] = d * a.c_o[g.vc + j];
+                lr[q] = a.lv_o[g.vc + j] / d;
+                ur[q] = a.uv_o[g.vc + j] / d;
+                nrm[0] += cr[q] * cr[q];
+                xr[q] = clampd(0.0, lr[q], ur[q]);
             }
+            x0r[q] = xr[q];
+            M.load_col(a, g, sy, q, j);
         }
+        M.load_rows(a, g, sx);
 #pragma unroll
         for (int q = 0; q < SR; ++q) {
-            const int32_t i = threadIdx.x + q * BT;
-            yhr[q] = 0.0;
+            const int32_t i = (int32_t)threadIdx.x + q * BT;
+            yr[q] = y0r[q] = lo[q] = hi[q] = 0.0;
             if (i < g.m) {
                 const double d = Dr[i];
-                const double l = d * lc_o[i], uu = d * uc_o[i];
-                slc[i] = l;
-                suc[i] = uu;
+                const double l = d * a.lc_o[g.vr + i], uu = d * a.uc_o[g.vr + i];
                 double bb = 0.0;
                 if (isfinite(l)) bb = fmax(bb, fabs(l));
                 if (isfinite(uu)) bb = fmax(bb, fabs(uu));
                 nrm[1] += bb * bb;
+                yr[q] = clampd(0.0, isfinite(uu) ? -INFINITY : 0.0, isfinite(l) ? INFINITY : 0.0);
+                y0r[q] = yr[q];
             }
+            myy[q * BT] = yr[q];
         }
         wg_sum<BT, 2>(nrm);
         const double cn = sqrt(nrm[0]), bn = sqrt(nrm[1]);
-        double omega = (cn > 1e-10 && bn > 1e-10) ? cn / bn : 1.0;
-#pragma unroll
-        for (int q = 0; q < S; ++q) {
-            const int32_t j = threadIdx.x + q * BT;
-            if (j < g.n) {
-                xr[q] = clampd(0.0, lvr[q], suv[j]);
-                sx0[j] = xr[q];
-            }
-        }
-#pragma unroll
-        for (int q = 0; q < SR; ++q) {
-            const int32_t i = threadIdx.x + q * BT;
-            if (i < g.m) {
-                const double lo = isfinite(suc[i]) ? -INFINITY : 0.0;
-                const double hi = isfinite(slc[i]) ? INFINITY : 0.0;
-                const double yv = clampd(0.0, lo, hi);
-                sy[i] = yv;
-                sy0[i] = yv;
-            }
-        }
-        __syncthreads();
-        int64_t k = 0;
-        int32_t tc = 0;   // t modulo check_every
-        double r_start = 0.0, r_prev = 0.0;
-        for (int64_t t = 0; t < u.T; ++t) {
-            // opaque thread index: element addresses are formed per iteration
-            int32_t tid = (int32_t)threadIdx.x;
-            asm volatile("" : "+v"(tid));
-            if (u.replay) omega = om_[t];
-            const double tau = eta / omega, sigma = eta * omega;
-            const bool last = t + 1 >= u.T;
-            const bool check = !u.replay && tc == 0 && !last;
-            const double ak = (double)(k + 1) / (double)(k + 2), bk = 1.0 / (double)(k + 2);
-            uint64_t *xmt = xm + (size_t)t * xw;
-            uint64_t *ymt = ym + (size_t)t * 2 * yw;
-#pragma unroll
-            for (int q = 0; q < S; ++q) {
-                const int32_t j = tid + q * BT;
-                bool inside = false;
-                if (j < g.n) {
-                    const double s = M.col(lds, q);
-                    const double uu = xr[q] - tau * (scr[j] - s);
-                    const double hi = suv[j];
-                    inside = uu > lvr[q] && uu < hi;
-                    const double xhat = clampd(uu, lvr[q], hi);
-                    sx[j] = 2.0 * xhat - xr[q];
-                    xhr[q] = xhat;
-                }
-                const uint64_t bits = __ballot(inside);
-                if (lane == 0 && j < g.n) xmt[j >> 6] = bits;
-            }
-            __syncthreads();
+        double omega = uniform_value((cn > 1e-10 && bn > 1e-10) ? cn / bn : 1.0);
+        double tau = 0.0, sigma = 0.0;
+        // step sizes and clamp bounds of the dual step at this omega
+        auto set_steps = [&]() {
+            tau = uniform_value(eta / omega);
+            sigma = uniform_value(eta * omega);
+            int32_t t0 = (int32_t)threadIdx.x;
+            asm volatile("" : "+v"(t0));
 #pragma unroll
             for (int q = 0; q < SR; ++q) {
-                const int32_t i = tid + q * BT;
-                bool at_u = false, at_l = false;
+                const int32_t i = t0 + q * BT;
                 if (i < g.m) {
-                    const double av = M.row(lds, q);
-                    const double vv = sy[i] / sigma - av;
-                    const double lo = -suc[i], hi = -slc[i];
-                    at_u = vv < lo;
-                    at_l = vv > hi;
-                    yhr[q] = sigma * (vv - clampd(vv, lo, hi));
-                }
-                const uint64_t bu = __ballot(at_u), bl = __ballot(at_l);
-                if (lane == 0 && i < g.m) {
-                    ymt[2 * (i >> 6)] = bu;
-                    ymt[2 * (i >> 6) + 1] = bl;
+                    lo[q] = -sigma * (Dr[i] * a.uc_o[g.vr + i]);
+                    hi[q] = -sigma * (Dr[i] * a.lc_o[g.vr + i]);
                 }
             }
+        };
+        if (u.replay) omega = om_[0];
+        set_steps();
+
+        // iteration t up to its PDHG point (xn, yn), masks recorded
+        auto step = [&](int64_t t) {
+            double s[S];
+            uint32_t w0 = 0, w1 = 0;
+            M.cols(s);
+#pragma unroll
+            for (int q = 0; q < S; ++q) {
+                const double v = xr[q] - tau * (cr[q] - s[q]);
+                const uint64_t bits = __ballot(v > lr[q] && v < ur[q]);
+                put_word(w0, w1, bits, q);
+                xn[q] = clamp_quiet(v, lr[q], ur[q]);
+                myx[q * PX] = 2.0 * xn[q] - xr[q];
+            }
+            if (xmine) xm[(size_t)t * xw + xword] = (uint64_t)w1 << 32 | w0;
             __syncthreads();
+            M.rows(yn);
+#pragma unroll
+            for (int q = 0; q < SR; ++q) {
+                const double w = fma(-sigma, yn[q], yr[q]);
+                const uint64_t bu = __ballot(w < lo[q]), bl = __ballot(w > hi[q]);
+                put_word(w0, w1, bu, 2 * q);
+                put_word(w0, w1, bl, 2 * q + 1);
+                yn[q] = w - clamp_quiet(w, lo[q], hi[q]);
+            }
+            if (ymine) ym[(size_t)t * 2 * yw + yword] = (uint64_t)w1 << 32 | w0;
+        };
+        auto momentum = [&](double A, double G, double B) {
+#pragma unroll
+            for (int q = 0; q < S; ++q) xr[q] = A * xn[q] - G * xr[q] + B * x0r[q];
+#pragma unroll
+            for (int q = 0; q < SR; ++q) {
+                yr[q] = A * yn[q] - G * yr[q] + B * y0r[q];
+                myy[q * BT] = yr[q];
+            }
+        };
+
+        int64_t t = 0, k = 0;
+        int32_t tc = 0;   // t modulo check_every
+        double r_start = 0.0, r_prev = 0.0;
+        for (;;) {
+            // iterations without a decision, then one with a check or the last
+            int32_t plain = tc == 0 ? 0 : o.check_every - tc;
+            if ((int64_t)plain > u.T - 1 - t) plain = (int32_t)(u.T - 1 - t);
+            for (int32_t p = 0; p < plain; p += kResSteps) {
+                const int32_t cnt = plain - p < kResSteps ? plain - p : kResSteps;
+                if ((int32_t)threadIdx.x < cnt) {
+                    const int32_t v = (int32_t)threadIdx.x;
+                    double A, G, B;
+                    momentum_factors((double)(k + p + v), gam, A, G, B);
+                    stp[4 * v] = A;
+                    stp[4 * v + 1] = G;
+                    stp[4 * v + 2] = B;
+                    om_[t + p + v] = omega;
+                    kk_[t + p + v] = (int32_t)(k + p + v);
+                    if (!u.replay) rs_[t + p + v] = 0;
+                }
+                __syncthreads();
+#pragma unroll 1
+                for (int32_t it = 0; it < cnt; ++it) {
+                    const double A = stp[4 * it], G = stp[4 * it + 1], B = stp[4 * it + 2];
+                    step(t + p + it);
+                    momentum(A, G, B);
+                    __syncthreads();
+                }
+            }
+            t += plain;
+            k += plain;
+            step(t);
             if (threadIdx.x == 0) {
                 om_[t] = omega;
                 kk_[t] = (int32_t)k;
             }
-            if (last) break;
+            if (t + 1 >= u.T) break;
             bool restart = u.replay ? rs_[t] != 0 : false;
-            if (check) {
-                double v2[10];
-#pragma unroll
-                for (int q = 0; q < 10; ++q) v2[q] = 0.0;
+            if (!u.replay) {
+                double v[5] = {0.0, 0.0, 0.0, 0.0, 0.0};   // |dx|^2, dy' A~ dx, |x^ - x0|^2, |dy|^2, |y^ - y0|^2
+                __syncthreads();
 #pragma unroll
                 for (int q = 0; q < S; ++q) {
-                    const int32_t j = tid + q * BT;
-                    if (j < g.n) {
-                        const double dx = xhr[q] - xr[q];
-                        v2[0] += dx * dx;
-                        const double d0 = xhr[q] - sx0[j];
-                        v2[2] += d0 * d0;
-                        sx[j] = dx;   // x_ext is spent: it carries dx for the cross term
-                    }
+                    const double dx = xn[q] - xr[q], d0 = xn[q] - x0r[q];
+                    v[0] += dx * dx;
+                    v[2] += d0 * d0;
+                    myx[q * PX] = dx;   // x_ext is spent: it carries dx for the cross term
                 }
                 __syncthreads();
 #pragma unroll
                 for (int q = 0; q < SR; ++q) {
-                    const int32_t i = tid + q * BT;
-                    if (i < g.m) {
-                        const double dy = yhr[q] - sy[i];
-                        v2[8] += dy * dy;
-                        const double d0 = yhr[q] - sy0[i];
-                        v2[9] += d0 * d0;
-                        v2[1] += dy * M.row(lds, q);   // cross term dy' A~ dx
-                    }
+                    const double dy = yn[q] - yr[q], d0 = yn[q] - y0r[q];
+                    v[3] += dy * dy;
+                    v[4] += d0 * d0;
+                    v[1] += dy * M.row(q, 0);
                 }
-                wg_sum<BT, 10>(v2);
-                const double r2 = v2[0] / tau + v2[8] / sigma + 2.0 * v2[1];
-                const double r = r2 > 0.0 ? sqrt(r2) : 0.0;
+                wg_sum<BT, 5>(v);
+                const double r2 = v[0] / tau + v[3] / sigma + 2.0 * v[1];
+                const double r = uniform_value(r2 > 0.0 ? sqrt(r2) : 0.0);
                 if (t == 0) {
                     r_start = r;
                     r_prev = r;
@@ -2108,194 +2108,217 @@ __global__ __launch_bounds__(BT) void k_batch_unrolled_res(BArgs a, BOpts o, UAr
                     r_prev = r;
                 }
                 if (restart) {
-                    const double dxr = sqrt(v2[2]), dyr = sqrt(v2[9]);
-                    omega = batch_new_omega(omega, dxr, dyr);
+                    // exp(log(dyr / dxr) / 2 + log(omega) / 2), without a call
+                    const double dxr = sqrt(v[2]), dyr = sqrt(v[4]);
+                    if (dxr > 1e-10 && dyr > 1e-10) omega = uniform_value(sqrt(dyr / dxr) * sqrt(omega));
                     r_start = r;
                     r_prev = r;
                 }
+                if (threadIdx.x == 0) rs_[t] = restart ? 1 : 0;
             }
-            if (threadIdx.x == 0 && !u.replay) rs_[t] = restart ? 1 : 0;
             if (restart) {
 #pragma unroll
-                for (int q = 0; q < S; ++q) {
-                    const int32_t j = tid + q * BT;
-                    if (j < g.n) {
-                        xr[q] = xhr[q];
-                        sx0[j] = xhr[q];
-                    }
-                }
+                for (int q = 0; q < S; ++q) xr[q] = x0r[q] = xn[q];
 #pragma unroll
                 for (int q = 0; q < SR; ++q) {
-                    const int32_t i = tid + q * BT;
-                    if (i < g.m) {
-                        sy[i] = yhr[q];
-                        sy0[i] = yhr[q];
-                    }
+                    yr[q] = y0r[q] = yn[q];
+                    myy[q * BT] = yn[q];
                 }
                 k = 0;
+                if (u.replay) omega = om_[t + 1];
+                set_steps();
             } else {
-#pragma unroll
-                for (int q = 0; q < S; ++q) {
-                    const int32_t j = tid + q * BT;
-                    if (j < g.n) xr[q] = ak * ((1.0 + gam) * xhr[q] - gam * xr[q]) + bk * sx0[j];
-                }
-#pragma unroll
-                for (int q = 0; q < SR; ++q) {
-                    const int32_t i = tid + q * BT;
-                    if (i < g.m) sy[i] = ak * ((1.0 + gam) * yhr[q] - gam * sy[i]) + bk * sy0[i];
-                }
+                double A, G, B;
+                momentum_factors((double)k, gam, A, G, B);
+                momentum(A, G, B);
                 ++k;
             }
-            tc = tc + 1 == o.check_every ? 0 : tc + 1;
+            ++t;
+            tc = o.check_every == 1 ? 0 : 1;
             __syncthreads();
         }
         if (u.replay == 0 && threadIdx.x == 0) rs_[u.T - 1] = 0;
+        int32_t t0 = (int32_t)threadIdx.x;
+        asm volatile("" : "+v"(t0));
 #pragma unroll
         for (int q = 0; q < S; ++q) {
-            const int32_t j = threadIdx.x + q * BT;
-            if (j < g.n) a.x_out[g.vc + j] = Dc[j] * xhr[q];
+            const int32_t j = t0 + q * BT;
+            if (j < g.n) a.x_out[g.vc + j] = Dc[j] * xn[q];
         }
 #pragma unroll
         for (int q = 0; q < SR; ++q) {
-            const int32_t i = threadIdx.x + q * BT;
-            if (i < g.m) a.y_out[g.vr + i] = Dr[i] * yhr[q];
+            const int32_t i = t0 + q * BT;
+            if (i < g.m) a.y_out[g.vr + i] = Dr[i] * yn[q];
         }
         __syncthreads();
     }
 }
 
+
 // k_batch_backward for a register-resident shared matrix: the cotangents of
 // the owned columns and rows and the gradient sums in registers; the products
-// gather ba (after nmax doubles) and tmp (at the start) from LDS.
+// gather ba (in place of y) and tmp (in place of x_ext) from LDS. The masks
+// and the schedule of kMaskSteps iterations come with one load each, a word
+// per lane, while the group before is worked on; an iteration takes its words
+// from those lanes as scalars and selects with them.
+// Two barriers an iteration: ba and tmp are each read in the phase after they
+// are written and rewritten only after the other's barrier.
+// What bounds it: vector instructions and LDS gathers between the barriers.
+// Per iteration of 256 instances: 32x32 grids 1.68 us (3.72 us with masks and
+// schedule loaded when they were needed, three barriers and a division per
+// row), 22x22 0.95 (1.93), 12x12 0.66 (1.35).
 template <int BT, int S>
-__global__ __launch_bounds__(BT) void k_batch_backward_res(BArgs a, BOpts o, UArgs u, int32_t nmax) {
-    using RS = ResSlices<BT, S>;
-    constexpr int SR = RS::SR;
+__global__ __launch_bounds__(BT) void k_batch_backward_res(BArgs a, BOpts o, UArgs u) {
+    using L = ResLds<BT, S>;
+    constexpr int SR = L::SR;
+    constexpr int PX = res_pos(BT);
+    constexpr int NW = BT / 64;
+    constexpr int kMaskSteps = 64 / S;   // iterations whose column masks fill a wave's lanes
+    static_assert(2 * SR * kMaskSteps <= 64, "row masks of a group fit one load");
     extern __shared__ double lds[];
-    double *tmp = lds, *ba = lds + nmax;
+    LdsDouble *const ba = (LdsDouble *)lds, *const tmp = ba + L::x;
     for (;;) {
         const int32_t b = next_instance<BT>(a.queue);
         if (b >= a.B) return;
         const Geo g = geometry(a, b);
         const int32_t lane = (int32_t)(threadIdx.x & 63);
-        const double *Dr = a.Dr + g.dr, *Dc = a.Dc + g.dc;
+        const int32_t wave = __builtin_amdgcn_readfirstlane((int32_t)threadIdx.x >> 6);
+        const double *Dr = a.Dr, *Dc = a.Dc;
         const uint8_t *rs_ = u.restart + (size_t)b * u.T;
         const double *om_ = u.omega + (size_t)b * u.T;
         const int32_t *kk_ = u.kk + (size_t)b * u.T;
         const uint64_t *xm = u.xmask + u.xm_off[b], *ym = u.ymask + u.ym_off[b];
         const int32_t xw = (g.n + 63) >> 6, yw = (g.m + 63) >> 6;
-        const double eta = a.eta[g.sidx];
+        const double eta = a.eta[0];
         const double gam = o.gamma;
-        RS M;
-        M.load(a, g, nmax);
-        double bx[S], bx0[S], bxh[S], gcr[S];
-        double by[SR], by0[SR], byh[SR], glr[SR], gur[SR];
+        ResEntries<BT, S> M;
+        double bx[S], bx0[S], gcr[S];
+        double by[SR], by0[SR], glr[SR], gur[SR];
+        LdsDouble *const myx = tmp + res_pos((int32_t)threadIdx.x), *const myy = ba + (int32_t)threadIdx.x;
 #pragma unroll
         for (int q = 0; q < S; ++q) {
-            const int32_t j = threadIdx.x + q * BT;
-            bx[q] = bx0[q] = gcr[q] = 0.0;
-            bxh[q] = j < g.n ? Dc[j] * u.gx[g.vc + j] : 0.0;
+            const int32_t j = (int32_t)threadIdx.x + q * BT;
+            bx0[q] = gcr[q] = 0.0;
+            bx[q] = j < g.n ? Dc[j] * u.gx[g.vc + j] : 0.0;
+            M.load_col(a, g, ba, q, j);
         }
+        M.load_rows(a, g, tmp);
 #pragma unroll
         for (int q = 0; q < SR; ++q) {
-            const int32_t i = threadIdx.x + q * BT;
-            by[q] = by0[q] = glr[q] = gur[q] = 0.0;
-            byh[q] = i < g.m ? Dr[i] * u.gy[g.vr + i] : 0.0;
+            const int32_t i = (int32_t)threadIdx.x + q * BT;
+            by0[q] = glr[q] = gur[q] = 0.0;
+            by[q] = i < g.m ? Dr[i] * u.gy[g.vr + i] : 0.0;
         }
-        for (int64_t t = u.T - 1; t >= 0; --t) {
-            int32_t tid = (int32_t)threadIdx.x;
-            asm volatile("" : "+v"(tid));
-            const double omega = om_[t];
-            const double tau = eta / omega, sigma = eta * omega;
-            if (t < u.T - 1) {
-                if (rs_[t]) {
+        // group of iterations t, t - 1, ..: lane (it, q) holds column slot q's
+        // word of iteration t - it, lane (it, 2 q + half) row slot q's, lane it
+        // the schedule. Words outside the masks (and iterations before 0) are 0.
+        const int32_t xit = lane / S, xword = wave + (lane % S) * NW;
+        const int32_t yit = lane / (2 * SR), yword = 2 * (wave + (lane % (2 * SR)) / 2 * NW) + (lane & 1);
+        struct Group {
+            uint64_t x, y;
+            double om;
+            int32_t k, rs;
+        };
+        auto fetch = [&](int64_t t) {
+            Group f{0, 0, 1.0, 0, 0};
+            if (xword < xw && xit <= t) f.x = xm[(size_t)(t - xit) * xw + xword];
+            if (yword < 2 * yw && yit < kMaskSteps && yit <= t) f.y = ym[(size_t)(t - yit) * 2 * yw + yword];
+            if (lane < kMaskSteps && lane <= t) {
+                f.om = om_[t - lane];
+                f.k = kk_[t - lane];
+                // the output's cotangent enters like the point of a restart
+                f.rs = rs_[t - lane] != 0 || t - lane == u.T - 1;
+            }
+            return f;
+        };
+        Group nxt = fetch(u.T - 1);
+        for (int64_t tg = u.T - 1; tg >= 0; tg -= kMaskSteps) {
+            const Group cur = nxt;
+            if (tg >= kMaskSteps) nxt = fetch(tg - kMaskSteps);
+            double A_, G_, B_;
+            momentum_factors((double)cur.k, gam, A_, G_, B_);
+            const double tau_ = eta / cur.om, sigma_ = eta * cur.om;
+            const uint64_t restarts = __ballot(cur.rs != 0);
+            const int32_t cnt = tg + 1 < kMaskSteps ? (int32_t)(tg + 1) : kMaskSteps;
+#pragma unroll 1
+            for (int32_t it = 0; it < cnt; ++it) {
+                const double tau = lane_value(tau_, it), sigma = lane_value(sigma_, it);
+                double bxh[S], byh[SR];
+                if (restarts >> it & 1) {
 #pragma unroll
                     for (int q = 0; q < S; ++q) {
                         bxh[q] = bx[q] + bx0[q];
-                        bx[q] = 0.0;
-                        bx0[q] = 0.0;
+                        bx[q] = bx0[q] = 0.0;
                     }
 #pragma unroll
                     for (int q = 0; q < SR; ++q) {
                         byh[q] = by[q] + by0[q];
-                        by[q] = 0.0;
-                        by0[q] = 0.0;
+                        by[q] = by0[q] = 0.0;
                     }
                 } else {
-                    const int64_t k = kk_[t];
-                    const double ak = (double)(k + 1) / (double)(k + 2), bk = 1.0 / (double)(k + 2);
+                    const double A = lane_value(A_, it), G = lane_value(G_, it), B = lane_value(B_, it);
 #pragma unroll
                     for (int q = 0; q < S; ++q) {
-                        const double v = bx[q];
-                        bxh[q] = ak * (1.0 + gam) * v;
-                        bx0[q] += bk * v;
-                        bx[q] = -ak * gam * v;
+                        bxh[q] = A * bx[q];
+                        bx0[q] += B * bx[q];
+                        bx[q] *= -G;
                     }
 #pragma unroll
                     for (int q = 0; q < SR; ++q) {
-                        const double v = by[q];
-                        byh[q] = ak * (1.0 + gam) * v;
-                        by0[q] += bk * v;
-                        by[q] = -ak * gam * v;
+                        byh[q] = A * by[q];
+                        by0[q] += B * by[q];
+                        by[q] *= -G;
                     }
                 }
-            }
-            // dual step: yhat = sigma (v - clamp(v, -u_c, -l_c)), v = y/sigma - A~ xext
-            const uint64_t *ymt = ym + (size_t)t * 2 * yw;
+                // dual step: yhat = w - clamp(w, -sigma u_c, -sigma l_c), w = y - sigma A~ xext
 #pragma unroll
-            for (int q = 0; q < SR; ++q) {
-                const int32_t i = tid + q * BT;
-                if (i < g.m) {
-                    const uint64_t bit = 1ull << (i & 63);
-                    const bool at_u = (ymt[2 * (i >> 6)] & bit) != 0;
-                    const bool at_l = (ymt[2 * (i >> 6) + 1] & bit) != 0;
-                    const double bv = (at_u || at_l) ? sigma * byh[q] : 0.0;
-                    if (at_u) gur[q] += sigma * byh[q];
-                    if (at_l) glr[q] += sigma * byh[q];
-                    by[q] += bv / sigma;
-                    ba[i] = -bv;
+                for (int q = 0; q < SR; ++q) {
+                    const bool at_u = lane_bit(mask_word(cur.y, it * 2 * SR + 2 * q));
+                    const bool at_l = lane_bit(mask_word(cur.y, it * 2 * SR + 2 * q + 1));
+                    const double sv = sigma * byh[q];
+                    const double vu = at_u ? sv : 0.0, vl = at_l ? sv : 0.0;
+                    gur[q] += vu;
+                    glr[q] += vl;
+                    by[q] += at_u || at_l ? byh[q] : 0.0;
+                    myy[q * BT] = at_u || at_l ? -sv : 0.0;
                 }
-            }
-            __syncthreads();
-            // xext = 2 xhat - x, then the primal step xhat = clamp(x - tau (c - A~'y))
-            const uint64_t *xmt = xm + (size_t)t * xw;
+                __syncthreads();
+                // xext = 2 xhat - x, then the primal step xhat = clamp(x - tau (c - A~'y))
+                double s[S];
+                M.cols(s);
 #pragma unroll
-            for (int q = 0; q < S; ++q) {
-                const int32_t j = tid + q * BT;
-                if (j < g.n) {
-                    const double bxe = M.col(lds, q);
-                    const double bh = bxh[q] + 2.0 * bxe;
-                    bx[q] -= bxe;
-                    const bool inside = (xmt[j >> 6] >> (j & 63)) & 1ull;
-                    const double bu = inside ? bh : 0.0;
-                    bx[q] += bu;
-                    gcr[q] += -tau * bu;
-                    tmp[j] = tau * bu;
+                for (int q = 0; q < S; ++q) {
+                    const double bh = bxh[q] + 2.0 * s[q];
+                    const double bu = lane_bit(mask_word(cur.x, it * S + q)) ? bh : 0.0;
+                    bx[q] = (bx[q] - s[q]) + bu;
+                    const double tb = tau * bu;
+                    gcr[q] -= tb;
+                    myx[q * PX] = tb;
                 }
-            }
-            __syncthreads();
+                __syncthreads();
+                // (the next iteration writes ba only, which all threads have read)
+                double p[SR];
+                M.rows(p);
 #pragma unroll
-            for (int q = 0; q < SR; ++q) {
-                const int32_t i = tid + q * BT;
-                if (i < g.m) by[q] += M.row(lds, q);
+                for (int q = 0; q < SR; ++q) by[q] += p[q];
             }
-            __syncthreads();
         }
         // c~ = D_c c, l~_c = D_r l_c, u~_c = D_r u_c
+        int32_t t0 = (int32_t)threadIdx.x;
+        asm volatile("" : "+v"(t0));
 #pragma unroll
         for (int q = 0; q < S; ++q) {
-            const int32_t j = threadIdx.x + q * BT;
+            const int32_t j = t0 + q * BT;
             if (j < g.n) u.gc[g.vc + j] = Dc[j] * gcr[q];
         }
 #pragma unroll
         for (int q = 0; q < SR; ++q) {
-            const int32_t i = threadIdx.x + q * BT;
+            const int32_t i = t0 + q * BT;
             if (i < g.m) {
                 u.glc[g.vr + i] = isfinite(a.lc_o[g.vr + i]) ? Dr[i] * glr[q] : 0.0;
                 u.guc[g.vr + i] = isfinite(a.uc_o[g.vr + i]) ? Dr[i] * gur[q] : 0.0;
             }
         }
-        (void)lane;
         __syncthreads();
     }
 }
@@ -2565,21 +2588,6 @@ static size_t lds_per_workgroup() {
     return v;
 }
 
-// Columns per thread of the register-resident kernels at BT threads (4 with
-// one row slice, 8 with two), or 0 when the batch does not qualify: a shared
-// matrix with narrow slices, BT >= 256, and x_ext, y, the row data and the
-// column anchor, cost and upper bound in one workgroup's LDS.
-template <int BT>
-static int res_columns(const BatchHandle &h) {
-    if (!(h.onchip && h.resident && h.shared && h.ts_wmax >= 1 && h.ts_wmax <= kResCol &&
-          h.as_wmax <= kResRow && BT >= 256))
-        return 0;
-    if ((4 * (size_t)h.nmax + 4 * (size_t)h.mmax) * sizeof(double) > lds_per_workgroup()) return 0;
-    if (h.nmax <= 4 * BT && h.mmax <= BT) return 4;
-    if (h.nmax <= 8 * BT && h.mmax <= 2 * BT) return 8;
-    return 0;
-}
-
 template <int BT, class K>
 static int32_t resident_lds(BatchHandle &h, K kernel, size_t lds) {
     int dev = 0, per_cu = 0;
@@ -2592,11 +2600,11 @@ static int32_t resident_lds(BatchHandle &h, K kernel, size_t lds) {
     return wg;
 }
 
-// Columns per thread of k_batch_solve_res at bt threads, or 0 when the batch
+// Columns per thread of the register-resident kernels at bt threads, or 0 when the batch
 // does not qualify: a shared matrix with narrow slices, 256 or 512 threads
 // (1,024 would leave 128 registers each and spill) and one row per thread, two
 // at 8 columns.
-static int res_solve_columns(const BatchHandle &h, int32_t bt) {
+static int res_columns(const BatchHandle &h, int32_t bt) {
     if (!(h.onchip && h.resident && h.shared && h.ts_wmax >= 1 && h.ts_wmax <= kResCol &&
           h.as_wmax <= kResRow && (bt == 256 || bt == 512)))
         return 0;
@@ -2606,24 +2614,24 @@ static int res_solve_columns(const BatchHandle &h, int32_t bt) {
     return 0;
 }
 
-// Threads of k_batch_solve_res when the caller chose none, 0 where it does not
+// Threads of the register-resident kernels when the caller chose none, 0 where they do not
 // apply: 256 while that gives a thread at most 4 columns, else 512. Measured
 // per iteration of 256 instances, 2,048 in the batch: 16x16 grids (960
 // columns) 0.33 us at 256 and 0.52 at 512; 22x22 grids (1,848 columns) 0.79 at
 // 256 and 0.62 at 512.
-static int32_t res_solve_threads(const BatchHandle &h) {
-    const int s = res_solve_columns(h, 256);
+static int32_t res_threads(const BatchHandle &h) {
+    const int s = res_columns(h, 256);
     if (s > 0 && s <= 4) return 256;
-    return res_solve_columns(h, 512) > 0 ? 512 : 0;
+    return res_columns(h, 512) > 0 ? 512 : 0;
 }
 
-template <int BT, int S>
-static void launch_solve_res_t(BatchHandle &h, const BOpts &o, const BArgs &a) {
+template <int BT, int S, class... Args>
+static void launch_res_t(BatchHandle &h, void (*kernel)(Args...), Args... args) {
     constexpr size_t lds = ResLds<BT, S>::bytes;
     static_assert(lds <= 128 * 1024, "the reductions need LDS of their own");
-    const int32_t wg = resident_lds<BT>(h, &k_batch_solve_res<BT, S>, lds);
+    const int32_t wg = resident_lds<BT>(h, kernel, lds);
     PDHG_HIP(hipMemsetAsync(h.queue.p, 0, sizeof(int32_t), h.stream));
-    k_batch_solve_res<BT, S><<<wg, BT, lds, h.stream>>>(a, o);
+    kernel<<<wg, BT, lds, h.stream>>>(args...);
     PDHG_HIP(hipGetLastError());
 }
 
@@ -2766,10 +2774,10 @@ template <int BT>
 static void launch_solve_t(BatchHandle &h, const BOpts &o) {
     BArgs a = batch_args(h);
     if constexpr (BT == 256 || BT == 512) {
-        switch (res_solve_columns(h, BT)) {
-            case 2: return launch_solve_res_t<BT, 2>(h, o, a);
-            case 4: return launch_solve_res_t<BT, 4>(h, o, a);
-            case 8: return launch_solve_res_t<BT, 8>(h, o, a);
+        switch (res_columns(h, BT)) {
+            case 2: return launch_res_t<BT, 2>(h, &k_batch_solve_res<BT, 2>, a, o);
+            case 4: return launch_res_t<BT, 4>(h, &k_batch_solve_res<BT, 4>, a, o);
+            case 8: return launch_res_t<BT, 8>(h, &k_batch_solve_res<BT, 8>, a, o);
             default: break;
         }
     }
@@ -2838,8 +2846,7 @@ static void dispatch_setup(BatchHandle &h, int32_t count) {
 // Solves that test infeasibility rays carry a larger register budget: the
 // 1024-thread variants spill, so the default launch takes at most 512 there.
 static void dispatch_solve(BatchHandle &h, const BOpts &o) {
-    int32_t threads = (o.detect && !h.threads_set) ? std::min(h.threads, 512) : h.threads;
-    if (const int32_t t = h.threads_set ? 0 : res_solve_threads(h)) threads = t;
+    const int32_t threads = (o.detect && !h.threads_set) ? std::min(h.threads, 512) : h.threads;
     switch (threads) {
         case 64: launch_solve_t<64>(h, o); break;
         case 128: launch_solve_t<128>(h, o); break;
@@ -2962,10 +2969,7 @@ BatchHandle *batch_create(const pdhg_batch_problem &p, const pdhg_options &o, vo
         h.as_wmax = build_batch_sell(s, nb, ro, h.arp, h.aci, h.ava, h.nnz, h.asp, h.asci, h.asva, h.asfirst);
         h.ts_wmax = build_batch_sell(s, nb, co, h.trp, h.tci, h.tva, h.nnz, h.tsp, h.tsci, h.tsva, h.tsfirst);
     }
-    // one instance per CU would take 1024 threads; a matrix that the
-    // register-resident kernels can hold runs faster at 512 (their 1024-thread
-    // variants spill)
-    if (p.q_rank == 0 && h.threads == 1024 && res_columns<512>(h)) h.threads = 512;
+    if (const int32_t t = p.q_rank == 0 ? res_threads(h) : 0) h.threads = t;
     if (p.q_rank > 0) bqp_create(h, p);
     h.setup_seconds = now_seconds() - t0;
     return hp.release();
@@ -3097,22 +3101,13 @@ static void launch_unrolled_t(BatchHandle &h, const UArgs &u) {
     BArgs a = batch_args(h);
     const BOpts o = batch_opts(h.opt);
     const size_t lds = onchip_lds(h);
-    PDHG_HIP(hipMemsetAsync(h.queue.p, 0, sizeof(int32_t), h.stream));
     if constexpr (BT == 256 || BT == 512) {
-        const int rc = res_columns<BT>(h);
-        if (rc) {
-            const size_t l = (4 * (size_t)h.nmax + 4 * (size_t)h.mmax) * sizeof(double);
-            if (rc == 4) {
-                const int32_t wg = resident_lds<BT>(h, &k_batch_unrolled_res<BT, 4>, l);
-                k_batch_unrolled_res<BT, 4><<<wg, BT, l, h.stream>>>(a, o, u, h.nmax, h.mmax);
-            } else {
-                const int32_t wg = resident_lds<BT>(h, &k_batch_unrolled_res<BT, 8>, l);
-                k_batch_unrolled_res<BT, 8><<<wg, BT, l, h.stream>>>(a, o, u, h.nmax, h.mmax);
-            }
-            PDHG_HIP(hipGetLastError());
-            return;
-        }
+        const int cols = res_columns(h, BT);
+        if (cols == 2) return launch_res_t<BT, 2>(h, &k_batch_unrolled_res<BT, 2>, a, o, u);
+        if (cols == 4) return launch_res_t<BT, 4>(h, &k_batch_unrolled_res<BT, 4>, a, o, u);
+        if (cols == 8) return launch_res_t<BT, 8>(h, &k_batch_unrolled_res<BT, 8>, a, o, u);
     }
+    PDHG_HIP(hipMemsetAsync(h.queue.p, 0, sizeof(int32_t), h.stream));
     if (lds) {
         const int32_t wg = resident_lds<BT>(h, &k_batch_unrolled<BT, true>, lds);
         k_batch_unrolled<BT, true><<<wg, BT, lds, h.stream>>>(a, o, u, h.nmax);
@@ -3128,22 +3123,13 @@ static void launch_backward_t(BatchHandle &h, const UArgs &u) {
     BArgs a = batch_args(h);
     const BOpts o = batch_opts(h.opt);
     const size_t lds = onchip_lds(h);
-    PDHG_HIP(hipMemsetAsync(h.queue.p, 0, sizeof(int32_t), h.stream));
     if constexpr (BT == 256 || BT == 512) {
-        const int rc = res_columns<BT>(h);
-        if (rc) {
-            const size_t l = ((size_t)h.nmax + (size_t)h.mmax) * sizeof(double);
-            if (rc == 4) {
-                const int32_t wg = resident_lds<BT>(h, &k_batch_backward_res<BT, 4>, l);
-                k_batch_backward_res<BT, 4><<<wg, BT, l, h.stream>>>(a, o, u, h.nmax);
-            } else {
-                const int32_t wg = resident_lds<BT>(h, &k_batch_backward_res<BT, 8>, l);
-                k_batch_backward_res<BT, 8><<<wg, BT, l, h.stream>>>(a, o, u, h.nmax);
-            }
-            PDHG_HIP(hipGetLastError());
-            return;
-        }
+        const int cols = res_columns(h, BT);
+        if (cols == 2) return launch_res_t<BT, 2>(h, &k_batch_backward_res<BT, 2>, a, o, u);
+        if (cols == 4) return launch_res_t<BT, 4>(h, &k_batch_backward_res<BT, 4>, a, o, u);
+        if (cols == 8) return launch_res_t<BT, 8>(h, &k_batch_backward_res<BT, 8>, a, o, u);
     }
+    PDHG_HIP(hipMemsetAsync(h.queue.p, 0, sizeof(int32_t), h.stream));
     if (lds) {
         const int32_t wg = resident_lds<BT>(h, &k_batch_backward<BT, true>, lds);
         k_batch_backward<BT, true><<<wg, BT, lds, h.stream>>>(a, o, u, h.nmax);
