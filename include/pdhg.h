@@ -294,14 +294,16 @@ pdhg_err pdhg_batch_solve(pdhg_batch *b, const double *x_init, const double *y_i
 
 /* Launch shape of the persistent kernels: threads per instance (64, 128,
  * 256, 512 or 1024) and the number of resident workgroups (<= 0: as many as
- * the GPU holds). The default after create is 1024 threads when the batch
- * has at most one instance per compute unit, else the fewest threads, from
- * 256, that give each thread at most 8 columns and 8 rows of the largest
- * instance; QP batches, and LP solves that test infeasibility rays, take at
- * most 512 of them unless this call or pdhg_batch_autotune chose the shape.
- * LP batches on a shared matrix with at most 2 entries a column and 8 a row
- * (the matrix then stays in registers) start at 256 threads up to 1,024
- * columns and 256 rows, and at 512 up to 4,096 and 1,024. */
+ * the GPU holds). Unless this call or pdhg_batch_autotune chose the shape, an
+ * LP solve takes one column or row of the largest instance per thread up to
+ * 512 threads (two per thread when the batch has more instances than run at
+ * once), 512 up to 1,024 columns and 1,024 beyond. The unrolled passes start
+ * at 1024 threads when the batch has at most one instance per compute unit,
+ * else at the fewest, from 256, that give each thread at most 8 columns and 8
+ * rows; QP batches take at most 512 of them. LP batches on a shared matrix
+ * with at most 2 entries a column and 8 a row (the matrix then stays in
+ * registers) start at 256 threads up to 1,024 columns and 256 rows, and at
+ * 512 up to 4,096 and 1,024. */
 pdhg_err pdhg_batch_set_launch(pdhg_batch *b, int32_t threads, int32_t workgroups);
 
 /* Time `iterations` iterations of every instance for each supported thread

@@ -45,9 +45,15 @@ struct BArgs {
     double *x_out, *y_out;
     BatchRes *res;
     int32_t *queue;
-    // SELL-64 copies (entry k of local row i at sp[sfirst + i/64] + 64 k + i%64)
-    const int32_t *asp, *asci, *asfirst, *tsp, *tsci, *tsfirst;
-    const double *asva, *tsva;
+    // SELL-64 copies of A~ and A~' over positions: position i of an instance
+    // is its row perm[i] (ragged batches: rows by falling length, so that a
+    // slice's rows fill its width; null: position = row). Pair k of position
+    // i, its entries 2k and 2k + 1, is at 64 (sp[sfirst + i/64] + k) + i%64:
+    // the two positions gathered, as byte offsets 8 j in the halves of sci,
+    // and the two values; past a row's end they are (0, 0.0).
+    const int32_t *asp, *asfirst, *aperm, *tsp, *tsfirst, *tperm;
+    const uint32_t *asci, *tsci;
+    const double2 *asva, *tsva;
     double *lhist;    // Lanczos alpha / beta per instance, stride 2 (power_max_iters + 1)
     // infeasibility rays: the anchor's products A~x0 (like y), A~'y0 (like x)
     // and this check's A~xhat, A~'yhat
@@ -215,53 +221,34 @@ __device__ __forceinline__ void csr_rescale(const int32_t *__restrict__ rp, cons
     for (; e < e1; ++e) va[e] = va[e] / (r * f[ci[e]]);
 }
 
-// Row sum of a SELL-64 slice row: lane `lane` of slice `sl`; entries walked in
-// row order (padding entries are (column 0, value 0.0)).
-__device__ __forceinline__ double sell_dot_bw(const int32_t *__restrict__ ci, const double *__restrict__ va,
-                                              int32_t base, int32_t w, int32_t lane,
-                                              const double *__restrict__ v);
-
-__device__ __forceinline__ double sell_dot(const int32_t *__restrict__ sp, const int32_t *__restrict__ ci,
-                                           const double *__restrict__ va, int32_t sl, int32_t lane,
-                                           const double *__restrict__ v) {
-    const int32_t b = sp[sl], w = (sp[sl + 1] - b) >> 6;
-    return sell_dot_bw(ci, va, b, w, lane, v);
+// The two gathers of one pair of SELL-64 entries, added in row order.
+template <class V>
+__device__ __forceinline__ double sell_pair(uint32_t c, double2 a, const V *v, double acc) {
+    acc = fma(a.x, v[(c & 0xffffu) >> 3], acc);
+    return fma(a.y, v[c >> 19], acc);
 }
 
-// Same with the slice's first entry and width already known. Entries are
-// fetched four at a time before they are used (independent loads in flight),
-// and added in row order.
-__device__ __forceinline__ double sell_dot_bw(const int32_t *__restrict__ ci, const double *__restrict__ va,
-                                              int32_t base, int32_t w, int32_t lane,
-                                              const double *__restrict__ v) {
+// Row sum of a SELL-64 slice row: lane `lane` of slice `sl`; entries walked in
+// row order, two pairs' loads in flight.
+__device__ __forceinline__ double sell_dot(const int32_t *__restrict__ sp, const uint32_t *__restrict__ ci,
+                                           const double2 *__restrict__ va, int32_t sl, int32_t lane,
+                                           const double *__restrict__ v) {
+    const int32_t k1 = sp[sl + 1];
+    int32_t k = sp[sl];
     double acc = 0.0;
-    int32_t k = 0;
-    for (; k + 4 <= w; k += 4) {
-        int32_t c[4];
-        double a[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int32_t e = base + 64 * (k + q) + lane;
-            c[q] = ci[e];
-            a[q] = va[e];
-        }
-#pragma unroll
-        for (int q = 0; q < 4; ++q) acc = fma(a[q], v[c[q]], acc);
+    for (; k + 2 <= k1; k += 2) {
+        const int32_t e = 64 * k + lane;
+        const uint32_t c0 = ci[e], c1 = ci[e + 64];
+        const double2 a0 = va[e], a1 = va[e + 64];
+        acc = sell_pair(c0, a0, v, acc);
+        acc = sell_pair(c1, a1, v, acc);
     }
-    if (k + 2 <= w) {
-        const int32_t e0 = base + 64 * k + lane, e1 = e0 + 64;
-        const int32_t c0 = ci[e0], c1 = ci[e1];
-        const double a0 = va[e0], a1 = va[e1];
-        acc = fma(a0, v[c0], acc);
-        acc = fma(a1, v[c1], acc);
-        k += 2;
-    }
-    if (k < w) {
-        const int32_t e = base + 64 * k + lane;
-        acc = fma(va[e], v[ci[e]], acc);
-    }
+    if (k < k1) acc = sell_pair(ci[64 * k + lane], va[64 * k + lane], v, acc);
     return acc;
 }
+
+// The row (column) at position i of an instance whose permutation starts at p.
+__device__ __forceinline__ int32_t row_at(const int32_t *p, int32_t off, int32_t i) { return p ? p[off + i] : i; }
 
 __device__ __forceinline__ uint64_t splitmix64_b(uint64_t x) {
     uint64_t z = x + 0x9e3779b97f4a7c15ull;
@@ -515,8 +502,7 @@ __global__ __launch_bounds__(BT) void k_batch_setup(BArgs a, BOpts o, int32_t co
 // dual-ray bound terms over the rows) and maxima rm = (dual-ray violation,
 // primal-ray violation), every thread receiving the totals, for the
 // memory-resident k_batch_solve (a pass of its own there; x0 is read from
-// memory). k_batch_solve_lds sums the same terms in the same order inside its
-// check loops.
+// memory). The on-chip kernels sum the same terms inside their check loops.
 template <int BT>
 __device__ __forceinline__ void batch_ray_pass(const BArgs &a, const Geo &g,
                                             const double *__restrict__ xh, const double *__restrict__ yh,
@@ -809,356 +795,6 @@ __global__ __launch_bounds__(BT) void k_batch_solve(BArgs a, BOpts o) {
     }
 }
 
-// Same iteration with the gathered vectors held on chip: y (for A~'y) and
-// x_ext (for A~x_ext; at checks the PDHG points) live in LDS, next to the
-// per-row anchor and bounds; each thread owns S columns and S rows, in SELL-64
-// slices, so a wave's slices are whole. The matrix entries stream from the
-// SELL-64 copies (L2) on every product; the per-column iterate, anchor, cost
-// and bounds stay in registers. Same arithmetic and summation order as
-// k_batch_solve.
-template <int BT, int S, bool RAYS>
-__global__ __launch_bounds__(BT) void k_batch_solve_lds(BArgs a, BOpts o, int32_t nmax, int32_t mmax) {
-    extern __shared__ double lds[];
-    double *sx = lds;                 // x_ext, at checks x^
-    double *sy = lds + nmax;          // y, at checks y^
-    double *slc = sy + mmax;          // scaled row bounds
-    double *suc = slc + mmax;
-    double *y0 = suc + mmax;          // dual anchor
-    for (;;) {
-        const int32_t b = next_instance<BT>(a.queue);
-        if (b >= a.B) return;
-        const Geo g = geometry(a, b);
-        const int32_t as0 = a.shared ? 0 : a.asfirst[b], ts0 = a.shared ? 0 : a.tsfirst[b];
-        const int32_t lane = (int32_t)(threadIdx.x & 63);
-        const double *Dr = a.Dr + g.dr, *Dc = a.Dc + g.dc;
-        const double *c_o = a.c_o + g.vc, *lv_o = a.lv_o + g.vc, *uv_o = a.uv_o + g.vc;
-        const double *lc_o = a.lc_o + g.vr, *uc_o = a.uc_o + g.vr;
-        double *__restrict__ xh = a.xh + g.vc;
-        double *__restrict__ aty = a.aty + g.vc;
-        double *__restrict__ y = a.y + g.vr;
-        double *__restrict__ yh = a.yh + g.vr;
-        const int32_t *__restrict__ tsci = a.tsci;
-        const int32_t *__restrict__ asci = a.asci;
-        const double *__restrict__ tsva = a.tsva;
-        const double *__restrict__ asva = a.asva;
-        const double eta = a.eta[g.sidx];
-        const double gam = o.gamma;
-
-        // slice start and width of each owned column / row
-        int32_t tbase[S], tw[S], abase[S], aw[S];
-        // per-column iterate, anchor, cost and bounds
-        double xr[S], x0r[S], cr[S], lvr[S], uvr[S];
-        double nrm[4] = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-        for (int q = 0; q < S; ++q) {
-            const int32_t j = threadIdx.x + q * BT;
-            tbase[q] = tw[q] = abase[q] = aw[q] = 0;
-            xr[q] = x0r[q] = cr[q] = lvr[q] = uvr[q] = 0.0;
-            if (j < g.n) {
-                const int32_t sl = ts0 + (j >> 6);
-                tbase[q] = a.tsp[sl];
-                tw[q] = (a.tsp[sl + 1] - tbase[q]) >> 6;
-            }
-            if (j < g.m) {
-                const int32_t sl = as0 + (j >> 6);
-                abase[q] = a.asp[sl];
-                aw[q] = (a.asp[sl + 1] - abase[q]) >> 6;
-            }
-            if (j < g.n) {
-                const double d = Dc[j];
-                const double cj = d * c_o[j];
-                const double l = lv_o[j] / d, u = uv_o[j] / d;
-                cr[q] = cj;
-                lvr[q] = l;
-                uvr[q] = u;
-                nrm[0] += cj * cj;
-                nrm[2] += c_o[j] * c_o[j];
-                const double v0 = a.x_init ? a.x_init[g.vc + j] / d : 0.0;
-                xr[q] = clampd(v0, l, u);
-                x0r[q] = xr[q];
-            }
-            const int32_t i = j;
-            if (i < g.m) {
-                const double d = Dr[i];
-                const double l = d * lc_o[i], u = d * uc_o[i];
-                slc[i] = l;
-                suc[i] = u;
-                double bb = 0.0, bo = 0.0;
-                if (isfinite(l)) bb = fmax(bb, fabs(l));
-                if (isfinite(u)) bb = fmax(bb, fabs(u));
-                if (isfinite(lc_o[i])) bo = fmax(bo, fabs(lc_o[i]));
-                if (isfinite(uc_o[i])) bo = fmax(bo, fabs(uc_o[i]));
-                nrm[1] += bb * bb;
-                nrm[3] += bo * bo;
-                const double v0 = a.y_init ? a.y_init[g.vr + i] / d : 0.0;
-                const double lo = isfinite(u) ? -INFINITY : 0.0;
-                const double hi = isfinite(l) ? INFINITY : 0.0;
-                const double yv = clampd(v0, lo, hi);
-                sy[i] = yv;
-                y0[i] = yv;
-            }
-        }
-        // A~'y (gathering y from LDS) for owned column q; A~x_ext for owned row q
-        auto col_dot = [&](int q) -> double {
-            return sell_dot_bw(tsci, tsva, tbase[q], tw[q], lane, sy);
-        };
-        auto row_dot = [&](int q) -> double {
-            return sell_dot_bw(asci, asva, abase[q], aw[q], lane, sx);
-        };
-        wg_sum<BT, 4>(nrm);
-        const double cn = sqrt(nrm[0]), bn = sqrt(nrm[1]);
-        const double cnorm = sqrt(nrm[2]), bnorm = sqrt(nrm[3]);
-        double omega = (cn > 1e-10 && bn > 1e-10) ? cn / bn : 1.0;
-        double tau = eta / omega, sigma = eta * omega;
-
-        int64_t t = 0, k = 0, restarts = 0;
-        int32_t tc = 0;   // t modulo check_every, without a 64-bit division per iteration
-        double r_start = 0.0, r_prev = 0.0;
-        int32_t status = 0;
-        bool anchor_valid = false;   // the anchor's products are stored (after a restart)
-        double ray_scale = 0.0;
-        double kkt = 0.0, rel_p = 0.0, rel_d = 0.0, rel_g = 0.0, P = 0.0, D = 0.0;
-        for (;;) {
-            // an opaque copy of the thread index: the element addresses are
-            // recomputed each iteration (two VALU ops) instead of being hoisted
-            // into ~40 registers per slot, which would spill
-            int32_t tid = (int32_t)threadIdx.x;
-            asm volatile("" : "+v"(tid));
-            const bool check = tc == 0;
-            const bool last = t + 1 >= o.limit;
-            const bool keep = check || last;
-            const double ak = (double)(k + 1) / (double)(k + 2), bk = 1.0 / (double)(k + 2);
-#pragma unroll
-            for (int q = 0; q < S; ++q) {
-                const int32_t j = tid + q * BT;
-                if (j < g.n) {
-                    const double s = col_dot(q);
-                    const double xhat = clampd(xr[q] - tau * (cr[q] - s), lvr[q], uvr[q]);
-                    sx[j] = 2.0 * xhat - xr[q];
-                    if (keep) {
-                        xh[j] = xhat;
-                        aty[j] = s;
-                    } else {
-                        xr[q] = ak * ((1.0 + gam) * xhat - gam * xr[q]) + bk * x0r[q];
-                    }
-                }
-            }
-            __syncthreads();
-#pragma unroll
-            for (int q = 0; q < S; ++q) {
-                const int32_t i = tid + q * BT;
-                if (i < g.m) {
-                    const double av = row_dot(q);
-                    const double li = slc[i], ui = suc[i];
-                    const double yv = sy[i];
-                    const double yhat = dual_prox(yv, av, sigma, li, ui);
-                    if (keep) {
-                        yh[i] = yhat;
-                        y[i] = yv;
-                    } else {
-                        sy[i] = ak * ((1.0 + gam) * yhat - gam * yv) + bk * y0[i];
-                    }
-                }
-            }
-            __syncthreads();
-            if (!keep) {
-                ++k;
-                ++t;
-                tc = tc + 1 == o.check_every ? 0 : tc + 1;
-                continue;
-            }
-            // check: the PDHG points replace x_ext and y in LDS for the products
-#pragma unroll
-            for (int q = 0; q < S; ++q) {
-                const int32_t j = tid + q * BT;
-                if (j < g.n) sx[j] = xh[j];
-                if (j < g.m) sy[j] = yh[j];
-            }
-            __syncthreads();
-            // KKT sums, then (RAYS) the ray sums: v[10], v[11] over the columns
-            // (bound terms, c'dx), v[12] over the rows; rmx the ray violations
-            constexpr int NV = RAYS ? 13 : 10;
-            double v[NV], rmx[2] = {0.0, 0.0};
-#pragma unroll
-            for (int q = 0; q < NV; ++q) v[q] = 0.0;
-#pragma unroll
-            for (int q = 0; q < S; ++q) {
-                const int32_t j = tid + q * BT;
-                if (j < g.n) {
-                    const double qq = col_dot(q);
-                    const double xhv = xh[j];
-                    const double dx = xhv - xr[q];
-                    v[0] += dx * dx;
-                    v[1] += (qq - aty[j]) * dx;
-                    const double d0 = xhv - x0r[q];
-                    v[2] += d0 * d0;
-                    const double d = Dc[j];
-                    const double gr = c_o[j] - qq / d;
-                    const double lo = lv_o[j], hi = uv_o[j];
-                    const bool lf = isfinite(lo), uf = isfinite(hi);
-                    const double lam = (!lf && !uf) ? 0.0 : (lf && !uf) ? fmax(gr, 0.0) : (!lf && uf) ? fmin(gr, 0.0) : gr;
-                    const double rd = gr - lam;
-                    v[3] += rd * rd;
-                    v[4] += c_o[j] * (d * xhv);
-                    v[5] += (lf ? lo * fmax(lam, 0.0) : 0.0) - (uf ? hi * fmax(-lam, 0.0) : 0.0);
-                    if constexpr (RAYS) {
-                        a.qh[g.vc + j] = qq;
-                        double s2[2], m2[2];
-                        ray_col_terms(qq, a.q0[g.vc + j], d, xhv - x0r[q], c_o[j], lo, hi, s2, m2);
-                        v[10] += s2[0];
-                        v[11] += s2[1];
-                        rmx[0] = fmax(rmx[0], m2[0]);
-                        rmx[1] = fmax(rmx[1], m2[1]);
-                    }
-                }
-            }
-#pragma unroll
-            for (int q = 0; q < S; ++q) {
-                const int32_t i = tid + q * BT;
-                if (i < g.m) {
-                    const double p = row_dot(q);
-                    const double d = Dr[i];
-                    const double ax = p / d;
-                    const double lo = lc_o[i], hi = uc_o[i];
-                    const double rpr = ax - clampd(ax, lo, hi);
-                    v[6] += rpr * rpr;
-                    const double yhv = yh[i];
-                    const double yo = d * yhv;
-                    v[7] += (isfinite(lo) ? lo * fmax(yo, 0.0) : 0.0) - (isfinite(hi) ? hi * fmax(-yo, 0.0) : 0.0);
-                    const double dy = yhv - y[i];
-                    v[8] += dy * dy;
-                    const double d0 = yhv - y0[i];
-                    v[9] += d0 * d0;
-                    if constexpr (RAYS) {
-                        a.ph[g.vr + i] = p;
-                        double s1[1], m2[2];
-                        ray_row_terms(p, a.p0[g.vr + i], d, d0, lo, hi, s1, m2);
-                        v[12] += s1[0];
-                        rmx[0] = fmax(rmx[0], m2[0]);
-                        rmx[1] = fmax(rmx[1], m2[1]);
-                    }
-                }
-            }
-            wg_sum<BT, NV>(v);
-            P = v[4];
-            D = v[7] + v[5];
-            rel_p = sqrt(v[6]) / (1.0 + bnorm);
-            rel_d = sqrt(v[3]) / (1.0 + cnorm);
-            rel_g = fabs(P - D) / (1.0 + fabs(P) + fabs(D));
-            kkt = rel_p;
-            if (rel_d > kkt || isnan(rel_d)) kkt = rel_d;
-            if (rel_g > kkt || isnan(rel_g)) kkt = rel_g;
-            if (isnan(kkt)) {
-                status = PDHG_NUMERICAL_ERROR;
-                break;
-            }
-            if (kkt <= o.eps) {
-                status = PDHG_OPTIMAL;
-                break;
-            }
-            if (RAYS && anchor_valid) {
-                // the rays' terms were summed in the check loops above, in
-                // the order of the separate pass of k_batch_solve
-                double rs[3] = {v[RAYS ? 10 : 0], v[RAYS ? 11 : 0], v[RAYS ? 12 : 0]};
-                double rm[2] = {rmx[0], rmx[1]};
-                wg_max<BT, 2>(rm);
-                const double obj_d = rs[0] + rs[2], obj_p = rs[1];
-                if (o.eps_pinf > 0.0 && obj_d > 0.0 && rm[0] <= o.eps_pinf * obj_d) {
-                    status = PDHG_PRIMAL_INFEASIBLE;
-                    ray_scale = 1.0 / obj_d;
-                    break;
-                }
-                if (o.eps_dinf > 0.0 && obj_p < 0.0 && rm[1] <= o.eps_dinf * (-obj_p)) {
-                    status = PDHG_DUAL_INFEASIBLE;
-                    ray_scale = -1.0 / obj_p;
-                    break;
-                }
-            }
-            if (last) {
-                status = PDHG_ITERATION_LIMIT;
-                break;
-            }
-            const double r2 = v[0] / tau + v[8] / sigma + 2.0 * v[1];
-            const double r = r2 > 0.0 ? sqrt(r2) : 0.0;
-            bool restart = false;
-            if (t == 0) {
-                r_start = r;
-                r_prev = r;
-            } else if (r <= o.beta_suff * r_start || (r <= o.beta_nec * r_start && r > r_prev) ||
-                       (double)k >= o.beta_art * (double)t) {
-                restart = true;
-            } else {
-                r_prev = r;
-            }
-            if (restart) {
-                const double dxr = sqrt(v[2]), dyr = sqrt(v[9]);
-                omega = batch_new_omega(omega, dxr, dyr);
-                tau = eta / omega;
-                sigma = eta * omega;
-#pragma unroll
-                for (int q = 0; q < S; ++q) {
-                    const int32_t j = tid + q * BT;
-                    if (j < g.n) {
-                        xr[q] = xh[j];
-                        x0r[q] = xr[q];
-                    }
-                    if (j < g.m) {
-                        sy[j] = yh[j];
-                        y0[j] = yh[j];
-                    }
-                }
-                if (RAYS) {   // the new anchor's products, from this check
-                    int32_t t0 = (int32_t)threadIdx.x;
-                    asm volatile("" : "+v"(t0));
-                    for (int32_t j = t0; j < g.n; j += BT) a.q0[g.vc + j] = a.qh[g.vc + j];
-                    for (int32_t i = t0; i < g.m; i += BT) a.p0[g.vr + i] = a.ph[g.vr + i];
-                    anchor_valid = true;
-                }
-                k = 0;
-                r_start = r;
-                r_prev = r;
-                ++restarts;
-            } else {
-#pragma unroll
-                for (int q = 0; q < S; ++q) {
-                    const int32_t j = tid + q * BT;
-                    if (j < g.n) xr[q] = ak * ((1.0 + gam) * xh[j] - gam * xr[q]) + bk * x0r[q];
-                    if (j < g.m) sy[j] = ak * ((1.0 + gam) * yh[j] - gam * y[j]) + bk * y0[j];
-                }
-                ++k;
-            }
-            ++t;
-            tc = tc + 1 == o.check_every ? 0 : tc + 1;
-            __syncthreads();
-        }
-        // original-space output of the last PDHG point, or the certifying ray
-        const bool xray = status == PDHG_DUAL_INFEASIBLE, yray = status == PDHG_PRIMAL_INFEASIBLE;
-#pragma unroll
-        for (int q = 0; q < S; ++q) {
-            const int32_t j = threadIdx.x + q * BT;
-            if (j < g.n) a.x_out[g.vc + j] = Dc[j] * (xray ? (xh[j] - x0r[q]) * ray_scale : xh[j]);
-            if (j < g.m) a.y_out[g.vr + j] = Dr[j] * (yray ? (yh[j] - y0[j]) * ray_scale : yh[j]);
-        }
-        if (threadIdx.x == 0) {
-            BatchRes r;
-            r.pobj = P;
-            r.dobj = D;
-            r.rel_p = rel_p;
-            r.rel_d = rel_d;
-            r.rel_g = rel_g;
-            r.kkt = kkt;
-            r.omega = omega;
-            r.eta = eta;
-            r.iterations = t + 1;
-            r.restarts = restarts;
-            r.status = status;
-            r.power_iters = a.power_iters[g.sidx];
-            a.res[b] = r;
-        }
-        __syncthreads();
-    }
-}
-
 // ---------------------------------------------------------------------------
 // solve with a register-resident matrix
 
@@ -1218,14 +854,18 @@ struct ResEntries {
         int32_t e0 = 0, w = 0;
         if (j < g.n) {
             e0 = a.tsp[j >> 6];
-            w = (a.tsp[(j >> 6) + 1] - e0) >> 6;
+            w = a.tsp[(j >> 6) + 1] - e0;
         }
 #pragma unroll
-        for (int u = 0; u < kResCol; ++u) {
+        for (int u = 0; u < kResCol / 2; ++u) {
             const bool in = u < w;
-            const int32_t e = e0 + 64 * u + (j & 63);
-            tci[q][u] = sy + (in ? a.tsci[e] : 0);
-            tva[q][u] = in ? a.tsva[e] : 0.0;
+            const int32_t e = 64 * (e0 + u) + (j & 63);
+            const uint32_t c = in ? a.tsci[e] : 0;
+            const double2 v = in ? a.tsva[e] : double2{0.0, 0.0};
+            tci[q][2 * u] = sy + ((c & 0xffffu) >> 3);
+            tci[q][2 * u + 1] = sy + (c >> 19);
+            tva[q][2 * u] = v.x;
+            tva[q][2 * u + 1] = v.y;
         }
     }
     __device__ __forceinline__ void load_rows(const BArgs &a, const Geo &g, const LdsDouble *sx) {
@@ -1237,14 +877,18 @@ struct ResEntries {
             int32_t e0 = 0, w = 0;
             if (i < g.m) {
                 e0 = a.asp[i >> 6];
-                w = (a.asp[(i >> 6) + 1] - e0) >> 6;
+                w = a.asp[(i >> 6) + 1] - e0;
             }
 #pragma unroll
-            for (int u = 0; u < kResRow; ++u) {
+            for (int u = 0; u < kResRow / 2; ++u) {
                 const bool in = u < w;
-                const int32_t e = e0 + 64 * u + (i & 63);
-                rci[q][u] = sx + res_pos(in ? a.asci[e] : 0);
-                rva[q][u] = in ? a.asva[e] : 0.0;
+                const int32_t e = 64 * (e0 + u) + (i & 63);
+                const uint32_t c = in ? a.asci[e] : 0;
+                const double2 v = in ? a.asva[e] : double2{0.0, 0.0};
+                rci[q][2 * u] = sx + res_pos((c & 0xffffu) >> 3);
+                rci[q][2 * u + 1] = sx + res_pos(c >> 19);
+                rva[q][2 * u] = v.x;
+                rva[q][2 * u + 1] = v.y;
             }
         }
     }
@@ -1680,6 +1324,525 @@ __global__ __launch_bounds__(BT) void k_batch_solve_res(BArgs a, BOpts o) {
 }
 
 // ---------------------------------------------------------------------------
+// on-chip solve of any instance with at most 8 columns and rows per thread
+
+// Pairs of entries of each owned column (row) that stay in registers: what
+// fits beside the iterates (40 registers a column and row at two of each) in
+// 256 registers, or in 128 at 1,024 threads.
+template <int BT, int S, int SR>
+struct LdsShape {
+    static constexpr int KC = BT == 1024 ? 0 : S == 1 ? 8 : S == 2 ? 6 : S == 4 ? 2 : 0;
+    static constexpr int KR = BT == 1024 || S == 8 ? 0 : S == 1 ? 14 : SR == 1 ? 12 : SR == 2 ? 6 : 2;
+    static constexpr int U = BT == 1024 && S == 8 ? 2 : 4;
+    static constexpr bool ahead = BT < 1024, keep = BT < 1024 || S < 4;
+    static constexpr int32_t x = SR * BT;                  // x_ext after y
+    static constexpr int32_t step = x + S * BT;            // momentum factors
+    static constexpr size_t bytes = ((size_t)step + 4 * kResSteps) * sizeof(double);
+};
+
+typedef __attribute__((address_space(3))) char LdsByte;
+
+// sell_pair for a vector in LDS.
+__device__ __forceinline__ double lds_pair(uint32_t c, double2 a, const LdsDouble *v, double acc) {
+    const LdsByte *p = (const LdsByte *)v;
+    acc = fma(a.x, *(const LdsDouble *)(p + (c & 0xffffu)), acc);
+    return fma(a.y, *(const LdsDouble *)(p + (c >> 16)), acc);
+}
+
+// The pairs of one position of a SELL-64 slice: the first K in registers, the
+// next lc in LDS, the rest streamed. In LDS a slice's pair takes kPairBytes:
+// 64 pairs of values, then 64 words of positions.
+constexpr int kPairBytes = 64 * (16 + 4);
+typedef double DoublePair __attribute__((ext_vector_type(2)));
+typedef __attribute__((address_space(3))) DoublePair LdsDoublePair;
+typedef __attribute__((address_space(3))) uint32_t LdsWord;
+
+template <int K, int U, bool AHEAD>
+struct SellRow {
+    uint32_t c[K > 0 ? K : 1];
+    double2 v[K > 0 ? K : 1];
+    int32_t w, lc;   // pairs of the slice, of them in LDS (scalars)
+    int32_t e0;      // this lane's first pair
+    LdsByte *lv;     // and its first pair of values in LDS
+
+    // cache: room pairs at byte off are the slice's share of the LDS
+    __device__ __forceinline__ void load(const uint32_t *__restrict__ ci, const double2 *__restrict__ va, int32_t first,
+                                         int32_t end, int32_t lane, LdsByte *cache, int32_t off, int32_t room) {
+        w = __builtin_amdgcn_readfirstlane(end - first);
+        lc = __builtin_amdgcn_readfirstlane(w - K < room ? (w > K ? w - K : 0) : room);
+        e0 = 64 * first + lane;
+        lv = cache + off + 16 * lane;
+#pragma unroll
+        for (int u = 0; u < K; ++u) {
+            c[u] = u < w ? ci[e0 + 64 * u] : 0;
+            v[u] = u < w ? va[e0 + 64 * u] : double2{0.0, 0.0};
+        }
+        LdsByte *p = cache + off;
+        for (int32_t k = 0; k < lc; ++k, p += kPairBytes) {
+            const double2 t = va[e0 + 64 * (K + k)];
+            *(LdsDoublePair *)(p + 16 * lane) = DoublePair{t.x, t.y};
+            *(LdsWord *)(p + 1024 + 4 * lane) = ci[e0 + 64 * (K + k)];
+        }
+    }
+    // row sum in row order; the streamed pairs come in groups of U (AHEAD: one
+    // group ahead of the products)
+    __device__ __forceinline__ double dot(const uint32_t *__restrict__ ci, const double2 *__restrict__ va,
+                                          const LdsDouble *vec, int32_t lane) const {
+        uint32_t nc[U];
+        double2 nv[U];
+        auto fetch = [&](int32_t k) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int32_t kk = k + u < w ? k + u : w - 1;
+                nc[u] = ci[e0 + 64 * kk];
+                nv[u] = va[e0 + 64 * kk];
+            }
+        };
+        if (AHEAD && w > K + lc) fetch(K + lc);
+        double acc = 0.0;
+#pragma unroll
+        for (int k = 0; k < K; k += 2)
+            if (k < w) {
+#pragma unroll
+                for (int u = k; u < k + 2 && u < K; ++u) acc = lds_pair(c[u], v[u], vec, acc);
+            }
+        const LdsByte *p = lv, *pw = lv + 1024 - 12 * lane;
+#pragma unroll 1
+        for (int32_t k = 0; k < lc; k += 2) {
+            // the second pair of an odd count lies in the next slice's share or
+            // past it, inside the allocation; it is read and not used
+            const DoublePair v0 = *(const LdsDoublePair *)p, v1 = *(const LdsDoublePair *)(p + kPairBytes);
+            const uint32_t c0 = *(const LdsWord *)pw, c1 = *(const LdsWord *)(pw + kPairBytes);
+            acc = lds_pair(c0, double2{v0.x, v0.y}, vec, acc);
+            if (k + 1 < lc) acc = lds_pair(c1, double2{v1.x, v1.y}, vec, acc);
+            p += 2 * kPairBytes;
+            pw += 2 * kPairBytes;
+        }
+#pragma unroll 1
+        for (int32_t k = K + lc; k < w; k += U) {
+            if (!AHEAD) fetch(k);
+            uint32_t cc[U];
+            double2 cv[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                cc[u] = nc[u];
+                cv[u] = nv[u];
+            }
+            if (AHEAD && k + U < w) fetch(k + U);
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (k + u < w) acc = lds_pair(cc[u], cv[u], vec, acc);
+        }
+        return acc;
+    }
+};
+
+// The iteration of k_batch_solve on chip: a workgroup's instance lives in
+// position space (see BArgs), S columns and SR rows per thread in whole
+// SELL-64 slices; iterates, anchors, costs and bounds in registers, the
+// gathered vectors x_ext and y (at checks the PDHG point) in LDS, the first
+// pairs of every row and column in registers and the others streamed from L2
+// or the memory-side cache. Iterations between checks, the dual step and the
+// momentum factors are those of k_batch_solve_res.
+//
+// What bounds it: up to about 300 rows (5% dense) the latency of the two
+// phases - gathers, the sum of a row in its order, a barrier -, beyond that
+// the entries that neither registers nor LDS hold. Rows sorted by length cut
+// the padding from 1.6 to 1.1, positions of 16 bits and pairs the bytes from
+// 12 to 10 an entry at half the loads. Per iteration of 256 instances, 1,024
+// in the batch, n = 2 m: m = 57 0.98 -> 0.36 us, 120 2.45 -> 0.77, 250 8.2 ->
+// 2.6, 480 33 -> 11.2 (4.9 TB/s from the memory-side cache).
+template <int BT, int S, int SR>
+__global__ __launch_bounds__(BT) __attribute__((amdgpu_waves_per_eu(BT == 1024 ? 4 : 2))) void k_batch_solve_lds(BArgs a, BOpts o, int32_t cache_pairs) {
+    using L = LdsShape<BT, S, SR>;
+    constexpr int NW = BT / 64;
+    extern __shared__ __attribute__((aligned(16))) double lds[];
+    LdsByte *const cache = (LdsByte *)(LdsDouble *)lds + L::bytes;
+    LdsDouble *const sy = (LdsDouble *)lds, *const sx = sy + L::x, *const stp = sy + L::step;
+    for (;;) {
+        const int32_t b = next_instance<BT>(a.queue);
+        if (b >= a.B) return;
+        const Geo g = geometry(a, b);
+        const int32_t wave = __builtin_amdgcn_readfirstlane((int32_t)threadIdx.x >> 6);
+        const int32_t lane = (int32_t)(threadIdx.x & 63);
+        const double *Dr = a.Dr + g.dr, *Dc = a.Dc + g.dc;
+        const double *lc_o = a.lc_o + g.vr, *uc_o = a.uc_o + g.vr;
+        const double eta = a.eta[g.sidx];
+        const double gam = o.gamma;
+        SellRow<L::KC, L::U, L::ahead> col[S];
+        SellRow<L::KR, L::U, L::ahead> row[SR];
+        double xr[S], x0r[S], crr[S], lrr[S], urr[S];
+        // scaled cost and bounds of the owned columns, in memory where the
+        // registers would spill
+        auto c_of = [&](int q) { return L::keep ? crr[q] : a.c[g.vc + (int32_t)threadIdx.x + q * BT]; };
+        auto l_of = [&](int q) { return L::keep ? lrr[q] : a.lv[g.vc + (int32_t)threadIdx.x + q * BT]; };
+        auto u_of = [&](int q) { return L::keep ? urr[q] : a.uv[g.vc + (int32_t)threadIdx.x + q * BT]; };
+        double yr[SR], y0r[SR], lo[SR], hi[SR];   // lo, hi: -sigma u_c, -sigma l_c
+        LdsDouble *const myx = sx + (int32_t)threadIdx.x, *const myy = sy + (int32_t)threadIdx.x;
+        // an equal share of the cache for every slice
+        const int32_t ncs = (g.n + 63) >> 6, nrs = (g.m + 63) >> 6, room = cache_pairs / (ncs + nrs);
+        double nrm[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int q = 0; q < S; ++q) {
+            const int32_t j = (int32_t)threadIdx.x + q * BT, sl = wave + q * NW;
+            int32_t k0 = 0, k1 = 0;
+            if (64 * sl < g.n) {
+                const int32_t f = a.shared ? 0 : a.tsfirst[b];
+                k0 = a.tsp[f + sl];
+                k1 = a.tsp[f + sl + 1];
+            }
+            col[q].load(a.tsci, a.tsva, k0, k1, lane, cache, kPairBytes * room * sl, room);
+            xr[q] = crr[q] = lrr[q] = urr[q] = 0.0;
+            if (j < g.n) {
+                const int32_t jo = row_at(a.tperm, g.c0, j);
+                const double d = Dc[jo], co = a.c_o[g.vc + jo];
+                const double c = d * co, l = a.lv_o[g.vc + jo] / d, u = a.uv_o[g.vc + jo] / d;
+                if (L::keep) {
+                    crr[q] = c;
+                    lrr[q] = l;
+                    urr[q] = u;
+                } else {
+                    a.c[g.vc + j] = c;
+                    a.lv[g.vc + j] = l;
+                    a.uv[g.vc + j] = u;
+                }
+                nrm[0] += c * c;
+                nrm[2] += co * co;
+                xr[q] = clampd(a.x_init ? a.x_init[g.vc + jo] / d : 0.0, l, u);
+            }
+            x0r[q] = xr[q];
+        }
+#pragma unroll
+        for (int q = 0; q < SR; ++q) {
+            const int32_t i = (int32_t)threadIdx.x + q * BT, sl = wave + q * NW;
+            int32_t k0 = 0, k1 = 0;
+            if (64 * sl < g.m) {
+                const int32_t f = a.shared ? 0 : a.asfirst[b];
+                k0 = a.asp[f + sl];
+                k1 = a.asp[f + sl + 1];
+            }
+            row[q].load(a.asci, a.asva, k0, k1, lane, cache, kPairBytes * room * (ncs + sl), room);
+            yr[q] = lo[q] = hi[q] = 0.0;
+            if (i < g.m) {
+                const int32_t io = row_at(a.aperm, g.r0, i);
+                const double d = Dr[io], loo = lc_o[io], hio = uc_o[io];
+                const double l = d * loo, u = d * hio;
+                double bb = 0.0, bo = 0.0;
+                if (isfinite(l)) bb = fmax(bb, fabs(l));
+                if (isfinite(u)) bb = fmax(bb, fabs(u));
+                if (isfinite(loo)) bo = fmax(bo, fabs(loo));
+                if (isfinite(hio)) bo = fmax(bo, fabs(hio));
+                nrm[1] += bb * bb;
+                nrm[3] += bo * bo;
+                yr[q] = clampd(a.y_init ? a.y_init[g.vr + io] / d : 0.0, isfinite(u) ? -INFINITY : 0.0,
+                               isfinite(l) ? INFINITY : 0.0);
+            }
+            y0r[q] = yr[q];
+            myy[q * BT] = yr[q];
+        }
+        wg_sum<BT, 4>(nrm);
+        const double cn = sqrt(nrm[0]), bn = sqrt(nrm[1]);
+        const double cnorm = uniform_value(sqrt(nrm[2])), bnorm = uniform_value(sqrt(nrm[3]));
+        double omega = uniform_value((cn > 1e-10 && bn > 1e-10) ? cn / bn : 1.0);
+        double tau = uniform_value(eta / omega), sigma = uniform_value(eta * omega);
+        auto dual_bounds = [&]() {
+            int32_t t0 = (int32_t)threadIdx.x;
+            asm volatile("" : "+v"(t0));
+#pragma unroll
+            for (int q = 0; q < SR; ++q) {
+                const int32_t i = t0 + q * BT;
+                if (i < g.m) {
+                    const int32_t io = row_at(a.aperm, g.r0, i);
+                    lo[q] = -sigma * (Dr[io] * uc_o[io]);
+                    hi[q] = -sigma * (Dr[io] * lc_o[io]);
+                }
+            }
+        };
+        dual_bounds();
+        // s = A~'y, x^ of the owned columns, x_ext to LDS; y^ of the owned rows
+        auto columns = [&](double (&s)[S], double (&xn)[S]) {
+#pragma unroll
+            for (int q = 0; q < S; ++q) {
+                s[q] = xn[q] = 0.0;
+                if (L::keep ? 64 * (wave + q * NW) < g.n : (int32_t)threadIdx.x + q * BT < g.n) {
+                    s[q] = col[q].dot(a.tsci, a.tsva, sy, lane);
+                    xn[q] = clamp_quiet(xr[q] - tau * (c_of(q) - s[q]), l_of(q), u_of(q));
+                    myx[q * BT] = 2.0 * xn[q] - xr[q];
+                }
+            }
+        };
+        auto rows = [&](double (&yn)[SR]) {
+#pragma unroll
+            for (int q = 0; q < SR; ++q) {
+                yn[q] = 0.0;
+                if (64 * (wave + q * NW) < g.m) {
+                    const double w = fma(-sigma, row[q].dot(a.asci, a.asva, sx, lane), yr[q]);
+                    yn[q] = w - clamp_quiet(w, lo[q], hi[q]);
+                }
+            }
+        };
+
+        int64_t t = 0, k = 0, restarts = 0;
+        int32_t tc = 0;   // t modulo check_every
+        double r_start = 0.0, r_prev = 0.0;
+        int32_t status = 0;
+        bool anchor_valid = false;   // the anchor's products are stored (after a restart)
+        double ray_scale = 0.0;
+        double kkt = 0.0, rel_p = 0.0, rel_d = 0.0, rel_g = 0.0, P = 0.0, D = 0.0;
+        for (;;) {
+            // iterations t .. t + plain - 1 run without a check, then one that
+            // keeps its PDHG point for the check
+            int32_t plain = tc == 0 ? 0 : o.check_every - tc;
+            if ((int64_t)plain > o.limit - 1 - t) plain = (int32_t)(o.limit - 1 - t);
+            plain = __builtin_amdgcn_readfirstlane(plain);
+            for (int32_t p = 0; p < plain; p += kResSteps) {
+                const int32_t cnt = plain - p < kResSteps ? plain - p : kResSteps;
+                for (int32_t u = (int32_t)threadIdx.x; u < cnt; u += BT) {
+                    double A, G, B;
+                    momentum_factors((double)(k + p + u), gam, A, G, B);
+                    stp[4 * u] = A;
+                    stp[4 * u + 1] = G;
+                    stp[4 * u + 2] = B;
+                }
+                __syncthreads();
+#pragma unroll 1
+                for (int32_t it = 0; it < cnt; ++it) {
+                    const double A = stp[4 * it], G = stp[4 * it + 1], B = stp[4 * it + 2];
+                    double s[S], xn[S], yn[SR];
+                    columns(s, xn);
+#pragma unroll
+                    for (int q = 0; q < S; ++q) xr[q] = A * xn[q] - G * xr[q] + B * x0r[q];
+                    __syncthreads();
+                    rows(yn);
+#pragma unroll
+                    for (int q = 0; q < SR; ++q) {
+                        yr[q] = A * yn[q] - G * yr[q] + B * y0r[q];
+                        myy[q * BT] = yr[q];
+                    }
+                    __syncthreads();
+                }
+            }
+            t += plain;
+            k += plain;
+            const bool last = t + 1 >= o.limit;
+            // the iteration before the check: its PDHG point replaces x_ext and y in LDS
+            double s[S];
+            {
+                double xn[S], yn[SR];
+                columns(s, xn);
+                __syncthreads();
+                rows(yn);
+                __syncthreads();
+#pragma unroll
+                for (int q = 0; q < S; ++q) myx[q * BT] = xn[q];
+#pragma unroll
+                for (int q = 0; q < SR; ++q) myy[q * BT] = yn[q];
+            }
+            __syncthreads();
+            // KKT sums, then the ray sums: v[10], v[11] over the columns
+            // (bound terms, c'dx), v[12] over the rows; rmx the ray violations
+            int32_t t0 = (int32_t)threadIdx.x;
+            asm volatile("" : "+v"(t0));   // addresses are formed here, not kept over the loop
+            const bool rays = o.detect && anchor_valid;
+            double v[13], rmx[2] = {0.0, 0.0};
+#pragma unroll
+            for (int q = 0; q < 13; ++q) v[q] = 0.0;
+#pragma unroll
+            for (int q = 0; q < SR; ++q) {
+                const int32_t i = t0 + q * BT;
+                if (64 * (wave + q * NW) < g.m) {
+                    const double p = row[q].dot(a.asci, a.asva, sx, lane);
+                    if (i < g.m) {
+                        const int32_t io = row_at(a.aperm, g.r0, i);
+                        const double d = Dr[io], loo = lc_o[io], hio = uc_o[io], yh = myy[q * BT];
+                        const double ax = p / d;
+                        const double rpr = ax - clampd(ax, loo, hio);
+                        v[6] += rpr * rpr;
+                        const double yo = d * yh;
+                        v[7] += (isfinite(loo) ? loo * fmax(yo, 0.0) : 0.0) -
+                                (isfinite(hio) ? hio * fmax(-yo, 0.0) : 0.0);
+                        const double dy = yh - yr[q];
+                        v[8] += dy * dy;
+                        const double d0 = yh - y0r[q];
+                        v[9] += d0 * d0;
+                        if (o.detect) a.ph[g.vr + i] = p;
+                        if (rays) {
+                            double s1[1], m2[2];
+                            ray_row_terms(p, a.p0[g.vr + i], d, d0, loo, hio, s1, m2);
+                            v[12] += s1[0];
+                            rmx[0] = fmax(rmx[0], m2[0]);
+                            rmx[1] = fmax(rmx[1], m2[1]);
+                        }
+                    }
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+#pragma unroll
+            for (int q = 0; q < S; ++q) {
+                const int32_t j = t0 + q * BT;
+                if (64 * (wave + q * NW) < g.n) {
+                    const double qq = col[q].dot(a.tsci, a.tsva, sy, lane);
+                    if (j < g.n) {
+                        const int32_t jo = row_at(a.tperm, g.c0, j);
+                        const double d = Dc[jo], xh = myx[q * BT];
+                        const double dx = xh - xr[q];
+                        v[0] += dx * dx;
+                        v[1] += (qq - s[q]) * dx;
+                        const double d0 = xh - x0r[q];
+                        v[2] += d0 * d0;
+                        const double c = c_of(q), l = l_of(q), u = u_of(q);
+                        const double gr = c - qq;   // D_c times the original-space gradient
+                        const bool lf = isfinite(l), uf = isfinite(u);
+                        const double lam = (!lf && !uf) ? 0.0 : (lf && !uf) ? fmax(gr, 0.0) : (!lf && uf) ? fmin(gr, 0.0) : gr;
+                        const double rd = (gr - lam) / d;
+                        v[3] += rd * rd;
+                        v[4] += c * xh;
+                        v[5] += (lf ? l * fmax(lam, 0.0) : 0.0) - (uf ? u * fmax(-lam, 0.0) : 0.0);
+                        if (o.detect) a.qh[g.vc + j] = qq;
+                        if (rays) {
+                            double s2[2], m2[2];
+                            ray_col_terms(qq, a.q0[g.vc + j], d, d0, c / d, l * d, u * d, s2, m2);
+                            v[10] += s2[0];
+                            v[11] += s2[1];
+                            rmx[0] = fmax(rmx[0], m2[0]);
+                            rmx[1] = fmax(rmx[1], m2[1]);
+                        }
+                    }
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            wg_sum<BT, 13>(v);
+            P = uniform_value(v[4]);
+            D = uniform_value(v[7] + v[5]);
+            rel_p = uniform_value(sqrt(v[6]) / (1.0 + bnorm));
+            rel_d = uniform_value(sqrt(v[3]) / (1.0 + cnorm));
+            rel_g = uniform_value(fabs(P - D) / (1.0 + fabs(P) + fabs(D)));
+            kkt = rel_p;
+            if (rel_d > kkt || isnan(rel_d)) kkt = rel_d;
+            if (rel_g > kkt || isnan(rel_g)) kkt = rel_g;
+            if (isnan(kkt)) {
+                status = PDHG_NUMERICAL_ERROR;
+                break;
+            }
+            if (kkt <= o.eps) {
+                status = PDHG_OPTIMAL;
+                break;
+            }
+            if (rays) {
+                wg_max<BT, 2>(rmx);
+                const double obj_d = v[10] + v[12], obj_p = v[11];
+                if (o.eps_pinf > 0.0 && obj_d > 0.0 && rmx[0] <= o.eps_pinf * obj_d) {
+                    status = PDHG_PRIMAL_INFEASIBLE;
+                    ray_scale = uniform_value(1.0 / obj_d);
+                    break;
+                }
+                if (o.eps_dinf > 0.0 && obj_p < 0.0 && rmx[1] <= o.eps_dinf * (-obj_p)) {
+                    status = PDHG_DUAL_INFEASIBLE;
+                    ray_scale = uniform_value(-1.0 / obj_p);
+                    break;
+                }
+            }
+            if (last) {
+                status = PDHG_ITERATION_LIMIT;
+                break;
+            }
+            const double r2 = v[0] / tau + v[8] / sigma + 2.0 * v[1];
+            const double r = uniform_value(r2 > 0.0 ? sqrt(r2) : 0.0);
+            bool restart = false;
+            if (t == 0) {
+                r_start = r;
+                r_prev = r;
+            } else if (r <= o.beta_suff * r_start || (r <= o.beta_nec * r_start && r > r_prev) ||
+                       (double)k >= o.beta_art * (double)t) {
+                restart = true;
+            } else {
+                r_prev = r;
+            }
+            if (restart) {
+                // exp(log(dyr / dxr) / 2 + log(omega) / 2), without a call that
+                // would save half of the registers
+                const double dxr = sqrt(v[2]), dyr = sqrt(v[9]);
+                if (dxr > 1e-10 && dyr > 1e-10) omega = uniform_value(sqrt(dyr / dxr) * sqrt(omega));
+                tau = uniform_value(eta / omega);
+                sigma = uniform_value(eta * omega);
+                // the check's products are those of the new anchor
+#pragma unroll
+                for (int q = 0; q < S; ++q) {
+                    const int32_t j = t0 + q * BT;
+                    xr[q] = x0r[q] = j < g.n ? myx[q * BT] : 0.0;
+                    if (o.detect && j < g.n) a.q0[g.vc + j] = a.qh[g.vc + j];
+                }
+#pragma unroll
+                for (int q = 0; q < SR; ++q) {
+                    const int32_t i = t0 + q * BT;
+                    yr[q] = y0r[q] = myy[q * BT];
+                    if (o.detect && i < g.m) a.p0[g.vr + i] = a.ph[g.vr + i];
+                }
+                dual_bounds();
+                anchor_valid = true;
+                k = 0;
+                r_start = r;
+                r_prev = r;
+                ++restarts;
+            } else {
+                double A, G, B;
+                momentum_factors((double)k, gam, A, G, B);
+#pragma unroll
+                for (int q = 0; q < S; ++q) xr[q] = A * myx[q * BT] - G * xr[q] + B * x0r[q];
+#pragma unroll
+                for (int q = 0; q < SR; ++q) {
+                    yr[q] = A * myy[q * BT] - G * yr[q] + B * y0r[q];
+                    myy[q * BT] = yr[q];
+                }
+                ++k;
+            }
+            ++t;
+            tc = o.check_every == 1 ? 0 : 1;
+            __syncthreads();
+        }
+        // original-space output of the last PDHG point, or the certifying ray
+        const bool xray = status == PDHG_DUAL_INFEASIBLE, yray = status == PDHG_PRIMAL_INFEASIBLE;
+        int32_t t0 = (int32_t)threadIdx.x;
+        asm volatile("" : "+v"(t0));
+#pragma unroll
+        for (int q = 0; q < S; ++q) {
+            const int32_t j = t0 + q * BT;
+            if (j < g.n) {
+                const int32_t jo = row_at(a.tperm, g.c0, j);
+                const double xh = myx[q * BT];
+                a.x_out[g.vc + jo] = Dc[jo] * (xray ? (xh - x0r[q]) * ray_scale : xh);
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < SR; ++q) {
+            const int32_t i = t0 + q * BT;
+            if (i < g.m) {
+                const int32_t io = row_at(a.aperm, g.r0, i);
+                const double yh = myy[q * BT];
+                a.y_out[g.vr + io] = Dr[io] * (yray ? (yh - y0r[q]) * ray_scale : yh);
+            }
+        }
+        if (threadIdx.x == 0) {
+            BatchRes r;
+            r.pobj = P;
+            r.dobj = D;
+            r.rel_p = rel_p;
+            r.rel_d = rel_d;
+            r.rel_g = rel_g;
+            r.kkt = kkt;
+            r.omega = omega;
+            r.eta = eta;
+            r.iterations = t + 1;
+            r.restarts = restarts;
+            r.status = status;
+            r.power_iters = a.power_iters[g.sidx];
+            a.res[b] = r;
+        }
+        __syncthreads();
+    }
+}
+
+// ---------------------------------------------------------------------------
 // unrolled iterations with a frozen schedule, and their reverse pass
 
 struct UArgs {
@@ -1712,6 +1875,9 @@ __global__ __launch_bounds__(BT) void k_batch_unrolled(BArgs a, BOpts o, UArgs u
         const int32_t *arp = a.arp + g.r0, *trp = a.trp + g.c0;
         const int32_t *aci = a.aci, *tci = a.tci;
         const double *ava = a.ava, *tva = a.tva;
+        // on chip the instance lives in position space: only its inputs and
+        // outputs go through the permutations
+        const int32_t *aperm = ONCHIP ? a.aperm : nullptr, *tperm = ONCHIP ? a.tperm : nullptr;
         const double *Dr = a.Dr + g.dr, *Dc = a.Dc + g.dc;
         const double *c_o = a.c_o + g.vc, *lv_o = a.lv_o + g.vc, *uv_o = a.uv_o + g.vc;
         const double *lc_o = a.lc_o + g.vr, *uc_o = a.uc_o + g.vr;
@@ -1734,16 +1900,18 @@ __global__ __launch_bounds__(BT) void k_batch_unrolled(BArgs a, BOpts o, UArgs u
         const double gam = o.gamma;
         double nrm[2] = {0.0, 0.0};
         for (int32_t j = threadIdx.x; j < g.n; j += BT) {
-            const double d = Dc[j];
-            const double cj = d * c_o[j];
+            const int32_t jo = row_at(tperm, g.c0, j);
+            const double d = Dc[jo];
+            const double cj = d * c_o[jo];
             c[j] = cj;
-            lv[j] = lv_o[j] / d;
-            uv[j] = uv_o[j] / d;
+            lv[j] = lv_o[jo] / d;
+            uv[j] = uv_o[jo] / d;
             nrm[0] += cj * cj;
         }
         for (int32_t i = threadIdx.x; i < g.m; i += BT) {
-            const double d = Dr[i];
-            const double l = d * lc_o[i], uu = d * uc_o[i];
+            const int32_t io = row_at(aperm, g.r0, i);
+            const double d = Dr[io];
+            const double l = d * lc_o[io], uu = d * uc_o[io];
             lc[i] = l;
             uc[i] = uu;
             double bb = 0.0;
@@ -1888,8 +2056,14 @@ __global__ __launch_bounds__(BT) void k_batch_unrolled(BArgs a, BOpts o, UArgs u
             __syncthreads();
         }
         if (u.replay == 0 && threadIdx.x == 0) rs_[u.T - 1] = 0;
-        for (int32_t j = threadIdx.x; j < g.n; j += BT) a.x_out[g.vc + j] = Dc[j] * xh[j];
-        for (int32_t i = threadIdx.x; i < g.m; i += BT) a.y_out[g.vr + i] = Dr[i] * yh[i];
+        for (int32_t j = threadIdx.x; j < g.n; j += BT) {
+            const int32_t jo = row_at(tperm, g.c0, j);
+            a.x_out[g.vc + jo] = Dc[jo] * xh[j];
+        }
+        for (int32_t i = threadIdx.x; i < g.m; i += BT) {
+            const int32_t io = row_at(aperm, g.r0, i);
+            a.y_out[g.vr + io] = Dr[io] * yh[i];
+        }
         __syncthreads();
     }
 }
@@ -2352,17 +2526,21 @@ __global__ __launch_bounds__(BT) void k_batch_backward(BArgs a, BOpts o, UArgs u
         }
         const int32_t as0 = (ONCHIP && !a.shared) ? a.asfirst[b] : 0;
         const int32_t ts0 = (ONCHIP && !a.shared) ? a.tsfirst[b] : 0;
-        double *gc = u.gc + g.vc, *glc = u.glc + g.vr, *guc = u.guc + g.vr;
+        const int32_t *aperm = ONCHIP ? a.aperm : nullptr, *tperm = ONCHIP ? a.tperm : nullptr;
+        // gradient sums, by position
+        double *gc = a.aty + g.vc, *glc = a.lc + g.vr, *guc = a.uc + g.vr;
         for (int32_t j = threadIdx.x; j < g.n; j += BT) {
             bx[j] = 0.0;
             bx0[j] = 0.0;
-            bxh[j] = Dc[j] * u.gx[g.vc + j];
+            const int32_t jo = row_at(tperm, g.c0, j);
+            bxh[j] = Dc[jo] * u.gx[g.vc + jo];
             gc[j] = 0.0;
         }
         for (int32_t i = threadIdx.x; i < g.m; i += BT) {
             by[i] = 0.0;
             by0[i] = 0.0;
-            byh[i] = Dr[i] * u.gy[g.vr + i];
+            const int32_t io = row_at(aperm, g.r0, i);
+            byh[i] = Dr[io] * u.gy[g.vr + io];
             glc[i] = 0.0;
             guc[i] = 0.0;
         }
@@ -2432,10 +2610,14 @@ __global__ __launch_bounds__(BT) void k_batch_backward(BArgs a, BOpts o, UArgs u
             __syncthreads();
         }
         // c~ = D_c c, l~_c = D_r l_c, u~_c = D_r u_c
-        for (int32_t j = threadIdx.x; j < g.n; j += BT) gc[j] = Dc[j] * gc[j];
+        for (int32_t j = threadIdx.x; j < g.n; j += BT) {
+            const int32_t jo = row_at(tperm, g.c0, j);
+            u.gc[g.vc + jo] = Dc[jo] * gc[j];
+        }
         for (int32_t i = threadIdx.x; i < g.m; i += BT) {
-            glc[i] = isfinite(a.lc_o[g.vr + i]) ? Dr[i] * glc[i] : 0.0;
-            guc[i] = isfinite(a.uc_o[g.vr + i]) ? Dr[i] * guc[i] : 0.0;
+            const int32_t io = row_at(aperm, g.r0, i);
+            u.glc[g.vr + io] = isfinite(a.lc_o[g.vr + io]) ? Dr[io] * glc[i] : 0.0;
+            u.guc[g.vr + io] = isfinite(a.uc_o[g.vr + io]) ? Dr[io] * guc[i] : 0.0;
         }
         __syncthreads();
     }
@@ -2551,10 +2733,12 @@ static BArgs batch_args(BatchHandle &h) {
     a.asci = h.asci.p;
     a.asva = h.asva.p;
     a.asfirst = h.asfirst.p;
+    a.aperm = h.aperm.p;
     a.tsp = h.tsp.p;
     a.tsci = h.tsci.p;
     a.tsva = h.tsva.p;
     a.tsfirst = h.tsfirst.p;
+    a.tperm = h.tperm.p;
     a.lhist = h.lhist.p;
     a.p0 = h.rp0.p;
     a.q0 = h.rq0.p;
@@ -2625,121 +2809,176 @@ static int32_t res_threads(const BatchHandle &h) {
     return res_columns(h, 512) > 0 ? 512 : 0;
 }
 
-template <int BT, int S, class... Args>
-static void launch_res_t(BatchHandle &h, void (*kernel)(Args...), Args... args) {
-    constexpr size_t lds = ResLds<BT, S>::bytes;
-    static_assert(lds <= 128 * 1024, "the reductions need LDS of their own");
+// Launch of a persistent kernel: as many workgroups as fit, or as asked for.
+template <int BT, class... Args>
+static void launch_queue_t(BatchHandle &h, size_t lds, void (*kernel)(Args...), Args... args) {
     const int32_t wg = resident_lds<BT>(h, kernel, lds);
     PDHG_HIP(hipMemsetAsync(h.queue.p, 0, sizeof(int32_t), h.stream));
     kernel<<<wg, BT, lds, h.stream>>>(args...);
     PDHG_HIP(hipGetLastError());
 }
-
-template <int BT, int S>
-static void launch_solve_lds_t(BatchHandle &h, const BOpts &o, BArgs a, size_t lds) {
-    const void *kern = o.detect ? reinterpret_cast<const void *>(&k_batch_solve_lds<BT, S, true>)
-                                : reinterpret_cast<const void *>(&k_batch_solve_lds<BT, S, false>);
-    int dev = 0, per_cu = 0;
-    PDHG_HIP(hipGetDevice(&dev));
-    hipDeviceProp_t prop;
-    PDHG_HIP(hipGetDeviceProperties(&prop, dev));
-    PDHG_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, BT, lds));
-    int32_t wg = std::min(h.B, std::max(1, per_cu) * prop.multiProcessorCount);
-    if (h.workgroups > 0) wg = std::min(wg, h.workgroups);
-    PDHG_HIP(hipMemsetAsync(h.queue.p, 0, sizeof(int32_t), h.stream));
-    if (o.detect)
-        k_batch_solve_lds<BT, S, true><<<wg, BT, lds, h.stream>>>(a, o, h.nmax, h.mmax);
-    else
-        k_batch_solve_lds<BT, S, false><<<wg, BT, lds, h.stream>>>(a, o, h.nmax, h.mmax);
-    PDHG_HIP(hipGetLastError());
+template <int BT, int S, class... Args>
+static void launch_res_t(BatchHandle &h, void (*kernel)(Args...), Args... args) {
+    constexpr size_t lds = ResLds<BT, S>::bytes;
+    static_assert(lds <= 150 * 1024, "the reductions need LDS of their own");
+    launch_queue_t<BT>(h, lds, kernel, args...);
+}
+template <int BT, int S, int SR>
+static void launch_solve_lds_t(BatchHandle &h, const BOpts &o, const BArgs &a) {
+    constexpr size_t lds = LdsShape<BT, S, SR>::bytes;
+    static_assert(lds <= 150 * 1024 && lds % 16 == 0, "the reductions need LDS of their own");
+    // matrix entries take the rest of the LDS of as many workgroups as the
+    // registers hold (two waves per SIMD); one pair more is read, not used
+    const size_t share = lds_per_workgroup() * std::min(BT, 512) / 512;
+    const int32_t pairs = share > lds + 6144 ? (int32_t)((share - lds - 6144) / kPairBytes) : 0;
+    launch_queue_t<BT>(h, lds + (size_t)(pairs + 1) * kPairBytes, &k_batch_solve_lds<BT, S, SR>, a, o, pairs);
 }
 
 template <class T>
 static void load(DBuf<T> &dst, const T *src, size_t count, int mem, hipStream_t s);
 
-// SELL-64 copy of a batch matrix (rows of every instance padded to whole
-// slices) from the scaled CSR after the setup kernel: slice widths on the
-// device, their prefix sum on the host (a few thousand slices), entries placed
-// by one thread per slice row.
-__global__ __launch_bounds__(kBlock) void k_sell_widths(const int32_t *__restrict__ rp,
-                                                        const int32_t *__restrict__ r0,
-                                                        const int32_t *__restrict__ r1, int32_t ns,
-                                                        int32_t *__restrict__ width) {
-    const int32_t sl = (int32_t)(blockIdx.x * kBlock + threadIdx.x);
-    if (sl >= ns) return;
-    int32_t w = 0;
-    for (int32_t r = r0[sl]; r < r1[sl]; ++r) w = max(w, rp[r + 1] - rp[r]);
-    width[sl] = w;
+// Largest instance that gets SELL-64 copies: 8 columns (rows) for each of
+// 1,024 threads, and byte offsets 8 j of its positions fit 16 bits.
+constexpr int32_t kSellRows = 8192;
+
+// Order and widths of an instance's slices, one workgroup each: with perm,
+// position = rank of the row by falling length (equal lengths in row order),
+// else position = row. width[slice] becomes the longest row of each slice.
+__global__ __launch_bounds__(1024) void k_sell_order(const int32_t *__restrict__ rp, const int32_t *__restrict__ off,
+                                                     int32_t total, const int32_t *__restrict__ sfirst,
+                                                     int32_t *__restrict__ perm, int32_t *__restrict__ inv,
+                                                     int32_t *__restrict__ width) {
+    extern __shared__ int32_t len[];
+    const int32_t b = blockIdx.x;
+    const int32_t r0 = off ? off[b] : 0, n = (off ? off[b + 1] : total) - r0;
+    for (int32_t i = threadIdx.x; i < n; i += 1024) len[i] = rp[r0 + i + 1] - rp[r0 + i];
+    __syncthreads();
+    for (int32_t i = threadIdx.x; i < n; i += 1024) {
+        const int32_t l = len[i];
+        int32_t r = i;
+        if (perm) {
+            r = 0;
+#pragma unroll 8
+            for (int32_t k = 0; k < n; ++k) r += len[k] > l || (len[k] == l && k < i);
+            perm[r0 + r] = i;
+            inv[r0 + i] = r;
+        }
+        atomicMax(&width[sfirst[b] + (r >> 6)], l);
+    }
 }
 
-__global__ __launch_bounds__(kBlock) void k_sell_fill(const int32_t *__restrict__ rp,
-                                                      const int32_t *__restrict__ ci,
-                                                      const double *__restrict__ va,
-                                                      const int32_t *__restrict__ r0,
-                                                      const int32_t *__restrict__ r1,
-                                                      const int32_t *__restrict__ sp, int32_t ns,
-                                                      int32_t *__restrict__ sci,
-                                                      double *__restrict__ sva) {
+// Entries of the slices, one thread per position: slice sl covers the global
+// positions r0[sl] .. r1[sl] of instance inst[sl]; column indices become the
+// other side's positions.
+__global__ __launch_bounds__(kBlock) void k_sell_fill(
+    const int32_t *__restrict__ rp, const int32_t *__restrict__ ci, const double *__restrict__ va,
+    const int32_t *__restrict__ r0, const int32_t *__restrict__ r1, const int32_t *__restrict__ inst,
+    const int32_t *__restrict__ off, const int32_t *__restrict__ other_off, const int32_t *__restrict__ perm,
+    const int32_t *__restrict__ other_inv, const int32_t *__restrict__ sp, int32_t ns, uint32_t *__restrict__ sci,
+    double2 *__restrict__ sva) {
     const int64_t t = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     const int32_t sl = (int32_t)(t >> 6), lane = (int32_t)(t & 63);
     if (sl >= ns) return;
-    const int32_t row = r0[sl] + lane;
-    if (row >= r1[sl]) return;
-    const int32_t e0 = rp[row], e1 = rp[row + 1];
-    for (int32_t e = e0; e < e1; ++e) {
-        const int64_t o = (int64_t)sp[sl] + 64 * (int64_t)(e - e0) + lane;
-        sci[o] = ci[e];
-        sva[o] = va[e];
+    const int32_t pos = r0[sl] + lane;
+    int32_t e = 0, e1 = 0;
+    if (pos < r1[sl]) {
+        const int32_t row = perm ? off[inst[sl]] + perm[pos] : pos;
+        e = rp[row];
+        e1 = rp[row + 1];
+    }
+    const int32_t *oinv = other_inv ? other_inv + other_off[inst[sl]] : nullptr;
+    for (int32_t k = sp[sl]; k < sp[sl + 1]; ++k) {
+        uint32_t c[2] = {0, 0};
+        double v[2] = {0.0, 0.0};
+#pragma unroll
+        for (int u = 0; u < 2; ++u, ++e)
+            if (e < e1) {
+                c[u] = 8u * (uint32_t)(oinv ? oinv[ci[e]] : ci[e]);
+                v[u] = va[e];
+            }
+        sci[64 * (int64_t)k + lane] = c[1] << 16 | c[0];
+        sva[64 * (int64_t)k + lane] = double2{v[0], v[1]};
     }
 }
 
-static int32_t build_batch_sell(hipStream_t s, int32_t nb, const std::vector<int32_t> &roff,
-                                const DBuf<int32_t> &rp, const DBuf<int32_t> &ci, const DBuf<double> &va,
-                                int64_t nnz, DBuf<int32_t> &sp, DBuf<int32_t> &sci, DBuf<double> &sva,
-                                DBuf<int32_t> &sfirst) {
-    (void)nnz;
-    std::vector<int32_t> first((size_t)nb + 1), h0, h1;
-    for (int32_t b = 0; b < nb; ++b) {
-        first[b] = (int32_t)h0.size();
-        for (int32_t r = roff[b]; r < roff[b + 1]; r += 64) {
-            h0.push_back(r);
-            h1.push_back(std::min(r + 64, roff[b + 1]));
+// SELL-64 copies of A~ and A~' (rows of every instance padded to whole
+// slices) from the scaled CSR after the setup kernel: order and slice widths on
+// the device, prefix sums on the host (a few thousand slices), entries placed
+// by one thread per position. Nothing is built for instances that no kernel
+// would read them for.
+static void build_batch_sell(BatchHandle &h) {
+    hipStream_t s = h.stream;
+    if (std::max(h.nmax, h.mmax) > kSellRows) return;
+    const bool sorted = !h.shared;
+    const int32_t nb = h.shared ? 1 : h.B;
+    struct Side {
+        const DBuf<int32_t> &rp, &ci;
+        const DBuf<double> &va;
+        std::vector<int32_t> roff;
+        const int32_t *off;
+        int32_t total, rows_max;
+        DBuf<int32_t> &sp, &sfirst, &perm;
+        DBuf<uint32_t> &sci;
+        DBuf<double2> &sva;
+        int32_t &wmax;
+        DBuf<int32_t> inv, d0, d1, inst, width;
+        std::vector<int32_t> h0, h1, hi, first, hw, pairs;
+        int32_t ns = 0;
+    };
+    const int32_t *ro = h.shared ? nullptr : h.row_off.p, *co = h.shared ? nullptr : h.col_off.p;
+    Side side[2] = {{h.arp, h.aci, h.ava, h.shared ? std::vector<int32_t>{0, h.m} : h.row_off_h, ro, h.m, h.mmax,
+                     h.asp, h.asfirst, h.aperm, h.asci, h.asva, h.as_wmax},
+                    {h.trp, h.tci, h.tva, h.shared ? std::vector<int32_t>{0, h.n} : h.col_off_h, co, h.n, h.nmax,
+                     h.tsp, h.tsfirst, h.tperm, h.tsci, h.tsva, h.ts_wmax}};
+    for (Side &d : side) {
+        d.first.resize((size_t)nb + 1);
+        for (int32_t b = 0; b < nb; ++b) {
+            d.first[b] = (int32_t)d.h0.size();
+            for (int32_t r = d.roff[b]; r < d.roff[b + 1]; r += 64) {
+                d.h0.push_back(r);
+                d.h1.push_back(std::min(r + 64, d.roff[b + 1]));
+                d.hi.push_back(b);
+            }
         }
+        d.ns = d.first[nb] = (int32_t)d.h0.size();
+        load(d.sfirst, d.first.data(), d.first.size(), PDHG_MEM_HOST, s);
+        load(d.d0, d.h0.data(), d.h0.size(), PDHG_MEM_HOST, s);
+        load(d.d1, d.h1.data(), d.h1.size(), PDHG_MEM_HOST, s);
+        load(d.inst, d.hi.data(), d.hi.size(), PDHG_MEM_HOST, s);
+        d.width.alloc((size_t)std::max(1, d.ns));
+        d.hw.resize((size_t)d.ns);
+        if (d.ns == 0) continue;
+        if (sorted) {
+            d.perm.alloc((size_t)d.total);
+            d.inv.alloc((size_t)d.total);
+        }
+        PDHG_HIP(hipMemsetAsync(d.width.p, 0, (size_t)d.ns * 4, s));
+        k_sell_order<<<nb, 1024, (size_t)std::max(1, d.rows_max) * 4, s>>>(
+            d.rp.p, d.off, d.total, d.sfirst.p, sorted ? d.perm.p : nullptr, d.inv.p, d.width.p);
+        PDHG_HIP(hipMemcpyAsync(d.hw.data(), d.width.p, (size_t)d.ns * 4, hipMemcpyDeviceToHost, s));
     }
-    const int32_t ns = (int32_t)h0.size();
-    first[nb] = ns;
-    DBuf<int32_t> d0, d1, width;
-    load(d0, h0.data(), h0.size(), PDHG_MEM_HOST, s);
-    load(d1, h1.data(), h1.size(), PDHG_MEM_HOST, s);
-    width.alloc((size_t)std::max(1, ns));
-    std::vector<int32_t> hw((size_t)ns), off((size_t)ns + 1, 0);
-    if (ns > 0) {
-        k_sell_widths<<<(unsigned)ceil_div(ns, kBlock), kBlock, 0, s>>>(rp.p, d0.p, d1.p, ns, width.p);
-        PDHG_HIP(hipMemcpyAsync(hw.data(), width.p, (size_t)ns * 4, hipMemcpyDeviceToHost, s));
-        PDHG_HIP(hipStreamSynchronize(s));
-    }
-    int64_t total = 0;
-    int32_t wmax = 0;
-    for (int32_t i = 0; i < ns; ++i) {
-        wmax = std::max(wmax, hw[i]);
-        total += 64 * (int64_t)hw[i];
-        if (total >= INT32_MAX) fail(PDHG_ERR_UNSUPPORTED, "batch matrix too large for 32-bit offsets");
-        off[(size_t)i + 1] = (int32_t)total;
-    }
-    load(sp, off.data(), off.size(), PDHG_MEM_HOST, s);
-    load(sfirst, first.data(), first.size(), PDHG_MEM_HOST, s);
-    // at least one slice's worth: empty slices read the first 64 entries
-    const size_t cap = (size_t)std::max<int64_t>(total, 64);
-    sci.alloc(cap);
-    sva.alloc(cap);
-    PDHG_HIP(hipMemsetAsync(sci.p, 0, cap * 4, s));
-    PDHG_HIP(hipMemsetAsync(sva.p, 0, cap * 8, s));
-    if (ns > 0)
-        k_sell_fill<<<(unsigned)ceil_div((int64_t)ns * 64, kBlock), kBlock, 0, s>>>(
-            rp.p, ci.p, va.p, d0.p, d1.p, sp.p, ns, sci.p, sva.p);
-    PDHG_HIP(hipGetLastError());
     PDHG_HIP(hipStreamSynchronize(s));
-    return wmax;
+    for (int k = 0; k < 2; ++k) {
+        Side &d = side[k], &other = side[1 - k];
+        d.pairs.assign((size_t)d.ns + 1, 0);
+        int64_t total = 0;
+        for (int32_t i = 0; i < d.ns; ++i) {
+            d.wmax = std::max(d.wmax, d.hw[i]);
+            total += (d.hw[i] + 1) / 2;
+            if (64 * total >= INT32_MAX) fail(PDHG_ERR_UNSUPPORTED, "batch matrix too large for 32-bit offsets");
+            d.pairs[(size_t)i + 1] = (int32_t)total;
+        }
+        load(d.sp, d.pairs.data(), d.pairs.size(), PDHG_MEM_HOST, s);
+        const size_t cap = 64 * (size_t)std::max<int64_t>(total, 1);
+        d.sci.alloc(cap);
+        d.sva.alloc(cap);
+        if (d.ns > 0)
+            k_sell_fill<<<(unsigned)ceil_div((int64_t)d.ns * 64, kBlock), kBlock, 0, s>>>(
+                d.rp.p, d.ci.p, d.va.p, d.d0.p, d.d1.p, d.inst.p, d.off, other.off, sorted ? d.perm.p : nullptr,
+                sorted ? other.inv.p : nullptr, d.sp.p, d.ns, d.sci.p, d.sva.p);
+        PDHG_HIP(hipGetLastError());
+    }
+    PDHG_HIP(hipStreamSynchronize(s));
 }
 
 // Largest instance column / row counts (LDS sizing of the on-chip solve).
@@ -2786,11 +3025,14 @@ static void launch_solve_t(BatchHandle &h, const BOpts &o) {
     const size_t lds = ((size_t)h.nmax + 4 * (size_t)h.mmax) * sizeof(double);
     const int32_t need = std::max(h.nmax, h.mmax);
     if (h.onchip && lds <= lds_per_workgroup() && need <= 8 * BT) {
-        const size_t l = std::max<size_t>(lds, 8);
-        if (need <= BT) return launch_solve_lds_t<BT, 1>(h, o, a, l);
-        if (need <= 2 * BT) return launch_solve_lds_t<BT, 2>(h, o, a, l);
-        if (need <= 4 * BT) return launch_solve_lds_t<BT, 4>(h, o, a, l);
-        return launch_solve_lds_t<BT, 8>(h, o, a, l);
+        if (need <= BT) return launch_solve_lds_t<BT, 1, 1>(h, o, a);
+        if (need <= 2 * BT)
+            return h.mmax <= BT ? launch_solve_lds_t<BT, 2, 1>(h, o, a) : launch_solve_lds_t<BT, 2, 2>(h, o, a);
+        if (need <= 4 * BT)
+            return h.mmax <= BT ? launch_solve_lds_t<BT, 4, 1>(h, o, a)
+                   : h.mmax <= 2 * BT ? launch_solve_lds_t<BT, 4, 2>(h, o, a) : launch_solve_lds_t<BT, 4, 4>(h, o, a);
+        return h.mmax <= 2 * BT ? launch_solve_lds_t<BT, 8, 2>(h, o, a)
+               : h.mmax <= 4 * BT ? launch_solve_lds_t<BT, 8, 4>(h, o, a) : launch_solve_lds_t<BT, 8, 8>(h, o, a);
     }
 
     int32_t wg = std::min(h.B, resident<BT>(o.detect ? reinterpret_cast<const void *>(&k_batch_solve<BT, true>)
@@ -2843,10 +3085,31 @@ static void dispatch_setup(BatchHandle &h, int32_t count) {
     }
 }
 
-// Solves that test infeasibility rays carry a larger register budget: the
-// 1024-thread variants spill, so the default launch takes at most 512 there.
+// Threads of the solve when the caller chose none. Register-resident: see
+// res_threads. Else, while one column or row per thread takes at most 512
+// threads, that many; two per thread once the batch has more instances than
+// run at once (two waves per SIMD). Up to 1,024 columns 512 threads (register
+// pairs, a wave ahead in the stream), from there 1,024. Per iteration of 256
+// instances, 5% dense, n = 2 m: 1,024 of n = 114: 0.42 us at 64 threads, 0.36
+// at 128, 0.69 at 256; 1,024 (300) of n = 240: 0.77 (2.45) at 128, 0.94
+// (1.6) at 256; 1,024 (128) of n = 500: 2.6 (4.8) at 256, 3.05 (3.4) at 512;
+// 300 of n = 960: 25.9 at 256, 17.1 at 512, 24.2 at 1,024; of n = 2,000: 105
+// at 512, 101 at 1,024.
+static int32_t solve_threads(const BatchHandle &h) {
+    if (const int32_t t = res_threads(h)) return t;
+    int dev = 0, cus = 0;
+    PDHG_HIP(hipGetDevice(&dev));
+    PDHG_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
+    const int32_t need = std::max(h.nmax, h.mmax);
+    if (need > 1024) return 1024;
+    int32_t bt = 64;
+    while (bt < 512 && bt < need) bt *= 2;
+    if (need <= bt && bt > 64 && h.B > cus * (512 / bt)) bt /= 2;
+    return bt;
+}
+
 static void dispatch_solve(BatchHandle &h, const BOpts &o) {
-    const int32_t threads = (o.detect && !h.threads_set) ? std::min(h.threads, 512) : h.threads;
+    const int32_t threads = h.threads_set ? h.threads : solve_threads(h);
     switch (threads) {
         case 64: launch_solve_t<64>(h, o); break;
         case 128: launch_solve_t<128>(h, o); break;
@@ -2962,13 +3225,7 @@ BatchHandle *batch_create(const pdhg_batch_problem &p, const pdhg_options &o, vo
     dispatch_setup(h, nscal);
     PDHG_HIP(hipStreamSynchronize(s));
     h.lhist.release();
-    {
-        const int32_t nb = h.shared ? 1 : h.B;
-        std::vector<int32_t> ro = h.shared ? std::vector<int32_t>{0, h.m} : h.row_off_h;
-        std::vector<int32_t> co = h.shared ? std::vector<int32_t>{0, h.n} : h.col_off_h;
-        h.as_wmax = build_batch_sell(s, nb, ro, h.arp, h.aci, h.ava, h.nnz, h.asp, h.asci, h.asva, h.asfirst);
-        h.ts_wmax = build_batch_sell(s, nb, co, h.trp, h.tci, h.tva, h.nnz, h.tsp, h.tsci, h.tsva, h.tsfirst);
-    }
+    build_batch_sell(h);
     if (const int32_t t = p.q_rank == 0 ? res_threads(h) : 0) h.threads = t;
     if (p.q_rank > 0) bqp_create(h, p);
     h.setup_seconds = now_seconds() - t0;

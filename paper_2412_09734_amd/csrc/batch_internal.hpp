@@ -32,10 +32,12 @@ struct BatchHandle {
     const double *x_init_ = nullptr, *y_init_ = nullptr;
     double *x_out_ = nullptr, *y_out_ = nullptr;
     std::vector<int32_t> row_off_h, col_off_h;
-    // SELL-64 copies of the scaled A~ and A~' (built after scaling): slices
-    // never cross instances; slice s of instance b is sfirst[b] + local row / 64
-    DBuf<int32_t> asp, asci, asfirst, tsp, tsci, tsfirst;
-    DBuf<double> asva, tsva;
+    // SELL-64 copies of the scaled A~ and A~' (built after scaling) over
+    // positions (perm: ragged batches): slices never cross instances; slice s
+    // of instance b is sfirst[b] + position / 64
+    DBuf<int32_t> asp, asfirst, aperm, tsp, tsfirst, tperm;
+    DBuf<uint32_t> asci, tsci;
+    DBuf<double2> asva, tsva;
     DBuf<double> lhist;                   // Lanczos coefficients during setup
     DBuf<double> rp0, rq0, rph, rqh;      // LP: A~x0, A~'y0 of each anchor; this check's products
     // QP batches: Q_b = F F' + diag(d_b), F shared (scaled copy), d per instance
