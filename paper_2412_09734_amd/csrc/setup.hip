@@ -416,6 +416,47 @@ __global__ __launch_bounds__(kBlock) void k_lanczos_scale(const double *__restri
     if (i < len && nw > 0.0) out[i] = w[i] / nw;
 }
 
+// k_lanczos_sub, k_total and k_lanczos_scale of one half step in one launch
+// for vectors of at most kLanczosOne elements: one workgroup, a thread's
+// elements stay in registers between the sum and the division. The sum is the
+// one of the three launches, bit for bit: wave sums, four of them per block of
+// kBlock elements, then the blocks over the lanes of a wave.
+// What bounds it: the latency of one launch, a read and a wave sum (2.3 us for
+// vectors of hundreds, 3.9 us for thousands; the three launches 4.6 us and two
+// gaps). Creating a small LP: 2.4 -> 1.7 ms.
+constexpr int kLanczosThreads = 1024, kLanczosMost = 8, kLanczosOne = kLanczosThreads * kLanczosMost;
+__global__ __launch_bounds__(kLanczosThreads) void k_lanczos_one(const double *__restrict__ w,
+                                                                 double *__restrict__ prev,
+                                                                 const double *__restrict__ coef, int32_t len,
+                                                                 double *__restrict__ slot) {
+    static_assert(kBlock == 256 && kLanczosOne / kBlock <= 64, "four waves a block, one lane a block");
+    __shared__ double ws[kLanczosOne / 64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const double c = coef[0];
+    double r[kLanczosMost];
+#pragma unroll
+    for (int k = 0; k < kLanczosMost; ++k)
+        if (k * kLanczosThreads < len) {
+            const int32_t i = (int32_t)threadIdx.x + k * kLanczosThreads;
+            r[k] = i < len ? w[i] - c * prev[i] : 0.0;
+            const double s = wave_sum(r[k] * r[k]);
+            if (lane == 0) ws[k * (kLanczosThreads / 64) + wave] = s;
+        }
+    __syncthreads();
+    double t = 0.0;
+    if (lane * kBlock < len)
+#pragma unroll
+        for (int q = 0; q < kBlock / 64; ++q) t += ws[4 * lane + q];
+    const double nw = sqrt(wave_sum(t));
+    if (threadIdx.x == 0) slot[0] = nw;
+    if (!(nw > 0.0)) return;
+#pragma unroll
+    for (int k = 0; k < kLanczosMost; ++k) {
+        const int32_t i = (int32_t)threadIdx.x + k * kLanczosThreads;
+        if (i < len) prev[i] = r[k] / nw;
+    }
+}
+
 // ---------------------------------------------------------------------------
 // host side
 
@@ -1013,6 +1054,17 @@ void estimate_steps(Handle &h) {
         k_power_start<<<bn, kBlock, 0, s>>>(h.perm_c.p, n, v.p, pu.p);
         k_total<1><<<1, kBlock, 0, s>>>(pu.p, bn, tot.p);
         k_div_sqrt<<<bn, kBlock, 0, s>>>(v.p, n, tot.p);
+        // out <- (w - coef out) / |w - coef out|, the norm into slot
+        auto half = [&](double *wv, double *out, const double *coef, int32_t len, double *slot) {
+            if (len <= kLanczosOne) {
+                k_lanczos_one<<<1, kLanczosThreads, 0, s>>>(wv, out, coef, len, slot);
+                return;
+            }
+            const int32_t nb = (int32_t)blocks_for(len);
+            k_lanczos_sub<<<nb, kBlock, 0, s>>>(wv, out, coef, len, ps.p);
+            k_total<1><<<1, kBlock, 0, s>>>(ps.p, nb, tot.p);
+            k_lanczos_scale<<<nb, kBlock, 0, s>>>(wv, out, len, tot.p, slot);
+        };
         const int batch = 16;
         std::vector<double> hh(2 * ((size_t)maxit + 2), 0.0);
         std::vector<double> al, be;
@@ -1023,13 +1075,9 @@ void estimate_steps(Handle &h) {
             const int it1 = std::min(maxit, it0 + batch - 1);
             for (int it = it0; it <= it1; ++it) {
                 mul_a(v.p, w.p, pw.p);
-                k_lanczos_sub<<<bm, kBlock, 0, s>>>(w.p, u.p, hist.p + 2 * (it - 1) + 1, m, ps.p);
-                k_total<1><<<1, kBlock, 0, s>>>(ps.p, bm, tot.p);
-                k_lanczos_scale<<<bm, kBlock, 0, s>>>(w.p, u.p, m, tot.p, hist.p + 2 * it);
+                half(w.p, u.p, hist.p + 2 * (it - 1) + 1, m, hist.p + 2 * it);
                 mul_at(u.p, z.p, pu.p);
-                k_lanczos_sub<<<bn, kBlock, 0, s>>>(z.p, v.p, hist.p + 2 * it, n, ps.p);
-                k_total<1><<<1, kBlock, 0, s>>>(ps.p, bn, tot.p + 1);
-                k_lanczos_scale<<<bn, kBlock, 0, s>>>(z.p, v.p, n, tot.p + 1, hist.p + 2 * it + 1);
+                half(z.p, v.p, hist.p + 2 * it, n, hist.p + 2 * it + 1);
             }
             PDHG_HIP(hipMemcpyAsync(hh.data() + 2 * it0, hist.p + 2 * it0,
                                     sizeof(double) * 2 * (it1 - it0 + 1), hipMemcpyDeviceToHost,
