@@ -217,7 +217,8 @@ pdhg_err pdhg_debug_step(pdhg_handle *h, const double *x, const double *y,
  * sigma, writes the Halpern point (xnew, ynew). It runs the kernels and
  * product layouts of the solve's plain iterations (the LDS panels and hot
  * columns of a large sparse A), which pdhg_debug_step (check kernels) does
- * not. Device pointers; outputs may be NULL. LP handles only (UNSUPPORTED
+ * not; small sparse LPs, whose solve runs the same formulas in one workgroup,
+ * run the standard kernels here. Device pointers; outputs may be NULL. LP handles only (UNSUPPORTED
  * otherwise). */
 pdhg_err pdhg_debug_plain_step(pdhg_handle *h, const double *x, const double *y,
                                const double *x0, const double *y0, int64_t k, double tau,
@@ -337,8 +338,9 @@ pdhg_err pdhg_batch_unrolled_forward(pdhg_batch *b, int64_t T, int32_t replay, d
  * the original c (gc), row bounds (glc, guc; 0 for infinite bounds) and, for
  * QP batches, the diagonal d of Q (gd); NULL skips glc / guc / gd. Two sparse
  * products per reversed iteration. QP batches (rAPDHG, whose output is the
- * average) keep the state every 50 iterations during the forward pass and
- * recompute each segment to get the momentum points. Device pointers. */
+ * average) keep every momentum point of the forward pass (up to 16 GiB) when
+ * their instances run on chip, else the state every 50 iterations, and
+ * recompute each segment. Device pointers. */
 pdhg_err pdhg_batch_unrolled_backward(pdhg_batch *b, const double *gx, const double *gy,
                                       double *gc, double *glc, double *guc, double *gd);
 

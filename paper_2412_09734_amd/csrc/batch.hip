@@ -1453,7 +1453,8 @@ struct SellRow {
 // in the batch, n = 2 m: m = 57 0.98 -> 0.36 us, 120 2.45 -> 0.77, 250 8.2 ->
 // 2.6, 480 33 -> 11.2 (4.9 TB/s from the memory-side cache).
 template <int BT, int S, int SR>
-__global__ __launch_bounds__(BT) __attribute__((amdgpu_waves_per_eu(BT == 1024 ? 4 : 2))) void k_batch_solve_lds(BArgs a, BOpts o, int32_t cache_pairs) {
+__global__ __launch_bounds__(BT) __attribute__((amdgpu_waves_per_eu(BT == 1024 ? 4 : 2))) void
+k_batch_solve_lds(BArgs a, BOpts o, int32_t cache_pairs) {
     using L = LdsShape<BT, S, SR>;
     constexpr int NW = BT / 64;
     extern __shared__ __attribute__((aligned(16))) double lds[];
