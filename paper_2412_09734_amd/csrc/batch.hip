@@ -2824,6 +2824,14 @@ static void launch_res_t(BatchHandle &h, void (*kernel)(Args...), Args... args) 
     static_assert(lds <= 150 * 1024, "the reductions need LDS of their own");
     launch_queue_t<BT>(h, lds, kernel, args...);
 }
+// Whether k_batch_solve_lds takes the batch at bt threads: at most 8 columns
+// and 8 rows per thread, and not so many rows that (n + 4 m) doubles exceed a
+// workgroup's LDS.
+static bool solve_on_chip(const BatchHandle &h, int32_t bt) {
+    return h.onchip && ((size_t)h.nmax + 4 * (size_t)h.mmax) * sizeof(double) <= lds_per_workgroup() &&
+           std::max(h.nmax, h.mmax) <= 8 * bt;
+}
+
 template <int BT, int S, int SR>
 static void launch_solve_lds_t(BatchHandle &h, const BOpts &o, const BArgs &a) {
     constexpr size_t lds = LdsShape<BT, S, SR>::bytes;
@@ -3021,11 +3029,8 @@ static void launch_solve_t(BatchHandle &h, const BOpts &o) {
             default: break;
         }
     }
-    // on-chip variant when x_ext, y and the three per-row vectors fit the
-    // workgroup's LDS and every thread owns at most 8 columns and 8 rows
-    const size_t lds = ((size_t)h.nmax + 4 * (size_t)h.mmax) * sizeof(double);
-    const int32_t need = std::max(h.nmax, h.mmax);
-    if (h.onchip && lds <= lds_per_workgroup() && need <= 8 * BT) {
+    if (solve_on_chip(h, BT)) {
+        const int32_t need = std::max(h.nmax, h.mmax);
         if (need <= BT) return launch_solve_lds_t<BT, 1, 1>(h, o, a);
         if (need <= 2 * BT)
             return h.mmax <= BT ? launch_solve_lds_t<BT, 2, 1>(h, o, a) : launch_solve_lds_t<BT, 2, 2>(h, o, a);
@@ -3095,9 +3100,12 @@ static void dispatch_setup(BatchHandle &h, int32_t count) {
 // at 128, 0.69 at 256; 1,024 (300) of n = 240: 0.77 (2.45) at 128, 0.94
 // (1.6) at 256; 1,024 (128) of n = 500: 2.6 (4.8) at 256, 3.05 (3.4) at 512;
 // 300 of n = 960: 25.9 at 256, 17.1 at 512, 24.2 at 1,024; of n = 2,000: 105
-// at 512, 101 at 1,024.
-static int32_t solve_threads(const BatchHandle &h) {
+// at 512, 101 at 1,024. Instances beyond the chip keep the threads of
+// default_threads, at most 512 with the ray tests (k_batch_solve<1024, true>
+// spills).
+static int32_t solve_threads(const BatchHandle &h, bool detect) {
     if (const int32_t t = res_threads(h)) return t;
+    if (!solve_on_chip(h, 1024)) return detect ? std::min(h.threads, 512) : h.threads;
     int dev = 0, cus = 0;
     PDHG_HIP(hipGetDevice(&dev));
     PDHG_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
@@ -3110,7 +3118,7 @@ static int32_t solve_threads(const BatchHandle &h) {
 }
 
 static void dispatch_solve(BatchHandle &h, const BOpts &o) {
-    const int32_t threads = h.threads_set ? h.threads : solve_threads(h);
+    const int32_t threads = h.threads_set ? h.threads : solve_threads(h, o.detect);
     switch (threads) {
         case 64: launch_solve_t<64>(h, o); break;
         case 128: launch_solve_t<128>(h, o); break;
