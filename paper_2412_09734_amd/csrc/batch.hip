@@ -9,8 +9,10 @@
 // depend on which workgroup ran it.
 //
 // Matrices are plain CSR (rows in original order) with instance-local column
-// indices; row pointers hold global entry offsets. Per-instance vectors live
-// in HBM and stay in L2 while the instance runs.
+// indices; row pointers hold global entry offsets. The setup and the
+// memory-resident kernels walk it, their vectors staying in L2 while the
+// instance runs; the on-chip kernels read SELL-64 copies (see BArgs) and keep
+// an instance in registers and LDS as far as it fits.
 #include <algorithm>
 #include <climits>
 #include <memory>
