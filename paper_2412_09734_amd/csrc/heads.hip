@@ -17,6 +17,7 @@ constexpr int kHeadPmax = 64;     // most features of the linear cost model
 constexpr int kScratchDoubles = 32768;   // partial sums of the weight gradient (64 features x 512 chunks)
 constexpr int kGradChunks = 1024;         // most chunks
 constexpr int kMaxDevices = 64;
+constexpr int64_t kMostEntries = ((int64_t)1 << 32) - 1;   // of an array that a thread per entry walks
 
 // Partial sums of the allocation-free weight gradient (256 KB on every GPU the
 // library runs on, kept until the process ends). Host code never uses this
@@ -305,28 +306,45 @@ __global__ __launch_bounds__(BT) void k_spo_plus(int32_t n, const double *__rest
 // Perturbed Fenchel-Young (Berthet et al.), minimisation form: sample (b, m)
 // has costs c_hat_b + eps Z_bm; entry i of the [B][M][n] output. Rounded as
 // a product then a sum, so the costs equal the textbook expression exactly.
-// A workgroup takes kPfyTile entries of one sample (tiles of them to a sample),
-// so that no entry needs a division.
+// A workgroup takes kPfyTile entries in a row, whatever samples they belong to
+// (a workgroup per sample left 256 threads with 24 entries, and grids beyond
+// the limit of 2^32 work-items at 2^24 samples). One division a workgroup finds
+// its first sample; from there an entry is at most one sample on where a sample
+// fills a tile, and shorter samples are counted by a multiplication with magic =
+// ceil(2^32 / n), exact while dividend times n is below 2^32 (here below 2^21).
+// What bounds it: 16 bytes of memory an entry. 200,000 x 24 samples of one draw
+// take 20 us (144 with a workgroup per sample), 2,048 x 4 of 1,025 27 (40).
 constexpr int kPfyTile = 4 * kBlock;
-__global__ __launch_bounds__(kBlock) void k_pfy_costs(int32_t M, int32_t n, int32_t tiles,
+__global__ __launch_bounds__(kBlock) void k_pfy_costs(int64_t N, int32_t M, int32_t n, uint32_t magic,
                                                       const double *__restrict__ ch,
                                                       const double *__restrict__ Z, double eps,
                                                       double *__restrict__ out) {
 #pragma clang fp contract(off)
-    const int64_t row = blockIdx.x / (uint32_t)tiles;
-    const int32_t a0 = (int32_t)(blockIdx.x - (uint32_t)row * (uint32_t)tiles) * kPfyTile + (int32_t)threadIdx.x;
-    const double *__restrict__ c = ch + (row / M) * n;
+    const int64_t i0 = (int64_t)blockIdx.x * kPfyTile;
+    // first sample of the tile, its instance, and the tile's start in the sample
+    const uint32_t row = (uint32_t)i0 / (uint32_t)n, b = row / (uint32_t)M;
+    const uint32_t first = (uint32_t)i0 - row * (uint32_t)n, m0 = row - b * (uint32_t)M;
     double z[4], h[4];
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-        const int32_t a = min(a0 + u * kBlock, n - 1);
-        z[u] = Z[row * n + a];
-        h[u] = c[a];
+        const int64_t i = min(i0 + (int32_t)threadIdx.x + u * kBlock, N - 1);
+        const uint32_t a = first + (uint32_t)(i - i0);
+        uint32_t q, up;   // samples and instances past the first
+        if (n >= kPfyTile) {
+            q = a >= (uint32_t)n;
+            up = m0 + q >= (uint32_t)M;
+        } else {
+            q = n == 1 ? a : __umulhi(a, magic);
+            up = (m0 + q) / (uint32_t)M;
+        }
+        z[u] = Z[i];
+        h[u] = ch[(int64_t)(b + up) * n + (a - q * (uint32_t)n)];
     }
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
+        const int64_t i = i0 + (int32_t)threadIdx.x + u * kBlock;
         const double pz = eps * z[u];
-        if (a0 + u * kBlock < n) out[row * n + a0 + u * kBlock] = h[u] + pz;
+        if (i < N) out[i] = h[u] + pz;
     }
 }
 
@@ -483,9 +501,9 @@ void head_pfy_costs(hipStream_t s, int32_t B, int32_t M, int32_t n, const double
                     const double *Z, double eps, double *out) {
     const int64_t N = (int64_t)B * M * n;
     if (N == 0) return;
-    const int64_t tiles = ceil_div(n, kPfyTile), blocks = (int64_t)B * M * tiles;
-    if (blocks > INT32_MAX) fail(PDHG_ERR_UNSUPPORTED, "too many samples for one launch");
-    k_pfy_costs<<<(unsigned)blocks, kBlock, 0, s>>>(M, n, (int32_t)tiles, c_hat, Z, eps, out);
+    if (N > kMostEntries) fail(PDHG_ERR_UNSUPPORTED, "too many samples for one launch");
+    const uint32_t magic = n > 1 ? (uint32_t)((((uint64_t)1 << 32) + (uint32_t)n - 1) / (uint32_t)n) : 0;
+    k_pfy_costs<<<(unsigned)ceil_div(N, kPfyTile), kBlock, 0, s>>>(N, M, n, magic, c_hat, Z, eps, out);
     PDHG_HIP(hipGetLastError());
 }
 

@@ -1,0 +1,40 @@
+"""Loss heads on many small samples, rows or instances: calls whose arrays fit
+the card, up to the 2^32 work-items that one launch can hold, and the entry
+arithmetic of the kernels at the edges of their tiles. Entries that are formed
+one by one are compared exactly."""
+
+import sys
+
+import numpy as np
+import pytest
+
+from gpu_util import to_np
+
+pytestmark = pytest.mark.gpu
+
+
+def _say(*a):
+    print("case:", *a, file=sys.stderr, flush=True)
+
+
+@pytest.mark.parametrize("B,M,n", [(1, 1, 1), (5, 9, 1), (1, 5000, 2), (300, 1, 7), (7, 3, 341), (2, 3, 1023),
+                                   (2, 3, 1024), (1, 4, 1025), (3, 2, 2047), (40, 100, 24)])
+def test_perturbed_costs_tiles(B, M, n):
+    from paper_2412_09734_amd import heads as h
+    _say(f"perturbed costs B={B} M={M} n={n}")
+    rng = np.random.default_rng(B + M + n)
+    ch, Z = rng.standard_normal((B, n)), rng.standard_normal((B, M, n))
+    assert np.array_equal(to_np(h.pfy_costs(ch, Z, 0.3)), ch[:, None] + 0.3 * Z)
+
+
+@pytest.mark.parametrize("B,M,n", [(1, (1 << 24) + 3, 1), ((1 << 24) + 5, 1, 2), (1 << 13, 1 << 12, 3)])
+def test_perturbed_costs_of_many_samples(B, M, n):
+    import torch
+    from paper_2412_09734_amd import heads as h
+    _say(f"perturbed costs of {B} x {M} samples, n={n}")
+    g = torch.Generator(device="cuda").manual_seed(n)
+    ch = torch.rand(B, n, dtype=torch.float64, device="cuda", generator=g)
+    Z = torch.rand(B, M, n, dtype=torch.float64, device="cuda", generator=g)
+    want = 0.5 * Z
+    want += ch[:, None]
+    assert torch.equal(h.pfy_costs(ch, Z, 0.5), want)
