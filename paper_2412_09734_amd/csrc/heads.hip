@@ -63,26 +63,30 @@ __global__ __launch_bounds__(kBlock) void k_linear_costs(int64_t N, int32_t p,
                                                          const double *__restrict__ W,
                                                          double *__restrict__ c) {
     __shared__ double sh[kBlock * (kCostsLds + 1)];
-    const int64_t i0 = (int64_t)blockIdx.x * kBlock;
-    const int32_t rows = (int32_t)min((int64_t)kBlock, N - i0), len = rows * p, st = p | 1;
-    const double *__restrict__ src = f + i0 * p;
-    int32_t r = (int32_t)threadIdx.x / p, k = (int32_t)threadIdx.x - r * p;
-    const int32_t dr = kBlock / p, dk = kBlock - dr * p;
-    for (int32_t e = (int32_t)threadIdx.x; e < len; e += kBlock) {
-        sh[r * st + k] = src[e];
-        r += dr;
-        k += dk;
-        if (k >= p) {
-            k -= p;
-            ++r;
+    const int32_t r0 = (int32_t)threadIdx.x / p, k0 = (int32_t)threadIdx.x - r0 * p;
+    const int32_t dr = kBlock / p, dk = kBlock - dr * p, st = p | 1;
+    for (int64_t i0 = (int64_t)blockIdx.x * kBlock; i0 < N; i0 += (int64_t)gridDim.x * kBlock) {
+        const int32_t rows = (int32_t)min((int64_t)kBlock, N - i0), len = rows * p;
+        const double *__restrict__ src = f + i0 * p;
+        int32_t r = r0, k = k0;
+        for (int32_t e = (int32_t)threadIdx.x; e < len; e += kBlock) {
+            sh[r * st + k] = src[e];
+            r += dr;
+            k += dk;
+            if (k >= p) {
+                k -= p;
+                ++r;
+            }
         }
+        __syncthreads();
+        if ((int32_t)threadIdx.x < rows) {
+            const double *mine = sh + threadIdx.x * st;
+            double s = 0.0;
+            for (int32_t q = 0; q < p; ++q) s = fma(W[q], mine[q], s);
+            c[i0 + threadIdx.x] = s;
+        }
+        __syncthreads();
     }
-    __syncthreads();
-    if ((int32_t)threadIdx.x >= rows) return;
-    const double *mine = sh + threadIdx.x * st;
-    double s = 0.0;
-    for (int32_t q = 0; q < p; ++q) s = fma(W[q], mine[q], s);
-    c[i0 + threadIdx.x] = s;
 }
 
 // Many features: 16 lanes per row, up to four entries each.
@@ -91,11 +95,9 @@ __global__ __launch_bounds__(kBlock) void k_linear_costs_wide(int64_t N, int32_t
                                                               const double *__restrict__ W,
                                                               double *__restrict__ c) {
     static_assert(kHeadPmax == 64, "four entries per lane");
-    const int64_t i = ((int64_t)blockIdx.x * kBlock + threadIdx.x) >> 4;
     const int32_t lane = threadIdx.x & 15;
-    double s = 0.0;
-    if (i < N) {
-        double a[4], w[4];
+    for (int64_t i = ((int64_t)blockIdx.x * kBlock + threadIdx.x) >> 4; i < N; i += (int64_t)gridDim.x * (kBlock / 16)) {
+        double a[4], w[4], s = 0.0;
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
             const int32_t k = min(lane + 16 * u, p - 1);
@@ -104,9 +106,9 @@ __global__ __launch_bounds__(kBlock) void k_linear_costs_wide(int64_t N, int32_t
         }
 #pragma unroll
         for (int u = 0; u < 4; ++u) s = lane + 16 * u < p ? fma(w[u], a[u], s) : s;
+        s = group_reduce(s, 4, [](double x, double y) { return x + y; });
+        if (lane == 0) c[i] = s;
     }
-    s = group_reduce(s, 4, [](double x, double y) { return x + y; });
-    if (i < N && lane == 0) c[i] = s;
 }
 
 // One workgroup per instance: loss[b] = c_true_b' x_b - v_star[b].
@@ -266,8 +268,8 @@ __global__ __launch_bounds__(kBlock) void k_qp_value(int32_t n, int32_t r, const
 __global__ __launch_bounds__(kBlock) void k_spo_costs(int64_t N, const double *__restrict__ ch,
                                                       const double *__restrict__ ct,
                                                       double *__restrict__ out) {
-    const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (i < N) out[i] = 2.0 * ch[i] - ct[i];
+    for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < N; i += (int64_t)gridDim.x * kBlock)
+        out[i] = 2.0 * ch[i] - ct[i];
 }
 
 // One workgroup per instance: with w* optimal under c_true (value z*) and w~
@@ -389,7 +391,12 @@ __global__ __launch_bounds__(BT) void k_pfy(int32_t M, int32_t n, const double *
     if (threadIdx.x == 0) loss[b] = v;
 }
 
-static unsigned grid1(int64_t N) { return (unsigned)std::max<int64_t>(1, ceil_div(N, kBlock)); }
+// Workgroups for N threads. A launch holds fewer than 2^32 work-items in a
+// dimension, and one beyond is cut without an error: from 2^31 on the kernels
+// below walk on by the grid's size.
+static unsigned grid1(int64_t N) {
+    return (unsigned)std::max<int64_t>(1, std::min<int64_t>(ceil_div(N, kBlock), ((int64_t)1 << 31) / kBlock));
+}
 
 void head_linear_costs(hipStream_t s, int32_t B, int32_t n, int32_t p, const double *f,
                        const double *W, double *c) {

@@ -38,3 +38,36 @@ def test_perturbed_costs_of_many_samples(B, M, n):
     want = 0.5 * Z
     want += ch[:, None]
     assert torch.equal(h.pfy_costs(ch, Z, 0.5), want)
+
+
+@pytest.mark.parametrize("rows,p", [((1 << 28) + 5, 17), ((1 << 32) + 5, 1)])
+def test_costs_of_many_rows(rows, p):
+    """Features that are zero but for the first, the last and a few other rows."""
+    import torch
+    from paper_2412_09734_amd import heads as h
+    _say(f"cost model on {rows} rows of {p} features")
+    B = 3
+    assert rows % B == 0
+    f = torch.zeros(B, rows // B, p, dtype=torch.float64, device="cuda")
+    flat = f.view(-1, p)
+    at = torch.tensor([0, 1, 255, 256, 4096, (1 << 28) - 1, rows // 2, rows - 2, rows - 1], device="cuda")
+    flat[at] = torch.arange(1.0, at.numel() * p + 1, dtype=torch.float64, device="cuda").view(-1, p)
+    W = torch.arange(1.0, p + 1, dtype=torch.float64, device="cuda")
+    c = h.linear_costs(f, W).view(-1)
+    # whole numbers: the sums are exact in any order
+    assert torch.equal(c[at], (flat[at] * W).sum(1))
+    assert int(torch.count_nonzero(c)) == at.numel()
+
+
+def test_spo_costs_of_many_entries():
+    import torch
+    from paper_2412_09734_amd import heads as h
+    B, n = 3, ((1 << 32) + 2) // 3
+    _say(f"SPO+ costs of {B} x {n} entries")
+    c = torch.zeros(B, n, dtype=torch.float64, device="cuda")
+    flat = c.view(-1)
+    at = torch.tensor([0, 1, 256, (1 << 31) + 1, B * n - 300, B * n - 1], device="cuda")
+    flat[at] = torch.arange(1.0, 7.0, dtype=torch.float64, device="cuda")
+    out = h.spo_plus_costs(c, c).view(-1)
+    assert torch.equal(out[at], flat[at])
+    assert int(torch.count_nonzero(out)) == at.numel()
