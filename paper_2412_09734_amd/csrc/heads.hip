@@ -113,18 +113,20 @@ __global__ __launch_bounds__(kBlock) void k_linear_costs_wide(int64_t N, int32_t
 
 // One workgroup per instance: loss[b] = c_true_b' x_b - v_star[b].
 template <int BT>
-__global__ __launch_bounds__(BT) void k_regret(int32_t n, const double *__restrict__ ct,
+__global__ __launch_bounds__(BT) void k_regret(int32_t B, int32_t n, const double *__restrict__ ct,
                                                          const double *__restrict__ x,
                                                          const double *__restrict__ vs,
                                                          double *__restrict__ loss) {
     constexpr int U = 4;
-    const int32_t b = blockIdx.x;
-    const size_t o = (size_t)b * n;
-    double v = 0.0, c[U], w[U];
-    strided<BT, U>(n, [&](int u, int32_t a) { c[u] = ct[o + a]; w[u] = x[o + a]; },
-                             [&](int u, int32_t) { v = fma(c[u], w[u], v); });
-    v = head_sum<BT>(v);
-    if (threadIdx.x == 0) loss[b] = v - vs[b];
+    for (uint32_t b = blockIdx.x; b < (uint32_t)B; b += gridDim.x) {
+        const size_t o = (size_t)b * n;
+        double v = 0.0, c[U], w[U];
+        strided<BT, U>(n, [&](int u, int32_t a) { c[u] = ct[o + a]; w[u] = x[o + a]; },
+                                 [&](int u, int32_t) { v = fma(c[u], w[u], v); });
+        v = head_sum<BT>(v);
+        if (threadIdx.x == 0) loss[b] = v - vs[b];
+        __syncthreads();
+    }
 }
 
 // out[k] = the sum of the step values v of the threads k, k + p, ... (t < step p),
@@ -205,7 +207,7 @@ __global__ __launch_bounds__(BT) void k_costs_grad_final(int32_t p, int32_t chun
 // G: groups of eight factor columns (a runtime rank would put t in scratch
 // memory); t reaches the lanes as scalars.
 template <int G>
-__global__ __launch_bounds__(kBlock) void k_qp_value(int32_t n, int32_t r, const double *__restrict__ F,
+__global__ __launch_bounds__(kBlock) void k_qp_value(int32_t B, int32_t n, int32_t r, const double *__restrict__ F,
                                                      const double *__restrict__ d,
                                                      const double *__restrict__ c,
                                                      const double *__restrict__ x,
@@ -213,54 +215,57 @@ __global__ __launch_bounds__(kBlock) void k_qp_value(int32_t n, int32_t r, const
                                                      double *__restrict__ gx) {
     constexpr int R = 8 * G;
     __shared__ double sh[R > 0 ? R : 1][kBlock / 64];
-    const int32_t b = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const size_t o = (size_t)b * n;
+    const int32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     auto factor_row = [&](int32_t j, double (&f)[R > 0 ? R : 1]) {
 #pragma unroll
         for (int k = 0; k < R; ++k) f[k] = F[(size_t)j * r + min(k, r - 1)];
 #pragma unroll
         for (int k = 0; k < R; ++k) f[k] = k < r ? f[k] : 0.0;
     };
-    double t[R > 0 ? R : 1], f[R > 0 ? R : 1];
-    if constexpr (G > 0) {
-#pragma unroll
-        for (int k = 0; k < R; ++k) t[k] = 0.0;
-        for (int32_t j = threadIdx.x; j < n; j += kBlock) {
-            const double xj = x[o + j];
-            factor_row(j, f);
-#pragma unroll
-            for (int k = 0; k < R; ++k) t[k] = fma(f[k], xj, t[k]);
-        }
-#pragma unroll
-        for (int g = 0; g < G; ++g) {
-            double v[8];
-#pragma unroll
-            for (int k = 0; k < 8; ++k) v[k] = t[8 * g + k];
-            const double w = wave_sum_x8(v);
-            if ((lane & 7) == 0) sh[8 * g + 4 * ((lane >> 3) & 1) + 2 * ((lane >> 4) & 1) + ((lane >> 5) & 1)][wave] = w;
-        }
-        __syncthreads();
-        const int32_t p = lane < R ? lane : 0;
-        double tp = sh[p][0];
-#pragma unroll
-        for (int w = 1; w < kBlock / 64; ++w) tp += sh[p][w];
-#pragma unroll
-        for (int k = 0; k < R; ++k) t[k] = lane_value(tp, k);
-    }
-    double v = 0.0;
-    for (int32_t j = threadIdx.x; j < n; j += kBlock) {
-        const double xj = x[o + j], cj = c[o + j];
-        double qx = d[o + j] * xj;
+    for (uint32_t b = blockIdx.x; b < (uint32_t)B; b += gridDim.x) {
+        const size_t o = (size_t)b * n;
+        double t[R > 0 ? R : 1], f[R > 0 ? R : 1];
         if constexpr (G > 0) {
-            factor_row(j, f);
 #pragma unroll
-            for (int k = 0; k < R; ++k) qx = fma(f[k], t[k], qx);
+            for (int k = 0; k < R; ++k) t[k] = 0.0;
+            for (int32_t j = threadIdx.x; j < n; j += kBlock) {
+                const double xj = x[o + j];
+                factor_row(j, f);
+#pragma unroll
+                for (int k = 0; k < R; ++k) t[k] = fma(f[k], xj, t[k]);
+            }
+#pragma unroll
+            for (int g = 0; g < G; ++g) {
+                double v[8];
+#pragma unroll
+                for (int k = 0; k < 8; ++k) v[k] = t[8 * g + k];
+                const double w = wave_sum_x8(v);
+                if ((lane & 7) == 0) sh[8 * g + 4 * ((lane >> 3) & 1) + 2 * ((lane >> 4) & 1) + ((lane >> 5) & 1)][wave] = w;
+            }
+            __syncthreads();
+            const int32_t p = lane < R ? lane : 0;
+            double tp = sh[p][0];
+#pragma unroll
+            for (int w = 1; w < kBlock / 64; ++w) tp += sh[p][w];
+#pragma unroll
+            for (int k = 0; k < R; ++k) t[k] = lane_value(tp, k);
         }
-        if (gx) gx[o + j] = qx + cj;
-        v += xj * (0.5 * qx + cj);
+        double v = 0.0;
+        for (int32_t j = threadIdx.x; j < n; j += kBlock) {
+            const double xj = x[o + j], cj = c[o + j];
+            double qx = d[o + j] * xj;
+            if constexpr (G > 0) {
+                factor_row(j, f);
+#pragma unroll
+                for (int k = 0; k < R; ++k) qx = fma(f[k], t[k], qx);
+            }
+            if (gx) gx[o + j] = qx + cj;
+            v += xj * (0.5 * qx + cj);
+        }
+        v = head_sum<kBlock>(v);
+        if (threadIdx.x == 0) value[b] = v;
+        __syncthreads();
     }
-    v = head_sum<kBlock>(v);
-    if (threadIdx.x == 0) value[b] = v;
 }
 
 // SPO+ (Elmachtoub-Grigas) for min_{w in S} c'w: the inner problem's costs
@@ -277,7 +282,7 @@ __global__ __launch_bounds__(kBlock) void k_spo_costs(int64_t N, const double *_
 // summed as 2 c_hat'(w* - w~) + c'w~ - z* (the same value, without the
 // cancellation of two large products), and the subgradient 2 (w* - w~).
 template <int BT>
-__global__ __launch_bounds__(BT) void k_spo_plus(int32_t n, const double *__restrict__ ch,
+__global__ __launch_bounds__(BT) void k_spo_plus(int32_t B, int32_t n, const double *__restrict__ ch,
                                                            const double *__restrict__ ct,
                                                            const double *__restrict__ ws,
                                                            const double *__restrict__ zs,
@@ -285,24 +290,26 @@ __global__ __launch_bounds__(BT) void k_spo_plus(int32_t n, const double *__rest
                                                            double *__restrict__ loss,
                                                            double *__restrict__ grad) {
     constexpr int U = 4;
-    const int32_t b = blockIdx.x;
-    const size_t o = (size_t)b * n;
-    double v = 0.0, h[U], c[U], s[U], w[U];
-    strided<BT, U>(
-        n,
-        [&](int u, int32_t a) {
-            h[u] = ch[o + a];
-            c[u] = ct[o + a];
-            s[u] = ws[o + a];
-            w[u] = wt[o + a];
-        },
-        [&](int u, int32_t a) {
-            const double dw = s[u] - w[u];
-            v += 2.0 * h[u] * dw + c[u] * w[u];
-            grad[o + a] = 2.0 * dw;
-        });
-    v = head_sum<BT>(v);
-    if (threadIdx.x == 0) loss[b] = v - zs[b];
+    for (uint32_t b = blockIdx.x; b < (uint32_t)B; b += gridDim.x) {
+        const size_t o = (size_t)b * n;
+        double v = 0.0, h[U], c[U], s[U], w[U];
+        strided<BT, U>(
+            n,
+            [&](int u, int32_t a) {
+                h[u] = ch[o + a];
+                c[u] = ct[o + a];
+                s[u] = ws[o + a];
+                w[u] = wt[o + a];
+            },
+            [&](int u, int32_t a) {
+                const double dw = s[u] - w[u];
+                v += 2.0 * h[u] * dw + c[u] * w[u];
+                grad[o + a] = 2.0 * dw;
+            });
+        v = head_sum<BT>(v);
+        if (threadIdx.x == 0) loss[b] = v - zs[b];
+        __syncthreads();
+    }
 }
 
 // Perturbed Fenchel-Young (Berthet et al.), minimisation form: sample (b, m)
@@ -355,40 +362,42 @@ __global__ __launch_bounds__(kBlock) void k_pfy_costs(int64_t N, int32_t M, int3
 // eps Z_m)'w_m (the loss up to the constant Omega(w*)); samples summed in m
 // order per variable.
 template <int BT>
-__global__ __launch_bounds__(BT) void k_pfy(int32_t M, int32_t n, const double *__restrict__ ch,
+__global__ __launch_bounds__(BT) void k_pfy(int32_t B, int32_t M, int32_t n, const double *__restrict__ ch,
                                                       const double *__restrict__ ws,
                                                       const double *__restrict__ Z, double eps,
                                                       const double *__restrict__ wm,
                                                       double *__restrict__ loss,
                                                       double *__restrict__ grad) {
     constexpr int U = 4;   // samples whose loads are in flight together
-    const int32_t b = blockIdx.x;
-    const size_t o = (size_t)b * n;
-    const double dm = (double)M;
-    double v = 0.0;
-    for (int32_t a = threadIdx.x; a < n; a += BT) {
-        const double c = ch[o + a], s = ws[o + a];
-        double wsum = 0.0, acc = 0.0;
-        for (int32_t m0 = 0; m0 < M; m0 += U) {
-            double w[U], z[U];
+    for (uint32_t b = blockIdx.x; b < (uint32_t)B; b += gridDim.x) {
+        const size_t o = (size_t)b * n;
+        const double dm = (double)M;
+        double v = 0.0;
+        for (int32_t a = threadIdx.x; a < n; a += BT) {
+            const double c = ch[o + a], s = ws[o + a];
+            double wsum = 0.0, acc = 0.0;
+            for (int32_t m0 = 0; m0 < M; m0 += U) {
+                double w[U], z[U];
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const size_t e = ((size_t)b * M + min(m0 + u, M - 1)) * n + a;
-                w[u] = wm[e];
-                z[u] = Z[e];
-            }
+                for (int u = 0; u < U; ++u) {
+                    const size_t e = ((size_t)b * M + min(m0 + u, M - 1)) * n + a;
+                    w[u] = wm[e];
+                    z[u] = Z[e];
+                }
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                if (m0 + u >= M) break;
-                wsum += w[u];
-                acc += (c + eps * z[u]) * w[u];
+                for (int u = 0; u < U; ++u) {
+                    if (m0 + u >= M) break;
+                    wsum += w[u];
+                    acc += (c + eps * z[u]) * w[u];
+                }
             }
+            grad[o + a] = s - wsum / dm;
+            v += c * s - acc / dm;
         }
-        grad[o + a] = s - wsum / dm;
-        v += c * s - acc / dm;
+        v = head_sum<BT>(v);
+        if (threadIdx.x == 0) loss[b] = v;
+        __syncthreads();
     }
-    v = head_sum<BT>(v);
-    if (threadIdx.x == 0) loss[b] = v;
 }
 
 // Workgroups for N threads. A launch holds fewer than 2^32 work-items in a
@@ -397,6 +406,9 @@ __global__ __launch_bounds__(BT) void k_pfy(int32_t M, int32_t n, const double *
 static unsigned grid1(int64_t N) {
     return (unsigned)std::max<int64_t>(1, std::min<int64_t>(ceil_div(N, kBlock), ((int64_t)1 << 31) / kBlock));
 }
+
+// Workgroups (of up to 1,024 threads) for B instances, which walk on likewise.
+static unsigned instance_groups(int32_t B) { return (unsigned)std::min(B, 1 << 21); }
 
 void head_linear_costs(hipStream_t s, int32_t B, int32_t n, int32_t p, const double *f,
                        const double *W, double *c) {
@@ -412,8 +424,8 @@ void head_linear_costs(hipStream_t s, int32_t B, int32_t n, int32_t p, const dou
 void head_regret(hipStream_t s, int32_t B, int32_t n, const double *ct, const double *x,
                  const double *vs, double *loss) {
     if (B == 0) return;
-    if (n > kHeadWide) k_regret<1024><<<(unsigned)B, 1024, 0, s>>>(n, ct, x, vs, loss);
-    else k_regret<256><<<(unsigned)B, 256, 0, s>>>(n, ct, x, vs, loss);
+    if (n > kHeadWide) k_regret<1024><<<instance_groups(B), 1024, 0, s>>>(B, n, ct, x, vs, loss);
+    else k_regret<256><<<instance_groups(B), 256, 0, s>>>(B, n, ct, x, vs, loss);
     PDHG_HIP(hipGetLastError());
 }
 
@@ -476,11 +488,11 @@ void head_qp_value(hipStream_t s, int32_t B, int32_t n, int32_t r, const double 
     if (B == 0) return;
     if (r > kHeadRmax) fail(PDHG_ERR_UNSUPPORTED, "factor rank above 32");
     switch ((r + 7) / 8) {
-        case 0: k_qp_value<0><<<(unsigned)B, kBlock, 0, s>>>(n, r, F, d, c, x, value, gx); break;
-        case 1: k_qp_value<1><<<(unsigned)B, kBlock, 0, s>>>(n, r, F, d, c, x, value, gx); break;
-        case 2: k_qp_value<2><<<(unsigned)B, kBlock, 0, s>>>(n, r, F, d, c, x, value, gx); break;
-        case 3: k_qp_value<3><<<(unsigned)B, kBlock, 0, s>>>(n, r, F, d, c, x, value, gx); break;
-        default: k_qp_value<4><<<(unsigned)B, kBlock, 0, s>>>(n, r, F, d, c, x, value, gx); break;
+        case 0: k_qp_value<0><<<instance_groups(B), kBlock, 0, s>>>(B, n, r, F, d, c, x, value, gx); break;
+        case 1: k_qp_value<1><<<instance_groups(B), kBlock, 0, s>>>(B, n, r, F, d, c, x, value, gx); break;
+        case 2: k_qp_value<2><<<instance_groups(B), kBlock, 0, s>>>(B, n, r, F, d, c, x, value, gx); break;
+        case 3: k_qp_value<3><<<instance_groups(B), kBlock, 0, s>>>(B, n, r, F, d, c, x, value, gx); break;
+        default: k_qp_value<4><<<instance_groups(B), kBlock, 0, s>>>(B, n, r, F, d, c, x, value, gx); break;
     }
     PDHG_HIP(hipGetLastError());
 }
@@ -498,9 +510,9 @@ void head_spo_plus(hipStream_t s, int32_t B, int32_t n, const double *c_hat, con
                    double *grad) {
     if (B == 0) return;
     if (n > kHeadWide)
-        k_spo_plus<1024><<<(unsigned)B, 1024, 0, s>>>(n, c_hat, c_true, w_star, z_star, w_tilde, loss, grad);
+        k_spo_plus<1024><<<instance_groups(B), 1024, 0, s>>>(B, n, c_hat, c_true, w_star, z_star, w_tilde, loss, grad);
     else
-        k_spo_plus<256><<<(unsigned)B, 256, 0, s>>>(n, c_hat, c_true, w_star, z_star, w_tilde, loss, grad);
+        k_spo_plus<256><<<instance_groups(B), 256, 0, s>>>(B, n, c_hat, c_true, w_star, z_star, w_tilde, loss, grad);
     PDHG_HIP(hipGetLastError());
 }
 
@@ -518,8 +530,8 @@ void head_pfy(hipStream_t s, int32_t B, int32_t M, int32_t n, const double *c_ha
               const double *w_star, const double *Z, double eps, const double *w_samples, double *loss,
               double *grad) {
     if (B == 0) return;
-    if (n > kHeadWide) k_pfy<1024><<<(unsigned)B, 1024, 0, s>>>(M, n, c_hat, w_star, Z, eps, w_samples, loss, grad);
-    else k_pfy<256><<<(unsigned)B, 256, 0, s>>>(M, n, c_hat, w_star, Z, eps, w_samples, loss, grad);
+    if (n > kHeadWide) k_pfy<1024><<<instance_groups(B), 1024, 0, s>>>(B, M, n, c_hat, w_star, Z, eps, w_samples, loss, grad);
+    else k_pfy<256><<<instance_groups(B), 256, 0, s>>>(B, M, n, c_hat, w_star, Z, eps, w_samples, loss, grad);
     PDHG_HIP(hipGetLastError());
 }
 

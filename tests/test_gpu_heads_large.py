@@ -71,3 +71,28 @@ def test_spo_costs_of_many_entries():
     out = h.spo_plus_costs(c, c).view(-1)
     assert torch.equal(out[at], flat[at])
     assert int(torch.count_nonzero(out)) == at.numel()
+
+
+@pytest.mark.parametrize("B,n", [((1 << 22) + 3, 1025), ((1 << 24) + 3, 1)])
+def test_losses_of_many_instances(B, n):
+    """One buffer of small whole numbers in every role: all sums are exact."""
+    import torch
+    from paper_2412_09734_amd import heads as h
+    _say(f"regret, SPO+, Fenchel-Young and QP value of {B} instances, n={n}")
+    x = torch.zeros(B, n, dtype=torch.float64, device="cuda")
+    at = torch.tensor([0, 1, (1 << 21) - 1, 1 << 21, (1 << 22) - 1, B - 2, B - 1], device="cuda")
+    x[at] = torch.arange(1.0, at.numel() * n + 1, dtype=torch.float64, device="cuda").view(-1, n) % 64
+    vs = torch.ones(B, dtype=torch.float64, device="cuda")
+    want = torch.zeros(B, dtype=torch.float64, device="cuda")
+    want[at] = (x[at] ** 2).sum(1)
+    assert torch.equal(h.regret(x, x, vs), want - 1.0)
+    loss, grad = h.spo_plus(x, x, x, vs, x)
+    assert torch.equal(loss, want - 1.0) and int(torch.count_nonzero(grad)) == 0
+    del grad
+    loss, grad = h.pfy(x, x, x.view(B, 1, n), 1.0, x.view(B, 1, n))
+    assert torch.equal(loss, -want) and int(torch.count_nonzero(grad)) == 0
+    del grad
+    value, gx = h.qp_value(torch.zeros(n, 0, dtype=torch.float64, device="cuda"), x, x, x)
+    want[at] = (x[at] ** 2 + 0.5 * x[at] ** 3).sum(1)
+    assert torch.equal(value, want)
+    assert torch.equal(gx[at], x[at] ** 2 + x[at])
