@@ -11,7 +11,7 @@
 
 namespace pdhg {
 
-constexpr int kHeadWide = 1024;   // columns from which an instance gets a workgroup of 1,024 threads
+constexpr int kHeadWide = 2048;   // columns beyond which an instance gets a workgroup of 1,024 threads
 constexpr int kHeadRmax = 32;     // largest factor rank of pdhg_qp_value
 constexpr int kHeadPmax = 64;     // most features of the linear cost model
 constexpr int kScratchDoubles = 32768;   // partial sums of the weight gradient (64 features x 512 chunks)
@@ -25,19 +25,26 @@ constexpr int64_t kMostEntries = ((int64_t)1 << 32) - 1;   // of an array that a
 // hipGetSymbolAddress and passes that to the kernels.
 static __device__ __align__(256) double scratch[kScratchDoubles];
 
-// The positions t, t + BT, ... of thread t in [0, n), U at a time: load(u, a) for
-// all of them (clamped to n - 1), then use(u, a) for those that exist. With one
-// position's loads at a time the heads of eight 3,968-column instances took
-// 5.2 us where their launch alone is 2.
-template <int BT, int U, class Load, class Use>
-__device__ __forceinline__ void strided(int32_t n, Load load, Use use) {
-    for (int32_t a0 = (int32_t)threadIdx.x; a0 < n; a0 += U * BT) {
+// The positions t, t + BT, ... of thread t in [0, n), in groups of 4, the last
+// one of 4, 2 or 1: load(u, a) for all of a group (clamped to n - 1), then
+// use(u, a) for those that exist. With one position's loads at a time the heads
+// of eight 3,968-column instances took 5.2 us where their launch alone is 2; a
+// last group of always 4 made the regret of 2,048 x 1,025 columns twice as slow.
+template <int BT, class Load, class Use>
+__device__ __forceinline__ void strided(uint32_t n, Load load, Use use) {
+    uint32_t a0 = 0;
+    auto group = [&](auto width) {
+        constexpr int U = decltype(width)::value;
+        const uint32_t a = a0 + threadIdx.x;
 #pragma unroll
-        for (int u = 0; u < U; ++u) load(u, min(a0 + u * BT, n - 1));
+        for (int u = 0; u < U; ++u) load(u, min(a + u * BT, n - 1));
 #pragma unroll
         for (int u = 0; u < U; ++u)
-            if (a0 + u * BT < n) use(u, a0 + u * BT);
-    }
+            if (a + u * BT < n) use(u, a + u * BT);
+    };
+    for (; a0 + 2 * BT < n; a0 += 4 * BT) group(std::integral_constant<int, 4>());
+    if (a0 + BT < n) group(std::integral_constant<int, 2>());
+    else if (a0 < n) group(std::integral_constant<int, 1>());
 }
 
 // Workgroup sum in fixed order (waves in order), in every thread.
@@ -53,29 +60,52 @@ __device__ __forceinline__ double head_sum(double v) {
     return s;
 }
 
-// Cost model, few features: the workgroup's 256 rows pass through LDS, read
-// from memory in one coalesced run (a thread reading its own row of p values
-// touches a line per lane and entry); a row's products are added in order. Rows
-// in LDS are p | 1 apart, so that the lanes' banks differ.
+// Cost model, up to kCostsRow features: a thread per row. A wave's rows lie in a
+// few lines, which its loads of one feature after another find in the cache.
+// 8 M rows of 1 / 4 features: 21 / 60 us, through LDS 31 / 92.
+constexpr int kCostsRow = 4;
+__global__ __launch_bounds__(kBlock) void k_linear_costs_row(int64_t N, int32_t p,
+                                                             const double *__restrict__ f,
+                                                             const double *__restrict__ W,
+                                                             double *__restrict__ c) {
+    for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < N; i += (int64_t)gridDim.x * kBlock) {
+        double s = 0.0;
+        for (int32_t k = 0; k < p; ++k) s = fma(W[k], f[i * p + k], s);
+        c[i] = s;
+    }
+}
+
+// Up to P features: the workgroup's 256 rows pass through LDS, read from memory
+// in one coalesced run (a thread reading its own row of many values touches a
+// line per lane and entry), four values of a thread in flight; a row's products
+// are added in order. Rows in LDS are p | 1 apart, so that the lanes' banks
+// differ. P sets the LDS and with it the workgroups of a compute unit.
 constexpr int kCostsLds = 16;   // most features of this variant
+template <int P>
 __global__ __launch_bounds__(kBlock) void k_linear_costs(int64_t N, int32_t p,
                                                          const double *__restrict__ f,
                                                          const double *__restrict__ W,
                                                          double *__restrict__ c) {
-    __shared__ double sh[kBlock * (kCostsLds + 1)];
+    __shared__ double sh[kBlock * (P + 1)];
     const int32_t r0 = (int32_t)threadIdx.x / p, k0 = (int32_t)threadIdx.x - r0 * p;
     const int32_t dr = kBlock / p, dk = kBlock - dr * p, st = p | 1;
     for (int64_t i0 = (int64_t)blockIdx.x * kBlock; i0 < N; i0 += (int64_t)gridDim.x * kBlock) {
         const int32_t rows = (int32_t)min((int64_t)kBlock, N - i0), len = rows * p;
         const double *__restrict__ src = f + i0 * p;
         int32_t r = r0, k = k0;
-        for (int32_t e = (int32_t)threadIdx.x; e < len; e += kBlock) {
-            sh[r * st + k] = src[e];
-            r += dr;
-            k += dk;
-            if (k >= p) {
-                k -= p;
-                ++r;
+        for (int32_t e0 = (int32_t)threadIdx.x; e0 < len; e0 += 4 * kBlock) {
+            double v[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) v[u] = src[min(e0 + u * kBlock, len - 1)];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                if (e0 + u * kBlock < len) sh[r * st + k] = v[u];
+                r += dr;
+                k += dk;
+                if (k >= p) {
+                    k -= p;
+                    ++r;
+                }
             }
         }
         __syncthreads();
@@ -117,14 +147,15 @@ __global__ __launch_bounds__(BT) void k_regret(int32_t B, int32_t n, const doubl
                                                          const double *__restrict__ x,
                                                          const double *__restrict__ vs,
                                                          double *__restrict__ loss) {
-    constexpr int U = 4;
-    for (uint32_t b = blockIdx.x; b < (uint32_t)B; b += gridDim.x) {
+    for (uint32_t b = blockIdx.x;;) {
         const size_t o = (size_t)b * n;
-        double v = 0.0, c[U], w[U];
-        strided<BT, U>(n, [&](int u, int32_t a) { c[u] = ct[o + a]; w[u] = x[o + a]; },
-                                 [&](int u, int32_t) { v = fma(c[u], w[u], v); });
+        double v = 0.0, c[4], w[4];
+        strided<BT>((uint32_t)n, [&](int u, uint32_t a) { c[u] = ct[o + a]; w[u] = x[o + a]; },
+                    [&](int u, uint32_t) { v = fma(c[u], w[u], v); });
         v = head_sum<BT>(v);
         if (threadIdx.x == 0) loss[b] = v - vs[b];
+        b += gridDim.x;
+        if (b >= (uint32_t)B) return;   // a barrier would wait for the stores
         __syncthreads();
     }
 }
@@ -161,14 +192,16 @@ __global__ __launch_bounds__(BT) void k_costs_grad_part(int64_t N, int32_t p, in
                                                         const double *__restrict__ f,
                                                         const double *__restrict__ gc,
                                                         double *__restrict__ part) {
-    constexpr int U = 8;
     const int32_t step = BT / p, live = step * p;
     const int64_t len = (N + chunks - 1) / chunks;
     const int64_t i0 = blockIdx.x * len, i1 = min(N, i0 + len);
     double v = 0.0;
     if ((int32_t)threadIdx.x < live) {
         const int32_t r = (int32_t)threadIdx.x / p, k = (int32_t)threadIdx.x - r * p;
-        for (int64_t i = i0 + r; i < i1; i += (int64_t)U * step) {
+        int64_t base = i0;
+        auto rows = [&](auto width) {   // rows base + r, base + r + step, ...
+            constexpr int U = decltype(width)::value;
+            const int64_t i = base + r;
             double g[U], e[U];
 #pragma unroll
             for (int u = 0; u < U; ++u) {
@@ -178,7 +211,11 @@ __global__ __launch_bounds__(BT) void k_costs_grad_part(int64_t N, int32_t p, in
             }
 #pragma unroll
             for (int u = 0; u < U; ++u) v = i + (int64_t)u * step < i1 ? fma(g[u], e[u], v) : v;
-        }
+        };
+        for (; base + 4 * (int64_t)step < i1; base += 8 * (int64_t)step) rows(std::integral_constant<int, 8>());
+        if (base + 2 * step < i1) rows(std::integral_constant<int, 4>());
+        else if (base + step < i1) rows(std::integral_constant<int, 2>());
+        else if (base < i1) rows(std::integral_constant<int, 1>());
     }
     feature_totals<BT>(v, p, step, part + (size_t)blockIdx.x * p);
 }
@@ -222,7 +259,7 @@ __global__ __launch_bounds__(kBlock) void k_qp_value(int32_t B, int32_t n, int32
 #pragma unroll
         for (int k = 0; k < R; ++k) f[k] = k < r ? f[k] : 0.0;
     };
-    for (uint32_t b = blockIdx.x; b < (uint32_t)B; b += gridDim.x) {
+    for (uint32_t b = blockIdx.x;;) {
         const size_t o = (size_t)b * n;
         double t[R > 0 ? R : 1], f[R > 0 ? R : 1];
         if constexpr (G > 0) {
@@ -264,6 +301,8 @@ __global__ __launch_bounds__(kBlock) void k_qp_value(int32_t B, int32_t n, int32
         }
         v = head_sum<kBlock>(v);
         if (threadIdx.x == 0) value[b] = v;
+        b += gridDim.x;
+        if (b >= (uint32_t)B) return;   // a barrier would wait for the stores
         __syncthreads();
     }
 }
@@ -289,25 +328,26 @@ __global__ __launch_bounds__(BT) void k_spo_plus(int32_t B, int32_t n, const dou
                                                            const double *__restrict__ wt,
                                                            double *__restrict__ loss,
                                                            double *__restrict__ grad) {
-    constexpr int U = 4;
-    for (uint32_t b = blockIdx.x; b < (uint32_t)B; b += gridDim.x) {
+    for (uint32_t b = blockIdx.x;;) {
         const size_t o = (size_t)b * n;
-        double v = 0.0, h[U], c[U], s[U], w[U];
-        strided<BT, U>(
-            n,
-            [&](int u, int32_t a) {
+        double v = 0.0, h[4], c[4], s[4], w[4];
+        strided<BT>(
+            (uint32_t)n,
+            [&](int u, uint32_t a) {
                 h[u] = ch[o + a];
                 c[u] = ct[o + a];
                 s[u] = ws[o + a];
                 w[u] = wt[o + a];
             },
-            [&](int u, int32_t a) {
+            [&](int u, uint32_t a) {
                 const double dw = s[u] - w[u];
                 v += 2.0 * h[u] * dw + c[u] * w[u];
                 grad[o + a] = 2.0 * dw;
             });
         v = head_sum<BT>(v);
         if (threadIdx.x == 0) loss[b] = v - zs[b];
+        b += gridDim.x;
+        if (b >= (uint32_t)B) return;   // a barrier would wait for the stores
         __syncthreads();
     }
 }
@@ -320,10 +360,11 @@ __global__ __launch_bounds__(BT) void k_spo_plus(int32_t B, int32_t n, const dou
 // the limit of 2^32 work-items at 2^24 samples). One division a workgroup finds
 // its first sample; from there an entry is at most one sample on where a sample
 // fills a tile, and shorter samples are counted by a multiplication with magic =
-// ceil(2^32 / n), exact while dividend times n is below 2^32 (here below 2^21).
+// ceil(2^32 / n), exact while dividend times n is below 2^32 (here below 2^20).
 // What bounds it: 16 bytes of memory an entry. 200,000 x 24 samples of one draw
-// take 20 us (144 with a workgroup per sample), 2,048 x 4 of 1,025 27 (40).
-constexpr int kPfyTile = 4 * kBlock;
+// take 18 us (144 with a workgroup per sample), 2,048 x 4 of 1,025 29 (40). Four
+// entries a thread gain up to 10% on the largest calls and lose as much on others.
+constexpr int kPfyEach = 2, kPfyTile = kPfyEach * kBlock;
 __global__ __launch_bounds__(kBlock) void k_pfy_costs(int64_t N, int32_t M, int32_t n, uint32_t magic,
                                                       const double *__restrict__ ch,
                                                       const double *__restrict__ Z, double eps,
@@ -333,9 +374,9 @@ __global__ __launch_bounds__(kBlock) void k_pfy_costs(int64_t N, int32_t M, int3
     // first sample of the tile, its instance, and the tile's start in the sample
     const uint32_t row = (uint32_t)i0 / (uint32_t)n, b = row / (uint32_t)M;
     const uint32_t first = (uint32_t)i0 - row * (uint32_t)n, m0 = row - b * (uint32_t)M;
-    double z[4], h[4];
+    double z[kPfyEach], h[kPfyEach];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
+    for (int u = 0; u < kPfyEach; ++u) {
         const int64_t i = min(i0 + (int32_t)threadIdx.x + u * kBlock, N - 1);
         const uint32_t a = first + (uint32_t)(i - i0);
         uint32_t q, up;   // samples and instances past the first
@@ -350,7 +391,7 @@ __global__ __launch_bounds__(kBlock) void k_pfy_costs(int64_t N, int32_t M, int3
         h[u] = ch[(int64_t)(b + up) * n + (a - q * (uint32_t)n)];
     }
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
+    for (int u = 0; u < kPfyEach; ++u) {
         const int64_t i = i0 + (int32_t)threadIdx.x + u * kBlock;
         const double pz = eps * z[u];
         if (i < N) out[i] = h[u] + pz;
@@ -368,34 +409,43 @@ __global__ __launch_bounds__(BT) void k_pfy(int32_t B, int32_t M, int32_t n, con
                                                       const double *__restrict__ wm,
                                                       double *__restrict__ loss,
                                                       double *__restrict__ grad) {
-    constexpr int U = 4;   // samples whose loads are in flight together
-    for (uint32_t b = blockIdx.x; b < (uint32_t)B; b += gridDim.x) {
+    for (uint32_t b = blockIdx.x;;) {
         const size_t o = (size_t)b * n;
         const double dm = (double)M;
         double v = 0.0;
         for (int32_t a = threadIdx.x; a < n; a += BT) {
             const double c = ch[o + a], s = ws[o + a];
+            const double *pw = wm + o * M + a, *pz = Z + o * M + a;
             double wsum = 0.0, acc = 0.0;
-            for (int32_t m0 = 0; m0 < M; m0 += U) {
+            // the next samples, their loads in flight together
+            auto samples = [&](auto width) {
+                constexpr int U = decltype(width)::value;
                 double w[U], z[U];
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
-                    const size_t e = ((size_t)b * M + min(m0 + u, M - 1)) * n + a;
-                    w[u] = wm[e];
-                    z[u] = Z[e];
+                    w[u] = pw[(size_t)u * n];
+                    z[u] = pz[(size_t)u * n];
                 }
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
-                    if (m0 + u >= M) break;
                     wsum += w[u];
                     acc += (c + eps * z[u]) * w[u];
                 }
-            }
+                pw += (size_t)U * n;
+                pz += (size_t)U * n;
+            };
+            int32_t m = M;
+            for (; m >= 8; m -= 8) samples(std::integral_constant<int, 8>());
+            if (m & 4) samples(std::integral_constant<int, 4>());
+            if (m & 2) samples(std::integral_constant<int, 2>());
+            if (m & 1) samples(std::integral_constant<int, 1>());
             grad[o + a] = s - wsum / dm;
             v += c * s - acc / dm;
         }
         v = head_sum<BT>(v);
         if (threadIdx.x == 0) loss[b] = v;
+        b += gridDim.x;
+        if (b >= (uint32_t)B) return;   // a barrier would wait for the stores
         __syncthreads();
     }
 }
@@ -414,8 +464,9 @@ void head_linear_costs(hipStream_t s, int32_t B, int32_t n, int32_t p, const dou
                        const double *W, double *c) {
     const int64_t N = (int64_t)B * n;
     if (N == 0) return;
-    if (p <= kCostsLds)
-        k_linear_costs<<<grid1(N), kBlock, 0, s>>>(N, p, f, W, c);
+    if (p <= kCostsRow) k_linear_costs_row<<<grid1(N), kBlock, 0, s>>>(N, p, f, W, c);
+    else if (p <= 8) k_linear_costs<8><<<grid1(N), kBlock, 0, s>>>(N, p, f, W, c);
+    else if (p <= kCostsLds) k_linear_costs<kCostsLds><<<grid1(N), kBlock, 0, s>>>(N, p, f, W, c);
     else
         k_linear_costs_wide<<<grid1(N * 16), kBlock, 0, s>>>(N, p, f, W, c);
     PDHG_HIP(hipGetLastError());

@@ -17,14 +17,38 @@ def _say(*a):
     print("case:", *a, file=sys.stderr, flush=True)
 
 
-@pytest.mark.parametrize("B,M,n", [(1, 1, 1), (5, 9, 1), (1, 5000, 2), (300, 1, 7), (7, 3, 341), (2, 3, 1023),
-                                   (2, 3, 1024), (1, 4, 1025), (3, 2, 2047), (40, 100, 24)])
+@pytest.mark.parametrize("B,M,n", [(1, 1, 1), (5, 9, 1), (1, 5000, 2), (300, 1, 7), (7, 3, 341), (2, 3, 511),
+                                   (2, 3, 512), (1, 4, 513), (3, 2, 1023), (40, 100, 24)])
 def test_perturbed_costs_tiles(B, M, n):
     from paper_2412_09734_amd import heads as h
     _say(f"perturbed costs B={B} M={M} n={n}")
     rng = np.random.default_rng(B + M + n)
     ch, Z = rng.standard_normal((B, n)), rng.standard_normal((B, M, n))
     assert np.array_equal(to_np(h.pfy_costs(ch, Z, 0.3)), ch[:, None] + 0.3 * Z)
+
+
+@pytest.mark.parametrize("n,M,p", [(255, 2, 4), (257, 5, 5), (512, 7, 8), (513, 8, 9), (768, 9, 16), (1023, 11, 1),
+                                   (2048, 13, 3), (2049, 1, 17), (4097, 3, 2), (6145, 15, 24)])
+def test_groups_of_loads(n, M, p):
+    """Columns, samples and features around the groups whose loads are in flight
+    together: small whole numbers, so that every sum is exact in any order."""
+    from paper_2412_09734_amd import heads as h
+    _say(f"groups of loads n={n} M={M} p={p}")
+    rng = np.random.default_rng(n)
+    i = lambda *s: rng.integers(-8, 9, s).astype(float)  # noqa: E731
+    B = 3
+    x, c, w, s, z = i(B, n), i(B, n), i(B, n), i(B, n), i(B)
+    assert np.array_equal(to_np(h.regret(c, x, z)), (c * x).sum(1) - z)
+    loss, grad = h.spo_plus(x, c, w, z, s)
+    assert np.array_equal(to_np(loss), (2 * x * (w - s) + c * s).sum(1) - z)
+    assert np.array_equal(to_np(grad), 2 * (w - s))
+    Z, wm = i(B, M, n), M * i(B, M, n)
+    loss, grad = h.pfy(c, w, Z, 2.0, wm)
+    assert np.array_equal(to_np(loss), (c * w).sum(1) - ((c[:, None] + 2 * Z) * wm).sum((1, 2)) / M)
+    assert np.array_equal(to_np(grad), w - wm.sum(1) / M)
+    f, W = i(B, n, p), i(p)
+    assert np.array_equal(to_np(h.linear_costs(f, W)), f @ W)
+    assert np.array_equal(to_np(h.linear_costs_backward(f, x)), (f * x[..., None]).sum((0, 1)))
 
 
 @pytest.mark.parametrize("B,M,n", [(1, (1 << 24) + 3, 1), ((1 << 24) + 5, 1, 2), (1 << 13, 1 << 12, 3)])
