@@ -285,7 +285,7 @@ __global__ __launch_bounds__(kBlock) void k_qp_value(int32_t B, int32_t n, int32
 #pragma unroll
             for (int w = 1; w < kBlock / 64; ++w) tp += sh[p][w];
 #pragma unroll
-            for (int k = 0; k < R; ++k) t[k] = lane_value(tp, k);
+            for (int k = 0; k < R; ++k) t[k] = k < r ? lane_value(tp, k) : 0.0;   // 0 x an infinite x is no 0
         }
         double v = 0.0;
         for (int32_t j = threadIdx.x; j < n; j += kBlock) {
