@@ -298,10 +298,14 @@ pdhg_err pdhg_batch_solve(pdhg_batch *b, const double *x_init, const double *y_i
  * the GPU holds). Unless this call or pdhg_batch_autotune chose the shape, an
  * LP solve takes one column or row of the largest instance per thread up to
  * 512 threads (two per thread when the batch has more instances than run at
- * once), 512 up to 1,024 columns and 1,024 beyond. The unrolled passes start
- * at 1024 threads when the batch has at most one instance per compute unit,
- * else at the fewest, from 256, that give each thread at most 8 columns and 8
- * rows; QP batches take at most 512 of them. LP batches on a shared matrix
+ * once), 512 up to 1,024 columns and 1,024 beyond (512 up to
+ * 4,096 with the infeasibility tests). A batch whose largest instance has more
+ * than 8,192 columns or rows, or more than 2,048 and n + 3 m doubles beyond a
+ * workgroup's LDS, runs from memory: with 1024 threads when it has at most one
+ * instance per compute unit, else with the fewest, from 256, that give each
+ * thread at most 8 columns and 8 rows, and at most 512 with the infeasibility
+ * tests. The unrolled passes start at 1024 or at the fewest by the same rule;
+ * QP batches take at most 512 of them. LP batches on a shared matrix
  * with at most 2 entries a column and 8 a row (the matrix then stays in
  * registers) start at 256 threads up to 1,024 columns and 256 rows, and at
  * 512 up to 4,096 and 1,024. */

@@ -1326,17 +1326,18 @@ __global__ __launch_bounds__(BT) void k_batch_solve_res(BArgs a, BOpts o) {
 }
 
 // ---------------------------------------------------------------------------
-// on-chip solve of any instance with at most 8 columns and rows per thread
+// on-chip solve of any instance with at most 2 columns and rows per thread
 
-// Pairs of entries of each owned column (row) that stay in registers: what
-// fits beside the iterates (40 registers a column and row at two of each) in
-// 256 registers, or in 128 at 1,024 threads.
+// Pairs of entries of each owned column (row) that stay in registers. More of
+// them spilled less elsewhere than they saved in LDS and streamed pairs: as
+// chosen, the compiler keeps 5 to 40 registers of a thread in scratch memory at
+// one column, 100 to 130 at two, of which the iterations reload at most 34.
 template <int BT, int S, int SR>
 struct LdsShape {
-    static constexpr int KC = BT == 1024 ? 0 : S == 1 ? 8 : S == 2 ? 6 : S == 4 ? 2 : 0;
-    static constexpr int KR = BT == 1024 || S == 8 ? 0 : S == 1 ? 14 : SR == 1 ? 12 : SR == 2 ? 6 : 2;
-    static constexpr int U = BT == 1024 && S == 8 ? 2 : 4;
-    static constexpr bool ahead = BT < 1024, keep = BT < 1024 || S < 4;
+    static constexpr int KC = BT == 1024 ? 0 : S == 1 ? 8 : 6;
+    static constexpr int KR = BT == 1024 ? 0 : S == 1 ? 14 : SR == 1 ? 12 : 6;
+    static constexpr int U = 4;
+    static constexpr bool ahead = BT < 1024;
     static constexpr int32_t x = SR * BT;                  // x_ext after y
     static constexpr int32_t step = x + S * BT;            // momentum factors
     static constexpr size_t bytes = ((size_t)step + 4 * kResSteps) * sizeof(double);
@@ -1474,12 +1475,7 @@ k_batch_solve_lds(BArgs a, BOpts o, int32_t cache_pairs) {
         const double gam = o.gamma;
         SellRow<L::KC, L::U, L::ahead> col[S];
         SellRow<L::KR, L::U, L::ahead> row[SR];
-        double xr[S], x0r[S], crr[S], lrr[S], urr[S];
-        // scaled cost and bounds of the owned columns, in memory where the
-        // registers would spill
-        auto c_of = [&](int q) { return L::keep ? crr[q] : a.c[g.vc + (int32_t)threadIdx.x + q * BT]; };
-        auto l_of = [&](int q) { return L::keep ? lrr[q] : a.lv[g.vc + (int32_t)threadIdx.x + q * BT]; };
-        auto u_of = [&](int q) { return L::keep ? urr[q] : a.uv[g.vc + (int32_t)threadIdx.x + q * BT]; };
+        double xr[S], x0r[S], cr[S], lr[S], ur[S];
         double yr[SR], y0r[SR], lo[SR], hi[SR];   // lo, hi: -sigma u_c, -sigma l_c
         LdsDouble *const myx = sx + (int32_t)threadIdx.x, *const myy = sy + (int32_t)threadIdx.x;
         // an equal share of the cache for every slice
@@ -1495,23 +1491,16 @@ k_batch_solve_lds(BArgs a, BOpts o, int32_t cache_pairs) {
                 k1 = a.tsp[f + sl + 1];
             }
             col[q].load(a.tsci, a.tsva, k0, k1, lane, cache, kPairBytes * room * sl, room);
-            xr[q] = crr[q] = lrr[q] = urr[q] = 0.0;
+            xr[q] = cr[q] = lr[q] = ur[q] = 0.0;
             if (j < g.n) {
                 const int32_t jo = row_at(a.tperm, g.c0, j);
                 const double d = Dc[jo], co = a.c_o[g.vc + jo];
-                const double c = d * co, l = a.lv_o[g.vc + jo] / d, u = a.uv_o[g.vc + jo] / d;
-                if (L::keep) {
-                    crr[q] = c;
-                    lrr[q] = l;
-                    urr[q] = u;
-                } else {
-                    a.c[g.vc + j] = c;
-                    a.lv[g.vc + j] = l;
-                    a.uv[g.vc + j] = u;
-                }
-                nrm[0] += c * c;
+                cr[q] = d * co;
+                lr[q] = a.lv_o[g.vc + jo] / d;
+                ur[q] = a.uv_o[g.vc + jo] / d;
+                nrm[0] += cr[q] * cr[q];
                 nrm[2] += co * co;
-                xr[q] = clampd(a.x_init ? a.x_init[g.vc + jo] / d : 0.0, l, u);
+                xr[q] = clampd(a.x_init ? a.x_init[g.vc + jo] / d : 0.0, lr[q], ur[q]);
             }
             x0r[q] = xr[q];
         }
@@ -1567,9 +1556,9 @@ k_batch_solve_lds(BArgs a, BOpts o, int32_t cache_pairs) {
 #pragma unroll
             for (int q = 0; q < S; ++q) {
                 s[q] = xn[q] = 0.0;
-                if (L::keep ? 64 * (wave + q * NW) < g.n : (int32_t)threadIdx.x + q * BT < g.n) {
+                if (64 * (wave + q * NW) < g.n) {
                     s[q] = col[q].dot(a.tsci, a.tsva, sy, lane);
-                    xn[q] = clamp_quiet(xr[q] - tau * (c_of(q) - s[q]), l_of(q), u_of(q));
+                    xn[q] = clamp_quiet(xr[q] - tau * (cr[q] - s[q]), lr[q], ur[q]);
                     myx[q * BT] = 2.0 * xn[q] - xr[q];
                 }
             }
@@ -1693,7 +1682,7 @@ k_batch_solve_lds(BArgs a, BOpts o, int32_t cache_pairs) {
                         v[1] += (qq - s[q]) * dx;
                         const double d0 = xh - x0r[q];
                         v[2] += d0 * d0;
-                        const double c = c_of(q), l = l_of(q), u = u_of(q);
+                        const double c = cr[q], l = lr[q], u = ur[q];
                         const double gr = c - qq;   // D_c times the original-space gradient
                         const bool lf = isfinite(l), uf = isfinite(u);
                         const double lam = (!lf && !uf) ? 0.0 : (lf && !uf) ? fmax(gr, 0.0) : (!lf && uf) ? fmin(gr, 0.0) : gr;
@@ -1823,6 +1812,387 @@ k_batch_solve_lds(BArgs a, BOpts o, int32_t cache_pairs) {
                 const int32_t io = row_at(a.aperm, g.r0, i);
                 const double yh = myy[q * BT];
                 a.y_out[g.vr + io] = Dr[io] * (yray ? (yh - y0r[q]) * ray_scale : yh);
+            }
+        }
+        if (threadIdx.x == 0) {
+            BatchRes r;
+            r.pobj = P;
+            r.dobj = D;
+            r.rel_p = rel_p;
+            r.rel_d = rel_d;
+            r.rel_g = rel_g;
+            r.kkt = kkt;
+            r.omega = omega;
+            r.eta = eta;
+            r.iterations = t + 1;
+            r.restarts = restarts;
+            r.status = status;
+            r.power_iters = a.power_iters[g.sidx];
+            a.res[b] = r;
+        }
+        __syncthreads();
+    }
+}
+
+// ---------------------------------------------------------------------------
+// on-chip solve with more than two columns or rows per thread
+
+// Row sum over the SELL-64 slice whose pairs `first` .. `end` - 1 (wave-uniform)
+// are this wave's, in row order: four pairs' loads in flight, the last ones in
+// groups of two and one.
+__device__ __forceinline__ double stream_dot(const uint32_t *__restrict__ ci, const double2 *__restrict__ va,
+                                             int32_t first, int32_t end, int32_t lane, const LdsDouble *vec) {
+    double acc = 0.0;
+    int32_t e = 64 * first + lane, w = end - first;
+    auto pairs = [&](auto width) {
+        constexpr int U = decltype(width)::value;
+        uint32_t c[U];
+        double2 v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            c[u] = ci[e + 64 * u];
+            v[u] = va[e + 64 * u];
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) acc = lds_pair(c[u], v[u], vec, acc);
+        e += 64 * U;
+    };
+    for (; w >= 4; w -= 4) pairs(std::integral_constant<int, 4>());
+    if (w & 2) pairs(std::integral_constant<int, 2>());
+    if (w & 1) pairs(std::integral_constant<int, 1>());
+    return acc;
+}
+
+// LDS of k_batch_solve_stream, in doubles: x_ext, then y, and the clamp bounds
+// -sigma u_c, -sigma l_c of the dual step.
+static size_t stream_doubles(int32_t n, int32_t m) { return (size_t)n + 3 * (size_t)m; }
+
+// The iteration of k_batch_solve on chip for instances of S > 2 columns or rows
+// per thread: the gathered vectors and the rows' bounds in LDS, the columns'
+// iterate, anchor, cost and bounds in registers, and every matrix entry streamed
+// from the SELL-64 slices on every product. The point and the dual anchor of a
+// check live in memory (xh, aty, yh, y, y0: read at checks, y0 once per row and
+// iteration), by position like everything here.
+//
+// What bounds it: the latency of the slices' pairs, four in flight a lane, from
+// L2 or the memory-side cache. Holding pairs in registers or LDS as
+// k_batch_solve_lds does left no registers at four or eight columns a thread: its
+// forms kept up to 2,400 of them in scratch memory. 600 instances of one matrix,
+// 193 iterations, ray tests on / off: 1,500 x 3,000 14.1 / 13.6 -> 7.2 / 6.1 ms,
+// 2,000 x 4,100 19.9 / 19.4 -> 11.3 / 9.6, 4,500 x 1,500 19.9 / 19.4 -> 8.0 / 7.2;
+// 700 ragged 2,000 x 4,100 14.7 / 14.1 -> 10.6 / 9.7.
+template <int BT, int S, bool RAYS>
+__global__ __launch_bounds__(BT) void k_batch_solve_stream(BArgs a, BOpts o, int32_t nmax, int32_t mmax) {
+    constexpr int NW = BT / 64;
+    extern __shared__ __attribute__((aligned(16))) double lds[];
+    LdsDouble *const sx = (LdsDouble *)lds, *const sy = sx + nmax, *const slo = sy + mmax, *const shi = slo + mmax;
+    for (;;) {
+        const int32_t b = next_instance<BT>(a.queue);
+        if (b >= a.B) return;
+        const Geo g = geometry(a, b);
+        const int32_t lane = (int32_t)(threadIdx.x & 63);
+        const int32_t wave = __builtin_amdgcn_readfirstlane((int32_t)threadIdx.x >> 6);
+        const int32_t *tsp = a.tsp + (a.shared ? 0 : a.tsfirst[b]), *asp = a.asp + (a.shared ? 0 : a.asfirst[b]);
+        const double *Dr = a.Dr + g.dr, *Dc = a.Dc + g.dc;
+        const double *c_o = a.c_o + g.vc, *lv_o = a.lv_o + g.vc, *uv_o = a.uv_o + g.vc;
+        const double *lc_o = a.lc_o + g.vr, *uc_o = a.uc_o + g.vr;
+        double *__restrict__ xh = a.xh + g.vc;
+        double *__restrict__ aty = a.aty + g.vc;
+        double *__restrict__ y = a.y + g.vr;
+        double *__restrict__ yh = a.yh + g.vr;
+        double *__restrict__ y0 = a.y0 + g.vr;
+        const double eta = a.eta[g.sidx];
+        const double gam = o.gamma;
+        double xr[S], x0r[S], cr[S], lr[S], ur[S];
+        double nrm[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int q = 0; q < S; ++q) {
+            const int32_t j = (int32_t)threadIdx.x + q * BT;
+            xr[q] = x0r[q] = cr[q] = lr[q] = ur[q] = 0.0;
+            if (j < g.n) {
+                const int32_t jo = row_at(a.tperm, g.c0, j);
+                const double d = Dc[jo], co = c_o[jo];
+                cr[q] = d * co;
+                lr[q] = lv_o[jo] / d;
+                ur[q] = uv_o[jo] / d;
+                nrm[0] += cr[q] * cr[q];
+                nrm[2] += co * co;
+                xr[q] = clampd(a.x_init ? a.x_init[g.vc + jo] / d : 0.0, lr[q], ur[q]);
+                x0r[q] = xr[q];
+            }
+        }
+        for (int32_t i = (int32_t)threadIdx.x; i < g.m; i += BT) {
+            const int32_t io = row_at(a.aperm, g.r0, i);
+            const double d = Dr[io], loo = lc_o[io], hio = uc_o[io];
+            const double l = d * loo, u = d * hio;
+            double bb = 0.0, bo = 0.0;
+            if (isfinite(l)) bb = fmax(bb, fabs(l));
+            if (isfinite(u)) bb = fmax(bb, fabs(u));
+            if (isfinite(loo)) bo = fmax(bo, fabs(loo));
+            if (isfinite(hio)) bo = fmax(bo, fabs(hio));
+            nrm[1] += bb * bb;
+            nrm[3] += bo * bo;
+            const double yv = clampd(a.y_init ? a.y_init[g.vr + io] / d : 0.0, isfinite(u) ? -INFINITY : 0.0,
+                                     isfinite(l) ? INFINITY : 0.0);
+            sy[i] = yv;
+            y0[i] = yv;
+        }
+        wg_sum<BT, 4>(nrm);
+        const double cn = sqrt(nrm[0]), bn = sqrt(nrm[1]);
+        const double cnorm = uniform_value(sqrt(nrm[2])), bnorm = uniform_value(sqrt(nrm[3]));
+        double omega = uniform_value((cn > 1e-10 && bn > 1e-10) ? cn / bn : 1.0);
+        double tau = uniform_value(eta / omega), sigma = uniform_value(eta * omega);
+        // clamp bounds of the dual step at this sigma, by the thread that reads them
+        auto dual_bounds = [&]() {
+            for (int32_t i = (int32_t)threadIdx.x; i < g.m; i += BT) {
+                const int32_t io = row_at(a.aperm, g.r0, i);
+                slo[i] = -sigma * (Dr[io] * uc_o[io]);
+                shi[i] = -sigma * (Dr[io] * lc_o[io]);
+            }
+        };
+        dual_bounds();
+        auto col_dot = [&](int q) {
+            const int32_t sl = wave + q * NW;
+            return stream_dot(a.tsci, a.tsva, tsp[sl], tsp[sl + 1], lane, sy);
+        };
+        auto row_dot = [&](int q) {
+            const int32_t sl = wave + q * NW;
+            return stream_dot(a.asci, a.asva, asp[sl], asp[sl + 1], lane, sx);
+        };
+        __syncthreads();
+
+        int64_t t = 0, k = 0, restarts = 0;
+        int32_t tc = 0;   // t modulo check_every
+        double r_start = 0.0, r_prev = 0.0;
+        int32_t status = 0;
+        bool anchor_valid = false;   // the anchor's products are stored (after a restart)
+        double ray_scale = 0.0;
+        double kkt = 0.0, rel_p = 0.0, rel_d = 0.0, rel_g = 0.0, P = 0.0, D = 0.0;
+        for (;;) {
+            // an opaque copy of the thread index: the element addresses are
+            // formed in each iteration instead of being kept in registers
+            int32_t tid = (int32_t)threadIdx.x;
+            asm volatile("" : "+v"(tid));
+            const bool last = t + 1 >= o.limit;
+            const bool keep = tc == 0 || last;
+            double A, G, B;
+            momentum_factors((double)k, gam, A, G, B);
+#pragma unroll
+            for (int q = 0; q < S; ++q) {
+                const int32_t j = tid + q * BT;
+                if (64 * (wave + q * NW) < g.n) {
+                    const double s = col_dot(q);
+                    if (j < g.n) {
+                        const double xn = clamp_quiet(xr[q] - tau * (cr[q] - s), lr[q], ur[q]);
+                        sx[j] = 2.0 * xn - xr[q];
+                        if (keep) {
+                            xh[j] = xn;
+                            aty[j] = s;
+                        } else {
+                            xr[q] = A * xn - G * xr[q] + B * x0r[q];
+                        }
+                    }
+                }
+            }
+            __syncthreads();
+#pragma unroll
+            for (int q = 0; q < S; ++q) {
+                const int32_t i = tid + q * BT;
+                if (64 * (wave + q * NW) < g.m) {
+                    const double ya = i < g.m ? y0[i] : 0.0;
+                    const double s = row_dot(q);
+                    if (i < g.m) {
+                        const double yv = sy[i], w = fma(-sigma, s, yv), yn = w - clamp_quiet(w, slo[i], shi[i]);
+                        if (keep) {
+                            yh[i] = yn;
+                            y[i] = yv;
+                        } else {
+                            sy[i] = A * yn - G * yv + B * ya;
+                        }
+                    }
+                }
+            }
+            __syncthreads();
+            if (!keep) {
+                ++k;
+                ++t;
+                tc = tc + 1 == o.check_every ? 0 : tc + 1;
+                continue;
+            }
+            // check: the PDHG point replaces x_ext and y in LDS for the products
+#pragma unroll
+            for (int q = 0; q < S; ++q) {
+                const int32_t j = tid + q * BT;
+                if (j < g.n) sx[j] = xh[j];
+                if (j < g.m) sy[j] = yh[j];
+            }
+            __syncthreads();
+            // KKT sums, then (RAYS) the ray sums: v[10], v[11] over the columns
+            // (bound terms, c'dx), v[12] over the rows; rmx the ray violations
+            constexpr int NV = RAYS ? 13 : 10;
+            double v[NV], rmx[2] = {0.0, 0.0};
+#pragma unroll
+            for (int q = 0; q < NV; ++q) v[q] = 0.0;
+#pragma unroll
+            for (int q = 0; q < S; ++q) {
+                const int32_t j = tid + q * BT;
+                if (64 * (wave + q * NW) < g.n) {
+                    const double qq = col_dot(q);
+                    if (j < g.n) {
+                        const int32_t jo = row_at(a.tperm, g.c0, j);
+                        const double xn = xh[j], dx = xn - xr[q], d0 = xn - x0r[q];
+                        v[0] += dx * dx;
+                        v[1] += (qq - aty[j]) * dx;
+                        v[2] += d0 * d0;
+                        const double d = Dc[jo], co = c_o[jo], lo = lv_o[jo], hi = uv_o[jo];
+                        const double gr = co - qq / d;
+                        const bool lf = isfinite(lo), uf = isfinite(hi);
+                        const double lam = (!lf && !uf) ? 0.0 : (lf && !uf) ? fmax(gr, 0.0) : (!lf && uf) ? fmin(gr, 0.0) : gr;
+                        const double rd = gr - lam;
+                        v[3] += rd * rd;
+                        v[4] += co * (d * xn);
+                        v[5] += (lf ? lo * fmax(lam, 0.0) : 0.0) - (uf ? hi * fmax(-lam, 0.0) : 0.0);
+                        if constexpr (RAYS) {
+                            a.qh[g.vc + j] = qq;
+                            if (anchor_valid) {
+                                double s2[2], m2[2];
+                                ray_col_terms(qq, a.q0[g.vc + j], d, d0, co, lo, hi, s2, m2);
+                                v[10] += s2[0];
+                                v[11] += s2[1];
+                                rmx[0] = fmax(rmx[0], m2[0]);
+                                rmx[1] = fmax(rmx[1], m2[1]);
+                            }
+                        }
+                    }
+                }
+            }
+#pragma unroll
+            for (int q = 0; q < S; ++q) {
+                const int32_t i = tid + q * BT;
+                if (64 * (wave + q * NW) < g.m) {
+                    const double p = row_dot(q);
+                    if (i < g.m) {
+                        const int32_t io = row_at(a.aperm, g.r0, i);
+                        const double d = Dr[io], lo = lc_o[io], hi = uc_o[io];
+                        const double ax = p / d;
+                        const double rpr = ax - clampd(ax, lo, hi);
+                        v[6] += rpr * rpr;
+                        const double yn = yh[i], yo = d * yn;
+                        v[7] += (isfinite(lo) ? lo * fmax(yo, 0.0) : 0.0) - (isfinite(hi) ? hi * fmax(-yo, 0.0) : 0.0);
+                        const double dy = yn - y[i], d0 = yn - y0[i];
+                        v[8] += dy * dy;
+                        v[9] += d0 * d0;
+                        if constexpr (RAYS) {
+                            a.ph[g.vr + i] = p;
+                            if (anchor_valid) {
+                                double s1[1], m2[2];
+                                ray_row_terms(p, a.p0[g.vr + i], d, d0, lo, hi, s1, m2);
+                                v[12] += s1[0];
+                                rmx[0] = fmax(rmx[0], m2[0]);
+                                rmx[1] = fmax(rmx[1], m2[1]);
+                            }
+                        }
+                    }
+                }
+            }
+            wg_sum<BT, NV>(v);
+            P = uniform_value(v[4]);
+            D = uniform_value(v[7] + v[5]);
+            rel_p = uniform_value(sqrt(v[6]) / (1.0 + bnorm));
+            rel_d = uniform_value(sqrt(v[3]) / (1.0 + cnorm));
+            rel_g = uniform_value(fabs(P - D) / (1.0 + fabs(P) + fabs(D)));
+            kkt = rel_p;
+            if (rel_d > kkt || isnan(rel_d)) kkt = rel_d;
+            if (rel_g > kkt || isnan(rel_g)) kkt = rel_g;
+            if (isnan(kkt)) {
+                status = PDHG_NUMERICAL_ERROR;
+                break;
+            }
+            if (kkt <= o.eps) {
+                status = PDHG_OPTIMAL;
+                break;
+            }
+            if (RAYS && anchor_valid) {
+                wg_max<BT, 2>(rmx);
+                const double obj_d = v[RAYS ? 10 : 0] + v[RAYS ? 12 : 0], obj_p = v[RAYS ? 11 : 0];
+                if (o.eps_pinf > 0.0 && obj_d > 0.0 && rmx[0] <= o.eps_pinf * obj_d) {
+                    status = PDHG_PRIMAL_INFEASIBLE;
+                    ray_scale = uniform_value(1.0 / obj_d);
+                    break;
+                }
+                if (o.eps_dinf > 0.0 && obj_p < 0.0 && rmx[1] <= o.eps_dinf * (-obj_p)) {
+                    status = PDHG_DUAL_INFEASIBLE;
+                    ray_scale = uniform_value(-1.0 / obj_p);
+                    break;
+                }
+            }
+            if (last) {
+                status = PDHG_ITERATION_LIMIT;
+                break;
+            }
+            const double r2 = v[0] / tau + v[8] / sigma + 2.0 * v[1];
+            const double r = uniform_value(r2 > 0.0 ? sqrt(r2) : 0.0);
+            bool restart = false;
+            if (t == 0) {
+                r_start = r;
+                r_prev = r;
+            } else if (r <= o.beta_suff * r_start || (r <= o.beta_nec * r_start && r > r_prev) ||
+                       (double)k >= o.beta_art * (double)t) {
+                restart = true;
+            } else {
+                r_prev = r;
+            }
+            // (yh, y and sy of a row belong to the thread that wrote them)
+            if (restart) {
+                // exp(log(dyr / dxr) / 2 + log(omega) / 2), without a call
+                const double dxr = sqrt(v[2]), dyr = sqrt(v[9]);
+                if (dxr > 1e-10 && dyr > 1e-10) omega = uniform_value(sqrt(dyr / dxr) * sqrt(omega));
+                tau = uniform_value(eta / omega);
+                sigma = uniform_value(eta * omega);
+                // the check's products are those of the new anchor
+#pragma unroll
+                for (int q = 0; q < S; ++q) {
+                    const int32_t j = tid + q * BT;
+                    if (j < g.n) {
+                        xr[q] = x0r[q] = xh[j];
+                        if (RAYS) a.q0[g.vc + j] = a.qh[g.vc + j];
+                    }
+                    if (j < g.m) {
+                        y0[j] = yh[j];   // sy holds it already
+                        if (RAYS) a.p0[g.vr + j] = a.ph[g.vr + j];
+                    }
+                }
+                dual_bounds();
+                anchor_valid = true;
+                k = 0;
+                r_start = r;
+                r_prev = r;
+                ++restarts;
+            } else {
+#pragma unroll
+                for (int q = 0; q < S; ++q) {
+                    const int32_t j = tid + q * BT;
+                    if (j < g.n) xr[q] = A * xh[j] - G * xr[q] + B * x0r[q];
+                    if (j < g.m) sy[j] = A * yh[j] - G * y[j] + B * y0[j];
+                }
+                ++k;
+            }
+            ++t;
+            tc = o.check_every == 1 ? 0 : 1;
+            __syncthreads();
+        }
+        // original-space output of the last PDHG point, or the certifying ray
+        const bool xray = status == PDHG_DUAL_INFEASIBLE, yray = status == PDHG_PRIMAL_INFEASIBLE;
+#pragma unroll
+        for (int q = 0; q < S; ++q) {
+            const int32_t j = (int32_t)threadIdx.x + q * BT;
+            if (j < g.n) {
+                const int32_t jo = row_at(a.tperm, g.c0, j);
+                a.x_out[g.vc + jo] = Dc[jo] * (xray ? (xh[j] - x0r[q]) * ray_scale : xh[j]);
+            }
+            if (j < g.m) {
+                const int32_t io = row_at(a.aperm, g.r0, j);
+                a.y_out[g.vr + io] = Dr[io] * (yray ? (yh[j] - y0[j]) * ray_scale : yh[j]);
             }
         }
         if (threadIdx.x == 0) {
@@ -2826,12 +3196,18 @@ static void launch_res_t(BatchHandle &h, void (*kernel)(Args...), Args... args) 
     static_assert(lds <= 150 * 1024, "the reductions need LDS of their own");
     launch_queue_t<BT>(h, lds, kernel, args...);
 }
-// Whether k_batch_solve_lds takes the batch at bt threads: at most 8 columns
-// and 8 rows per thread, and not so many rows that (n + 4 m) doubles exceed a
-// workgroup's LDS.
+// Largest instance that gets SELL-64 copies: 8 columns (rows) for each of
+// 1,024 threads, and byte offsets 8 j of its positions fit 16 bits.
+constexpr int32_t kSellRows = 8192;
+
+// Whether the on-chip kernels take the batch at bt threads: k_batch_solve_lds up
+// to 2 columns and rows per thread, k_batch_solve_stream up to 8 where its
+// vectors fit the LDS (3 KB stay for the reductions).
 static bool solve_on_chip(const BatchHandle &h, int32_t bt) {
-    return h.onchip && ((size_t)h.nmax + 4 * (size_t)h.mmax) * sizeof(double) <= lds_per_workgroup() &&
-           std::max(h.nmax, h.mmax) <= 8 * bt;
+    const int32_t need = std::max(h.nmax, h.mmax);
+    return h.onchip && need <= kSellRows &&
+           (need <= 2 * bt ||
+            (need <= 8 * bt && stream_doubles(h.nmax, h.mmax) * sizeof(double) + 3072 <= lds_per_workgroup()));
 }
 
 template <int BT, int S, int SR>
@@ -2845,12 +3221,15 @@ static void launch_solve_lds_t(BatchHandle &h, const BOpts &o, const BArgs &a) {
     launch_queue_t<BT>(h, lds + (size_t)(pairs + 1) * kPairBytes, &k_batch_solve_lds<BT, S, SR>, a, o, pairs);
 }
 
+template <int BT, int S>
+static void launch_solve_stream_t(BatchHandle &h, const BOpts &o, const BArgs &a) {
+    const size_t lds = stream_doubles(h.nmax, h.mmax) * sizeof(double);
+    if (o.detect) launch_queue_t<BT>(h, lds, &k_batch_solve_stream<BT, S, true>, a, o, h.nmax, h.mmax);
+    else launch_queue_t<BT>(h, lds, &k_batch_solve_stream<BT, S, false>, a, o, h.nmax, h.mmax);
+}
+
 template <class T>
 static void load(DBuf<T> &dst, const T *src, size_t count, int mem, hipStream_t s);
-
-// Largest instance that gets SELL-64 copies: 8 columns (rows) for each of
-// 1,024 threads, and byte offsets 8 j of its positions fit 16 bits.
-constexpr int32_t kSellRows = 8192;
 
 // Most workgroups of the kernels that give one to every instance; they walk on
 // from there (a launch holds fewer than 2^32 work-items, and the runtime cuts
@@ -3063,11 +3442,8 @@ static void launch_solve_t(BatchHandle &h, const BOpts &o) {
         if (need <= BT) return launch_solve_lds_t<BT, 1, 1>(h, o, a);
         if (need <= 2 * BT)
             return h.mmax <= BT ? launch_solve_lds_t<BT, 2, 1>(h, o, a) : launch_solve_lds_t<BT, 2, 2>(h, o, a);
-        if (need <= 4 * BT)
-            return h.mmax <= BT ? launch_solve_lds_t<BT, 4, 1>(h, o, a)
-                   : h.mmax <= 2 * BT ? launch_solve_lds_t<BT, 4, 2>(h, o, a) : launch_solve_lds_t<BT, 4, 4>(h, o, a);
-        return h.mmax <= 2 * BT ? launch_solve_lds_t<BT, 8, 2>(h, o, a)
-               : h.mmax <= 4 * BT ? launch_solve_lds_t<BT, 8, 4>(h, o, a) : launch_solve_lds_t<BT, 8, 8>(h, o, a);
+        if (need <= 4 * BT) return launch_solve_stream_t<BT, 4>(h, o, a);
+        return launch_solve_stream_t<BT, 8>(h, o, a);
     }
 
     int32_t wg = std::min(h.B, resident<BT>(o.detect ? reinterpret_cast<const void *>(&k_batch_solve<BT, true>)
@@ -3122,16 +3498,20 @@ static void dispatch_setup(BatchHandle &h, int32_t count) {
 
 // Threads of the solve when the caller chose none. Register-resident: see
 // res_threads. Else, while one column or row per thread takes at most 512
-// threads, that many; two per thread once the batch has more instances than
-// run at once (two waves per SIMD). Up to 1,024 columns 512 threads (register
-// pairs, a wave ahead in the stream), from there 1,024. Per iteration of 256
-// instances, 5% dense, n = 2 m: 1,024 of n = 114: 0.42 us at 64 threads, 0.36
-// at 128, 0.69 at 256; 1,024 (300) of n = 240: 0.77 (2.45) at 128, 0.94
-// (1.6) at 256; 1,024 (128) of n = 500: 2.6 (4.8) at 256, 3.05 (3.4) at 512;
-// 300 of n = 960: 25.9 at 256, 17.1 at 512, 24.2 at 1,024; of n = 2,000: 105
-// at 512, 101 at 1,024. Instances beyond the chip keep the threads of
-// default_threads, at most 512 with the ray tests (k_batch_solve<1024, true>
-// spills).
+// threads, that many; two columns per thread once the batch has more instances
+// than run at once (two waves per SIMD). Up to
+// 1,024 columns 512 threads (register pairs, a wave ahead in the stream), from
+// there 1,024, but 512 for up to 4,096 with the ray tests, whose checks spill at
+// 1,024. Instances beyond the chip keep the threads of default_threads, at most
+// 512 with the ray tests (k_batch_solve<1024, true> spills).
+// Per iteration of 256 instances, 5% dense, n = 2 m: 1,024 of n = 114: 0.42 us at
+// 64 threads, 0.36 at 128, 0.69 at 256; 1,024 (300) of n = 240: 0.77 (2.45) at
+// 128, 0.94 (1.6) at 256; 1,024 (128) of n = 500: 2.6 (4.8) at 256, 3.05 (3.4) at
+// 512; 300 of n = 960: 25.9 at 256, 17.1 at 512, 24.2 at 1,024; of n = 2,000: 105
+// at 512, 101 at 1,024. Sharing one matrix, 600 instances, 193 iterations:
+// 1,500 x 3,000 with the
+// ray tests 6.8 at 512 and at 1,024, narrow 1,100 x 4,000 3.6 at 512, 4.5 at
+// 1,024, without them 3.5 and 3.2.
 static int32_t solve_threads(const BatchHandle &h, bool detect) {
     if (const int32_t t = res_threads(h)) return t;
     if (!solve_on_chip(h, 1024)) return detect ? std::min(h.threads, 512) : h.threads;
@@ -3139,7 +3519,7 @@ static int32_t solve_threads(const BatchHandle &h, bool detect) {
     PDHG_HIP(hipGetDevice(&dev));
     PDHG_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
     const int32_t need = std::max(h.nmax, h.mmax);
-    if (need > 1024) return 1024;
+    if (need > 1024) return detect && need > 2048 && need <= 4096 ? 512 : 1024;
     int32_t bt = 64;
     while (bt < 512 && bt < need) bt *= 2;
     if (need <= bt && bt > 64 && h.B > cus * (512 / bt)) bt /= 2;
