@@ -298,7 +298,8 @@ pdhg_err pdhg_batch_solve(pdhg_batch *b, const double *x_init, const double *y_i
  * the GPU holds). Unless this call or pdhg_batch_autotune chose the shape, an
  * LP solve takes one column or row of the largest instance per thread up to
  * 512 threads (two per thread when the batch has more instances than run at
- * once), 512 up to 1,024 columns and 1,024 beyond (512 up to
+ * once; on a shared matrix only with at most half as many rows as threads and
+ * 16 entries a column), 512 up to 1,024 columns and 1,024 beyond (512 up to
  * 4,096 with the infeasibility tests). A batch whose largest instance has more
  * than 8,192 columns or rows, or more than 2,048 and n + 3 m doubles beyond a
  * workgroup's LDS, runs from memory: with 1024 threads when it has at most one

@@ -3499,7 +3499,9 @@ static void dispatch_setup(BatchHandle &h, int32_t count) {
 // Threads of the solve when the caller chose none. Register-resident: see
 // res_threads. Else, while one column or row per thread takes at most 512
 // threads, that many; two columns per thread once the batch has more instances
-// than run at once (two waves per SIMD). Up to
+// than run at once (two waves per SIMD). On a shared matrix only where that
+// leaves one row per thread and short columns: its entries come from L2 at no
+// cost beside ragged ones, and a second set of them is a longer chain. Up to
 // 1,024 columns 512 threads (register pairs, a wave ahead in the stream), from
 // there 1,024, but 512 for up to 4,096 with the ray tests, whose checks spill at
 // 1,024. Instances beyond the chip keep the threads of default_threads, at most
@@ -3509,7 +3511,8 @@ static void dispatch_setup(BatchHandle &h, int32_t count) {
 // 128, 0.94 (1.6) at 256; 1,024 (128) of n = 500: 2.6 (4.8) at 256, 3.05 (3.4) at
 // 512; 300 of n = 960: 25.9 at 256, 17.1 at 512, 24.2 at 1,024; of n = 2,000: 105
 // at 512, 101 at 1,024. Sharing one matrix, 600 instances, 193 iterations:
-// 1,500 x 3,000 with the
+// 200 x 250 1.50 ms at 128, 0.79 at 256; 250 x 500 with 5 entries a column 0.87
+// at 256, 0.98 at 512, with 12 2.28 at 256, 1.79 at 512; 1,500 x 3,000 with the
 // ray tests 6.8 at 512 and at 1,024, narrow 1,100 x 4,000 3.6 at 512, 4.5 at
 // 1,024, without them 3.5 and 3.2.
 static int32_t solve_threads(const BatchHandle &h, bool detect) {
@@ -3522,7 +3525,8 @@ static int32_t solve_threads(const BatchHandle &h, bool detect) {
     if (need > 1024) return detect && need > 2048 && need <= 4096 ? 512 : 1024;
     int32_t bt = 64;
     while (bt < 512 && bt < need) bt *= 2;
-    if (need <= bt && bt > 64 && h.B > cus * (512 / bt)) bt /= 2;
+    const bool pairs = !h.shared || (2 * h.mmax <= bt && h.ts_wmax <= 16);
+    if (pairs && need <= bt && bt > 64 && h.B > cus * (512 / bt)) bt /= 2;
     return bt;
 }
 
