@@ -50,31 +50,31 @@ struct DenseVecs {
 
 constexpr int kGroupRows = 4;   // rows that a wave, or a workgroup, sums together
 
-// Columns c, c + L, ..., U of them, of kGroupRows rows: every load is issued
+// Columns c, c + L, ..., U of them, of R rows: every load is issued
 // before the first f(row, k, entry). TAIL: some of the columns are past n;
 // their loads are clamped to the last one and come out as 0.
-template <int U, bool NT, bool TAIL, class F>
-__device__ __forceinline__ void row_columns(const double *const (&Ar)[kGroupRows], int32_t c, int32_t L, int32_t n, F f) {
-    double a[kGroupRows][U];
+template <int U, bool NT, bool TAIL, int R, class F>
+__device__ __forceinline__ void row_columns(const double *const (&Ar)[R], int32_t c, int32_t L, int32_t n, F f) {
+    double a[R][U];
 #pragma unroll
-    for (int q = 0; q < kGroupRows; ++q)
+    for (int q = 0; q < R; ++q)
 #pragma unroll
         for (int k = 0; k < U; ++k) a[q][k] = load_entry<NT>(Ar[q] + (TAIL ? min(c + k * L, n - 1) : c + k * L));
     __builtin_amdgcn_sched_barrier(0);   // the scheduler would sink loads between the products
 #pragma unroll
-    for (int q = 0; q < kGroupRows; ++q)
+    for (int q = 0; q < R; ++q)
 #pragma unroll
         for (int k = 0; k < U; ++k) f(q, k, TAIL && c + k * L >= n ? 0.0 : a[q][k]);
 }
 
 // acc over a lane's columns c, c + L, ... of the rows: products with v, or
-// (MODE) maxima and sums of absolute values. U columns x 4 rows of independent
+// (MODE) maxima and sums of absolute values. U columns x R rows of independent
 // loads in flight per lane, each row added in column order; the last columns go
 // in one clamped group of 4, 8 or 16 (one at a time they cost a lane of a
 // 3,001-column row 15 round trips).
-template <int MODE, bool NT>
-__device__ __forceinline__ void row_sums(const double *const (&Ar)[kGroupRows], const double *__restrict__ v, int32_t c,
-                                         int32_t L, int32_t n, double (&acc)[kGroupRows]) {
+template <int MODE, bool NT, int R>
+__device__ __forceinline__ void row_sums(const double *const (&Ar)[R], const double *__restrict__ v, int32_t c,
+                                         int32_t L, int32_t n, double (&acc)[R]) {
     constexpr int U = 16;
     constexpr bool NORM = MODE == ROW_ABSMAX || MODE == ROW_ABSSUM;
     double x[U];
@@ -106,19 +106,20 @@ __device__ __forceinline__ void row_sums(const double *const (&Ar)[kGroupRows], 
     }
 }
 
-// Row pass: a = sum_c A[i][c] v[c], or |A| norms, for groups of four rows, each
-// v[c] loaded once for the four. W = 1: a wave per group (lanes strided over the
+// Row pass: a = sum_c A[i][c] v[c], or |A| norms, for groups of R rows (four; one
+// where the matrix has fewer, which a group of four would read again for the
+// rows it misses: 1 x 3,000,000 1.72 ms per iteration, so 0.73), each
+// v[c] loaded once for the group. W = 1: a wave per group (lanes strided over the
 // columns, butterflies), four groups per workgroup; W = 4, 8: a workgroup of W
 // waves per group (few rows: enough waves and loads in flight), wave totals
 // added in wave order. stream: the matrix is larger than the caches.
-template <int MODE, int W>
+template <int MODE, int W, int R>
 __global__ __launch_bounds__(W == 1 ? kBlock : 64 * W) void k_dense_rows(
     const double *__restrict__ A, int32_t m, int32_t n, const double *__restrict__ v, DenseVecs d, int32_t stream) {
     if (d.st && d.st->done) return;
     constexpr bool WIDE = W > 1;
     constexpr int BS = WIDE ? 64 * W : kBlock;        // threads per workgroup
     constexpr int L = WIDE ? BS : 64;                 // lanes per row
-    constexpr int R = kGroupRows;
     const int64_t row0 = WIDE ? (int64_t)blockIdx.x * R
                               : (((int64_t)blockIdx.x * kBlock + threadIdx.x) >> 6) * R;
     const int32_t lane = WIDE ? (int32_t)threadIdx.x : (int32_t)(threadIdx.x & 63);
@@ -436,8 +437,9 @@ static int32_t row_waves(int32_t m, int32_t n) {
     if (m >= 2048) return 1;
     return m < 1024 && n >= 16384 ? 8 : 4;
 }
+static int32_t group_rows(int32_t m) { return m < kGroupRows ? 1 : kGroupRows; }
 static unsigned row_blocks(int32_t m, int32_t n) {
-    return row_waves(m, n) > 1 ? (unsigned)std::max<int64_t>(1, ceil_div(m, kGroupRows))
+    return row_waves(m, n) > 1 ? (unsigned)std::max<int64_t>(1, ceil_div(m, group_rows(m)))
                             : dblk(ceil_div(m, kGroupRows) * 64);
 }
 
@@ -452,9 +454,15 @@ template <int MODE>
 static void launch_rows(hipStream_t s, const double *A, int32_t m, int32_t n, const double *v,
                         const DenseVecs &d) {
     const int32_t w = row_waves(m, n), stream = dense_stream(m, n);
-    if (w == 8) k_dense_rows<MODE, 8><<<row_blocks(m, n), 512, 0, s>>>(A, m, n, v, d, stream);
-    else if (w == 4) k_dense_rows<MODE, 4><<<row_blocks(m, n), 256, 0, s>>>(A, m, n, v, d, stream);
-    else k_dense_rows<MODE, 1><<<row_blocks(m, n), kBlock, 0, s>>>(A, m, n, v, d, stream);
+    const unsigned nb = row_blocks(m, n);
+    if (group_rows(m) == 1) {
+        if (w == 8) k_dense_rows<MODE, 8, 1><<<nb, 512, 0, s>>>(A, m, n, v, d, stream);
+        else k_dense_rows<MODE, 4, 1><<<nb, 256, 0, s>>>(A, m, n, v, d, stream);
+        return;
+    }
+    if (w == 8) k_dense_rows<MODE, 8, kGroupRows><<<nb, 512, 0, s>>>(A, m, n, v, d, stream);
+    else if (w == 4) k_dense_rows<MODE, 4, kGroupRows><<<nb, 256, 0, s>>>(A, m, n, v, d, stream);
+    else k_dense_rows<MODE, 1, kGroupRows><<<nb, kBlock, 0, s>>>(A, m, n, v, d, stream);
 }
 static unsigned col_blocks(int32_t n) { return dblk(n); }
 
