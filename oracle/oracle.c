@@ -389,7 +389,15 @@ static double power_norm_a(const orc_ctx *s, int32_t *iters) {
         a_mul(s, v, p);
         for (int32_t i = 0; i < m; ++i) p[i] = p[i] - bprev * uprev[i];
         const double a = (double)sqrtl(sumsq(p, m));
-        if (!(a > 0.0)) { if (it == 1) lam = 0.0; break; }
+        if (!(a > 0.0)) {
+            /* the block still gains the row of the last beta (with one row of
+             * A~, the whole norm) */
+            if (it > 1) {
+                alpha[it - 1] = beta[it - 1] = 0.0;
+                lam = tridiag_max(alpha, beta, it);
+            }
+            break;
+        }
         for (int32_t i = 0; i < m; ++i) { u[i] = p[i] / a; uprev[i] = u[i]; }
         at_mul(s, u, q);
         for (int32_t j = 0; j < n; ++j) q[j] = q[j] - a * v[j];

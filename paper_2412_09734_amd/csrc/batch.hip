@@ -450,8 +450,17 @@ __global__ __launch_bounds__(BT) void k_batch_setup(BArgs a, BOpts o, int32_t co
                 wg_sum<BT, 1>(sp);
                 const double al_k = sqrt(sp[0]);
                 if (!(al_k > 0.0)) {
-                    const int32_t at = it - 1 > done ? settle(it - 1, false) : 0;
-                    if (at) it = at;
+                    // the Krylov space closes; the block still gains the row of the
+                    // last beta, the whole norm where A~ has one row
+                    if (it == 1) break;
+                    if (threadIdx.x == 0) {
+                        al[it - 1] = be[it - 1] = 0.0;
+                        if (it <= kTriLds) {
+                            tri_d[it - 1] = bprev * bprev;
+                            tri_e[it - 1] = 0.0;
+                        }
+                    }
+                    it = settle(it, true);
                     break;
                 }
                 for (int32_t i = threadIdx.x; i < g.m; i += BT) u[i] = pr[i] / al_k;

@@ -1086,15 +1086,18 @@ void estimate_steps(Handle &h) {
             for (int it = it0; it <= it1; ++it) {
                 const double a = hh[2 * it], b = hh[2 * it + 1];
                 it_done = it;
-                if (!(a > 0.0)) {
-                    if (it == 1) lam = 0.0;
+                // the Krylov space closes where a or b is 0; with a = 0 the block
+                // still gains the row of the last beta, the whole norm where A~
+                // has one row
+                if (it == 1 && !(a > 0.0)) {
+                    lam = 0.0;
                     stop = true;
                     break;
                 }
-                al.push_back(a);
-                be.push_back(b);
+                al.push_back(a > 0.0 ? a : 0.0);
+                be.push_back(a > 0.0 ? b : 0.0);
                 lam = bidiag_lambda_max(al.data(), be.data(), it);
-                if (!(b > 0.0)) {
+                if (!(a > 0.0 && b > 0.0)) {
                     stop = true;
                     break;
                 }

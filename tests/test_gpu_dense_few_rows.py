@@ -1,6 +1,5 @@
-"""Dense passes with fewer rows than a group of four, and with infinite entries in
-the gathered vectors: scaling and one iteration against the CPU oracle, within
-the 1e-12 of the other step-parity tests."""
+"""Dense passes with fewer rows than a group of four: scaling and one iteration
+against the CPU oracle, within the 1e-12 of the other step-parity tests."""
 
 import sys
 
@@ -34,7 +33,7 @@ def test_fewer_rows_than_a_group(oracle_lib, m, n):
         gs = s.scaling()
         assert rel_inf(to_np(gs["dc"]), sc["dc"]) <= 1e-12 and rel_inf(to_np(gs["dr"]), sc["dr"]) <= 1e-12
         got = [*s.debug_step(x, y, x0, y0, 5, tau, sigma), *s.debug_plain_step(x, y, x0, y0, 5, tau, sigma)]
-        kkt = s.solve()[2]["kkt_rel"]
     for g, r in zip(got, [*ref, *ref[2:]]):
         assert rel_inf(to_np(g), r) <= 1e-12
-    assert np.isfinite(kkt)
+    with Solver.from_lp(lp, iteration_limit=20000) as s:   # one norm step is too few for a solve
+        assert s.solve()[2]["status_name"] == "optimal"
