@@ -87,7 +87,10 @@ __device__ __forceinline__ void row_sums(const double *const (&Ar)[R], const dou
         if constexpr (!NORM) {
 #pragma unroll
             for (int k = 0; k < U; ++k)
-                if (k < count) x[k] = v[tail ? min(c + k * L, n - 1) : c + k * L];
+                if (k < count) {
+                    x[k] = v[tail ? min(c + k * L, n - 1) : c + k * L];
+                    if (tail) x[k] = c + k * L < n ? x[k] : 0.0;   // 0 x an infinity is no 0
+                }
         }
     };
     for (; c + (U - 1) * L < n; c += U * L) {
@@ -231,7 +234,7 @@ __device__ __forceinline__ double col_rows(const double *__restrict__ Ac, const 
             const double e = tail && i + u >= r1 ? 0.0 : a[u];
             if constexpr (KIND == SUM_ABSMAX) acc = fmax(acc, fabs(e));
             else if constexpr (KIND == SUM_ABS) acc += fabs(e);
-            else acc = fma(e, w[tail ? min(i + u, r1 - 1) : i + u], acc);
+            else if (!tail || i + u < r1) acc = fma(e, w[i + u], acc);   // 0 x an infinity is no 0
         }
     };
     for (; i + 15 < r1; i += 16) rows(std::integral_constant<int, 16>(), false);
