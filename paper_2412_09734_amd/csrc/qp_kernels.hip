@@ -209,6 +209,30 @@ __device__ __forceinline__ void qv_lowrank(int32_t b, const QpOperator &Q) {
     Q.qv[i] = acc + Q.d[i] * Q.v[i];
 }
 
+// Sums of runs of the primal step's partial sums of F~'v, kQpSums of them in run
+// order: with thousands of partial sums every workgroup of the F~ t product would
+// read all of them, which grows with n squared.
+constexpr int kQpSums = 64;
+__global__ __launch_bounds__(kBlock) void k_qp_sum_partials(const DevState *__restrict__ st, int32_t nb, int32_t R,
+                                                            const double *__restrict__ part,
+                                                            double *__restrict__ out) {
+    if (st->done) return;
+    __shared__ double sh[8][kQpRankMax];
+    const int32_t q = threadIdx.x & 31, g = threadIdx.x >> 5, per = (nb + kQpSums - 1) / kQpSums;
+    const int32_t k0 = (int32_t)blockIdx.x * per, k1 = min(nb, k0 + per);
+    double s = 0.0;
+    if (q < R)
+        for (int32_t k = k0 + g; k < k1; k += 8) s += part[(size_t)k * R + q];
+    sh[g][q] = s;
+    __syncthreads();
+    if ((int32_t)threadIdx.x < R) {
+        double a = 0.0;
+#pragma unroll
+        for (int u = 0; u < 8; ++u) a += sh[u][threadIdx.x];
+        out[blockIdx.x * R + threadIdx.x] = a;
+    }
+}
+
 // Primal step. G >= 0: also v of the next iteration (without a restart), and for
 // a low-rank Q of 8 G padded columns the workgroup's partial sums of F~'v (the
 // factor row's loads do not wait for the step, one barrier for all sums).
@@ -679,6 +703,13 @@ static QpOperator qp_operator(const Handle &h) {
     return q;
 }
 
+// Partial sums of F~'v beyond which they pass through k_qp_sum_partials. Measured,
+// us per iteration without / with, at ranks 1, 20 and 32: n = 40,000 (157 of them)
+// 10.1 / 11.4, 13.7 / 14.6, 15.1 / 15.8; 200,000 33.5 / 29.2, 44.5 / 40.8, 49.3 /
+// 46.6; 1,000,000 316 / 106, 388 / 186, 433 / 237; 3,000,000 2,160 / 367, 2,456 /
+// 652, 2,549 / 756.
+constexpr int32_t kQpDirect = 512;
+
 static int32_t qv_blocks(const Handle &h) {
     const int32_t rows = h.q_kind == PDHG_FMT_CSR ? kQpCsrRows : h.q_kind == PDHG_FMT_DENSE ? kQpDenseRows : kBlock;
     return (int32_t)ceil_div(h.n, rows);
@@ -686,7 +717,7 @@ static int32_t qv_blocks(const Handle &h) {
 
 void launch_qp_iteration(Handle &h, int32_t j) {
     const unsigned nbt = (unsigned)h.AT.nblocks(), nbd = (unsigned)h.A.nblocks();
-    const QpOperator Q = qp_operator(h);
+    QpOperator Q = qp_operator(h);
     auto primal = [&](auto groups) {
         k_primal_qp<decltype(groups)::value><<<nbt, kBlock, 0, h.stream>>>(
             view(h.AT), h.y.p, h.x.p, h.xbar.p, h.qv.p, h.c.p, h.lv.p, h.uv.p, h.xext.p, h.st.p, j, h.norm_q,
@@ -706,6 +737,12 @@ void launch_qp_iteration(Handle &h, int32_t j) {
         case 2: primal(std::integral_constant<int, 2>()); break;
         case 3: primal(std::integral_constant<int, 3>()); break;
         default: primal(std::integral_constant<int, 4>()); break;
+    }
+    if (h.q_kind == PDHG_FMT_LOWRANK_DIAG && Q.nb > kQpDirect) {
+        double *sums = Q.part + (size_t)Q.nb * Q.r_pad;
+        k_qp_sum_partials<<<kQpSums, kBlock, 0, h.stream>>>(h.st.p, Q.nb, Q.r_pad, Q.part, sums);
+        Q.part = sums;
+        Q.nb = kQpSums;
     }
     k_dual_qp<true><<<nbd + (unsigned)qv_blocks(h), kBlock, 0, h.stream>>>(
         view(h.A), h.xext.p, h.y.p, h.ybar.p, h.lc.p, h.uc.p, h.st.p, j, (int32_t)nbd, Q);
@@ -805,7 +842,7 @@ void qp_build(Handle &h, const pdhg_problem &p) {
         if (qp_fused(h)) {
             const int32_t r_pad = (h.q_rank + 7) & ~7;
             h.q_ft.alloc((size_t)r_pad * n);
-            h.qpart_next.alloc((size_t)std::max(1, h.AT.nblocks()) * r_pad);
+            h.qpart_next.alloc(((size_t)std::max(1, h.AT.nblocks()) + kQpSums) * r_pad);   // and the runs' sums
             k_qp_transpose_factor<<<nblk((int64_t)r_pad * n), kBlock, 0, s>>>(n, h.q_rank, r_pad, h.q_f.p, h.q_ft.p);
         }
     } else if (h.q_kind == PDHG_FMT_DENSE) {
