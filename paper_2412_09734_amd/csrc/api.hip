@@ -24,7 +24,9 @@ namespace pdhg {
 
 static thread_local std::string g_err = "";
 constexpr int kTimingEvents = 7;   // per timed plain iteration
-constexpr int kSmallPeriods = 8;   // check periods per launch of the one-workgroup solve
+// Check periods per launch of the one-workgroup solve, and its most iterations
+// (about 17 ms): a longer period takes several launches.
+constexpr int kSmallPeriods = 8, kSmallSteps = 4096;
 
 void fail(pdhg_err code, const std::string &msg) { throw Error{code, msg}; }
 
@@ -215,12 +217,14 @@ static void run_solve(Handle &h, const double *x_init, const double *y_init, dou
     if (h.q_kind) launch_qp_init(h);
     const int32_t C = h.opt.check_every;
     const int64_t L = h.opt.iteration_limit;
-    // graphs hold the solve's controller constants: polishing phases run unrolled
     // a small LP's check periods run inside one workgroup, several to a launch
     // unless the host has to look between them; kernel timings ask for the
     // multi-kernel iteration
     const bool small = h.opt.timing_chunk < 0 && small_lp_fits(h) > 0;
-    const int32_t periods = h.opt.verbose || h.opt.time_limit_s > 0.0 ? 1 : kSmallPeriods;
+    const int32_t periods = h.opt.verbose || h.opt.time_limit_s > 0.0
+                                ? 1 : std::max(1, std::min(kSmallPeriods, kSmallSteps / C));
+    int64_t left = 0, period_plain = 0;   // small: plain iterations of a period still to launch, of all
+    // graphs hold the solve's controller constants: polishing phases run unrolled
     const bool graphs = h.opt.use_graph && !h.polish && !small;
     if (graphs) build_graph(h);
 
@@ -230,6 +234,7 @@ static void run_solve(Handle &h, const double *x_init, const double *y_init, dou
     std::vector<hipEvent_t> ring(h.st_ring);
     for (auto &e : ring) PDHG_HIP(hipEventCreateWithFlags(&e, hipEventDisableTiming));
     std::deque<int> inflight;
+    std::vector<char> has_check(h.st_ring);
     int64_t t = 0, chunk = 0;
     bool stop = false;
     int64_t checks_seen = 0;
@@ -240,12 +245,23 @@ static void run_solve(Handle &h, const double *x_init, const double *y_init, dou
             bool final = false;
             const bool time_up = h.opt.time_limit_s > 0.0 && now_s() - t0 > h.opt.time_limit_s;
             int64_t plain = 0;
-            if (small) {
-                launch_small_lp(h, periods, time_up ? PDHG_TIME_LIMIT : 0);
+            const bool rest = left > 0;   // of a period whose check has run
+            if (rest) {
+                const int64_t now = std::min<int64_t>(left, kSmallSteps);
+                launch_small_lp(h, 1, (int32_t)(period_plain - left), kSmallSteps, 0);
+                left -= now;
+                plain = now - 1;
+            } else if (small) {
+                launch_small_lp(h, periods, 0, kSmallSteps, time_up ? PDHG_TIME_LIMIT : 0);
                 // the launch ends at iteration min(t + periods C, L - 1), and runs
                 // the last check itself when that falls inside its periods
                 final = time_up || L - 1 - t <= (int64_t)(periods - 1) * C;
                 plain = std::min((int64_t)periods * C, L - 1 - t) - 1;
+                if (!final && plain > kSmallSteps) {   // one period, the first part of it
+                    period_plain = plain;
+                    left = plain - kSmallSteps;
+                    plain = kSmallSteps;
+                }
             } else if (time_up) {
                 enqueue_check(h, 0, 1, PDHG_TIME_LIMIT);
                 final = true;
@@ -286,6 +302,7 @@ static void run_solve(Handle &h, const double *x_init, const double *y_init, dou
                                     hipMemcpyDeviceToHost, s));
             PDHG_HIP(hipEventRecord(ring[slot], s));
             if (timing_t == t && timing_slot < 0) timing_slot = slot;
+            has_check[slot] = !rest;
             inflight.push_back(slot);
             t += 1 + plain;
             ++chunk;
@@ -300,8 +317,8 @@ static void run_solve(Handle &h, const double *x_init, const double *y_init, dou
                     have_timing_state = true;
                     timing_slot = -2;
                 }
-                ++checks_seen;
-                if (h.opt.verbose && (checks_seen % h.opt.display_frequency) == 0) print_check(sv);
+                if (has_check[q]) ++checks_seen;
+                if (h.opt.verbose && has_check[q] && (checks_seen % h.opt.display_frequency) == 0) print_check(sv);
                 if (sv.done) stop = true;
             }
             if (final) stop = true;

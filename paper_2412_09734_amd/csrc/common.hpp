@@ -365,7 +365,7 @@ void batch_destroy(BatchHandle *b);
 
 // ---- one-workgroup solve of a small LP (lp_small.hip) --------------------------
 int32_t small_lp_fits(const Handle &h);
-void launch_small_lp(Handle &h, int32_t periods, int32_t force_last);
+void launch_small_lp(Handle &h, int32_t periods, int32_t skip, int32_t most, int32_t force_last);
 
 // ---- iteration kernels (lp_kernels.hip) -------------------------------------
 CtlConst lp_constants(const Handle &h);

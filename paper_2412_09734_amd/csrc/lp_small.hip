@@ -35,6 +35,7 @@ struct SmallArgs {
     double gamma;
     int64_t limit;
     int32_t check_every, periods;
+    int32_t skip, most;         // skip > 0: plain iterations of a period from the skip-th on; at most `most` of a period
     int32_t tasks_a, tasks_t;   // wave tasks of A~ and A~'
     int32_t force_last;   // not 0: one check that ends the solve with this status
 };
@@ -236,116 +237,120 @@ __global__ __launch_bounds__(kSmallThreads) void k_lp_small(SmallArgs a) {
     const bool detect = a.K.detect != 0;
     __syncthreads();
     for (int32_t period = 0; period < a.periods; ++period) {
-        // ---- the check iteration
         double tau = st.tau, sigma = st.sigma;
-        const int64_t t = st.t_next;
-        const bool is_last = a.force_last != 0 || t >= a.limit - 1;
-        const int32_t plain = is_last ? 0 : (int32_t)min((int64_t)a.check_every - 1, a.limit - 2 - t);
-        small_each(a.AT, a.tasks_t, y, [&](int32_t r, double s) {
-            const double xr = x[r], xh = clampd(xr - tau * (c[r] - s), lv[r], uv[r]);
-            sx[r] = 2.0 * xh - xr;
-            a.xhat[r] = xh;
-            a.aty[r] = s;
-        });
-        __syncthreads();
-        small_each(a.A, a.tasks_a, sx, [&](int32_t r, double s) {
-            const double h = dual_prox(y[r], s, sigma, lc[r], uc[r]);
-            yh[r] = h;
-            a.yhat[r] = h;
-        });
-        __syncthreads();
-        for (int32_t r = tid; r < n; r += kSmallThreads) sx[r] = a.xhat[r];
-        __syncthreads();
-        double v[13], mx[2] = {0.0, 0.0};
+        int32_t plain = st.plain_prev;
+        if (a.skip == 0) {
+            // ---- the check iteration
+            const int64_t t = st.t_next;
+            const bool is_last = a.force_last != 0 || t >= a.limit - 1;
+            plain = is_last ? 0 : (int32_t)min((int64_t)a.check_every - 1, a.limit - 2 - t);
+            small_each(a.AT, a.tasks_t, y, [&](int32_t r, double s) {
+                const double xr = x[r], xh = clampd(xr - tau * (c[r] - s), lv[r], uv[r]);
+                sx[r] = 2.0 * xh - xr;
+                a.xhat[r] = xh;
+                a.aty[r] = s;
+            });
+            __syncthreads();
+            small_each(a.A, a.tasks_a, sx, [&](int32_t r, double s) {
+                const double h = dual_prox(y[r], s, sigma, lc[r], uc[r]);
+                yh[r] = h;
+                a.yhat[r] = h;
+            });
+            __syncthreads();
+            for (int32_t r = tid; r < n; r += kSmallThreads) sx[r] = a.xhat[r];
+            __syncthreads();
+            double v[13], mx[2] = {0.0, 0.0};
 #pragma unroll
-        for (int q = 0; q < 13; ++q) v[q] = 0.0;
-        small_each(a.AT, a.tasks_t, yh, [&](int32_t r, double q) {
-            double w[6], rsum[2], rmax[2];
-            check_n_terms(r, q, sx, x, x0, a.aty, a.Dc, a.c_o, a.lv_o, a.uv_o, a.q0, a.qhat, w, rsum, rmax);
+            for (int q = 0; q < 13; ++q) v[q] = 0.0;
+            small_each(a.AT, a.tasks_t, yh, [&](int32_t r, double q) {
+                double w[6], rsum[2], rmax[2];
+                check_n_terms(r, q, sx, x, x0, a.aty, a.Dc, a.c_o, a.lv_o, a.uv_o, a.q0, a.qhat, w, rsum, rmax);
 #pragma unroll
-            for (int i = 0; i < 6; ++i) v[i] += w[i];
-            v[10] += rsum[0];
-            v[11] += rsum[1];
-            mx[0] = fmax(mx[0], rmax[0]);
-            mx[1] = fmax(mx[1], rmax[1]);
-        });
-        small_each(a.A, a.tasks_a, sx, [&](int32_t r, double p) {
-            double w[4], rsum[1], rmax[2];
-            check_m_terms(r, p, yh, y, y0, a.Dr, a.lc_o, a.uc_o, a.p0, a.phat, w, rsum, rmax);
+                for (int i = 0; i < 6; ++i) v[i] += w[i];
+                v[10] += rsum[0];
+                v[11] += rsum[1];
+                mx[0] = fmax(mx[0], rmax[0]);
+                mx[1] = fmax(mx[1], rmax[1]);
+            });
+            small_each(a.A, a.tasks_a, sx, [&](int32_t r, double p) {
+                double w[4], rsum[1], rmax[2];
+                check_m_terms(r, p, yh, y, y0, a.Dr, a.lc_o, a.uc_o, a.p0, a.phat, w, rsum, rmax);
 #pragma unroll
-            for (int i = 0; i < 4; ++i) v[6 + i] += w[i];
-            v[12] += rsum[0];
-            mx[0] = fmax(mx[0], rmax[0]);
-            mx[1] = fmax(mx[1], rmax[1]);
-        });
+                for (int i = 0; i < 4; ++i) v[6 + i] += w[i];
+                v[12] += rsum[0];
+                mx[0] = fmax(mx[0], rmax[0]);
+                mx[1] = fmax(mx[1], rmax[1]);
+            });
 #pragma unroll
-        for (int q = 0; q < 13; ++q) {
-            const double s = wave_sum(v[q]);
-            if ((tid & 63) == 0) red[q][tid >> 6] = s;
-        }
-        const double m0 = wave_max(mx[0]), m1 = wave_max(mx[1]);
-        if ((tid & 63) == 0) {
-            red[13][tid >> 6] = m0;
-            red[14][tid >> 6] = m1;
-        }
-        __syncthreads();
-        if (tid < 15) {   // the waves in order
-            double s = red[tid][0];
-            for (int w = 1; w < kSmallWaves; ++w) s = tid < 13 ? s + red[tid][w] : fmax(s, red[tid][w]);
-            red[tid][0] = s;
-        }
-        __syncthreads();
-        if (tid == 0) {
-            double vn[6], vm[4], rs[3], rx[2];
+            for (int q = 0; q < 13; ++q) {
+                const double s = wave_sum(v[q]);
+                if ((tid & 63) == 0) red[q][tid >> 6] = s;
+            }
+            const double m0 = wave_max(mx[0]), m1 = wave_max(mx[1]);
+            if ((tid & 63) == 0) {
+                red[13][tid >> 6] = m0;
+                red[14][tid >> 6] = m1;
+            }
+            __syncthreads();
+            if (tid < 15) {   // the waves in order
+                double s = red[tid][0];
+                for (int w = 1; w < kSmallWaves; ++w) s = tid < 13 ? s + red[tid][w] : fmax(s, red[tid][w]);
+                red[tid][0] = s;
+            }
+            __syncthreads();
+            if (tid == 0) {
+                double vn[6], vm[4], rs[3], rx[2];
 #pragma unroll
-            for (int i = 0; i < 6; ++i) vn[i] = red[i][0];
+                for (int i = 0; i < 6; ++i) vn[i] = red[i][0];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) vm[i] = red[6 + i][0];
+                for (int i = 0; i < 4; ++i) vm[i] = red[6 + i][0];
 #pragma unroll
-            for (int i = 0; i < 3; ++i) rs[i] = red[10 + i][0];
-            rx[0] = red[13][0];
-            rx[1] = red[14][0];
-            check_decide(&st, vn, vm, rs, rx, detect && st.anchor_valid, a.K, plain, is_last ? 1 : 0,
-                         a.force_last ? a.force_last : (int32_t)PDHG_ITERATION_LIMIT);
-        }
-        __syncthreads();
-        if (st.done) break;
-        {
-            // restart, or the Halpern step of the check iteration
-            const bool restart = st.action == 1;
-            const int64_t k = st.k_check;
-            const double ak = (double)(k + 1) / (double)(k + 2), bk = 1.0 / (double)(k + 2);
-            for (int32_t r = tid; r < n; r += kSmallThreads) {
-                const double xh = sx[r];
-                if (restart) {
-                    x[r] = xh;
-                    x0[r] = xh;
-                    a.q0[r] = a.qhat[r];
-                } else {
-                    x[r] = ak * ((1.0 + gam) * xh - gam * x[r]) + bk * x0[r];
+                for (int i = 0; i < 3; ++i) rs[i] = red[10 + i][0];
+                rx[0] = red[13][0];
+                rx[1] = red[14][0];
+                check_decide(&st, vn, vm, rs, rx, detect && st.anchor_valid, a.K, plain, is_last ? 1 : 0,
+                             a.force_last ? a.force_last : (int32_t)PDHG_ITERATION_LIMIT);
+            }
+            __syncthreads();
+            if (st.done) break;
+            {
+                // restart, or the Halpern step of the check iteration
+                const bool restart = st.action == 1;
+                const int64_t k = st.k_check;
+                const double ak = (double)(k + 1) / (double)(k + 2), bk = 1.0 / (double)(k + 2);
+                for (int32_t r = tid; r < n; r += kSmallThreads) {
+                    const double xh = sx[r];
+                    if (restart) {
+                        x[r] = xh;
+                        x0[r] = xh;
+                        a.q0[r] = a.qhat[r];
+                    } else {
+                        x[r] = ak * ((1.0 + gam) * xh - gam * x[r]) + bk * x0[r];
+                    }
+                }
+                for (int32_t r = tid; r < m; r += kSmallThreads) {
+                    const double h = yh[r];
+                    if (restart) {
+                        y[r] = h;
+                        y0[r] = h;
+                        a.p0[r] = a.phat[r];
+                    } else {
+                        y[r] = ak * ((1.0 + gam) * h - gam * y[r]) + bk * y0[r];
+                    }
                 }
             }
-            for (int32_t r = tid; r < m; r += kSmallThreads) {
-                const double h = yh[r];
-                if (restart) {
-                    y[r] = h;
-                    y0[r] = h;
-                    a.p0[r] = a.phat[r];
-                } else {
-                    y[r] = ak * ((1.0 + gam) * h - gam * y[r]) + bk * y0[r];
-                }
-            }
+            tau = st.tau;
+            sigma = st.sigma;
+            __syncthreads();
         }
-        tau = st.tau;
-        sigma = st.sigma;
-        int64_t k = st.k_base;
-        __syncthreads();
+        int64_t k = st.k_base + a.skip;
+        plain = a.skip + min(plain - a.skip, a.most);
         // ---- plain iterations; their matrix registers are loaded once per
         // period, so that the check's epilogues have the registers to themselves
         SmallProduct<K> T, R;   // A~' and A~
         T.load(a.AT);
         R.load(a.A);
-        for (int32_t j = 0; j < plain; ++j, ++k) {
+        for (int32_t j = a.skip; j < plain; ++j, ++k) {
             const double ak = (double)(k + 1) / (double)(k + 2), bk = 1.0 / (double)(k + 2);
             T.each(a.AT, y, [&](int32_t r, double s) {
                 const double xr = x[r], xh = clampd(xr - tau * (c[r] - s), lv[r], uv[r]);
@@ -408,9 +413,10 @@ static void launch_small_t(Handle &h, const SmallArgs &a) {
     PDHG_HIP(hipGetLastError());
 }
 
-// Up to `periods` check periods from the handle's state; force_last: one check
-// that ends the solve with that status.
-void launch_small_lp(Handle &h, int32_t periods, int32_t force_last) {
+// Up to `periods` check periods from the handle's state, each with at most `most`
+// plain iterations; skip > 0: the plain iterations of the current period from the
+// skip-th on; force_last: one check that ends the solve with that status.
+void launch_small_lp(Handle &h, int32_t periods, int32_t skip, int32_t most, int32_t force_last) {
     SmallArgs a;
     a.A = view(h.A);
     a.AT = view(h.AT);
@@ -445,6 +451,8 @@ void launch_small_lp(Handle &h, int32_t periods, int32_t force_last) {
     a.limit = h.opt.iteration_limit;
     a.check_every = h.opt.check_every;
     a.periods = force_last ? 1 : periods;
+    a.skip = skip;
+    a.most = most;
     a.force_last = force_last;
     a.tasks_a = wave_tasks(h.A);
     a.tasks_t = wave_tasks(h.AT);
