@@ -99,6 +99,14 @@ __device__ __forceinline__ T load_entry(const T *__restrict__ p) {
     else return *p;
 }
 
+// The entry `step` past e, or the last of the `left` entries from e on. Formed from
+// what is left: e + step may exceed 32 bits at the end of a matrix.
+__host__ __device__ constexpr int32_t entry_at(int32_t e, int32_t left, int32_t step) {
+    return e + (step < left ? step : left - 1);
+}
+static_assert(entry_at(INT32_MAX - 3, 3, 7 * 64) == INT32_MAX - 1 && entry_at(INT32_MAX - 99, 99, 64) == INT32_MAX - 35,
+              "no overflow among the last entries");
+
 // acc + the products of the lane's entries e, e + L, ..., in that order, U at a
 // time: as in sell_group the U loads of a group are unconditional, at indices
 // clamped to the row's last entry, so that all of them (and then their gathers)
@@ -111,12 +119,12 @@ __device__ __forceinline__ double lane_entries_dot(const int32_t *__restrict__ c
                                                    const double *__restrict__ v, int32_t e, int32_t e1,
                                                    int32_t L) {
     double acc = 0.0;
-    for (; e < e1; e += U * L) {
+    for (int32_t left = e1 - e; left > 0; left -= U * L, e = (int32_t)((uint32_t)e + (uint32_t)(U * L))) {
         int32_t c[U];
         double a[U], x[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const int32_t q = min(e + u * L, e1 - 1);
+            const int32_t q = entry_at(e, left, u * L);
             c[u] = load_entry<NT>(colidx + q);
             a[u] = load_entry<NT>(val + q);
         }
@@ -125,7 +133,7 @@ __device__ __forceinline__ double lane_entries_dot(const int32_t *__restrict__ c
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const double t = fma(a[u], x[u], acc);
-            acc = e + u * L < e1 ? t : acc;
+            acc = u * L < left ? t : acc;
         }
     }
     return acc;
