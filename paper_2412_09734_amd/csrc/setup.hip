@@ -171,8 +171,9 @@ __global__ __launch_bounds__(kBlock) void k_fill_transpose(const int32_t *__rest
 }
 
 // Number of leading rows longer than the short-row limit (rows sorted by
-// descending length) and the length histogram of those rows by class
-// (class c >= 1: length in (2^(c-1), 2^c]).
+// descending length), out[0], and the end of each class's run among them (class
+// c >= 1: length in (2^(c-1), 2^c]), out[32 - c]. Written where a run ends:
+// counting rows with atomics took 266 us for 100,000 rows of two classes.
 __global__ __launch_bounds__(kBlock) void k_long_rows(const int32_t *__restrict__ rowptr,
                                                       int32_t rows, int32_t limit,
                                                       int32_t *__restrict__ out /*[1+32]*/) {
@@ -183,7 +184,7 @@ __global__ __launch_bounds__(kBlock) void k_long_rows(const int32_t *__restrict_
         const int32_t nl = (i + 1 < rows) ? rowptr[i + 2] - rowptr[i + 1] : 0;
         if (nl <= limit) out[0] = (int32_t)(i + 1);
         const int32_t cls = 32 - __clz(l - 1);
-        atomicAdd(&out[1 + (31 - cls)], 1);
+        if (nl <= limit || 32 - __clz(nl - 1) != cls) out[1 + (31 - cls)] = (int32_t)(i + 1);
     }
 }
 
@@ -555,7 +556,12 @@ static void to_hybrid(hipStream_t s, PlainCsr &P, int32_t cols, int32_t short_ma
     PDHG_HIP(hipMemcpyAsync(hinfo, info.p, sizeof(hinfo), hipMemcpyDeviceToHost, s));
     PDHG_HIP(hipStreamSynchronize(s));
     const int32_t r_long = hinfo[0];
-    std::vector<int32_t> cls(hinfo + 1, hinfo + 33);
+    std::vector<int32_t> cls(32);
+    for (int32_t q = 0, begin = 0; q < 32; ++q)
+        if (hinfo[1 + q] > 0) {
+            cls[q] = hinfo[1 + q] - begin;
+            begin = hinfo[1 + q];
+        }
     H.R_long = r_long;
     H.seg = make_segments(cls, r_long);
     const int32_t ns = (int32_t)ceil_div(R - r_long, 64);
