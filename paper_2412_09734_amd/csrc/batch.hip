@@ -1366,10 +1366,10 @@ __global__ __launch_bounds__(BT) void k_batch_solve_res(BArgs a, BOpts o) {
 // ---------------------------------------------------------------------------
 // on-chip solve of any instance with at most 2 columns and rows per thread
 
-// Pairs of entries of each owned column (row) that stay in registers. More of
-// them spilled less elsewhere than they saved in LDS and streamed pairs: as
-// chosen, the compiler keeps 5 to 40 registers of a thread in scratch memory at
-// one column, 100 to 130 at two, of which the iterations reload at most 34.
+// Pairs of entries of each owned column (row) that stay in registers: as measured,
+// not as fits. Of a thread's registers 16 to 23 are in scratch memory at one column
+// (5 at 1,024 threads) and 92 to 132 at two (22 to 37), most of them across checks
+// only; an iteration reloads at most 34.
 template <int BT, int S, int SR>
 struct LdsShape {
     static constexpr int KC = BT == 1024 ? 0 : S == 1 ? 8 : 6;

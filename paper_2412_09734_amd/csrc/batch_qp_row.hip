@@ -651,8 +651,9 @@ ROW_KERNEL void k_bqp_row_backward(QArgs a, QOpts) {
 // host side
 
 // Two columns per thread hold 2 R doubles of F~ in the 256 registers of a
-// two-waves-per-SIMD kernel (R <= 32: 128 of them); a third would spill. Up to
-// 256 columns take one per thread, and 512 threads carry up to 1,024 columns.
+// two-waves-per-SIMD kernel (R <= 32: 128 of them); the forms of rank 25 to 32 then
+// keep up to 58 others in scratch memory, across checks. Up to 256 columns take one
+// per thread, and 512 threads carry up to 1,024 columns.
 int32_t qrow_fits(const BatchHandle &h) {
     if (h.m != 1 || h.q_rank < 1 || h.q_rank > kRmax || h.n > 1024) return 0;
     return h.n <= 512 ? 256 : 512;

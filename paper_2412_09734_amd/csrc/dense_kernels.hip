@@ -12,9 +12,9 @@
 
 namespace pdhg {
 
-constexpr int kDenseSplits = 16;   // most row splits of the column pass
-constexpr int kSplitRows = 256;    // fewest rows per split of the column pass
-constexpr int kNarrowWgs = 1024;   // workgroups that the narrow column pass aims at
+constexpr int kDenseSplits = 16;   // most row splits of the column pass's wide tiles
+constexpr int kSplitRows = 256;    // fewest rows per split of the wide tiles
+constexpr int kNarrowWgs = 1024;   // workgroups that the narrow tiles aim at, with 64 rows or more per split
 
 enum RowMode : int32_t {
     ROW_DUAL = 0,      // y <- Halpern(prox)
