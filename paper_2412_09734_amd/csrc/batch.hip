@@ -1873,7 +1873,7 @@ k_batch_solve_lds(BArgs a, BOpts o, int32_t cache_pairs) {
 }
 
 // ---------------------------------------------------------------------------
-// on-chip solve with more than two columns or rows per thread
+// on-chip solve that streams its entries
 
 // Row sum over the SELL-64 slice whose pairs `first` .. `end` - 1 (wave-uniform)
 // are this wave's, in row order: four pairs' loads in flight, the last ones in
@@ -1906,11 +1906,12 @@ __device__ __forceinline__ double stream_dot(const uint32_t *__restrict__ ci, co
 static size_t stream_doubles(int32_t n, int32_t m) { return (size_t)n + 3 * (size_t)m; }
 
 // The iteration of k_batch_solve on chip for instances of S > 2 columns or rows
-// per thread: the gathered vectors and the rows' bounds in LDS, the columns'
-// iterate, anchor, cost and bounds in registers, and every matrix entry streamed
-// from the SELL-64 slices on every product. The point and the dual anchor of a
-// check live in memory (xh, aty, yh, y, y0: read at checks, y0 once per row and
-// iteration), by position like everything here.
+// per thread, or of two on a shared matrix with long slices: the gathered vectors
+// and the rows' bounds in LDS, the columns' iterate, anchor, cost and bounds in
+// registers, and every matrix entry streamed from the SELL-64 slices on every
+// product. The point and the dual anchor of a check live in memory (xh, aty, yh,
+// y, y0: read at checks, y0 once per row and iteration), by position like
+// everything here.
 //
 // What bounds it: the latency of the slices' pairs, four in flight a lane, from
 // L2 or the memory-side cache. Holding pairs in registers or LDS as
@@ -3238,9 +3239,9 @@ static void launch_res_t(BatchHandle &h, void (*kernel)(Args...), Args... args) 
 // 1,024 threads, and byte offsets 8 j of its positions fit 16 bits.
 constexpr int32_t kSellRows = 8192;
 
-// Whether the on-chip kernels take the batch at bt threads: k_batch_solve_lds up
-// to 2 columns and rows per thread, k_batch_solve_stream up to 8 where its
-// vectors fit the LDS (3 KB stay for the reductions).
+// Whether the on-chip kernels take the batch at bt threads: up to 2 columns and
+// rows per thread, and up to 8 where the vectors of k_batch_solve_stream fit the
+// LDS (3 KB stay for the reductions; two per thread need 64 KB at most).
 static bool solve_on_chip(const BatchHandle &h, int32_t bt) {
     const int32_t need = std::max(h.nmax, h.mmax);
     return h.onchip && need <= kSellRows &&
@@ -3478,8 +3479,15 @@ static void launch_solve_t(BatchHandle &h, const BOpts &o) {
     if (solve_on_chip(h, BT)) {
         const int32_t need = std::max(h.nmax, h.mmax);
         if (need <= BT) return launch_solve_lds_t<BT, 1, 1>(h, o, a);
-        if (need <= 2 * BT)
+        if (need <= 2 * BT) {
+            // A shared matrix with long slices comes from L2 faster than two
+            // columns' pairs pass through registers and LDS. 193 iterations, 256
+            // instances: 1,000 x 1,000 with 30 entries a row 3.7 -> 1.8 ms, with 10
+            // (20 at most) 1.5 -> 1.0; 400 x 1,000 with 30 1.30 -> 1.01, with 10 0.51 ->
+            // 0.68; 120 x 120 with 6 (13 at most) 0.52 -> 0.60.
+            if (h.shared && std::max(h.as_wmax, h.ts_wmax) > 16) return launch_solve_stream_t<BT, 2>(h, o, a);
             return h.mmax <= BT ? launch_solve_lds_t<BT, 2, 1>(h, o, a) : launch_solve_lds_t<BT, 2, 2>(h, o, a);
+        }
         if (need <= 4 * BT) return launch_solve_stream_t<BT, 4>(h, o, a);
         return launch_solve_stream_t<BT, 8>(h, o, a);
     }
