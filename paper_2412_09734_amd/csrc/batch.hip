@@ -11,8 +11,9 @@
 // Matrices are plain CSR (rows in original order) with instance-local column
 // indices; row pointers hold global entry offsets. The setup and the
 // memory-resident kernels walk it, their vectors staying in L2 while the
-// instance runs; the on-chip kernels read SELL-64 copies (see BArgs) and keep
-// an instance in registers and LDS as far as it fits.
+// instance runs; the on-chip kernels read SELL-64 copies (see BArgs), keep an
+// instance's vectors in registers and LDS and its entries as far as that pays
+// (k_batch_solve_res: all, _lds: the first of every row, _stream: none).
 #include <algorithm>
 #include <climits>
 #include <memory>
