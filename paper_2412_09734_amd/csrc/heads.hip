@@ -17,7 +17,7 @@ constexpr int kHeadPmax = 64;     // most features of the linear cost model
 constexpr int kScratchDoubles = 32768;   // partial sums of the weight gradient (64 features x 512 chunks)
 constexpr int kGradChunks = 1024;         // most chunks
 constexpr int kMaxDevices = 64;
-constexpr int64_t kMostEntries = ((int64_t)1 << 32) - 1;   // of an array that a thread per entry walks
+constexpr int64_t kMostEntries = ((int64_t)1 << 32) - 1;   // of a launch that counts them in 32 bits
 
 // Partial sums of the allocation-free weight gradient (256 KB on every GPU the
 // library runs on, kept until the process ends). Host code never uses this
@@ -569,11 +569,21 @@ void head_spo_plus(hipStream_t s, int32_t B, int32_t n, const double *c_hat, con
 
 void head_pfy_costs(hipStream_t s, int32_t B, int32_t M, int32_t n, const double *c_hat,
                     const double *Z, double eps, double *out) {
-    const int64_t N = (int64_t)B * M * n;
-    if (N == 0) return;
-    if (N > kMostEntries) fail(PDHG_ERR_UNSUPPORTED, "too many samples for one launch");
+    if (B == 0 || M == 0 || n == 0) return;
+    // the entries of one launch are counted in 32 bits: whole instances, or whole
+    // samples of one, as many as that takes
+    const int64_t samples = kMostEntries / n, each = samples / M;
     const uint32_t magic = n > 1 ? (uint32_t)((((uint64_t)1 << 32) + (uint32_t)n - 1) / (uint32_t)n) : 0;
-    k_pfy_costs<<<(unsigned)ceil_div(N, kPfyTile), kBlock, 0, s>>>(N, M, n, magic, c_hat, Z, eps, out);
+    auto launch = [&](int64_t b, int64_t m, int64_t count, int64_t of) {   // samples m .. of instances b ..
+        const int64_t N = count * of * n, at = (b * M + m) * n;
+        k_pfy_costs<<<(unsigned)ceil_div(N, kPfyTile), kBlock, 0, s>>>(N, (int32_t)of, n, magic, c_hat + b * n, Z + at, eps,
+                                                                      out + at);
+    };
+    if (each > 0)
+        for (int64_t b = 0; b < B; b += each) launch(b, 0, std::min<int64_t>(each, B - b), M);
+    else
+        for (int64_t b = 0; b < B; ++b)
+            for (int64_t m = 0; m < M; m += samples) launch(b, m, 1, std::min<int64_t>(samples, M - m));
     PDHG_HIP(hipGetLastError());
 }
 

@@ -64,6 +64,28 @@ def test_perturbed_costs_of_many_samples(B, M, n):
     assert torch.equal(h.pfy_costs(ch, Z, 0.5), want)
 
 
+@pytest.mark.parametrize("B,M,n", [(5, 1 << 20, 820), (1, 3, 1431655771), (1, (1 << 31) - 1, 3)])
+def test_perturbed_costs_past_32_bits(B, M, n):
+    """2^32 entries and more: several launches, of instances or of one's samples."""
+    import torch
+    from paper_2412_09734_amd import heads as h
+    _say(f"perturbed costs of {B * M * n} entries, n={n}")
+    ch = torch.arange(1.0, B * n + 1, dtype=torch.float64, device="cuda").view(B, n) % 1009.0
+    Z = torch.zeros(B, M, n, dtype=torch.float64, device="cuda")
+    flat = Z.view(-1)
+    N = B * M * n
+    at = torch.tensor([0, 511, (1 << 32) // n * n - 1, (1 << 32) // n * n, (1 << 32) - 1, 1 << 32, N - 1], device="cuda")
+    at = at[at < N]
+    flat[at] = 8.0
+    out = h.pfy_costs(ch, Z, 0.5)
+    # every entry, by blocks of samples: whole numbers, exact
+    step = max(1, (1 << 28) // n)
+    for b in range(B):
+        for m in range(0, M, step):
+            Z[b, m:m + step].mul_(0.5).add_(ch[b])
+    assert torch.equal(out, Z)
+
+
 @pytest.mark.parametrize("rows,p", [((1 << 28) + 5, 17), ((1 << 32) + 5, 1)])
 def test_costs_of_many_rows(rows, p):
     """Features that are zero but for the first, the last and a few other rows."""
