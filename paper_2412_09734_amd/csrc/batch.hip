@@ -3250,6 +3250,13 @@ static bool solve_on_chip(const BatchHandle &h, int32_t bt) {
             (need <= 8 * bt && stream_doubles(h.nmax, h.mmax) * sizeof(double) + 3072 <= lds_per_workgroup()));
 }
 
+// Dynamic LDS of the on-chip setup / unrolled / reverse kernels, or 0 when the
+// largest instance does not fit (then the memory-resident variant runs).
+static size_t onchip_lds(const BatchHandle &h) {
+    const size_t lds = ((size_t)h.nmax + (size_t)h.mmax) * sizeof(double);
+    return (h.onchip && lds <= 65536) ? std::max<size_t>(lds, 8) : 0;
+}
+
 template <int BT, int S, int SR>
 static void launch_solve_lds_t(BatchHandle &h, const BOpts &o, const BArgs &a) {
     constexpr size_t lds = LdsShape<BT, S, SR>::bytes;
@@ -3363,7 +3370,7 @@ __global__ __launch_bounds__(kBlock) void k_sell_fill(
 // would read them for.
 static void build_batch_sell(BatchHandle &h) {
     hipStream_t s = h.stream;
-    if (std::max(h.nmax, h.mmax) > kSellRows) return;
+    if (!solve_on_chip(h, 1024) && !onchip_lds(h)) return;
     const bool sorted = !h.shared;
     const int32_t nb = h.shared ? 1 : h.B;
     struct Side {
@@ -3502,13 +3509,6 @@ static void launch_solve_t(BatchHandle &h, const BOpts &o) {
     else
         k_batch_solve<BT, false><<<wg, BT, 0, h.stream>>>(a, o);
     PDHG_HIP(hipGetLastError());
-}
-
-// Dynamic LDS of the on-chip setup / unrolled / reverse kernels, or 0 when the
-// largest instance does not fit (then the memory-resident variant runs).
-static size_t onchip_lds(const BatchHandle &h) {
-    const size_t lds = ((size_t)h.nmax + (size_t)h.mmax) * sizeof(double);
-    return (h.onchip && lds <= 65536) ? std::max<size_t>(lds, 8) : 0;
 }
 
 template <int BT>
@@ -3694,7 +3694,7 @@ BatchHandle *batch_create(const pdhg_batch_problem &p, const pdhg_options &o, vo
     dispatch_setup(h, nscal);
     PDHG_HIP(hipStreamSynchronize(s));
     h.lhist.release();
-    build_batch_sell(h);
+    if (p.q_rank == 0) build_batch_sell(h);   // the QP kernels walk the CSR
     if (const int32_t t = p.q_rank == 0 ? res_threads(h) : 0) h.threads = t;
     if (p.q_rank > 0) bqp_create(h, p);
     h.setup_seconds = now_seconds() - t0;

@@ -151,10 +151,10 @@ def test_statuses_and_certificates(oracle_lib, threads, rays):
             assert rel_inf(got, want) <= 1e-6
 
 
-@pytest.mark.parametrize("m,n", [(200, 8300), (8300, 300)])
+@pytest.mark.parametrize("m,n", [(200, 8300), (8300, 300), (4700, 6000)])
 def test_off_chip_at_the_default_launch(oracle_lib, m, n):
-    """More than 8,192 columns (rows): the memory-resident kernel, 512 threads with
-    the ray tests."""
+    """More than 8,192 columns (rows), or n + 3 m doubles beyond the LDS: the
+    memory-resident kernel, 512 threads with the ray tests."""
     from paper_2412_09734_amd.solver import BatchSolver
     _say(f"off chip, {m} x {n}")
     lps = [gen.planted_sparse_lp(m, n, density=0.004, seed=3960), gen.ragged_planted_batch(1, 60, 60, seed=3961)[0]]
